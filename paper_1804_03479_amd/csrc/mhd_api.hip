@@ -191,6 +191,9 @@ Work make_work(const mhd_level* lv, int lo, int hi) {
   w.NS = w.N;
   w.sb = 0;
   w.soff = 0;
+  w.units = 0;
+  w.per = w.chunks = 0;
+  w.by_chunks = w.by_row = w.by_plane = FastDiv{0, 0, 0};
   return w;
 }
 
@@ -259,11 +262,28 @@ unsigned nblocks(const Work& w) { return (unsigned)((w.items + kBlock - 1) / kBl
 // grid of a stage kernel: capped by the context's launch shape
 thread_local long long g_max_blocks = 0;
 thread_local int g_threads = kBlock;
-unsigned sblocks(const Work& w, int threads = g_threads) {
-  long long b = (w.items + threads - 1) / threads;
+unsigned capped(long long b) {
   if (g_max_blocks > 0 && b > g_max_blocks) b = g_max_blocks;
-  if (b < 1) b = 1;
-  return (unsigned)b;
+  return (unsigned)(b < 1 ? 1 : b);
+}
+unsigned sblocks(const Work& w, int threads) { return capped((w.items + threads - 1) / threads); }
+
+// Block decomposition of a stage kernel (Cell) for blocks of `threads`: fills
+// the Work's unit fields and returns the grid
+unsigned decompose(Work& w, int threads) {
+  if (w.groups) {
+    w.per = (unsigned)(w.box * w.box * w.box);
+    w.units = (int)(w.items / w.per);
+    w.by_row = make_div((unsigned)w.box);
+    w.by_plane = make_div((unsigned)(w.box * w.box));
+  } else {
+    w.per = (unsigned)((long long)w.nx * w.ny);
+    w.units = w.nz;
+    w.by_row = make_div((unsigned)w.nx);
+  }
+  w.chunks = (w.per + (unsigned)threads - 1) / (unsigned)threads;
+  w.by_chunks = make_div(w.chunks);
+  return capped((long long)w.units * w.chunks);
 }
 
 // Batches of a group list: the middle stages (between the primitive pass,
@@ -313,13 +333,14 @@ StepBufs ctx_bufs(const mhd_ctx_s* c) {
 // cell per item (in float the tiles were 10-20 % slower for every shape
 // tried: 32 x 4 x 2, 32 x 8 x 2, 16 x 8 x 4, 64 x 2 x 2)
 template <typename T, bool L>
-void launch_emf(const Work& w, const T* F, const T* W, T* E, int nt, hipStream_t st) {
+void launch_emf(Work& w, const T* F, const T* R, T* E, int nt, hipStream_t st) {
   if constexpr (!L && sizeof(T) == 8) {
     constexpr int TX = 16, TY = 8, TZ = 4;
     const long long nb = (long long)((w.nx + TX - 1) / TX) * ((w.ny + TY - 1) / TY) * ((w.nz + TZ - 1) / TZ);
-    k_emf_tiled<T, TX, TY, TZ><<<(unsigned)nb, TX * TY * TZ, 0, st>>>(w, F, W, E);
+    k_emf_tiled<T, TX, TY, TZ><<<(unsigned)nb, TX * TY * TZ, 0, st>>>(w, F, R, E);
   } else {
-    k_emf<T, L><<<sblocks(w, nt), nt, 0, st>>>(w, F, W, E);
+    const unsigned nb = decompose(w, nt);
+    k_emf<T, L><<<nb, nt, 0, st>>>(w, F, R, E);
   }
 }
 
@@ -340,7 +361,9 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEven
   // ghost cells: 3 for PLM (the corrector's faces reach 2 cells below and 1
   // above), 4 for PPM (3 below and 2 above), and one more for each stage back
   constexpr int G = R == 2 ? 4 : 3;
-  const Work wp = stage_work(lv, G, G, G), wf1 = stage_work(lv, G, G, G), we1 = stage_work(lv, G - 1, G, G);
+  const int nt = g_threads;
+  Work wp = stage_work(lv, G, G, G);
+  const Work wf1 = stage_work(lv, G, G, G), we1 = stage_work(lv, G - 1, G, G);
   const Work wh = stage_work(lv, G - 1, G - 1, G), wf2 = stage_work(lv, 1, 1, G), we2 = stage_work(lv, 0, 1, G);
   Work wu = stage_work(lv, 0, 0, G);
   wu.occ = sb.occ;
@@ -348,30 +371,34 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEven
     if (ev) (void)hipEventRecord(ev[s], st);
   };
   mark(0);
+  unsigned nb = decompose(wp, nt);
   if (cfl) {
     k_reset_smax<<<1, 1, 0, st>>>(c->smax);
-    k_prim<T, true, MIX, L><<<sblocks(wp), g_threads, 0, st>>>(wp, U, B, mix, W, gam, c->smax, c->flag);
+    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
   } else {
-    k_prim<T, false, MIX, L><<<sblocks(wp), g_threads, 0, st>>>(wp, U, B, mix, W, gam, c->smax, c->flag);
+    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
   }
   mark(1);
-  const int nt = g_threads;
   const int batch = ev ? 0 : c->batch;   // profiling times whole stages
   for (int b = 0; b < num_batches(wf1, batch); ++b) {
-    const Work f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch), h = batch_of(wh, b, batch);
-    const Work f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
-    k_flux<T, 0, S, L><<<sblocks(f1), nt, 0, st>>>(f1, W, B, F, gam, c->nfb);
+    Work f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch), h = batch_of(wh, b, batch);
+    Work f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
+    nb = decompose(f1, nt);
+    k_flux<T, 0, S, L><<<nb, nt, 0, st>>>(f1, W, B, Bh, F, gam, c->nfb);
     mark(2);
-    launch_emf<T, L>(e1, F, W, E, nt, st);
+    launch_emf<T, L>(e1, F, Bh, E, nt, st);
     mark(3);
-    k_half<T, MIX, L><<<sblocks(h), nt, 0, st>>>(h, U, B, mix, F, E, dts, inv_dx, gam, W, Bh);
+    nb = decompose(h, nt);
+    k_half<T, MIX, false, L><<<nb, nt, 0, st>>>(h, U, B, mix, F, E, dts, inv_dx, gam, W, Bh);
     mark(4);
-    k_flux<T, R, S, L><<<sblocks(f2), nt, 0, st>>>(f2, W, Bh, F, gam, c->nfb);
+    nb = decompose(f2, nt);
+    k_flux<T, R, S, L><<<nb, nt, 0, st>>>(f2, W, B, Bh, F, gam, c->nfb);
     mark(5);
-    launch_emf<T, L>(e2, F, W, E, nt, st);
+    launch_emf<T, L>(e2, F, Bh, E, nt, st);
     mark(6);
   }
-  k_final<T, MIX, L><<<sblocks(wu), nt, 0, st>>>(wu, U, B, mix, F, E, dts, inv_dx);
+  nb = decompose(wu, nt);
+  k_final<T, MIX, L><<<nb, nt, 0, st>>>(wu, U, B, mix, F, E, dts, inv_dx);
   mark(7);
 }
 
@@ -428,7 +455,9 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
   const T gam = (T)c->cfg.gamma;
   const T inv_dx = (T)(1.0 / lv->dx);
   constexpr int G = 4;   // ghost cells of CTU + PPM
-  const Work wp = stage_work(lv, 4, 4, G), wq = stage_work(lv, 2, 2, G), wf1 = stage_work(lv, 2, 2, G);
+  const int nt = g_threads;
+  Work wp = stage_work(lv, 4, 4, G);
+  const Work wq = stage_work(lv, 2, 2, G), wf1 = stage_work(lv, 2, 2, G);
   const Work we1 = stage_work(lv, 1, 2, G), wh = stage_work(lv, 1, 1, G), wf2 = stage_work(lv, 1, 1, G);
   const Work we2 = stage_work(lv, 0, 1, G);
   Work wu = stage_work(lv, 0, 0, G);
@@ -437,58 +466,61 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
     if (ev) (void)hipEventRecord(ev[s], st);
   };
   mark(0);
+  unsigned nb = decompose(wp, nt);
   if (cfl) {
     k_reset_smax<<<1, 1, 0, st>>>(c->smax);
-    k_prim<T, true, MIX, L><<<sblocks(wp), g_threads, 0, st>>>(wp, U, B, mix, W, gam, c->smax, c->flag);
+    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
   } else {
-    k_prim<T, false, MIX, L><<<sblocks(wp), g_threads, 0, st>>>(wp, U, B, mix, W, gam, c->smax, c->flag);
+    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
   }
   mark(1);
   constexpr bool kMlp = S == 3 && std::is_same<T, float>::value;
   const float dp = (float)c->cfg.mlp_dp, drho = (float)c->cfg.mlp_drho;
-  const int nt = g_threads;
   const int batch = ev ? 0 : c->batch;   // profiling times whole stages
   for (int b = 0; b < num_batches(wq, batch); ++b) {
-    const Work q = batch_of(wq, b, batch), f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch);
-    const Work h = batch_of(wh, b, batch), f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
+    Work q = batch_of(wq, b, batch), f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch);
+    Work h = batch_of(wh, b, batch), f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
     // the HLL-family solvers (HLLE, HLLD, the learned flux standing in for
     // HLLD) take every wave in the tracing, Roe only those moving toward an edge
-    if (R != 1 || !c->lds_tiles || !launch_states_tiled<T, S != 0, L>(q, W, B, QL, QR, dts, inv_dx, gam, st))
-      k_ctu_states<T, R, S != 0, L><<<sblocks(q), nt, 0, st>>>(q, W, B, QL, QR, dts, inv_dx, gam);
+    if (R != 1 || !c->lds_tiles || !launch_states_tiled<T, S != 0, L>(q, W, B, QL, QR, dts, inv_dx, gam, st)) {
+      nb = decompose(q, nt);
+      k_ctu_states<T, R, S != 0, L><<<nb, nt, 0, st>>>(q, W, B, QL, QR, dts, inv_dx, gam);
+    }
     mark(2);
     if constexpr (kMlp) {
       // the network kernels keep 256-thread blocks (one LDS stage per wave)
-      const unsigned nb = sblocks(f1, kBlock);
-      const long long n7 = 7LL * f1.NS;
-      k_flux_dir_mlp<0, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb,
-                                                         c->capture);
-      k_flux_dir_mlp<1, L><<<nb, kBlock, 0, st>>>(f1, QL + n7, QR + n7, B, F1, gam, c->mlpw, dp, drho,
-                                                         c->nfb, c->capture);
-      k_flux_dir_mlp<2, L><<<nb, kBlock, 0, st>>>(f1, QL + 2 * n7, QR + 2 * n7, B, F1, gam, c->mlpw, dp,
-                                                         drho, c->nfb, c->capture);
-    } else
-      k_flux_q<T, S, L><<<sblocks(f1), nt, 0, st>>>(f1, QL, QR, B, F1, gam, c->nfb, c->capture);
+      nb = decompose(f1, kBlock);
+      k_flux_dir_mlp<0, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
+      k_flux_dir_mlp<1, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
+      k_flux_dir_mlp<2, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
+    } else {
+      nb = decompose(f1, nt);
+      k_flux_q<T, S, L><<<nb, nt, 0, st>>>(f1, QL, QR, B, F1, gam, c->nfb, c->capture);
+    }
     mark(3);
-    launch_emf<T, L>(e1, F1, W, E, nt, st);
+    launch_emf<T, L>(e1, F1, Bh, E, nt, st);
     mark(4);
-    k_half<T, MIX, L><<<sblocks(h), nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, W, Bh);
+    nb = decompose(h, nt);
+    k_half<T, MIX, true, L><<<nb, nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, W, Bh);
     mark(5);
     if constexpr (kMlp) {
-      const unsigned nb = sblocks(f2, kBlock);
+      nb = decompose(f2, kBlock);
       k_ctu_correct_mlp<0, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
                                                      drho, c->nfb, c->capture);
       k_ctu_correct_mlp<1, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
                                                      drho, c->nfb, c->capture);
       k_ctu_correct_mlp<2, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
                                                      drho, c->nfb, c->capture);
-    } else
-      k_ctu_correct<T, S, L><<<sblocks(f2), nt, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->nfb,
-                                                          c->capture);
+    } else {
+      nb = decompose(f2, nt);
+      k_ctu_correct<T, S, L><<<nb, nt, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->nfb, c->capture);
+    }
     mark(6);
     launch_emf<T, L>(e2, F2, W, E, nt, st);
     mark(7);
   }
-  k_final<T, MIX, L><<<sblocks(wu), nt, 0, st>>>(wu, U, B, mix, F2, E, dts, inv_dx);
+  nb = decompose(wu, nt);
+  k_final<T, MIX, L><<<nb, nt, 0, st>>>(wu, U, B, mix, F2, E, dts, inv_dx);
   mark(8);
 }
 
@@ -582,6 +614,25 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   for (int q = 0; q < 7; ++q) *dst[q] = n[q] ? (void*)(base + at[q]) : nullptr;
   sb->occ = list_mode(lv) ? (int*)(base + at[7]) : nullptr;
   return off;
+}
+
+// CFL maximum signal speed of a level into c->smax
+template <typename T, bool MIX>
+void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
+  Work w = make_work(lv, 0, 0);
+  g_max_blocks = 0;
+  const unsigned nb = decompose(w, kBlock);
+  const Mix mix{lv->E64, c->cfg.beta_fp64};
+  const T *U = (const T*)lv->U, *B = (const T*)lv->B;
+  if (w.groups) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->smax, c->flag);
+  else k_cfl<T, MIX, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->smax, c->flag);
+}
+
+void launch_cfl(mhd_ctx_s* c, const mhd_level* lv) {
+  k_reset_smax<<<1, 1, 0, c->stream>>>(c->smax);
+  if (c->cfg.prec == MHD_F64) launch_cfl_t<double, false>(c, lv);
+  else if (c->cfg.prec == MHD_F32) launch_cfl_t<float, false>(c, lv);
+  else launch_cfl_t<float, true>(c, lv);
 }
 
 int read_flag(mhd_ctx_s* c, int* flag) {
@@ -729,18 +780,7 @@ int mhd_cfl_dt(mhd_ctx c, const mhd_level* lv, double* dt_host, double* dt_dev) 
   if (!c) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  const Work w = make_work(lv, 0, 0);
-  k_reset_smax<<<1, 1, 0, c->stream>>>(c->smax);
-  const Mix mix{lv->E64, c->cfg.beta_fp64};
-  if (c->cfg.prec == MHD_F64)
-    k_cfl<double, false><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const double*)lv->U, (const double*)lv->B, mix,
-                                                                c->cfg.gamma, c->smax, c->flag);
-  else if (c->cfg.prec == MHD_F32)
-    k_cfl<float, false><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const float*)lv->U, (const float*)lv->B, mix,
-                                                               (float)c->cfg.gamma, c->smax, c->flag);
-  else
-    k_cfl<float, true><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const float*)lv->U, (const float*)lv->B, mix,
-                                                              (float)c->cfg.gamma, c->smax, c->flag);
+  launch_cfl(c, lv);
   const double cdx = c->cfg.courant * lv->dx;
   if (dt_dev) k_publish_dt<<<1, 1, 0, c->stream>>>(c->smax, cdx, dt_dev, nullptr);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
@@ -901,18 +941,7 @@ int mhd_cfl_dt_min(mhd_ctx c, const mhd_level* lv, double scale, double* dt_dev)
   if (!c || !dt_dev || !(scale > 0.0 && std::isfinite(scale))) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  const Work w = make_work(lv, 0, 0);
-  const Mix mix{lv->E64, c->cfg.beta_fp64};
-  k_reset_smax<<<1, 1, 0, c->stream>>>(c->smax);
-  if (c->cfg.prec == MHD_F64)
-    k_cfl<double, false><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const double*)lv->U, (const double*)lv->B, mix,
-                                                                c->cfg.gamma, c->smax, c->flag);
-  else if (c->cfg.prec == MHD_F32)
-    k_cfl<float, false><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const float*)lv->U, (const float*)lv->B, mix,
-                                                               (float)c->cfg.gamma, c->smax, c->flag);
-  else
-    k_cfl<float, true><<<nblocks(w), kBlock, 0, c->stream>>>(w, (const float*)lv->U, (const float*)lv->B, mix,
-                                                              (float)c->cfg.gamma, c->smax, c->flag);
+  launch_cfl(c, lv);
   k_min_dt<<<1, 1, 0, c->stream>>>(c->smax, c->cfg.courant * lv->dx * scale, dt_dev);
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }

@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mhd_device.hpp"
 #include "mhd_mlp.hpp"
 
@@ -30,6 +32,24 @@ namespace mhd {
 
 constexpr int kBlock = 256;      // threads per block of the fixed-shape kernels
 constexpr int kMaxBlock = 512;   // largest block of the step's stage kernels (tuned per context)
+
+// n / d for 0 <= n < 2^31 by a divisor fixed on the host (make_div): one high
+// multiply, an add and a shift instead of a division's reciprocal sequence.
+struct FastDiv {
+  unsigned m, a, s;
+};
+__host__ __device__ __forceinline__ unsigned fdiv(const FastDiv& f, unsigned n) {
+  return ((unsigned)(((unsigned long long)n * f.m) >> 32) + (n & f.a)) >> f.s;
+}
+// d = 1: n itself.  d > 1: s = ceil(log2 d) - 1, m = floor(2^(32 + s) / d) + 1
+// < 2^32; m d exceeds 2^(32 + s) by at most d <= 2^(s + 1), so the quotient is
+// exact for n < 2^31.
+inline FastDiv make_div(unsigned d) {
+  if (d <= 1) return FastDiv{0u, ~0u, 0u};
+  unsigned s = 0;
+  while ((2ull << s) < d) ++s;
+  return FastDiv{(unsigned)((1ull << (32 + s)) / d + 1), 0u, s};
+}
 
 struct Work {
   int nx, ny, nz;
@@ -53,6 +73,12 @@ struct Work {
   long long NS;         // component stride of the scratch arrays
   int sb;               // scratch box edge (0: scratch addressed like the level)
   int soff;             // offset of this stage's item box inside the scratch box
+  // Block decomposition of the stage kernels (Cell): units (the grid's
+  // z-planes, or the listed groups' item boxes) of `per` cells, each covered
+  // by `chunks` blocks.
+  int units;
+  unsigned per, chunks;
+  FastDiv by_chunks, by_row, by_plane;   // of the block rank; of a cell index by its row and by its plane
 };
 
 // A work item's cell: global coordinates, level index p and scratch slot s;
@@ -170,6 +196,143 @@ __device__ __forceinline__ Site site_nb(const Work& w, const Site& st, int di, i
 #define FOR_ITEMS(w, t) for (long long t = block_linear_id(), t##_n = work_items(w); t < t##_n; t += item_stride())
 
 
+// ---- addressing of the stage kernels
+//
+// A block covers part of one unit: one z-plane of a whole grid, or one listed
+// group's item box.  The plane or box is then the same for the whole block, so
+// its base address is scalar; a thread keeps one 32-bit byte offset inside it,
+// and a neighbour costs nothing (a group box: every neighbour at a constant
+// distance from the scalar base), one scalar address (a whole grid, along z)
+// or one add of a wrapped distance (along x and y).  The cell's coordinates
+// come from two multiplications.  (One 64-bit linear index per thread, split
+// by 64-bit divisions, and a 64-bit product per neighbour took 35-80 % of the
+// stages' vector instructions.)  A plane or box is below 4 GB: a plane of
+// 2^29 cells would need more memory than the device has, since a level has at
+// least four of them and at least 35 words of scratch per cell.
+template <typename T, bool L>
+struct Cell {
+  bool on;              // the thread has a cell
+  int i, j, k;          // cell of the level
+  int a, b, c;          // position in the group's item box (L)
+  unsigned o;           // byte offset in the plane or scratch box
+  long long u;          // element offset of the plane or scratch box (uniform)
+  long long p;          // level index (L)
+
+  __device__ __forceinline__ Cell(const Work& w, unsigned rank) {
+    const unsigned unit = fdiv(w.by_chunks, rank);
+    const unsigned l = (rank - unit * w.chunks) * blockDim.x + threadIdx.x;
+    on = l < w.per;
+    if constexpr (L) {
+      const unsigned box = w.box;
+      c = (int)fdiv(w.by_plane, l);
+      const unsigned r = l - (unsigned)c * box * box;
+      b = (int)fdiv(w.by_row, r);
+      a = (int)(r - (unsigned)b * box);
+      const int g = w.gbase + (int)unit;
+      const int* og = w.groups + 3LL * g;
+      i = wrapc((og[0] >> w.oshift) - w.halo + a, w.nx);
+      j = wrapc((og[1] >> w.oshift) - w.halo + b, w.ny);
+      k = wrapc((og[2] >> w.oshift) - w.halo + c, w.nz);
+      const long long sb = w.sb;
+      u = (g + 1LL) * sb * sb * sb;
+      o = (unsigned)(((c + w.soff) * w.sb + (b + w.soff)) * w.sb + (a + w.soff)) * (unsigned)sizeof(T);
+      p = lin(w, i, j, k);
+    } else {
+      j = (int)fdiv(w.by_row, l);
+      i = (int)(l - (unsigned)j * (unsigned)w.nx);
+      k = (int)unit;
+      a = i; b = j; c = k;
+      u = (long long)k * w.per;
+      o = l * (unsigned)sizeof(T);
+      p = 0;
+    }
+  }
+
+  // wrapped distances of the neighbours X cells along x and Y along y
+  template <int X>
+  __device__ __forceinline__ int dx(const Work& w) const {
+    return X == 0 ? 0 : (X < 0 ? (i < -X ? X + w.nx : X) : (i >= w.nx - X ? X - w.nx : X));
+  }
+  template <int Y>
+  __device__ __forceinline__ int dy(const Work& w) const {
+    return Y == 0 ? 0 : (Y < 0 ? (j < -Y ? Y + w.ny : Y) : (j >= w.ny - Y ? Y - w.ny : Y));
+  }
+  template <int X, int Y, int Z>
+  __device__ __forceinline__ const char* base(const Work& w, const T* arr) const {
+    if constexpr (L) return (const char*)(arr + (u + X + (long long)Y * w.sb + (long long)Z * w.sb * w.sb));
+    else if constexpr (Z == 0) return (const char*)(arr + u);
+    else return (const char*)(arr + (long long)wrapc(k + Z, w.nz) * w.per);
+  }
+  template <int X, int Y>
+  __device__ __forceinline__ unsigned off(const Work& w) const {
+    unsigned v = o;
+    if constexpr (!L && X != 0) v += (unsigned)(dx<X>(w) * (int)sizeof(T));
+    if constexpr (!L && Y != 0) v += (unsigned)(dy<Y>(w) * w.nx * (int)sizeof(T));
+    return v;
+  }
+  // one scratch component at the cell (X, Y, Z) away
+  template <int X, int Y, int Z>
+  __device__ __forceinline__ T at(const Work& w, const T* arr) const {
+    return *(const T*)(base<X, Y, Z>(w, arr) + off<X, Y>(w));
+  }
+  // ... n cells along direction D
+  template <int D, int n>
+  __device__ __forceinline__ T along(const Work& w, const T* arr) const {
+    return at<D == 0 ? n : 0, D == 1 ? n : 0, D == 2 ? n : 0>(w, arr);
+  }
+  __device__ __forceinline__ T here(const Work& w, const T* arr) const { return at<0, 0, 0>(w, arr); }
+  __device__ __forceinline__ void put(const Work& w, T* arr, T v) const {
+    *(T*)(const_cast<char*>(base<0, 0, 0>(w, arr)) + o) = v;
+  }
+  // ... stored at the cell n along D
+  template <int D, int n>
+  __device__ __forceinline__ void put_along(const Work& w, T* arr, T v) const {
+    constexpr int X = D == 0 ? n : 0, Y = D == 1 ? n : 0, Z = D == 2 ? n : 0;
+    *(T*)(const_cast<char*>(base<X, Y, Z>(w, arr)) + off<X, Y>(w)) = v;
+  }
+  // level index of the cell n along D (L)
+  template <int D, int n>
+  __device__ __forceinline__ long long level_index(const Work& w) const {
+    if constexpr (n == 0) return p;
+    else if constexpr (D == 0) return p + dx<n>(w);
+    else if constexpr (D == 1) return p + (long long)dy<n>(w) * w.nx;
+    else return p + (long long)(n < 0 ? (k < -n ? n + w.nz : n) : (k >= w.nz - n ? n - w.nz : n)) * w.nx * w.ny;
+  }
+  // one component of the level itself, n cells along D
+  template <int D, int n>
+  __device__ __forceinline__ T level(const Work& w, const T* arr) const {
+    if constexpr (L) return arr[level_index<D, n>(w)];
+    else return along<D, n>(w, arr);
+  }
+  template <int D, int n>
+  __device__ __forceinline__ void put_level(const Work& w, T* arr, T v) const {
+    if constexpr (L) arr[level_index<D, n>(w)] = v;
+    else put_along<D, n>(w, arr, v);
+  }
+  // the cell's level index (both modes)
+  __device__ __forceinline__ long long index(const Work& w) const { return L ? p : u + o / sizeof(T); }
+};
+
+// blocks of a stage: all units' chunks, the unit count of a group list read
+// from device memory where the list lives there
+template <bool L>
+__device__ __forceinline__ unsigned stage_blocks(const Work& w) {
+  int n = w.units;
+  if constexpr (L) {
+    if (w.n_dev) {
+      const int m = *w.n_dev - w.gbase;
+      n = m < 0 ? 0 : (m < n ? m : n);
+    }
+  }
+  return (unsigned)n * w.chunks;
+}
+
+// loop over this block's chunks: c is the thread's cell (c.on: it has one)
+#define FOR_CHUNKS(T, L, w, c)                                                           \
+  for (unsigned c##_r = block_rank(), c##_n = stage_blocks<L>(w); c##_r < c##_n; c##_r += gridDim.x) \
+    if (const Cell<T, L> c(w, c##_r); true)
+#define FOR_CELLS(T, L, w, c) FOR_CHUNKS(T, L, w, c) if (c.on)
+
 // time step source: explicit value, device scalar, or CFL maximum signal
 // speed (stored as the bit pattern of a positive double)
 struct DtSrc {
@@ -222,25 +385,44 @@ __device__ __forceinline__ T recover_pressure(double e, T d, T vx, T vy, T vz, T
   return pf;
 }
 
+// primitives of a cell from its conserved values and its six faces (lower and
+// upper of each direction)
 template <typename T, bool MIX>
-__device__ __forceinline__ void cell_prims(const Work& w, const T* __restrict__ U, const T* __restrict__ B,
-                                           const Mix& mix, int i, int j, int k, T gam, T out[8]) {
-  const long long N = w.N;
-  const long long p = lin(w, i, j, k);
-  const T bx = T(0.5) * (B[p] + B[nbr(w, i, j, k, 1, 0, 0)]);
-  const T by = T(0.5) * (B[N + p] + B[N + nbr(w, i, j, k, 0, 1, 0)]);
-  const T bz = T(0.5) * (B[2 * N + p] + B[2 * N + nbr(w, i, j, k, 0, 0, 1)]);
-  const T d = U[p];
+__device__ __forceinline__ void prims_from(T d, T mx, T my, T mz, T e, double e64, const T bl[3], const T bu[3], T gam,
+                                           double beta, T out[8]) {
+  const T bx = T(0.5) * (bl[0] + bu[0]);
+  const T by = T(0.5) * (bl[1] + bu[1]);
+  const T bz = T(0.5) * (bl[2] + bu[2]);
   const T id = T(1) / d;
-  const T vx = U[N + p] * id, vy = U[2 * N + p] * id, vz = U[3 * N + p] * id;
+  const T vx = mx * id, vy = my * id, vz = mz * id;
   T pr;
   if (MIX) {
-    pr = recover_pressure<T, true>(mix.E64[p], d, vx, vy, vz, bx, by, bz, gam, mix.beta);
+    pr = recover_pressure<T, true>(e64, d, vx, vy, vz, bx, by, bz, gam, beta);
   } else {
-    pr = (gam - T(1)) * (U[4 * N + p] - T(0.5) * d * (vx * vx + vy * vy + vz * vz) -
+    pr = (gam - T(1)) * (e - T(0.5) * d * (vx * vx + vy * vy + vz * vz) -
                          T(0.5) * (bx * bx + by * by + bz * bz));
   }
   out[0] = d; out[1] = vx; out[2] = vy; out[3] = vz; out[4] = pr; out[5] = bx; out[6] = by; out[7] = bz;
+}
+
+// primitives of a stage kernel's cell
+template <typename T, bool MIX, bool L>
+__device__ __forceinline__ void cell_prims(const Work& w, const T* __restrict__ U, const T* __restrict__ B,
+                                           const Mix& mix, const Cell<T, L>& c, T gam, T out[8]) {
+  const long long N = w.N;
+  const T bl[3] = {c.template level<0, 0>(w, B), c.template level<0, 0>(w, B + N), c.template level<0, 0>(w, B + 2 * N)};
+  const T bu[3] = {c.template level<0, 1>(w, B), c.template level<1, 1>(w, B + N), c.template level<2, 1>(w, B + 2 * N)};
+  T u[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) u[m] = (MIX && m == 4) ? T(0) : c.template level<0, 0>(w, U + m * N);
+  prims_from<T, MIX>(u[0], u[1], u[2], u[3], u[4], MIX ? mix.E64[c.index(w)] : 0.0, bl, bu, gam, mix.beta, out);
+}
+
+// component a of the cell's own EMF, -v x B, from its primitives
+template <typename T>
+__device__ __forceinline__ T cell_emf(const T q[8], int a) {
+  const int b = (a + 1) % 3, c = (a + 2) % 3;
+  return -(q[1 + b] * q[5 + c] - q[1 + c] * q[5 + b]);
 }
 
 // sum over directions of |v_d| + c_f,d, in double
@@ -271,19 +453,22 @@ __device__ __forceinline__ void block_max_atomic(double v, unsigned long long* s
   }
 }
 
-// Primitive state of every cell; optionally the CFL maximum signal speed and
-// the sticky non-physical flag.
+// Primitive state of every cell and the cell's EMF R = -v x B (three words that
+// the edge EMFs read instead of v and B, six, which each of the twelve edges
+// around a cell would multiply out again); optionally the CFL maximum signal
+// speed and the sticky non-physical flag.
 template <typename T, bool CFL, bool MIX, bool L>
 __global__ void __launch_bounds__(kMaxBlock) k_prim(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
-                                                 T* __restrict__ W, T gam, unsigned long long* smax,
+                                                 T* __restrict__ W, T* __restrict__ R, T gam, unsigned long long* smax,
                                                  int* flag) {
   double s = 0.0;
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
+  FOR_CELLS(T, L, w, c) {
     T q[8];
-    cell_prims<T, MIX>(w, U, B, mix, st.i, st.j, st.k, gam, q);
+    cell_prims<T, MIX, L>(w, U, B, mix, c, gam, q);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) W[m * w.NS + st.s] = q[m];
+    for (int m = 0; m < 8; ++m) c.put(w, W + m * w.NS, q[m]);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) c.put(w, R + m * w.NS, cell_emf(q, m));
     if (!(q[0] > T(0)) || !(q[4] > T(0))) atomicOr(flag, 1);
     else if (CFL) s = fmax(s, signal_speed(q, gam));
   }
@@ -291,15 +476,13 @@ __global__ void __launch_bounds__(kMaxBlock) k_prim(Work w, const T* __restrict_
 }
 
 // CFL maximum signal speed only
-template <typename T, bool MIX>
+template <typename T, bool MIX, bool L>
 __global__ void __launch_bounds__(kBlock) k_cfl(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
                                                 T gam, unsigned long long* smax, int* flag) {
   double s = 0.0;
-  FOR_ITEMS(w, t) {
-    int i, j, k;
-    cell_of(w, t, i, j, k);
+  FOR_CELLS(T, L, w, c) {
     T q[8];
-    cell_prims<T, MIX>(w, U, B, mix, i, j, k, gam, q);
+    cell_prims<T, MIX, L>(w, U, B, mix, c, gam, q);
     if (!(q[0] > T(0)) || !(q[4] > T(0))) atomicOr(flag, 1);
     else s = fmax(s, signal_speed(q, gam));
   }
@@ -334,26 +517,43 @@ __device__ __forceinline__ void load_w1d(const T* __restrict__ W, long long N, l
   w[6] = W[(5 + t2) * N + q];
 }
 
+// the same for the cell n along D of a stage kernel's cell
+template <typename T, int D, int n, bool L>
+__device__ __forceinline__ void load_frame(const Work& w, const T* __restrict__ W, const Cell<T, L>& c, T q[7]) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
+#pragma unroll
+  for (int m = 0; m < 7; ++m) q[m] = c.template along<D, n>(w, W + comp[m] * w.NS);
+}
+
+template <typename T, int D, bool L>
+__device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, const Cell<T, L>& c, const T f[7]) {
+  constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  const long long NS = w.NS;
+  T* Fd = F + (long long)D * 7 * NS;
+  c.put(w, Fd, f[0]);
+  c.put(w, Fd + (1 + n) * NS, f[1]);
+  c.put(w, Fd + (1 + t1) * NS, f[2]);
+  c.put(w, Fd + (1 + t2) * NS, f[3]);
+  c.put(w, Fd + 4 * NS, f[4]);
+  c.put(w, Fd + 5 * NS, f[6]);    // E_t1 = F_n[B_t2]
+  c.put(w, Fd + 6 * NS, -f[5]);   // E_t2 = -F_n[B_t1]
+}
+
 // RECON: 0 = first order (cell states), 1 = PLM with minmod on primitives,
 // 2 = PPM (the limited parabolas' upper edge of the left cell and lower edge
 // of the right cell, no tracing: the VL predictor centres the data in time).
-// The normal field Bn is the level's B (predictor, RECON 0: Bn[D N + p]) or
-// the half-step scratch Bh (corrector, RECON 1 and 2: Bn[D NS + s]).
+// bn: the face's normal field.
 template <typename T, int D, int RECON, int SOLVER, bool L>
-__device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W, const T* __restrict__ Bn,
-                                         T* __restrict__ F, const Site& st, T gam) {
-  const long long NS = w.NS;
-  const long long pR = st.s;
-  const long long pL = snb<L>(w, st, D == 0 ? -1 : 0, D == 1 ? -1 : 0, D == 2 ? -1 : 0);
+__device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W, T bn, T* __restrict__ F,
+                                         const Cell<T, L>& c, T gam) {
   T wl[7], wr[7];
-  load_w1d<T, D>(W, NS, pL, wl);
-  load_w1d<T, D>(W, NS, pR, wr);
-  if (RECON == 1) {
-    const long long pLL = snb<L>(w, st, D == 0 ? -2 : 0, D == 1 ? -2 : 0, D == 2 ? -2 : 0);
-    const long long pRR = snb<L>(w, st, D == 0 ? 1 : 0, D == 1 ? 1 : 0, D == 2 ? 1 : 0);
+  load_frame<T, D, -1, L>(w, W, c, wl);
+  load_frame<T, D, 0, L>(w, W, c, wr);
+  if constexpr (RECON == 1) {
     T wll[7], wrr[7];
-    load_w1d<T, D>(W, NS, pLL, wll);
-    load_w1d<T, D>(W, NS, pRR, wrr);
+    load_frame<T, D, -2, L>(w, W, c, wll);
+    load_frame<T, D, 1, L>(w, W, c, wrr);
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
       const T sL = minmod(wl[m] - wll[m], wr[m] - wl[m]);
@@ -361,13 +561,13 @@ __device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W,
       wl[m] = wl[m] + T(0.5) * sL;
       wr[m] = wr[m] - T(0.5) * sR;
     }
-  } else if (RECON == 2) {
+  } else if constexpr (RECON == 2) {
     // cells -3, -2 and 1, 2 around the face (-1 and 0 are wl, wr)
     T q3[7], q2[7], p1[7], p2[7];
-    load_w1d<T, D>(W, NS, snb<L>(w, st, D == 0 ? -3 : 0, D == 1 ? -3 : 0, D == 2 ? -3 : 0), q3);
-    load_w1d<T, D>(W, NS, snb<L>(w, st, D == 0 ? -2 : 0, D == 1 ? -2 : 0, D == 2 ? -2 : 0), q2);
-    load_w1d<T, D>(W, NS, snb<L>(w, st, D == 0 ? 1 : 0, D == 1 ? 1 : 0, D == 2 ? 1 : 0), p1);
-    load_w1d<T, D>(W, NS, snb<L>(w, st, D == 0 ? 2 : 0, D == 1 ? 2 : 0, D == 2 ? 2 : 0), p2);
+    load_frame<T, D, -3, L>(w, W, c, q3);
+    load_frame<T, D, -2, L>(w, W, c, q2);
+    load_frame<T, D, 1, L>(w, W, c, p1);
+    load_frame<T, D, 2, L>(w, W, c, p2);
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
       T lo, hi, lo2, hi2;
@@ -377,18 +577,9 @@ __device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W,
       wr[m] = lo2;
     }
   }
-  const T bn = RECON != 0 ? Bn[D * NS + st.s] : Bn[D * w.N + st.p];
   T f[7];
   const int fb = riemann<SOLVER>(wl, wr, bn, gam, f);
-  constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  T* Fd = F + (long long)D * 7 * NS;
-  Fd[pR] = f[0];
-  Fd[(1 + n) * NS + pR] = f[1];
-  Fd[(1 + t1) * NS + pR] = f[2];
-  Fd[(1 + t2) * NS + pR] = f[3];
-  Fd[4 * NS + pR] = f[4];
-  Fd[5 * NS + pR] = f[6];    // E_t1 = F_n[B_t2]
-  Fd[6 * NS + pR] = -f[5];   // E_t2 = -F_n[B_t1]
+  store_flux<T, D, L>(w, F, c, f);
   return fb;
 }
 
@@ -406,28 +597,34 @@ __device__ __forceinline__ void block_count_atomic(int v, unsigned long long* co
   }
 }
 
-// VL flux stage; B is the level's field for RECON 0 and the half-step
-// scratch Bh for RECON 1 and 2 (see face_flux).
+// VL flux stage.  RECON 0 (predictor): the normal field is the level's B.
+// RECON 1 and 2 (corrector): it is the half-step scratch Bh, which each thread
+// reads at its own cell only and then overwrites with that cell's EMF of the
+// half-step state, for the edge EMFs of the next stage.
 template <typename T, int RECON, int SOLVER, bool L>
-__global__ void __launch_bounds__(kMaxBlock) k_flux(Work w, const T* __restrict__ W, const T* __restrict__ B,
+__global__ void __launch_bounds__(kMaxBlock) k_flux(Work w, const T* __restrict__ W, const T* __restrict__ B, T* Bh,
                                                  T* __restrict__ F, T gam, unsigned long long* nfb) {
   int fb = 0;
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
-    fb += face_flux<T, 0, RECON, SOLVER, L>(w, W, B, F, st, gam);
-    fb += face_flux<T, 1, RECON, SOLVER, L>(w, W, B, F, st, gam);
-    fb += face_flux<T, 2, RECON, SOLVER, L>(w, W, B, F, st, gam);
+  FOR_CELLS(T, L, w, c) {
+    T bn[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      bn[d] = RECON == 0 ? c.template level<0, 0>(w, B + d * w.N) : c.here(w, (const T*)Bh + d * w.NS);
+    if constexpr (RECON != 0) {
+      T q[8];
+#pragma unroll
+      for (int m = 1; m < 8; ++m) q[m] = c.here(w, W + m * w.NS);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) c.put(w, Bh + m * w.NS, cell_emf(q, m));
+    }
+    fb += face_flux<T, 0, RECON, SOLVER, L>(w, W, bn[0], F, c, gam);
+    fb += face_flux<T, 1, RECON, SOLVER, L>(w, W, bn[1], F, c, gam);
+    fb += face_flux<T, 2, RECON, SOLVER, L>(w, W, bn[2], F, c, gam);
   }
   if (SOLVER == 0) block_count_atomic(fb, nfb);
 }
 
 // ------------------------------------------------------------ edge EMFs
-template <typename T>
-__device__ __forceinline__ T ref_emf(const T* __restrict__ W, long long N, long long q, int a) {
-  const int b = (a + 1) % 3, c = (a + 2) % 3;
-  return -(W[(1 + b) * N + q] * W[(5 + c) * N + q] - W[(1 + c) * N + q] * W[(5 + b) * N + q]);
-}
-
 template <typename T>
 __device__ __forceinline__ T upwind(T m, T pos, T neg) {
   return m > T(0) ? pos : (m < T(0) ? neg : T(0.5) * (pos + neg));
@@ -448,53 +645,50 @@ __device__ __forceinline__ T edge_emf_core(T eb0, T eb1, T ec0, T ec1, T mb0, T 
   return T(0.25) * (eb0 + eb1 + ec0 + ec1) + T(0.25) * ((dc0 - dc1) + (db0 - db1));
 }
 
-// E_a on the edge at the lower (b, c) corner of cell (i, j, k), (a, b, c)
-// cyclic, from the four faces around the edge (upwind CT average of
-// Gardiner & Stone 2005): each face value is extrapolated to the edge with
-// the derivative taken in the upwind cell (sign of the face mass flux), and
-// the four extrapolations are averaged.
+// E_a on the edge at the lower (b, c) corner of a cell, (a, b, c) cyclic, from
+// the four faces around the edge (upwind CT average of Gardiner & Stone 2005):
+// each face value is extrapolated to the edge with the derivative taken in the
+// upwind cell (sign of the face mass flux), and the four extrapolations are
+// averaged.  R: the cells' own EMFs (cell_emf).
 template <typename T, int A, bool L>
-__device__ __forceinline__ T edge_emf(const Work& w, const T* __restrict__ F, const T* __restrict__ W,
-                                      const Site& st) {
+__device__ __forceinline__ T edge_emf(const Work& w, const T* __restrict__ F, const T* __restrict__ R,
+                                      const Cell<T, L>& p) {
   constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
+  constexpr int bx = b == 0 ? -1 : 0, by = b == 1 ? -1 : 0, bz = b == 2 ? -1 : 0;   // one cell down along b
+  constexpr int cx = c == 0 ? -1 : 0, cy = c == 1 ? -1 : 0, cz = c == 2 ? -1 : 0;   // one cell down along c
   const long long N = w.NS;
   const T* Fb = F + (long long)b * 7 * N;
   const T* Fc = F + (long long)c * 7 * N;
-  const int ob[3] = {b == 0 ? -1 : 0, b == 1 ? -1 : 0, b == 2 ? -1 : 0};
-  const int oc[3] = {c == 0 ? -1 : 0, c == 1 ? -1 : 0, c == 2 ? -1 : 0};
-  const long long p = st.s;
-  const long long pb = snb<L>(w, st, ob[0], ob[1], ob[2]);
-  const long long pc = snb<L>(w, st, oc[0], oc[1], oc[2]);
-  const long long pbc = snb<L>(w, st, ob[0] + oc[0], ob[1] + oc[1], ob[2] + oc[2]);
-  const T eb0 = Fb[6 * N + pc], eb1 = Fb[6 * N + p];
-  const T ec0 = Fc[5 * N + pb], ec1 = Fc[5 * N + p];
-  const T mb0 = Fb[pc], mb1 = Fb[p], mc0 = Fc[pb], mc1 = Fc[p];
-  const T r00 = ref_emf(W, N, pbc, A), r10 = ref_emf(W, N, pc, A);
-  const T r01 = ref_emf(W, N, pb, A), r11 = ref_emf(W, N, p, A);
+  const T* Ra = R + (long long)A * N;
+  const T eb0 = p.template at<cx, cy, cz>(w, Fb + 6 * N), eb1 = p.here(w, Fb + 6 * N);
+  const T ec0 = p.template at<bx, by, bz>(w, Fc + 5 * N), ec1 = p.here(w, Fc + 5 * N);
+  const T mb0 = p.template at<cx, cy, cz>(w, Fb), mb1 = p.here(w, Fb);
+  const T mc0 = p.template at<bx, by, bz>(w, Fc), mc1 = p.here(w, Fc);
+  const T r00 = p.template at<bx + cx, by + cy, bz + cz>(w, Ra), r10 = p.template at<cx, cy, cz>(w, Ra);
+  const T r01 = p.template at<bx, by, bz>(w, Ra), r11 = p.here(w, Ra);
   return edge_emf_core(eb0, eb1, ec0, ec1, mb0, mb1, mc0, mc1, r00, r10, r01, r11);
 }
 
 template <typename T, bool L>
-__global__ void __launch_bounds__(kMaxBlock) k_emf(Work w, const T* __restrict__ F, const T* __restrict__ W,
+__global__ void __launch_bounds__(kMaxBlock) k_emf(Work w, const T* __restrict__ F, const T* __restrict__ R,
                                                 T* __restrict__ E) {
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
-    E[st.s] = edge_emf<T, 0, L>(w, F, W, st);
-    E[w.NS + st.s] = edge_emf<T, 1, L>(w, F, W, st);
-    E[2 * w.NS + st.s] = edge_emf<T, 2, L>(w, F, W, st);
+  FOR_CELLS(T, L, w, c) {
+    c.put(w, E, edge_emf<T, 0, L>(w, F, R, c));
+    c.put(w, E + w.NS, edge_emf<T, 1, L>(w, F, R, c));
+    c.put(w, E + 2 * w.NS, edge_emf<T, 2, L>(w, F, R, c));
   }
 }
 
 // Edge EMFs of a whole grid on LDS tiles: each block stages, for its
 // TX x TY x TZ cells and the layer below them along every direction, the
-// cells' reference EMFs -v x B (three components) and, per face direction,
+// cells' own EMFs R = -v x B (three components) and, per face direction,
 // the face's mass flux and its two EMF components (twelve values per cell,
 // each loaded once per tile instead of once per edge that uses it), then
 // computes the three lower-corner edges of each of its cells from LDS with
 // the arithmetic of k_emf.  Grids need not be multiples of the tile (cells
 // past the grid idle; the staged layer wraps periodically).
 template <typename T, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __restrict__ F, const T* __restrict__ W,
+__global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __restrict__ F, const T* __restrict__ R,
                                                          T* __restrict__ E) {
   constexpr int HX = TX + 1, HY = TY + 1, HZ = TZ + 1, NH = HX * HY * HZ, NT = TX * TY * TZ;
   __shared__ T sR[3][NH];
@@ -507,7 +701,7 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __r
     const int hx = h % HX, hy = (h / HX) % HY, hz = h / (HX * HY);
     const long long q = lin(w, wrapc(tx0 - 1 + hx, w.nx), wrapc(ty0 - 1 + hy, w.ny), wrapc(tz0 - 1 + hz, w.nz));
 #pragma unroll
-    for (int a = 0; a < 3; ++a) sR[a][h] = ref_emf(W, N, q, a);
+    for (int a = 0; a < 3; ++a) sR[a][h] = R[(long long)a * N + q];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       sF[d][0][h] = F[(long long)(7 * d) * N + q];
@@ -534,84 +728,89 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __r
 }
 
 // ------------------------------------------------------------ updates
-// U - r div F (Eq. 10), differences applied in the order x, y, z.  In the
-// mixed form the energy is updated in double from E64 (returned in e64).
-template <typename T, bool MIX, bool L>
-__device__ __forceinline__ void cell_update(const Work& w, const T* __restrict__ U, const T* __restrict__ F,
-                                            const Mix& mix, const Site& st, T r, T out[5], double& e64) {
+// U - r div F (Eq. 10), differences applied in the order x, y, z, for the first
+// NM components.  In the mixed form the energy is updated in double from E64
+// (returned in e64).
+template <typename T, bool MIX, bool L, int NM = 5>
+__device__ __forceinline__ void cell_update(const Work& w, const T* U, const T* __restrict__ F, const Mix& mix,
+                                            const Cell<T, L>& c, T r, T out[5], double& e64) {
   const long long N = w.N, NS = w.NS;
-  const long long p = st.p, s = st.s;
-  const long long px = snb<L>(w, st, 1, 0, 0), py = snb<L>(w, st, 0, 1, 0), pz = snb<L>(w, st, 0, 0, 1);
   const T* Fx = F;
   const T* Fy = F + 7 * NS;
   const T* Fz = F + 14 * NS;
 #pragma unroll
-  for (int m = 0; m < 5; ++m) {
+  for (int m = 0; m < NM; ++m) {
+    const T xu = c.template along<0, 1>(w, Fx + m * NS), xl = c.here(w, Fx + m * NS);
+    const T yu = c.template along<1, 1>(w, Fy + m * NS), yl = c.here(w, Fy + m * NS);
+    const T zu = c.template along<2, 1>(w, Fz + m * NS), zl = c.here(w, Fz + m * NS);
     if (MIX && m == 4) {
       const double rd = (double)r;
-      double v = mix.E64[p];
-      v -= rd * ((double)Fx[4 * NS + px] - (double)Fx[4 * NS + s]);
-      v -= rd * ((double)Fy[4 * NS + py] - (double)Fy[4 * NS + s]);
-      v -= rd * ((double)Fz[4 * NS + pz] - (double)Fz[4 * NS + s]);
+      double v = mix.E64[c.index(w)];
+      v -= rd * ((double)xu - (double)xl);
+      v -= rd * ((double)yu - (double)yl);
+      v -= rd * ((double)zu - (double)zl);
       e64 = v;
       out[4] = T(v);
       continue;
     }
-    T v = U[m * N + p];
-    v -= r * (Fx[m * NS + px] - Fx[m * NS + s]);
-    v -= r * (Fy[m * NS + py] - Fy[m * NS + s]);
-    v -= r * (Fz[m * NS + pz] - Fz[m * NS + s]);
+    T v = c.template level<0, 0>(w, U + m * N);
+    v -= r * (xu - xl);
+    v -= r * (yu - yl);
+    v -= r * (zu - zl);
     out[m] = v;
   }
-  if (!MIX) e64 = (double)out[4];
+  if (!MIX && NM == 5) e64 = (double)out[4];
 }
 
-// CT update of the three lower faces of cell (i, j, k) (Eq. 13)
-template <typename T, bool L>
-__device__ __forceinline__ void face_update(const Work& w, const T* __restrict__ B, const T* __restrict__ E,
-                                            const Site& st, T r, T out[3]) {
-  const long long N = w.N, NS = w.NS;
-  const long long p = st.p, s = st.s;
-  const long long px = snb<L>(w, st, 1, 0, 0), py = snb<L>(w, st, 0, 1, 0), pz = snb<L>(w, st, 0, 0, 1);
-  const T* Ex = E;
-  const T* Ey = E + NS;
-  const T* Ez = E + 2 * NS;
-  out[0] = B[p] - r * (Ez[py] - Ez[s]) + r * (Ey[pz] - Ey[s]);
-  out[1] = B[N + p] - r * (Ex[pz] - Ex[s]) + r * (Ez[px] - Ez[s]);
-  out[2] = B[2 * N + p] - r * (Ey[px] - Ey[s]) + r * (Ex[py] - Ex[s]);
+// CT update (Eq. 13) of the lower A-face of the cell (n = 0) or of the next
+// cell along A (n = 1)
+template <typename T, int A, int n, bool L>
+__device__ __forceinline__ T face_update(const Work& w, const T* B, const T* __restrict__ E, const Cell<T, L>& p, T r) {
+  constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
+  constexpr int X = A == 0 ? n : 0, Y = A == 1 ? n : 0, Z = A == 2 ? n : 0;
+  const T* Eb = E + (long long)b * w.NS;
+  const T* Ec = E + (long long)c * w.NS;
+  const T cu = p.template at<X + (b == 0), Y + (b == 1), Z + (b == 2)>(w, Ec), cl = p.template at<X, Y, Z>(w, Ec);
+  const T bu = p.template at<X + (c == 0), Y + (c == 1), Z + (c == 2)>(w, Eb), bl = p.template at<X, Y, Z>(w, Eb);
+  return p.template level<A, n>(w, B + A * w.N) - r * (cu - cl) + r * (bu - bl);
 }
 
 // Half step over dt/2: U^{n+1/2} and face B^{n+1/2} from the predictor fluxes
-// and EMFs, written as primitives Wh (cell-centred field from the updated
-// faces, including the upper faces owned by the neighbours) and Bh.
-template <typename T, bool MIX, bool L>
+// and EMFs (cell-centred field from the updated faces, including the upper
+// faces owned by the neighbours).  Writes Bh and, for VL, the primitives Wh;
+// CTU's later stages need of the half-step cell state only its EMF (step 7),
+// so there the energy is left out and three words R = -v x B replace Wh's
+// eight.
+template <typename T, bool MIX, bool CTU, bool L>
 __global__ void __launch_bounds__(kMaxBlock) k_half(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
                                                  const T* __restrict__ F, const T* __restrict__ E, DtSrc dts,
                                                  T inv_dx, T gam, T* __restrict__ Wh, T* __restrict__ Bh) {
   const T r = T(0.5 * get_dt(dts)) * inv_dx;
-  FOR_ITEMS(w, t) {
-  const Site st = site_of<L>(w, t);
-  T u[5], bl[3], bux[3], buy[3], buz[3];
-  double eh;
-  cell_update<T, MIX, L>(w, U, F, mix, st, r, u, eh);
-  face_update<T, L>(w, B, E, st, r, bl);
-  face_update<T, L>(w, B, E, site_nb<L>(w, st, 1, 0, 0), r, bux);
-  face_update<T, L>(w, B, E, site_nb<L>(w, st, 0, 1, 0), r, buy);
-  face_update<T, L>(w, B, E, site_nb<L>(w, st, 0, 0, 1), r, buz);
-  const T bx = T(0.5) * (bl[0] + bux[0]);
-  const T by = T(0.5) * (bl[1] + buy[1]);
-  const T bz = T(0.5) * (bl[2] + buz[2]);
-  const T d = u[0];
-  const T id = T(1) / d;
-  const T vx = u[1] * id, vy = u[2] * id, vz = u[3] * id;
-  T pr;
-  if (MIX) pr = recover_pressure<T, true>(eh, d, vx, vy, vz, bx, by, bz, gam, mix.beta);
-  else pr = (gam - T(1)) * (u[4] - T(0.5) * d * (vx * vx + vy * vy + vz * vz) - T(0.5) * (bx * bx + by * by + bz * bz));
-  const long long N = w.NS;
-  const long long p = st.s;
-  Wh[p] = d; Wh[N + p] = vx; Wh[2 * N + p] = vy; Wh[3 * N + p] = vz; Wh[4 * N + p] = pr;
-  Wh[5 * N + p] = bx; Wh[6 * N + p] = by; Wh[7 * N + p] = bz;
-  Bh[p] = bl[0]; Bh[N + p] = bl[1]; Bh[2 * N + p] = bl[2];
+  FOR_CELLS(T, L, w, c) {
+    T u[5];
+    double eh = 0.0;
+    cell_update<T, MIX, L, CTU ? 4 : 5>(w, U, F, mix, c, r, u, eh);
+    const T bl[3] = {face_update<T, 0, 0, L>(w, B, E, c, r), face_update<T, 1, 0, L>(w, B, E, c, r),
+                     face_update<T, 2, 0, L>(w, B, E, c, r)};
+    const T bu[3] = {face_update<T, 0, 1, L>(w, B, E, c, r), face_update<T, 1, 1, L>(w, B, E, c, r),
+                     face_update<T, 2, 1, L>(w, B, E, c, r)};
+    T q[8];
+    if constexpr (CTU) {
+      const T id = T(1) / u[0];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        q[1 + m] = u[1 + m] * id;
+        q[5 + m] = T(0.5) * (bl[m] + bu[m]);
+      }
+#pragma unroll
+      for (int m = 0; m < 3; ++m) c.put(w, Wh + m * w.NS, cell_emf(q, m));
+    } else {
+      prims_from<T, MIX>(u[0], u[1], u[2], u[3], u[4], eh, bl, bu, gam, mix.beta, q);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) c.put(w, Wh + m * w.NS, q[m]);
+    }
+#pragma unroll
+    for (int m = 0; m < 3; ++m) c.put(w, Bh + m * w.NS, bl[m]);
   }
 }
 
@@ -628,35 +827,41 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
                                                   T inv_dx) {
   const T r = T(get_dt(dts)) * inv_dx;
   const long long N = w.N;
-  FOR_ITEMS(w, t) {
-  const Site st = site_of<L>(w, t);
-  const int i = st.i, j = st.j, k = st.k, a = st.a, b = st.b, c = st.c;
-  T u[5], bf[3];
-  double e64;
-  cell_update<T, MIX, L>(w, U, F, mix, st, r, u, e64);
-  face_update<T, L>(w, B, E, st, r, bf);
-  T ux[3], uy[3], uz[3];
-  bool ex = false, ey = false, ez = false;
-  if constexpr (L) {
-    const int gi = i / w.edge, gj = j / w.edge, gk = k / w.edge;
-    auto listed = [&](int x, int y, int z) {
-      return w.occ[((long long)wrapc(z, w.gnz) * w.gny + wrapc(y, w.gny)) * w.gnx + wrapc(x, w.gnx)] != 0;
-    };
-    ex = a == w.edge - 1 && !listed(gi + 1, gj, gk);
-    ey = b == w.edge - 1 && !listed(gi, gj + 1, gk);
-    ez = c == w.edge - 1 && !listed(gi, gj, gk + 1);
-  }
-  if (ex) face_update<T, L>(w, B, E, site_nb<L>(w, st, 1, 0, 0), r, ux);
-  if (ey) face_update<T, L>(w, B, E, site_nb<L>(w, st, 0, 1, 0), r, uy);
-  if (ez) face_update<T, L>(w, B, E, site_nb<L>(w, st, 0, 0, 1), r, uz);
-  const long long p = st.p;
+  FOR_CELLS(T, L, w, c) {
+    T u[5], bf[3];
+    double e64;
+    cell_update<T, MIX, L>(w, U, F, mix, c, r, u, e64);
+    bf[0] = face_update<T, 0, 0, L>(w, B, E, c, r);
+    bf[1] = face_update<T, 1, 0, L>(w, B, E, c, r);
+    bf[2] = face_update<T, 2, 0, L>(w, B, E, c, r);
+    T ux = T(0), uy = T(0), uz = T(0);
+    bool ex = false, ey = false, ez = false;
+    if constexpr (L) {
+      // the group's place in the occupancy map: its boundary cells look at the next one
+      const auto listed = [&](int x, int y, int z) {
+        return w.occ[((long long)wrapc(z, w.gnz) * w.gny + wrapc(y, w.gny)) * w.gnx + wrapc(x, w.gnx)] != 0;
+      };
+      const bool lx = c.a == w.edge - 1, ly = c.b == w.edge - 1, lz = c.c == w.edge - 1;
+      if (lx || ly || lz) {
+        const int gi = c.i / w.edge, gj = c.j / w.edge, gk = c.k / w.edge;
+        ex = lx && !listed(gi + 1, gj, gk);
+        ey = ly && !listed(gi, gj + 1, gk);
+        ez = lz && !listed(gi, gj, gk + 1);
+        if (ex) ux = face_update<T, 0, 1, L>(w, B, E, c, r);
+        if (ey) uy = face_update<T, 1, 1, L>(w, B, E, c, r);
+        if (ez) uz = face_update<T, 2, 1, L>(w, B, E, c, r);
+      }
+    }
 #pragma unroll
-  for (int m = 0; m < 5; ++m) U[m * N + p] = u[m];
-  if (MIX) mix.E64[p] = e64;
-  B[p] = bf[0]; B[N + p] = bf[1]; B[2 * N + p] = bf[2];
-  if (ex) B[nbr(w, i, j, k, 1, 0, 0)] = ux[0];
-  if (ey) B[N + nbr(w, i, j, k, 0, 1, 0)] = uy[1];
-  if (ez) B[2 * N + nbr(w, i, j, k, 0, 0, 1)] = uz[2];
+    for (int m = 0; m < 5; ++m) c.template put_level<0, 0>(w, U + m * N, u[m]);
+    if (MIX) mix.E64[c.index(w)] = e64;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) c.template put_level<0, 0>(w, B + m * N, bf[m]);
+    if constexpr (L) {
+      if (ex) c.template put_level<0, 1>(w, B, ux);
+      if (ey) c.template put_level<1, 1>(w, B + N, uy);
+      if (ez) c.template put_level<2, 1>(w, B + 2 * N, uz);
+    }
   }
 }
 
@@ -667,23 +872,24 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
 // cell p - e_d; written by that cell as its upper-edge state).
 template <typename T, int D, int RECON, bool ALLW, bool L>
 __device__ __forceinline__ void cell_states(const Work& w, const T* __restrict__ W, const T* __restrict__ B,
-                                            T* __restrict__ QL, T* __restrict__ QR, const Site& st, T dtdx,
+                                            T* __restrict__ QL, T* __restrict__ QR, const Cell<T, L>& c, T dtdx,
                                             T gam) {
   const long long N = w.N, NS = w.NS;
   T q[5][7];
-#pragma unroll
-  for (int s = -2; s <= 2; ++s) {
-    const long long c = snb<L>(w, st, D == 0 ? s : 0, D == 1 ? s : 0, D == 2 ? s : 0);
-    load_w1d<T, D>(W, NS, c, q[s + 2]);
+  if (RECON == 1) {
+    load_frame<T, D, -2, L>(w, W, c, q[0]);
+    load_frame<T, D, 2, L>(w, W, c, q[4]);
   }
-  const long long pu = nbr(w, st.i, st.j, st.k, D == 0 ? 1 : 0, D == 1 ? 1 : 0, D == 2 ? 1 : 0);
-  const long long su = snb<L>(w, st, D == 0 ? 1 : 0, D == 1 ? 1 : 0, D == 2 ? 1 : 0);
+  load_frame<T, D, -1, L>(w, W, c, q[1]);
+  load_frame<T, D, 0, L>(w, W, c, q[2]);
+  load_frame<T, D, 1, L>(w, W, c, q[3]);
   T sl[7], sr[7];
-  trace_cell<T, RECON, ALLW>(q, B[D * N + st.p], B[D * N + pu], dtdx, gam, sl, sr);
+  trace_cell<T, RECON, ALLW>(q, c.template level<D, 0>(w, B + D * N), c.template level<D, 1>(w, B + D * N), dtdx, gam,
+                             sl, sr);
 #pragma unroll
   for (int m = 0; m < 7; ++m) {
-    QR[((long long)D * 7 + m) * NS + st.s] = sl[m];
-    QL[((long long)D * 7 + m) * NS + su] = sr[m];
+    c.put(w, QR + ((long long)D * 7 + m) * NS, sl[m]);
+    c.template put_along<D, 1>(w, QL + ((long long)D * 7 + m) * NS, sr[m]);
   }
 }
 
@@ -693,11 +899,10 @@ __global__ void __launch_bounds__(kMaxBlock) k_ctu_states(Work w, const T* __res
                                                        T* __restrict__ QL, T* __restrict__ QR, DtSrc dts,
                                                        T inv_dx, T gam) {
   const T dtdx = T(get_dt(dts)) * inv_dx;
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
-    cell_states<T, 0, RECON, ALLW, L>(w, W, B, QL, QR, st, dtdx, gam);
-    cell_states<T, 1, RECON, ALLW, L>(w, W, B, QL, QR, st, dtdx, gam);
-    cell_states<T, 2, RECON, ALLW, L>(w, W, B, QL, QR, st, dtdx, gam);
+  FOR_CELLS(T, L, w, c) {
+    cell_states<T, 0, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
+    cell_states<T, 1, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
+    cell_states<T, 2, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
   }
 }
 
@@ -942,17 +1147,30 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_ctu_states_tiled(Work w, const
   }
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void store_flux(T* __restrict__ F, long long N, long long p, const T f[7]) {
-  constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  T* Fd = F + (long long)D * 7 * N;
-  Fd[p] = f[0];
-  Fd[(1 + n) * N + p] = f[1];
-  Fd[(1 + t1) * N + p] = f[2];
-  Fd[(1 + t2) * N + p] = f[3];
-  Fd[4 * N + p] = f[4];
-  Fd[5 * N + p] = f[6];
-  Fd[6 * N + p] = -f[5];
+// the two states of the cell's lower D-face
+template <typename T, int D, bool L>
+__device__ __forceinline__ void load_states(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
+                                            const Cell<T, L>& c, T wl[7], T wr[7]) {
+#pragma unroll
+  for (int m = 0; m < 7; ++m) {
+    wl[m] = c.here(w, QL + ((long long)D * 7 + m) * w.NS);
+    wr[m] = c.here(w, QR + ((long long)D * 7 + m) * w.NS);
+  }
+}
+
+template <typename T, int D, int SOLVER, bool L>
+__device__ __forceinline__ int traced_face_flux(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
+                                                const T* __restrict__ B, T* __restrict__ F, const Cell<T, L>& c, T gam,
+                                                const Capture& cp) {
+  T wl[7], wr[7], f[7];
+  load_states<T, D, L>(w, QL, QR, c, wl, wr);
+  const T bn = c.template level<D, 0>(w, B + D * w.N);
+  const int fb = riemann<SOLVER>(wl, wr, bn, gam, f);
+  if constexpr (sizeof(T) == 4) {
+    if (cp.buf) capture_face(cp, 3 * c.index(w) + D, wl, wr, bn, f);
+  }
+  store_flux<T, D, L>(w, F, c, f);
+  return fb;
 }
 
 // Step 2: Riemann fluxes from the stored states with the time-n normal field
@@ -961,30 +1179,16 @@ __global__ void __launch_bounds__(kMaxBlock) k_flux_q(Work w, const T* __restric
                                                    const T* __restrict__ B, T* __restrict__ F, T gam,
                                                    unsigned long long* nfb, Capture cp) {
   int fb = 0;
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
-    const long long N = w.N, NS = w.NS;
-    const long long p = st.p, s = st.s;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T wl[7], wr[7], f[7];
-#pragma unroll
-      for (int m = 0; m < 7; ++m) {
-        wl[m] = QL[((long long)d * 7 + m) * NS + s];
-        wr[m] = QR[((long long)d * 7 + m) * NS + s];
-      }
-      fb += riemann<SOLVER>(wl, wr, B[d * N + p], gam, f);
-      if constexpr (sizeof(T) == 4) capture_face(cp, 3 * p + d, wl, wr, B[d * N + p], f);
-      if (d == 0) store_flux<T, 0>(F, NS, s, f);
-      else if (d == 1) store_flux<T, 1>(F, NS, s, f);
-      else store_flux<T, 2>(F, NS, s, f);
-    }
+  FOR_CELLS(T, L, w, c) {
+    fb += traced_face_flux<T, 0, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
+    fb += traced_face_flux<T, 1, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
+    fb += traced_face_flux<T, 2, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
   }
   if (SOLVER == 0) block_count_atomic(fb, nfb);
 }
 
 // Step 5: transverse correction of a state of direction D that comes from
-// cell (ci, cj, ck) and sits on a face with normal field bn at time n and bnh
+// the cell n along D (-1 or 0) and sits on a face with normal field bn at time n and bnh
 // after the half step.  Hydro variables: minus dt/2 times the transverse flux
 // differences of step 2 in that cell.  Transverse field: dt/2 times the
 // transverse part of -curl E with the step-3 edge EMFs E_D averaged to the
@@ -995,11 +1199,12 @@ __global__ void __launch_bounds__(kMaxBlock) k_flux_q(Work w, const T* __restric
 // energy get (dt/2)(B, v.B) dBn/dn with dbn the source cell's normal-field
 // difference (the field's share is in the traced state).  Non-physical
 // results keep the input.
-template <typename T, int D, bool L>
+template <typename T, int D, int n, bool L>
 __device__ __forceinline__ void correct_state(const Work& w, const T* __restrict__ F1, const T* __restrict__ E1,
-                                              const Site& src, T bn, T bnh, T dbn, T hr, T gam, const T s[7],
+                                              const Cell<T, L>& c, T bn, T bnh, T dbn, T hr, T gam, const T s[7],
                                               T out[7]) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  constexpr int X = D == 0 ? n : 0, Y = D == 1 ? n : 0, Z = D == 2 ? n : 0;   // the source cell
   const long long N = w.NS;
   T v[3], b[3];
   v[D] = s[1]; v[t1] = s[2]; v[t2] = s[3];
@@ -1015,28 +1220,26 @@ __device__ __forceinline__ void correct_state(const Work& w, const T* __restrict
 #pragma unroll
   for (int a = 0; a < 3; ++a) u[1 + a] += hr * dbn * b[a];
   u[4] += hr * dbn * vb;
-  const long long c = src.s;
-#pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int t = tt ? t2 : t1;
-    const long long cp = snb<L>(w, src, t == 0, t == 1, t == 2);
+  // transverse flux differences across the source cell
+  const auto fluxes = [&](auto dir) {
+    constexpr int t = decltype(dir)::value;
     const T* Ft = F1 + (long long)t * 7 * N;
 #pragma unroll
-    for (int m = 0; m < 5; ++m) u[m] -= hr * (Ft[m * N + cp] - Ft[m * N + c]);
-  }
+    for (int m = 0; m < 5; ++m)
+      u[m] -= hr * (c.template at<X + (t == 0), Y + (t == 1), Z + (t == 2)>(w, Ft + m * N) -
+                    c.template at<X, Y, Z>(w, Ft + m * N));
+  };
+  fluxes(std::integral_constant<int, t1>{});
+  fluxes(std::integral_constant<int, t2>{});
+  // the transverse field: E_D at the four D-edges of the source cell, averaged
+  // along the field's own axis to the two faces it is differenced between
   const T* Ed = E1 + (long long)D * N;
-#pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int bax = tt ? t2 : t1;
-    const int der = (bax == (D + 2) % 3) ? (D + 1) % 3 : (D + 2) % 3;
-    const long long e_der = snb<L>(w, src, der == 0, der == 1, der == 2);
-    const long long e_b = snb<L>(w, src, bax == 0, bax == 1, bax == 2);
-    const long long e_db = snb<L>(w, src, (der == 0) + (bax == 0), (der == 1) + (bax == 1), (der == 2) + (bax == 2));
-    const T up = T(0.5) * (Ed[e_der] + Ed[e_db]);
-    const T lo = T(0.5) * (Ed[c] + Ed[e_b]);
-    const T sign = (D == (bax + 1) % 3) ? T(1) : T(-1);
-    b[bax] += hr * sign * (up - lo);
-  }
+  const T e00 = c.template at<X, Y, Z>(w, Ed);
+  const T e10 = c.template at<X + (t1 == 0), Y + (t1 == 1), Z + (t1 == 2)>(w, Ed);
+  const T e01 = c.template at<X + (t2 == 0), Y + (t2 == 1), Z + (t2 == 2)>(w, Ed);
+  const T e11 = c.template at<X + (t1 == 0) + (t2 == 0), Y + (t1 == 1) + (t2 == 1), Z + (t1 == 2) + (t2 == 2)>(w, Ed);
+  b[t1] += hr * T(-1) * (T(0.5) * (e01 + e11) - T(0.5) * (e00 + e10));
+  b[t2] += hr * (T(0.5) * (e10 + e11) - T(0.5) * (e00 + e01));
   b[D] = bnh;
   const T id = T(1) / u[0];
   const T vx = u[1] * id, vy = u[2] * id, vz = u[3] * id;
@@ -1054,36 +1257,32 @@ __device__ __forceinline__ void correct_state(const Work& w, const T* __restrict
 template <typename T, int D, bool L>
 __device__ __forceinline__ void corrected_states(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
                                                  const T* __restrict__ F1, const T* __restrict__ E1,
-                                                 const T* __restrict__ B, T bnh, const Site& st, T hr, T gam,
+                                                 const T* __restrict__ B, T bnh, const Cell<T, L>& c, T hr, T gam,
                                                  T wl[7], T wr[7]) {
-  const long long NS = w.NS;
   T sl[7], sr[7];
-#pragma unroll
-  for (int m = 0; m < 7; ++m) {
-    sl[m] = QL[((long long)D * 7 + m) * NS + st.s];
-    sr[m] = QR[((long long)D * 7 + m) * NS + st.s];
-  }
-  const T bn = B[D * w.N + st.p];
-  const T bn_lo = B[D * w.N + nbr(w, st.i, st.j, st.k, -(D == 0), -(D == 1), -(D == 2))];
-  const T bn_hi = B[D * w.N + nbr(w, st.i, st.j, st.k, D == 0, D == 1, D == 2)];
-  correct_state<T, D, L>(w, F1, E1, site_nb<L>(w, st, -(D == 0), -(D == 1), -(D == 2)), bn, bnh, bn - bn_lo, hr,
-                         gam, sl, wl);
-  correct_state<T, D, L>(w, F1, E1, st, bn, bnh, bn_hi - bn, hr, gam, sr, wr);
+  load_states<T, D, L>(w, QL, QR, c, sl, sr);
+  const T* Bd = B + D * w.N;
+  const T bn = c.template level<D, 0>(w, Bd);
+  const T bn_lo = c.template level<D, -1>(w, Bd);
+  const T bn_hi = c.template level<D, 1>(w, Bd);
+  correct_state<T, D, -1, L>(w, F1, E1, c, bn, bnh, bn - bn_lo, hr, gam, sl, wl);
+  correct_state<T, D, 0, L>(w, F1, E1, c, bn, bnh, bn_hi - bn, hr, gam, sr, wr);
 }
 
 template <typename T, int D, int SOLVER, bool L>
 __device__ __forceinline__ int corrected_face_flux(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
                                                    const T* __restrict__ F1, const T* __restrict__ E1,
                                                    const T* __restrict__ B, const T* __restrict__ Bh,
-                                                   T* __restrict__ F2, const Site& st, T hr, T gam,
+                                                   T* __restrict__ F2, const Cell<T, L>& c, T hr, T gam,
                                                    const Capture& cp) {
-  const long long NS = w.NS;
   T wl[7], wr[7], f[7];
-  const T bn = Bh[D * NS + st.s];
-  corrected_states<T, D, L>(w, QL, QR, F1, E1, B, bn, st, hr, gam, wl, wr);
+  const T bn = c.here(w, Bh + D * w.NS);
+  corrected_states<T, D, L>(w, QL, QR, F1, E1, B, bn, c, hr, gam, wl, wr);
   const int fb = riemann<SOLVER>(wl, wr, bn, gam, f);
-  if constexpr (sizeof(T) == 4) capture_face(cp, 3 * st.p + D, wl, wr, bn, f);
-  store_flux<T, D>(F2, NS, st.s, f);
+  if constexpr (sizeof(T) == 4) {
+    if (cp.buf) capture_face(cp, 3 * c.index(w) + D, wl, wr, bn, f);
+  }
+  store_flux<T, D, L>(w, F2, c, f);
   return fb;
 }
 
@@ -1096,53 +1295,44 @@ __global__ void __launch_bounds__(kMaxBlock) k_ctu_correct(Work w, const T* __re
                                                         unsigned long long* nfb, Capture cp) {
   int fb = 0;
   const T hr = T(0.5 * get_dt(dts)) * inv_dx;
-  FOR_ITEMS(w, t) {
-    const Site st = site_of<L>(w, t);
-    fb += corrected_face_flux<T, 0, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, st, hr, gam, cp);
-    fb += corrected_face_flux<T, 1, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, st, hr, gam, cp);
-    fb += corrected_face_flux<T, 2, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, st, hr, gam, cp);
+  FOR_CELLS(T, L, w, c) {
+    fb += corrected_face_flux<T, 0, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
+    fb += corrected_face_flux<T, 1, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
+    fb += corrected_face_flux<T, 2, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
   }
   if (SOLVER == 0) block_count_atomic(fb, nfb);
 }
 
 // Learned flux (HLLD at strong jumps) of the D-faces in step 2 from the
-// traced states QLd[m * NS + s], QRd[m * NS + s] (m = 0..6) and the level's
-// time-n normal field B[D * N + p].  With capture on, the face's states and
+// traced states and the level's time-n normal field B.  With capture on, the face's states and
 // the flux it used are recorded.  Held to 128 VGPRs (four waves per SIMD,
 // a few spilled words): the network's dependent MFMA and transcendental
 // chains need the extra waves to hide their latency (12 % faster than
 // three waves at 135 VGPRs without spills).
 template <int D, bool L>
-__global__ void __launch_bounds__(kBlock, 4) k_flux_dir_mlp(Work w, const float* __restrict__ QLd,
-                                                         const float* __restrict__ QRd, const float* __restrict__ Bn,
+__global__ void __launch_bounds__(kBlock, 4) k_flux_dir_mlp(Work w, const float* __restrict__ QL,
+                                                         const float* __restrict__ QR, const float* __restrict__ B,
                                                          float* __restrict__ F, float gam, const MlpWeights* mw,
                                                          float dp, float drho, unsigned long long* nfb,
                                                          Capture cp) {
   __shared__ MlpShared sh;
   mlp_load_weights(sh, mw);
-  const long long N = w.N, NS = w.NS;
-  const long long nitems = work_items(w);
   int fb = 0;
   // block-uniform trips: every lane of a wave takes part in the network
-  for (long long base = block_linear_id() - threadIdx.x; base < nitems; base += item_stride()) {
-    const long long t = base + threadIdx.x;
-    const bool active = t < nitems;
-    long long p = 0, s = 0;
-    if (active) {
-      const Site st = site_of<L>(w, t);
-      p = st.p;
-      s = st.s;
-    }
+  FOR_CHUNKS(float, L, w, c) {
     float wl[7], wr[7], f[7];
     float bn = 1.0f;
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
-      wl[m] = active ? QLd[(long long)m * NS + s] : 1.0f;
-      wr[m] = active ? QRd[(long long)m * NS + s] : 1.0f;
+      wl[m] = 1.0f;
+      wr[m] = 1.0f;
     }
-    if (active) bn = Bn[D * N + p];
-    fb += mlp_or_hlld(sh, active, wl, wr, bn, gam, dp, drho, f, cp, 3 * p + D);
-    if (active) store_flux<float, D>(F, NS, s, f);
+    if (c.on) {
+      load_states<float, D, L>(w, QL, QR, c, wl, wr);
+      bn = c.template level<D, 0>(w, B + D * w.N);
+    }
+    fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
+    if (c.on) store_flux<float, D, L>(w, F, c, f);
   }
   block_count_atomic(fb, nfb);
 }
@@ -1160,14 +1350,9 @@ __global__ void __launch_bounds__(kBlock) k_ctu_correct_mlp(Work w, const float*
   __shared__ MlpShared sh;
   mlp_load_weights(sh, mw);
   const float hr = float(0.5 * get_dt(dts)) * inv_dx;
-  const long long NS = w.NS;
-  const long long nitems = work_items(w);
   int fb = 0;
   // block-uniform trips: every lane of a wave takes part in the network
-  for (long long base = block_linear_id() - threadIdx.x; base < nitems; base += item_stride()) {
-    const long long t = base + threadIdx.x;
-    const bool active = t < nitems;
-    long long p = 0, s = 0;
+  FOR_CHUNKS(float, L, w, c) {
     float wl[7], wr[7], f[7];
     float bn = 1.0f;
 #pragma unroll
@@ -1175,15 +1360,12 @@ __global__ void __launch_bounds__(kBlock) k_ctu_correct_mlp(Work w, const float*
       wl[m] = 1.0f;
       wr[m] = 1.0f;
     }
-    if (active) {
-      const Site st = site_of<L>(w, t);
-      p = st.p;
-      s = st.s;
-      bn = Bh[D * NS + s];
-      corrected_states<float, D, L>(w, QL, QR, F1, E1, B, bn, st, hr, gam, wl, wr);
+    if (c.on) {
+      bn = c.here(w, Bh + D * w.NS);
+      corrected_states<float, D, L>(w, QL, QR, F1, E1, B, bn, c, hr, gam, wl, wr);
     }
-    fb += mlp_or_hlld(sh, active, wl, wr, bn, gam, dp, drho, f, cp, 3 * p + D);
-    if (active) store_flux<float, D>(F2, NS, s, f);
+    fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
+    if (c.on) store_flux<float, D, L>(w, F2, c, f);
   }
   block_count_atomic(fb, nfb);
 }
