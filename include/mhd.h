@@ -104,14 +104,15 @@ typedef struct {
  * a listed group that must hold valid ghost data (mhd_prolong fills them). */
 int mhd_required_ghost(int scheme, int recon);
 
-/* Device bytes the context's stage scratch takes to update lv (in
- * *bytes): W, Bh, F, E (35 words per scratch cell; CTU adds QL, QR, F2: 98;
- * the learned flux needs no more) times the scratch cells (the level's cells,
- * or (groups + 2) boxes of (edge + 2 ghost)^3 cells for a group list), plus
- * the group occupancy map.  The context allocates this on the first update
- * of a level that needs more than it holds; the time-mean registers of
- * mhd_accumulate_registers (24 words per scratch cell) come on top.  No
- * HIP call. */
+/* Device bytes of stage scratch (in *bytes) that an update of lv is budgeted
+ * at: 35 words per scratch cell (W, Bh, F, E), 98 with CTU, times the scratch
+ * cells (the level's cells, or (groups + 2) boxes of (edge + 2 ghost)^3 cells
+ * for a group list), plus the group occupancy map.  An upper bound: the
+ * learned flux takes the 98 words, the other CTU forms 59.  mhd_step_noalloc
+ * accepts a level by this figure.  The context allocates its scratch on the
+ * first update of a level that needs more than it holds; the time-mean
+ * registers of mhd_accumulate_registers (24 words per scratch cell) come on
+ * top.  No HIP call. */
 int mhd_workspace_bytes(mhd_ctx ctx, const mhd_level* lv, size_t* bytes);
 
 /* Validate cfg and create a context bound to hip_stream (a hipStream_t, or
@@ -184,19 +185,10 @@ int mhd_advance_graph(mhd_ctx ctx, const mhd_level* lv, double* dt_dev, double* 
  *                      so its intermediates can stay in the caches (paper
  *                      Sec. 4 sends patch groups to the GPU in batches);
  *                      0 = the whole list in one launch per stage.
- *   lds_tiles          CTU with PPM, step 1 (reconstruction and characteristic
- *                      tracing): 0 = one thread per cell, each computing its
- *                      own stencil's MC slopes and PPM interface values;
- *                      1 = blocks of 16 x 4 x 4 cells (20 x 5 x 5 on the item
- *                      boxes of 16^3 groups; other group sizes keep the
- *                      per-cell form) that stage their primitives with two
- *                      ghost layers per direction in LDS and compute each
- *                      slope and interface value once (fewer VALU
- *                      instructions, but block barriers between the stages);
- *                      other configurations ignore it.  The same arithmetic
- *                      compiled in another code layout: results agree with
- *                      the per-cell form to rounding, not bit for bit.
- * For a given lds_tiles, every shape gives bit-identical results.  Drops any
+ *   lds_tiles          0 or 1; kept for callers that set it.  It chose between
+ *                      two kernels of CTU's reconstruction; one kernel has
+ *                      replaced both and the value changes nothing.
+ * Every shape gives bit-identical results.  Drops any
  * captured graph.  The reduction kernels of mhd_divB and mhd_sums and the
  * AMR transfer kernels keep their fixed shape. */
 int mhd_set_launch(mhd_ctx ctx, int blocks_per_cu, int threads_per_block, int batch_groups, int lds_tiles);

@@ -23,6 +23,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          # scaling, 8-10 % fewer VALU instructions in the flux stages; no
          # float value of the update comes near 1e-38
          "-fgpu-flush-denormals-to-zero",
+         # multiply-adds are fused inside an expression only: the same source
+         # then rounds the same way in every kernel it is inlined into, so a
+         # group list that covers a grid gives the whole grid's bits although
+         # the two forms keep different values in registers (the default also
+         # fuses across statements where a product has one use; same speed)
+         "-ffp-contract=on",
          "-Wno-unused-result", "-Wno-unused-value",
          "-I" + os.path.join(ROOT, "include")]
 SOURCES = ["mhd_api.hip"]

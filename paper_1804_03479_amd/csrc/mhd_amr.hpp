@@ -2,7 +2,7 @@
 // levels, ghost halos, optionally interpolated in time), restriction, the
 // correction operation across coarse-fine interfaces, time-mean registers of
 // sub-cycled levels, and regridding by the refinement criterion.  Included
-// after mhd_kernels.hpp, whose addressing (Work, Site, lin, wrapc, nbr,
+// after mhd_kernels.hpp, whose addressing (Work, lin, wrapc, nbr,
 // FOR_ITEMS) and slope limiter it uses.
 #pragma once
 

@@ -3,12 +3,12 @@
 //
 // Step sequence of the VL (MUSCL-Hancock) integrator, paper Sec. 3.2,
 // VL steps 1-7, one kernel per stage:
-//   k_prim   U^n, B^n            -> W^n (and the CFL maximum for mhd_advance)
+//   k_prim   U^n, B^n            -> W^n, R^n (the cells' EMFs), and the CFL maximum for mhd_advance
 //   k_flux   W^n, B^n  (1st ord) -> F      steps 1
-//   k_emf    F, W^n              -> E      step 2
+//   k_emf    F, R^n              -> E      step 2
 //   k_half   U^n, B^n, F, E      -> W^{n+1/2}, B^{n+1/2}   step 3
-//   k_flux   W^{n+1/2}, PLM      -> F      steps 4-5
-//   k_emf    F, W^{n+1/2}        -> E      step 6
+//   k_flux   W^{n+1/2}, PLM      -> F, R^{n+1/2}   steps 4-5
+//   k_emf    F, R^{n+1/2}        -> E      step 6
 //   k_final  U^n, B^n, F, E      -> U^{n+1}, B^{n+1} in place   step 7
 // With a patch-group list every stage covers the groups plus the halo that
 // the later stages read (3 ghost cells per side for U^n).
@@ -23,6 +23,7 @@
 
 #include "../../include/mhd.h"
 #include "mhd_kernels.hpp"
+#include "mhd_faces.hpp"
 #include "mhd_amr.hpp"
 
 using namespace mhd;
@@ -45,9 +46,10 @@ struct mhd_ctx_s {
   void* Bh;               // 3 * cap
   void* F;                // 21 * cap
   void* E;                // 3 * cap
-  void* QL;               // CTU: 21 * cap, states below each face
-  void* QR;               // CTU: 21 * cap, states above each face
+  void* QL;               // learned flux: 21 * cap, states below each face
+  void* QR;               // learned flux: 21 * cap, states above each face
   void* F2;               // CTU: 21 * cap, corrector fluxes
+  void* Rh;               // CTU: 3 * cap, the cells' EMFs at the half step (learned flux: in W, which it is done with)
   void* RF;               // time-averaged final fluxes of a sub-cycled level: 21 * cap_reg
   void* RE;               // time-averaged final EMFs: 3 * cap_reg
   long long cap_reg;
@@ -57,7 +59,7 @@ struct mhd_ctx_s {
   long long cap_occ_old;
   double* parts;          // reduction partials
   double* dres;           // 8 device doubles of reduction results
-  unsigned long long* smax;
+  Cfl* cfl;
   int* flag;
   unsigned long long* nfb;
   double* host;           // pinned host scratch (16 doubles)
@@ -72,7 +74,6 @@ struct mhd_ctx_s {
   long long max_blocks;   // cap on stage-kernel grids (0: none)
   int threads;            // threads per block of the stage kernels (64 .. 512)
   int batch;              // group-list batch: groups per launch of the middle stages (0: all)
-  int lds_tiles;          // CTU + PPM step 1 on LDS tiles (1) or per cell (0)
   hipGraph_t graph;       // captured mhd_advance
   hipGraphExec_t graph_exec;
   mhd_level graph_key;
@@ -125,7 +126,8 @@ int check_level(const mhd_ctx_s* ctx, const mhd_level* lv) {
   } while (0)
 
 void free_scratch(mhd_ctx_s* c) {
-  void** bufs[] = {&c->W, &c->Bh, &c->F, &c->E, &c->QL, &c->QR, &c->F2};
+  if (c->Rh == c->W) c->Rh = nullptr;
+  void** bufs[] = {&c->W, &c->Bh, &c->F, &c->E, &c->QL, &c->QR, &c->F2, &c->Rh};
   for (void** b : bufs) {
     hipFree(*b);
     *b = nullptr;
@@ -139,9 +141,13 @@ int ensure_capacity(mhd_ctx_s* c, long long cells) {
   const size_t e = c->elem;
   bool ok = hipMalloc(&c->W, 8 * cells * e) == hipSuccess && hipMalloc(&c->Bh, 3 * cells * e) == hipSuccess &&
             hipMalloc(&c->F, 21 * cells * e) == hipSuccess && hipMalloc(&c->E, 3 * cells * e) == hipSuccess;
-  if (ok && c->cfg.scheme == MHD_CTU)
-    ok = hipMalloc(&c->QL, 21 * cells * e) == hipSuccess && hipMalloc(&c->QR, 21 * cells * e) == hipSuccess &&
-         hipMalloc(&c->F2, 21 * cells * e) == hipSuccess;
+  if (ok && c->cfg.scheme == MHD_CTU) ok = hipMalloc(&c->F2, 21 * cells * e) == hipSuccess;
+  if (ok && c->cfg.riemann == MHD_MLP) {
+    ok = hipMalloc(&c->QL, 21 * cells * e) == hipSuccess && hipMalloc(&c->QR, 21 * cells * e) == hipSuccess;
+    c->Rh = c->W;
+  } else if (ok && c->cfg.scheme == MHD_CTU) {
+    ok = hipMalloc(&c->Rh, 3 * cells * e) == hipSuccess;
+  }
   if (!ok) {
     free_scratch(c);
     return MHD_ERR_OUT_OF_MEMORY;
@@ -192,6 +198,7 @@ Work make_work(const mhd_level* lv, int lo, int hi) {
   w.sb = 0;
   w.soff = 0;
   w.units = 0;
+  w.rev = 0;
   w.per = w.chunks = 0;
   w.by_chunks = w.by_row = w.by_plane = FastDiv{0, 0, 0};
   return w;
@@ -286,6 +293,50 @@ unsigned decompose(Work& w, int threads) {
   return capped((long long)w.units * w.chunks);
 }
 
+// Decomposition of the CTU face kernels (k_ctu_faces): slabs of planes of a whole
+// grid, the item boxes of a group list.  A march repeats the trace of one cell
+// before its first face, so long marches save work and short ones give small
+// grids enough waves.
+FaceGeo face_geometry(const Work& w) {
+  FaceGeo g;
+  const auto cut = [](int n, int len) { return (n + len - 1) / len; };
+  if (w.groups) {
+    // whole float step of 5 / 50 / 191 / 400 groups: 54 / 152 / 531 / 1098 us
+    // with marches of 2 cells, 64 / 152 / 504 / 1029 with 5, 80 / 167 / 510 /
+    // 1017 with 10
+    const long long n = 2 + (w.items >> 18);
+    const int len = n > 10 ? 10 : (int)n;
+    g.bx = g.by = g.bz = w.box;
+    g.units = (int)(w.items / ((long long)w.box * w.box * w.box));
+    g.cz = g.cy = len;
+    g.lx = w.box;
+  } else {
+    // marches of 2 (small grids: as many waves as can be had) to 8 cells; 128^3:
+    // 472-476 us for the whole float step with 4 or 8, 491 with 16, 500 with 2;
+    // 97 x 61 x 83: 137 us with 2, 158 with 8
+    const long long n = w.N >> 18;
+    const int len = n < 2 ? 2 : (n > 8 ? 8 : (int)n);
+    g.bx = w.nx;
+    g.by = w.ny;
+    g.bz = g.cz = g.cy = len;
+    g.units = cut(w.nz, g.bz);
+    g.lx = w.nx + 1;
+  }
+  const auto waves = [](long long n, int k) { return (unsigned)((n + k - 1) / k); };
+  g.w2c = waves((long long)g.bx * g.by, 64);
+  g.w2 = g.w2c * (unsigned)cut(g.bz, g.cz);
+  g.w1c = waves((long long)g.bx * g.bz, 64);
+  g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
+  g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
+  g.by_per = make_div(g.per);
+  g.by_w2c = make_div(g.w2c);
+  g.by_w1c = make_div(g.w1c);
+  g.by_bx = make_div((unsigned)g.bx);
+  g.by_by = make_div((unsigned)g.by);
+  g.by_lx = make_div((unsigned)g.lx);
+  return g;
+}
+
 // Batches of a group list: the middle stages (between the primitive pass,
 // which also reduces the CFL maximum over the whole list, and the final
 // update, which writes the level in place) run batch by batch, each batch
@@ -320,12 +371,18 @@ const char* stage_name(const mhd_ctx_s* c, int s) {
 // Stage scratch of one step: the context's (allocated on demand) or carved
 // from the static array of the allocation-free entry point.
 struct StepBufs {
-  void *W, *Bh, *F, *E, *QL, *QR, *F2;
+  void *W, *Bh, *F, *E, *QL, *QR, *F2, *Rh;
   int* occ;
 };
 
+// where a step that computes its own dt (CFL) also writes it: dt and the time
+// it advances (either may be null)
+struct CflOut {
+  double *dt, *t;
+};
+
 StepBufs ctx_bufs(const mhd_ctx_s* c) {
-  return StepBufs{c->W, c->Bh, c->F, c->E, c->QL, c->QR, c->F2, c->occ};
+  return StepBufs{c->W, c->Bh, c->F, c->E, c->QL, c->QR, c->F2, c->Rh, c->occ};
 }
 
 // EMF stage: in double on a whole grid LDS tiles of 16 x 8 x 4 cells (15 %
@@ -347,7 +404,7 @@ void launch_emf(Work& w, const T* F, const T* R, T* E, int nt, hipStream_t st) {
 // ev (optional): kNumStages + 1 events recorded around the stage kernels.
 // R: 1 = PLM (minmod), 2 = PPM at the half step.
 template <typename T, int S, int R, bool MIX, bool L>
-void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   const Mix mix{MIX ? lv->E64 : nullptr, c->cfg.beta_fp64};
   hipStream_t st = c->stream;
   T* U = (T*)lv->U;
@@ -373,16 +430,17 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEven
   mark(0);
   unsigned nb = decompose(wp, nt);
   if (cfl) {
-    k_reset_smax<<<1, 1, 0, st>>>(c->smax);
-    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
+    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
+    k_close_cfl<<<1, kCflSlots, 0, st>>>(c->cfl, c->cfg.courant * lv->dx, cfl->dt, cfl->t, 0);
   } else {
-    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
+    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
   }
   mark(1);
   const int batch = ev ? 0 : c->batch;   // profiling times whole stages
   for (int b = 0; b < num_batches(wf1, batch); ++b) {
     Work f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch), h = batch_of(wh, b, batch);
     Work f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
+    f1.rev = h.rev = e2.rev = 1;
     nb = decompose(f1, nt);
     k_flux<T, 0, S, L><<<nb, nt, 0, st>>>(f1, W, B, Bh, F, gam, c->nfb);
     mark(2);
@@ -403,44 +461,32 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEven
 }
 
 // CTU, paper Sec. 3.2 steps 1-8:
-//   k_prim         U^n, B^n             -> W^n
-//   k_ctu_states   W^n, B^n, dt         -> QL, QR     step 1 (PPM/PLM + tracing)
-//   k_flux_q       QL, QR, B^n          -> F1         step 2
-//   k_emf          F1, W^n              -> E          step 3
-//   k_half         U^n, B^n, F1, E      -> W^{n+1/2}, B^{n+1/2}   step 4
-//   k_ctu_correct  QL, QR, F1, E, B^{n+1/2} -> F2     steps 5-6
-//   k_emf          F2, W^{n+1/2}        -> E          step 7
+//   k_prim         U^n, B^n             -> W^n, R^n (the cells' EMFs, in Bh)
+//   k_ctu_faces    W^n, B^n, dt         -> F1         steps 1-2 (PPM/PLM + tracing, fluxes)
+//   k_emf          F1, R^n              -> E          step 3
+//   k_half         U^n, B^n, F1, E      -> R^{n+1/2}, B^{n+1/2}   step 4
+//   k_ctu_faces    W^n, F1, E, B^{n+1/2} -> F2        steps 1, 5 and 6
+//   k_emf          F2, R^{n+1/2}        -> E          step 7
 //   k_final        U^n, B^n, F2, E      -> U^{n+1}, B^{n+1}   step 8
-// Group halos (cells below, above each group): 4,4 / 2,2 / 2,2 / 1,2 / 1,1 /
-// 1,1 / 0,1 / 0,0, i.e. 4 ghost cells of U^n.
-// CTU step 1 with PPM on LDS tiles: 16 x 4 x 4 cells on a whole grid, 20 x 5
-// x 5 on the 20^3 item boxes of 16^3 groups; false (nothing launched) for
-// other group boxes, which take the per-cell kernel.  The tile kernels
-// have a fixed block of one thread per tile cell.
-template <typename T, bool ALLW, bool L, int TX, int TY, int TZ>
-void launch_tiles(const Work& w, const T* W, const T* B, T* QL, T* QR, DtSrc dts, T inv_dx, T gam, hipStream_t st) {
-  const long long units = L ? w.items / ((long long)w.box * w.box * w.box) : 1;
-  long long nb = units * (L ? unit_tiles<TX, TY, TZ>(w.box, w.box, w.box) : unit_tiles<TX, TY, TZ>(w.nx, w.ny, w.nz));
-  if (g_max_blocks > 0 && nb > g_max_blocks) nb = g_max_blocks;
-  if (nb < 1) nb = 1;
-  k_ctu_states_tiled<T, ALLW, L, TX, TY, TZ><<<(unsigned)nb, TX * TY * TZ, 0, st>>>(w, W, B, QL, QR, dts, inv_dx,
-                                                                                   gam);
-}
-
-template <typename T, bool ALLW, bool L>
-bool launch_states_tiled(const Work& w, const T* W, const T* B, T* QL, T* QR, DtSrc dts, T inv_dx, T gam,
-                         hipStream_t st) {
-  if constexpr (L) {
-    if (w.box != 20) return false;
-    launch_tiles<T, ALLW, L, 20, 5, 5>(w, W, B, QL, QR, dts, inv_dx, gam, st);
-  } else {
-    launch_tiles<T, ALLW, L, 16, 4, 4>(w, W, B, QL, QR, dts, inv_dx, gam, st);
+// (learned flux: k_ctu_faces stores the traced states and its own kernels take
+// them from there).
+// Group halos (cells below, above each group): 4,4 / 2,2 / 1,2 / 1,1 / 1,1 /
+// 0,1 / 0,0, i.e. 4 ghost cells of U^n.
+template <typename T, int R, bool ALLW, int S, int STAGE, bool L>
+void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_dx) {
+  const FaceGeo g = face_geometry(w);
+  unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
+  k_ctu_faces<T, R, ALLW, S, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+  if constexpr (std::is_same<T, float>::value && STAGE != FACE_STATES) {
+    if (c->capture.buf) {
+      nb = decompose(w, kBlock);
+      k_capture<R, ALLW, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, A, dts, inv_dx, c->capture);
+    }
   }
-  return true;
 }
 
 template <typename T, int S, int R, bool MIX, bool L>
-void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   const Mix mix{MIX ? lv->E64 : nullptr, c->cfg.beta_fp64};
   hipStream_t st = c->stream;
   T* U = (T*)lv->U;
@@ -452,6 +498,7 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
   T* E = (T*)sb.E;
   T* QL = (T*)sb.QL;
   T* QR = (T*)sb.QR;
+  T* Rh = (T*)sb.Rh;
   const T gam = (T)c->cfg.gamma;
   const T inv_dx = (T)(1.0 / lv->dx);
   constexpr int G = 4;   // ghost cells of CTU + PPM
@@ -468,10 +515,10 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
   mark(0);
   unsigned nb = decompose(wp, nt);
   if (cfl) {
-    k_reset_smax<<<1, 1, 0, st>>>(c->smax);
-    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
+    k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
+    k_close_cfl<<<1, kCflSlots, 0, st>>>(c->cfl, c->cfg.courant * lv->dx, cfl->dt, cfl->t, 0);
   } else {
-    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->smax, c->flag);
+    k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
   }
   mark(1);
   constexpr bool kMlp = S == 3 && std::is_same<T, float>::value;
@@ -480,28 +527,27 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
   for (int b = 0; b < num_batches(wq, batch); ++b) {
     Work q = batch_of(wq, b, batch), f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch);
     Work h = batch_of(wh, b, batch), f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
+    q.rev = e1.rev = f2.rev = wu.rev = 1;
     // the HLL-family solvers (HLLE, HLLD, the learned flux standing in for
     // HLLD) take every wave in the tracing, Roe only those moving toward an edge
-    if (R != 1 || !c->lds_tiles || !launch_states_tiled<T, S != 0, L>(q, W, B, QL, QR, dts, inv_dx, gam, st)) {
-      nb = decompose(q, nt);
-      k_ctu_states<T, R, S != 0, L><<<nb, nt, 0, st>>>(q, W, B, QL, QR, dts, inv_dx, gam);
-    }
-    mark(2);
+    const FaceArgs<T> A{W, B, QL, QR, F1, nullptr, nullptr, nullptr, T(0), T(0), gam};
     if constexpr (kMlp) {
+      launch_faces<T, R, true, S, FACE_STATES, L>(c, q, A, dts, inv_dx);
+      mark(2);
       // the network kernels keep 256-thread blocks (one LDS stage per wave)
       nb = decompose(f1, kBlock);
       k_flux_dir_mlp<0, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
       k_flux_dir_mlp<1, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
       k_flux_dir_mlp<2, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
     } else {
-      nb = decompose(f1, nt);
-      k_flux_q<T, S, L><<<nb, nt, 0, st>>>(f1, QL, QR, B, F1, gam, c->nfb, c->capture);
+      launch_faces<T, R, S != 0, S, FACE_PREDICT, L>(c, q, A, dts, inv_dx);
+      mark(2);
     }
     mark(3);
     launch_emf<T, L>(e1, F1, Bh, E, nt, st);
     mark(4);
     nb = decompose(h, nt);
-    k_half<T, MIX, true, L><<<nb, nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, W, Bh);
+    k_half<T, MIX, true, L><<<nb, nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, Rh, Bh);
     mark(5);
     if constexpr (kMlp) {
       nb = decompose(f2, kBlock);
@@ -512,11 +558,11 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
       k_ctu_correct_mlp<2, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
                                                      drho, c->nfb, c->capture);
     } else {
-      nb = decompose(f2, nt);
-      k_ctu_correct<T, S, L><<<nb, nt, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->nfb, c->capture);
+      launch_faces<T, R, S != 0, S, FACE_CORRECT, L>(c, f2, FaceArgs<T>{W, B, nullptr, nullptr, F2, F1, E, Bh, T(0), T(0), gam}, dts,
+                                                     inv_dx);
     }
     mark(6);
-    launch_emf<T, L>(e2, F2, W, E, nt, st);
+    launch_emf<T, L>(e2, F2, Rh, E, nt, st);
     mark(7);
   }
   nb = decompose(wu, nt);
@@ -525,7 +571,7 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent
 }
 
 template <typename T, int S, bool MIX, bool L>
-void launch_method(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+void launch_method(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   if constexpr (S == 3) {
     // learned flux: CTU only (validated at mhd_init)
     if (c->cfg.recon == MHD_PPM) launch_ctu<T, S, 1, MIX, L>(c, lv, dts, cfl, ev, sb);
@@ -542,23 +588,26 @@ void launch_method(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEv
 
 // group lists use per-group scratch boxes, whole grids the level's addressing
 template <typename T, int S, bool MIX>
-void launch_scheme(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+void launch_scheme(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   if (list_mode(lv)) launch_method<T, S, MIX, true>(c, lv, dts, cfl, ev, sb);
   else launch_method<T, S, MIX, false>(c, lv, dts, cfl, ev, sb);
 }
 
 template <typename T, bool MIX>
-void launch_step_t(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+void launch_step_t(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   switch (c->cfg.riemann) {
     case MHD_ROE: launch_scheme<T, 0, MIX>(c, lv, dts, cfl, ev, sb); break;
     case MHD_HLLE: launch_scheme<T, 1, MIX>(c, lv, dts, cfl, ev, sb); break;
     case MHD_HLLD: launch_scheme<T, 2, MIX>(c, lv, dts, cfl, ev, sb); break;
-    default: launch_scheme<T, 3, MIX>(c, lv, dts, cfl, ev, sb); break;
+    default:
+      // the learned flux runs in FP32 only (validated at mhd_init)
+      if constexpr (sizeof(T) == 4) launch_scheme<T, 3, MIX>(c, lv, dts, cfl, ev, sb);
+      break;
   }
 }
 
 // the stage kernels of one step on the given scratch
-int run_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev, const StepBufs& sb) {
+int run_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   g_max_blocks = c->max_blocks;
   g_threads = c->threads;
   if (c->cfg.prec == MHD_F64) launch_step_t<double, false>(c, lv, dts, cfl, ev, sb);
@@ -567,10 +616,14 @@ int run_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t*
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 
-int do_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, bool cfl, hipEvent_t* ev = nullptr) {
+int do_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev = nullptr) {
   int rc = check_level(c, lv);
   if (rc) return rc;
   if (c->cfg.riemann == MHD_MLP && !c->mlp_ready) return MHD_ERR_INVALID_ARG;
+  // the face kernels address one component of a whole grid by 32-bit byte
+  // offsets; a level beyond that does not fit the device either
+  if (c->cfg.scheme == MHD_CTU && !list_mode(lv) && scratch_cells(lv, 0) * (long long)c->elem > 0xffffffffLL)
+    return MHD_ERR_OUT_OF_MEMORY;
   rc = ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
   if (rc) return rc;
   rc = build_occupancy(c, lv);
@@ -585,7 +638,8 @@ constexpr int kMaxDevices = 64;
 std::mutex g_static_mutex;
 unsigned char* g_static_ptr[kMaxDevices];   // per device: its copy's device address
 
-// scratch words per cell of a context's step (W, Bh, F, E; CTU adds QL, QR, F2)
+// scratch words per cell an update is budgeted at (W, Bh, F, E; CTU adds F2 and,
+// for the learned flux, QL and QR; the other CTU forms use 3 of those 42 words)
 long long step_words(const mhd_ctx_s* c) {
   long long words = 8 + 3 + 21 + 3;
   if (c->cfg.scheme == MHD_CTU) words += 63;
@@ -612,6 +666,8 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   if (list_mode(lv)) off = align_up(off + (size_t)occupancy_cells(lv) * sizeof(int));
   if (off > kStaticScratchBytes) return off;
   for (int q = 0; q < 7; ++q) *dst[q] = n[q] ? (void*)(base + at[q]) : nullptr;
+  // the learned flux alone keeps the traced states; its half-step EMFs go into W
+  sb->Rh = c->cfg.riemann == MHD_MLP ? sb->W : sb->QL;
   sb->occ = list_mode(lv) ? (int*)(base + at[7]) : nullptr;
   return off;
 }
@@ -624,15 +680,16 @@ void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
   const unsigned nb = decompose(w, kBlock);
   const Mix mix{lv->E64, c->cfg.beta_fp64};
   const T *U = (const T*)lv->U, *B = (const T*)lv->B;
-  if (w.groups) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->smax, c->flag);
-  else k_cfl<T, MIX, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->smax, c->flag);
+  if (w.groups) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
+  else k_cfl<T, MIX, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
 }
 
-void launch_cfl(mhd_ctx_s* c, const mhd_level* lv) {
-  k_reset_smax<<<1, 1, 0, c->stream>>>(c->smax);
+// ... closed into the context's dt and, if given, an output scalar
+void launch_cfl(mhd_ctx_s* c, const mhd_level* lv, double courant_dx, double* dt_out, int least) {
   if (c->cfg.prec == MHD_F64) launch_cfl_t<double, false>(c, lv);
   else if (c->cfg.prec == MHD_F32) launch_cfl_t<float, false>(c, lv);
   else launch_cfl_t<float, true>(c, lv);
+  k_close_cfl<<<1, kCflSlots, 0, c->stream>>>(c->cfl, courant_dx, dt_out, nullptr, least);
 }
 
 int read_flag(mhd_ctx_s* c, int* flag) {
@@ -697,7 +754,6 @@ int mhd_init(const mhd_config* cfg, void* hip_stream, mhd_ctx* out) {
   c->elem = cfg->prec == MHD_F64 ? sizeof(double) : sizeof(float);
   c->threads = kBlock;
   c->batch = 0;
-  c->lds_tiles = 0;
   {
     // this device's copy of the static scratch array, looked up once per device
     std::lock_guard<std::mutex> lock(g_static_mutex);
@@ -721,7 +777,7 @@ int mhd_init(const mhd_config* cfg, void* hip_stream, mhd_ctx* out) {
     if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) c->num_cu = prop.multiProcessorCount;
     if (c->num_cu <= 0) c->num_cu = 256;
   }
-  if (hipMalloc(&c->dres, 8 * sizeof(double)) != hipSuccess || hipMalloc(&c->smax, sizeof(unsigned long long)) != hipSuccess ||
+  if (hipMalloc(&c->dres, 8 * sizeof(double)) != hipSuccess || hipMalloc(&c->cfl, sizeof(Cfl)) != hipSuccess ||
       hipMalloc(&c->flag, sizeof(int)) != hipSuccess || hipMalloc(&c->nfb, sizeof(unsigned long long)) != hipSuccess ||
       hipHostMalloc(&c->host, 16 * sizeof(double)) != hipSuccess) {
     mhd_finalize(c);
@@ -729,7 +785,7 @@ int mhd_init(const mhd_config* cfg, void* hip_stream, mhd_ctx* out) {
   }
   if (hipMemsetAsync(c->flag, 0, sizeof(int), c->stream) != hipSuccess ||
       hipMemsetAsync(c->nfb, 0, sizeof(unsigned long long), c->stream) != hipSuccess ||
-      hipMemsetAsync(c->smax, 0, sizeof(unsigned long long), c->stream) != hipSuccess) {
+      hipMemsetAsync(c->cfl, 0, sizeof(Cfl), c->stream) != hipSuccess) {
     mhd_finalize(c);
     return MHD_ERR_HIP;
   }
@@ -750,7 +806,7 @@ int mhd_finalize(mhd_ctx c) {
   hipFree(c->RE);
   hipFree(c->rflags);
   hipFree(c->occ_old);
-  hipFree(c->parts); hipFree(c->dres); hipFree(c->smax); hipFree(c->flag); hipFree(c->nfb); hipFree(c->occ);
+  hipFree(c->parts); hipFree(c->dres); hipFree(c->cfl); hipFree(c->flag); hipFree(c->nfb); hipFree(c->occ);
   if (c->host) hipHostFree(c->host);
   delete c;
   return MHD_OK;
@@ -780,12 +836,11 @@ int mhd_cfl_dt(mhd_ctx c, const mhd_level* lv, double* dt_host, double* dt_dev) 
   if (!c) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  launch_cfl(c, lv);
   const double cdx = c->cfg.courant * lv->dx;
-  if (dt_dev) k_publish_dt<<<1, 1, 0, c->stream>>>(c->smax, cdx, dt_dev, nullptr);
+  launch_cfl(c, lv, cdx, dt_dev, 0);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   if (dt_host) {
-    HIP_TRY(hipMemcpyAsync(c->host, c->smax, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(c->host, &c->cfl->smax, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
     int flag = 0;
     rc = read_flag(c, &flag);
     if (rc) return rc;
@@ -799,14 +854,12 @@ int mhd_cfl_dt(mhd_ctx c, const mhd_level* lv, double* dt_host, double* dt_dev) 
 
 int mhd_step(mhd_ctx c, const mhd_level* lv, double dt) {
   if (!c || !(dt > 0.0)) return MHD_ERR_INVALID_ARG;
-  DtSrc s{dt, nullptr, nullptr, 0.0};
-  return do_step(c, lv, s, false);
+  return do_step(c, lv, DtSrc{dt, nullptr}, nullptr);
 }
 
 int mhd_step_devdt(mhd_ctx c, const mhd_level* lv, const double* dt_dev) {
   if (!c || !dt_dev) return MHD_ERR_INVALID_ARG;
-  DtSrc s{0.0, dt_dev, nullptr, 0.0};
-  return do_step(c, lv, s, false);
+  return do_step(c, lv, DtSrc{0.0, dt_dev}, nullptr);
 }
 
 int mhd_step_noalloc(mhd_ctx c, const mhd_level* lv, const double* dt_dev) {
@@ -818,20 +871,13 @@ int mhd_step_noalloc(mhd_ctx c, const mhd_level* lv, const double* dt_dev) {
   StepBufs sb{};
   if (carve_static(c, lv, c->static_scratch, &sb) > kStaticScratchBytes) return MHD_ERR_SCRATCH_LIMIT;
   if (list_mode(lv)) fill_occupancy(c, lv, sb.occ);
-  DtSrc s{0.0, dt_dev, nullptr, 0.0};
-  return run_step(c, lv, s, false, nullptr, sb);
+  return run_step(c, lv, DtSrc{0.0, dt_dev}, nullptr, nullptr, sb);
 }
 
 int mhd_advance(mhd_ctx c, const mhd_level* lv, double* dt_dev, double* t_dev) {
   if (!c || !lv) return MHD_ERR_INVALID_ARG;
-  DtSrc s{0.0, nullptr, c->smax, c->cfg.courant * lv->dx};
-  int rc = do_step(c, lv, s, true);
-  if (rc) return rc;
-  if (dt_dev || t_dev) {
-    k_publish_dt<<<1, 1, 0, c->stream>>>(c->smax, c->cfg.courant * lv->dx, dt_dev, t_dev);
-    if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
-  }
-  return MHD_OK;
+  const CflOut out{dt_dev, t_dev};
+  return do_step(c, lv, DtSrc{0.0, &c->cfl->dt}, &out);
 }
 
 int mhd_num_stages(mhd_ctx c) {
@@ -853,9 +899,9 @@ int mhd_profile_step(mhd_ctx c, const mhd_level* lv, int nrep, double* stage_ms)
   for (int s = 0; s <= ns; ++s)
     if (hipEventCreate(&ev[s]) != hipSuccess) return MHD_ERR_HIP;
   for (int s = 0; s < ns; ++s) stage_ms[s] = 0.0;
-  DtSrc dts{0.0, nullptr, c->smax, c->cfg.courant * lv->dx};
+  const CflOut out{nullptr, nullptr};
   for (int r = 0; r < nrep && rc == MHD_OK; ++r) {
-    rc = do_step(c, lv, dts, true, ev);
+    rc = do_step(c, lv, DtSrc{0.0, &c->cfl->dt}, &out, ev);
     if (rc) break;
     if (hipEventSynchronize(ev[ns]) != hipSuccess) { rc = MHD_ERR_HIP; break; }
     for (int s = 0; s < ns; ++s) {
@@ -884,7 +930,6 @@ int mhd_set_launch(mhd_ctx c, int blocks_per_cu, int threads_per_block, int batc
   c->max_blocks = blocks_per_cu > 0 ? (long long)blocks_per_cu * c->num_cu : 0;
   c->threads = threads_per_block;
   c->batch = batch_groups;
-  c->lds_tiles = lds_tiles;
   drop_graph(c);
   return MHD_OK;
 }
@@ -914,10 +959,8 @@ int mhd_advance_graph(mhd_ctx c, const mhd_level* lv, double* dt_dev, double* t_
       }
     }
     if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return MHD_ERR_HIP;
-    DtSrc s{0.0, nullptr, c->smax, c->cfg.courant * lv->dx};
-    rc = do_step(c, lv, s, true);
-    if (rc == MHD_OK && (dt_dev || t_dev))
-      k_publish_dt<<<1, 1, 0, c->stream>>>(c->smax, c->cfg.courant * lv->dx, dt_dev, t_dev);
+    const CflOut out{dt_dev, t_dev};
+    rc = do_step(c, lv, DtSrc{0.0, &c->cfl->dt}, &out);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(c->stream, &g);
     if (rc) {
@@ -941,8 +984,7 @@ int mhd_cfl_dt_min(mhd_ctx c, const mhd_level* lv, double scale, double* dt_dev)
   if (!c || !dt_dev || !(scale > 0.0 && std::isfinite(scale))) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  launch_cfl(c, lv);
-  k_min_dt<<<1, 1, 0, c->stream>>>(c->smax, c->cfg.courant * lv->dx * scale, dt_dev);
+  launch_cfl(c, lv, c->cfg.courant * lv->dx * scale, dt_dev, 1);
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 

@@ -78,15 +78,8 @@ struct Work {
   // by `chunks` blocks.
   int units;
   unsigned per, chunks;
+  int rev;              // walk the blocks from the last to the first
   FastDiv by_chunks, by_row, by_plane;   // of the block rank; of a cell index by its row and by its plane
-};
-
-// A work item's cell: global coordinates, level index p and scratch slot s;
-// (a, b, c) is its position inside the stage's item box.
-struct Site {
-  int i, j, k;
-  int a, b, c;
-  long long p, s;
 };
 
 __device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -153,45 +146,6 @@ __device__ __forceinline__ void cell_of(const Work& w, long long t, int& i, int&
   cell_of(w, t, i, j, k, a, b, c);
 }
 
-// L: list mode with per-group scratch boxes (compile time, so the
-// whole-grid kernels carry no list arithmetic)
-template <bool L>
-__device__ __forceinline__ Site site_of(const Work& w, long long t) {
-  Site st;
-  cell_of(w, t, st.i, st.j, st.k, st.a, st.b, st.c);
-  st.p = lin(w, st.i, st.j, st.k);
-  if constexpr (L) {
-    const long long per = (long long)w.box * w.box * w.box;
-    const long long g = t / per + w.gbase;
-    const long long sb = w.sb;
-    st.s = (g + 1) * sb * sb * sb + ((long long)(st.c + w.soff) * sb + (st.b + w.soff)) * sb + (st.a + w.soff);
-  } else {
-    st.s = st.p;
-  }
-  return st;
-}
-
-// scratch slot of the cell (di, dj, dk) away
-template <bool L>
-__device__ __forceinline__ long long snb(const Work& w, const Site& st, int di, int dj, int dk) {
-  if constexpr (L) return st.s + di + (long long)dj * w.sb + (long long)dk * w.sb * w.sb;
-  else return nbr(w, st.i, st.j, st.k, di, dj, dk);
-}
-
-// the neighbouring cell as a site (level index and scratch slot)
-template <bool L>
-__device__ __forceinline__ Site site_nb(const Work& w, const Site& st, int di, int dj, int dk) {
-  Site n;
-  n.i = wrapc(st.i + di, w.nx);
-  n.j = wrapc(st.j + dj, w.ny);
-  n.k = wrapc(st.k + dk, w.nz);
-  n.a = st.a + di; n.b = st.b + dj; n.c = st.c + dk;
-  n.p = lin(w, n.i, n.j, n.k);
-  if constexpr (L) n.s = st.s + di + (long long)dj * w.sb + (long long)dk * w.sb * w.sb;
-  else n.s = n.p;
-  return n;
-}
-
 // loop over this thread's work items
 #define FOR_ITEMS(w, t) for (long long t = block_linear_id(), t##_n = work_items(w); t < t##_n; t += item_stride())
 
@@ -209,6 +163,25 @@ __device__ __forceinline__ Site site_nb(const Work& w, const Site& st, int di, i
 // stages' vector instructions.)  A plane or box is below 4 GB: a plane of
 // 2^29 cells would need more memory than the device has, since a level has at
 // least four of them and at least 35 words of scratch per cell.
+// A uniform address the compiler takes as it stands: without this it regroups
+// (array + component + plane) + thread into (array + thread) + component and
+// spends a 64-bit vector add per access instead of a scalar one (a tenth of
+// the vector instructions of the reconstruction stage).
+typedef __attribute__((address_space(1))) char gchar;   // device memory
+__device__ __forceinline__ gchar* scalar(const void* p) {
+  gchar* g = (gchar*)p;
+  asm("" : "+s"(g));
+  return g;
+}
+template <typename T>
+__device__ __forceinline__ T load_at(gchar* base, unsigned off) {
+  return *(__attribute__((address_space(1))) const T*)(base + off);
+}
+template <typename T>
+__device__ __forceinline__ void store_at(gchar* base, unsigned off, T v) {
+  *(__attribute__((address_space(1))) T*)(base + off) = v;
+}
+
 template <typename T, bool L>
 struct Cell {
   bool on;              // the thread has a cell
@@ -248,6 +221,15 @@ struct Cell {
     }
   }
 
+  // The same cell with its offset taken anew: the compiler selects "scalar base
+  // + 32-bit offset" addresses only where it sees the offset's extension in the
+  // same basic block, so accesses behind a branch take a fresh copy.
+  __device__ __forceinline__ Cell fresh() const {
+    Cell r = *this;
+    asm volatile("" : "+v"(r.o));
+    return r;
+  }
+
   // wrapped distances of the neighbours X cells along x and Y along y
   template <int X>
   __device__ __forceinline__ int dx(const Work& w) const {
@@ -257,11 +239,14 @@ struct Cell {
   __device__ __forceinline__ int dy(const Work& w) const {
     return Y == 0 ? 0 : (Y < 0 ? (j < -Y ? Y + w.ny : Y) : (j >= w.ny - Y ? Y - w.ny : Y));
   }
+  // the scalar part of an address: component offset e, plane or box, and the
+  // neighbour's share of it
   template <int X, int Y, int Z>
-  __device__ __forceinline__ const char* base(const Work& w, const T* arr) const {
-    if constexpr (L) return (const char*)(arr + (u + X + (long long)Y * w.sb + (long long)Z * w.sb * w.sb));
-    else if constexpr (Z == 0) return (const char*)(arr + u);
-    else return (const char*)(arr + (long long)wrapc(k + Z, w.nz) * w.per);
+  __device__ __forceinline__ gchar* base(const Work& w, const T* arr, long long e) const {
+    if constexpr (L) e += u + X + (long long)Y * w.sb + (long long)Z * w.sb * w.sb;
+    else if constexpr (Z == 0) e += u;
+    else e += (long long)wrapc(k + Z, w.nz) * w.per;
+    return scalar(arr + e);
   }
   template <int X, int Y>
   __device__ __forceinline__ unsigned off(const Work& w) const {
@@ -270,25 +255,19 @@ struct Cell {
     if constexpr (!L && Y != 0) v += (unsigned)(dy<Y>(w) * w.nx * (int)sizeof(T));
     return v;
   }
-  // one scratch component at the cell (X, Y, Z) away
+  // one scratch component (arr + e) at the cell (X, Y, Z) away
   template <int X, int Y, int Z>
-  __device__ __forceinline__ T at(const Work& w, const T* arr) const {
-    return *(const T*)(base<X, Y, Z>(w, arr) + off<X, Y>(w));
+  __device__ __forceinline__ T at(const Work& w, const T* arr, long long e) const {
+    return load_at<T>(base<X, Y, Z>(w, arr, e), off<X, Y>(w));
   }
   // ... n cells along direction D
   template <int D, int n>
-  __device__ __forceinline__ T along(const Work& w, const T* arr) const {
-    return at<D == 0 ? n : 0, D == 1 ? n : 0, D == 2 ? n : 0>(w, arr);
+  __device__ __forceinline__ T along(const Work& w, const T* arr, long long e) const {
+    return at<D == 0 ? n : 0, D == 1 ? n : 0, D == 2 ? n : 0>(w, arr, e);
   }
-  __device__ __forceinline__ T here(const Work& w, const T* arr) const { return at<0, 0, 0>(w, arr); }
-  __device__ __forceinline__ void put(const Work& w, T* arr, T v) const {
-    *(T*)(const_cast<char*>(base<0, 0, 0>(w, arr)) + o) = v;
-  }
-  // ... stored at the cell n along D
-  template <int D, int n>
-  __device__ __forceinline__ void put_along(const Work& w, T* arr, T v) const {
-    constexpr int X = D == 0 ? n : 0, Y = D == 1 ? n : 0, Z = D == 2 ? n : 0;
-    *(T*)(const_cast<char*>(base<X, Y, Z>(w, arr)) + off<X, Y>(w)) = v;
+  __device__ __forceinline__ T here(const Work& w, const T* arr, long long e) const { return at<0, 0, 0>(w, arr, e); }
+  __device__ __forceinline__ void put(const Work& w, T* arr, long long e, T v) const {
+    store_at<T>(base<0, 0, 0>(w, arr, e), o, v);
   }
   // level index of the cell n along D (L)
   template <int D, int n>
@@ -300,14 +279,13 @@ struct Cell {
   }
   // one component of the level itself, n cells along D
   template <int D, int n>
-  __device__ __forceinline__ T level(const Work& w, const T* arr) const {
-    if constexpr (L) return arr[level_index<D, n>(w)];
-    else return along<D, n>(w, arr);
+  __device__ __forceinline__ T level(const Work& w, const T* arr, long long e) const {
+    if constexpr (L) return arr[e + level_index<D, n>(w)];
+    else return along<D, n>(w, arr, e);
   }
-  template <int D, int n>
-  __device__ __forceinline__ void put_level(const Work& w, T* arr, T v) const {
-    if constexpr (L) arr[level_index<D, n>(w)] = v;
-    else put_along<D, n>(w, arr, v);
+  __device__ __forceinline__ void put_level(const Work& w, T* arr, long long e, T v) const {
+    if constexpr (L) arr[e + p] = v;
+    else put(w, arr, e, v);
   }
   // the cell's level index (both modes)
   __device__ __forceinline__ long long index(const Work& w) const { return L ? p : u + o / sizeof(T); }
@@ -330,23 +308,31 @@ __device__ __forceinline__ unsigned stage_blocks(const Work& w) {
 // loop over this block's chunks: c is the thread's cell (c.on: it has one)
 #define FOR_CHUNKS(T, L, w, c)                                                           \
   for (unsigned c##_r = block_rank(), c##_n = stage_blocks<L>(w); c##_r < c##_n; c##_r += gridDim.x) \
-    if (const Cell<T, L> c(w, c##_r); true)
+    if (const Cell<T, L> c(w, w.rev ? c##_n - 1 - c##_r : c##_r); true)
 #define FOR_CELLS(T, L, w, c) FOR_CHUNKS(T, L, w, c) if (c.on)
 
-// time step source: explicit value, device scalar, or CFL maximum signal
-// speed (stored as the bit pattern of a positive double)
+// time step source: explicit value or device scalar
 struct DtSrc {
   double val;
   const double* ptr;
-  const unsigned long long* smax;
-  double courant_dx;
 };
 
-__device__ __forceinline__ double get_dt(const DtSrc& s) {
-  if (s.smax) return s.courant_dx / __longlong_as_double((long long)*s.smax);
-  if (s.ptr) return *s.ptr;
-  return s.val;
-}
+__device__ __forceinline__ double get_dt(const DtSrc& s) { return s.ptr ? *s.ptr : s.val; }
+
+// CFL reduction of a context: the maximum signal speed (bit pattern of a
+// positive double), the time step it gives, and the slots the blocks reduce
+// into.  Thousands of blocks start together and all find their maximum larger
+// than what is stored, so one shared slot would serialise their atomics (20-30
+// us on 128^3, more than half of the primitive pass); 64 slots, each in a cache
+// line of its own, divide that.  k_close_cfl takes their maximum and clears
+// them for the next reduction.
+constexpr int kCflSlots = 64, kCflPitch = 16;
+struct Cfl {
+  unsigned long long smax;
+  double dt;
+  unsigned long long pad[kCflPitch - 2];
+  unsigned long long slot[kCflSlots * kCflPitch];
+};
 
 // ------------------------------------------------------------ reductions
 __device__ __forceinline__ double wave_max(double v) {
@@ -410,11 +396,11 @@ template <typename T, bool MIX, bool L>
 __device__ __forceinline__ void cell_prims(const Work& w, const T* __restrict__ U, const T* __restrict__ B,
                                            const Mix& mix, const Cell<T, L>& c, T gam, T out[8]) {
   const long long N = w.N;
-  const T bl[3] = {c.template level<0, 0>(w, B), c.template level<0, 0>(w, B + N), c.template level<0, 0>(w, B + 2 * N)};
-  const T bu[3] = {c.template level<0, 1>(w, B), c.template level<1, 1>(w, B + N), c.template level<2, 1>(w, B + 2 * N)};
+  const T bl[3] = {c.template level<0, 0>(w, B, 0), c.template level<0, 0>(w, B, N), c.template level<0, 0>(w, B, 2 * N)};
+  const T bu[3] = {c.template level<0, 1>(w, B, 0), c.template level<1, 1>(w, B, N), c.template level<2, 1>(w, B, 2 * N)};
   T u[5];
 #pragma unroll
-  for (int m = 0; m < 5; ++m) u[m] = (MIX && m == 4) ? T(0) : c.template level<0, 0>(w, U + m * N);
+  for (int m = 0; m < 5; ++m) u[m] = (MIX && m == 4) ? T(0) : c.template level<0, 0>(w, U, m * N);
   prims_from<T, MIX>(u[0], u[1], u[2], u[3], u[4], MIX ? mix.E64[c.index(w)] : 0.0, bl, bu, gam, mix.beta, out);
 }
 
@@ -438,7 +424,7 @@ __device__ __forceinline__ double signal_speed(const T q[8], T gam) {
   return s;
 }
 
-__device__ __forceinline__ void block_max_atomic(double v, unsigned long long* smax) {
+__device__ __forceinline__ void block_max_atomic(double v, Cfl* cfl) {
   __shared__ double red[kMaxBlock / 64];
   v = wave_max(v);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -448,8 +434,9 @@ __device__ __forceinline__ void block_max_atomic(double v, unsigned long long* s
     double m = red[0];
     for (int q = 1; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
     // most blocks see a maximum already reached: skip their atomic
+    unsigned long long* slot = cfl->slot + (blockIdx.x % kCflSlots) * kCflPitch;
     const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
-    if (m > 0.0 && bits > *(volatile unsigned long long*)smax) atomicMax(smax, bits);
+    if (m > 0.0 && bits > *(volatile unsigned long long*)slot) atomicMax(slot, bits);
   }
 }
 
@@ -459,26 +446,25 @@ __device__ __forceinline__ void block_max_atomic(double v, unsigned long long* s
 // speed and the sticky non-physical flag.
 template <typename T, bool CFL, bool MIX, bool L>
 __global__ void __launch_bounds__(kMaxBlock) k_prim(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
-                                                 T* __restrict__ W, T* __restrict__ R, T gam, unsigned long long* smax,
-                                                 int* flag) {
+                                                 T* __restrict__ W, T* __restrict__ R, T gam, Cfl* cfl, int* flag) {
   double s = 0.0;
   FOR_CELLS(T, L, w, c) {
     T q[8];
     cell_prims<T, MIX, L>(w, U, B, mix, c, gam, q);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) c.put(w, W + m * w.NS, q[m]);
+    for (int m = 0; m < 8; ++m) c.put(w, W, m * w.NS, q[m]);
 #pragma unroll
-    for (int m = 0; m < 3; ++m) c.put(w, R + m * w.NS, cell_emf(q, m));
+    for (int m = 0; m < 3; ++m) c.put(w, R, m * w.NS, cell_emf(q, m));
     if (!(q[0] > T(0)) || !(q[4] > T(0))) atomicOr(flag, 1);
     else if (CFL) s = fmax(s, signal_speed(q, gam));
   }
-  if (CFL) block_max_atomic(s, smax);
+  if (CFL) block_max_atomic(s, cfl);
 }
 
 // CFL maximum signal speed only
 template <typename T, bool MIX, bool L>
 __global__ void __launch_bounds__(kBlock) k_cfl(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
-                                                T gam, unsigned long long* smax, int* flag) {
+                                                T gam, Cfl* cfl, int* flag) {
   double s = 0.0;
   FOR_CELLS(T, L, w, c) {
     T q[8];
@@ -486,58 +472,48 @@ __global__ void __launch_bounds__(kBlock) k_cfl(Work w, const T* __restrict__ U,
     if (!(q[0] > T(0)) || !(q[4] > T(0))) atomicOr(flag, 1);
     else s = fmax(s, signal_speed(q, gam));
   }
-  block_max_atomic(s, smax);
+  block_max_atomic(s, cfl);
 }
 
-__global__ void k_reset_smax(unsigned long long* smax) { *smax = 0ull; }
-
-// *dt = min(*dt, courant dx / smax)
-__global__ void k_min_dt(const unsigned long long* smax, double courant_dx, double* dt) {
-  const double v = courant_dx / __longlong_as_double((long long)*smax);
-  if (v < *dt) *dt = v;
-}
-
-// dt = courant dx / smax into an output scalar, and t += dt
-__global__ void k_publish_dt(const unsigned long long* smax, double courant_dx, double* dt_out, double* t_out) {
-  const double dt = courant_dx / __longlong_as_double((long long)*smax);
-  if (dt_out) *dt_out = dt;
+// Close a CFL reduction (one wave): its maximum, dt = courant dx / smax, and
+// optionally dt into an output scalar (or, with `least`, the smaller of the two)
+// and t += dt.
+__global__ void __launch_bounds__(kCflSlots) k_close_cfl(Cfl* cfl, double courant_dx, double* dt_out, double* t_out,
+                                                         int least) {
+  unsigned long long* slot = cfl->slot + threadIdx.x * kCflPitch;
+  const double m = wave_max(__longlong_as_double((long long)*slot));
+  *slot = 0ull;
+  if (threadIdx.x) return;
+  const double dt = courant_dx / m;
+  cfl->smax = (unsigned long long)__double_as_longlong(m);
+  cfl->dt = dt;
+  if (dt_out && (!least || dt < *dt_out)) *dt_out = dt;
   if (t_out) *t_out += dt;
 }
 
 // ------------------------------------------------------------ fluxes
-template <typename T, int D>
-__device__ __forceinline__ void load_w1d(const T* __restrict__ W, long long N, long long q, T w[7]) {
-  constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  w[0] = W[q];
-  w[1] = W[(1 + n) * N + q];
-  w[2] = W[(1 + t1) * N + q];
-  w[3] = W[(1 + t2) * N + q];
-  w[4] = W[4 * N + q];
-  w[5] = W[(5 + t1) * N + q];
-  w[6] = W[(5 + t2) * N + q];
-}
-
-// the same for the cell n along D of a stage kernel's cell
+// 1D primitives of the cell n along D of a stage kernel's cell, in D's frame
 template <typename T, int D, int n, bool L>
 __device__ __forceinline__ void load_frame(const Work& w, const T* __restrict__ W, const Cell<T, L>& c, T q[7]) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
 #pragma unroll
-  for (int m = 0; m < 7; ++m) q[m] = c.template along<D, n>(w, W + comp[m] * w.NS);
+  for (int m = 0; m < 7; ++m) q[m] = c.template along<D, n>(w, W, comp[m] * w.NS);
 }
 
 template <typename T, int D, bool L>
-__device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, const Cell<T, L>& c, const T f[7]) {
+__device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, const Cell<T, L>& c0, const T f[7]) {
+  const Cell<T, L> c = c0.fresh();
   constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   const long long NS = w.NS;
-  T* Fd = F + (long long)D * 7 * NS;
-  c.put(w, Fd, f[0]);
-  c.put(w, Fd + (1 + n) * NS, f[1]);
-  c.put(w, Fd + (1 + t1) * NS, f[2]);
-  c.put(w, Fd + (1 + t2) * NS, f[3]);
-  c.put(w, Fd + 4 * NS, f[4]);
-  c.put(w, Fd + 5 * NS, f[6]);    // E_t1 = F_n[B_t2]
-  c.put(w, Fd + 6 * NS, -f[5]);   // E_t2 = -F_n[B_t1]
+  constexpr int d = 7 * D;
+  c.put(w, F, d * NS, f[0]);
+  c.put(w, F, (d + 1 + n) * NS, f[1]);
+  c.put(w, F, (d + 1 + t1) * NS, f[2]);
+  c.put(w, F, (d + 1 + t2) * NS, f[3]);
+  c.put(w, F, (d + 4) * NS, f[4]);
+  c.put(w, F, (d + 5) * NS, f[6]);    // E_t1 = F_n[B_t2]
+  c.put(w, F, (d + 6) * NS, -f[5]);   // E_t2 = -F_n[B_t1]
 }
 
 // RECON: 0 = first order (cell states), 1 = PLM with minmod on primitives,
@@ -546,7 +522,8 @@ __device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, con
 // bn: the face's normal field.
 template <typename T, int D, int RECON, int SOLVER, bool L>
 __device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W, T bn, T* __restrict__ F,
-                                         const Cell<T, L>& c, T gam) {
+                                         const Cell<T, L>& c0, T gam) {
+  const Cell<T, L> c = c0.fresh();
   T wl[7], wr[7];
   load_frame<T, D, -1, L>(w, W, c, wl);
   load_frame<T, D, 0, L>(w, W, c, wr);
@@ -609,13 +586,13 @@ __global__ void __launch_bounds__(kMaxBlock) k_flux(Work w, const T* __restrict_
     T bn[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d)
-      bn[d] = RECON == 0 ? c.template level<0, 0>(w, B + d * w.N) : c.here(w, (const T*)Bh + d * w.NS);
+      bn[d] = RECON == 0 ? c.template level<0, 0>(w, B, d * w.N) : c.here(w, (const T*)Bh, d * w.NS);
     if constexpr (RECON != 0) {
       T q[8];
 #pragma unroll
-      for (int m = 1; m < 8; ++m) q[m] = c.here(w, W + m * w.NS);
+      for (int m = 1; m < 8; ++m) q[m] = c.here(w, W, m * w.NS);
 #pragma unroll
-      for (int m = 0; m < 3; ++m) c.put(w, Bh + m * w.NS, cell_emf(q, m));
+      for (int m = 0; m < 3; ++m) c.put(w, Bh, m * w.NS, cell_emf(q, m));
     }
     fb += face_flux<T, 0, RECON, SOLVER, L>(w, W, bn[0], F, c, gam);
     fb += face_flux<T, 1, RECON, SOLVER, L>(w, W, bn[1], F, c, gam);
@@ -657,15 +634,13 @@ __device__ __forceinline__ T edge_emf(const Work& w, const T* __restrict__ F, co
   constexpr int bx = b == 0 ? -1 : 0, by = b == 1 ? -1 : 0, bz = b == 2 ? -1 : 0;   // one cell down along b
   constexpr int cx = c == 0 ? -1 : 0, cy = c == 1 ? -1 : 0, cz = c == 2 ? -1 : 0;   // one cell down along c
   const long long N = w.NS;
-  const T* Fb = F + (long long)b * 7 * N;
-  const T* Fc = F + (long long)c * 7 * N;
-  const T* Ra = R + (long long)A * N;
-  const T eb0 = p.template at<cx, cy, cz>(w, Fb + 6 * N), eb1 = p.here(w, Fb + 6 * N);
-  const T ec0 = p.template at<bx, by, bz>(w, Fc + 5 * N), ec1 = p.here(w, Fc + 5 * N);
-  const T mb0 = p.template at<cx, cy, cz>(w, Fb), mb1 = p.here(w, Fb);
-  const T mc0 = p.template at<bx, by, bz>(w, Fc), mc1 = p.here(w, Fc);
-  const T r00 = p.template at<bx + cx, by + cy, bz + cz>(w, Ra), r10 = p.template at<cx, cy, cz>(w, Ra);
-  const T r01 = p.template at<bx, by, bz>(w, Ra), r11 = p.here(w, Ra);
+  const long long fb = 7 * b * N, fc = 7 * c * N, ra = A * N;
+  const T eb0 = p.template at<cx, cy, cz>(w, F, fb + 6 * N), eb1 = p.here(w, F, fb + 6 * N);
+  const T ec0 = p.template at<bx, by, bz>(w, F, fc + 5 * N), ec1 = p.here(w, F, fc + 5 * N);
+  const T mb0 = p.template at<cx, cy, cz>(w, F, fb), mb1 = p.here(w, F, fb);
+  const T mc0 = p.template at<bx, by, bz>(w, F, fc), mc1 = p.here(w, F, fc);
+  const T r00 = p.template at<bx + cx, by + cy, bz + cz>(w, R, ra), r10 = p.template at<cx, cy, cz>(w, R, ra);
+  const T r01 = p.template at<bx, by, bz>(w, R, ra), r11 = p.here(w, R, ra);
   return edge_emf_core(eb0, eb1, ec0, ec1, mb0, mb1, mc0, mc1, r00, r10, r01, r11);
 }
 
@@ -673,9 +648,9 @@ template <typename T, bool L>
 __global__ void __launch_bounds__(kMaxBlock) k_emf(Work w, const T* __restrict__ F, const T* __restrict__ R,
                                                 T* __restrict__ E) {
   FOR_CELLS(T, L, w, c) {
-    c.put(w, E, edge_emf<T, 0, L>(w, F, R, c));
-    c.put(w, E + w.NS, edge_emf<T, 1, L>(w, F, R, c));
-    c.put(w, E + 2 * w.NS, edge_emf<T, 2, L>(w, F, R, c));
+    c.put(w, E, 0, edge_emf<T, 0, L>(w, F, R, c));
+    c.put(w, E, w.NS, edge_emf<T, 1, L>(w, F, R, c));
+    c.put(w, E, 2 * w.NS, edge_emf<T, 2, L>(w, F, R, c));
   }
 }
 
@@ -694,7 +669,7 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __r
   __shared__ T sR[3][NH];
   __shared__ T sF[3][3][NH];
   const int ntx = (w.nx + TX - 1) / TX, nty = (w.ny + TY - 1) / TY;
-  const int tile = (int)block_rank();
+  const int tile = (int)(w.rev ? gridDim.x - 1 - block_rank() : block_rank());
   const int tx0 = (tile % ntx) * TX, ty0 = ((tile / ntx) % nty) * TY, tz0 = (tile / (ntx * nty)) * TZ;
   const long long N = w.NS;
   for (int h = threadIdx.x; h < NH; h += NT) {
@@ -735,14 +710,11 @@ template <typename T, bool MIX, bool L, int NM = 5>
 __device__ __forceinline__ void cell_update(const Work& w, const T* U, const T* __restrict__ F, const Mix& mix,
                                             const Cell<T, L>& c, T r, T out[5], double& e64) {
   const long long N = w.N, NS = w.NS;
-  const T* Fx = F;
-  const T* Fy = F + 7 * NS;
-  const T* Fz = F + 14 * NS;
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
-    const T xu = c.template along<0, 1>(w, Fx + m * NS), xl = c.here(w, Fx + m * NS);
-    const T yu = c.template along<1, 1>(w, Fy + m * NS), yl = c.here(w, Fy + m * NS);
-    const T zu = c.template along<2, 1>(w, Fz + m * NS), zl = c.here(w, Fz + m * NS);
+    const T xu = c.template along<0, 1>(w, F, m * NS), xl = c.here(w, F, m * NS);
+    const T yu = c.template along<1, 1>(w, F, (7 + m) * NS), yl = c.here(w, F, (7 + m) * NS);
+    const T zu = c.template along<2, 1>(w, F, (14 + m) * NS), zl = c.here(w, F, (14 + m) * NS);
     if (MIX && m == 4) {
       const double rd = (double)r;
       double v = mix.E64[c.index(w)];
@@ -753,7 +725,7 @@ __device__ __forceinline__ void cell_update(const Work& w, const T* U, const T* 
       out[4] = T(v);
       continue;
     }
-    T v = c.template level<0, 0>(w, U + m * N);
+    T v = c.template level<0, 0>(w, U, m * N);
     v -= r * (xu - xl);
     v -= r * (yu - yl);
     v -= r * (zu - zl);
@@ -768,11 +740,10 @@ template <typename T, int A, int n, bool L>
 __device__ __forceinline__ T face_update(const Work& w, const T* B, const T* __restrict__ E, const Cell<T, L>& p, T r) {
   constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
   constexpr int X = A == 0 ? n : 0, Y = A == 1 ? n : 0, Z = A == 2 ? n : 0;
-  const T* Eb = E + (long long)b * w.NS;
-  const T* Ec = E + (long long)c * w.NS;
-  const T cu = p.template at<X + (b == 0), Y + (b == 1), Z + (b == 2)>(w, Ec), cl = p.template at<X, Y, Z>(w, Ec);
-  const T bu = p.template at<X + (c == 0), Y + (c == 1), Z + (c == 2)>(w, Eb), bl = p.template at<X, Y, Z>(w, Eb);
-  return p.template level<A, n>(w, B + A * w.N) - r * (cu - cl) + r * (bu - bl);
+  const long long eb = b * w.NS, ec = c * w.NS;
+  const T cu = p.template at<X + (b == 0), Y + (b == 1), Z + (b == 2)>(w, E, ec), cl = p.template at<X, Y, Z>(w, E, ec);
+  const T bu = p.template at<X + (c == 0), Y + (c == 1), Z + (c == 2)>(w, E, eb), bl = p.template at<X, Y, Z>(w, E, eb);
+  return p.template level<A, n>(w, B, A * w.N) - r * (cu - cl) + r * (bu - bl);
 }
 
 // Half step over dt/2: U^{n+1/2} and face B^{n+1/2} from the predictor fluxes
@@ -803,14 +774,14 @@ __global__ void __launch_bounds__(kMaxBlock) k_half(Work w, const T* __restrict_
         q[5 + m] = T(0.5) * (bl[m] + bu[m]);
       }
 #pragma unroll
-      for (int m = 0; m < 3; ++m) c.put(w, Wh + m * w.NS, cell_emf(q, m));
+      for (int m = 0; m < 3; ++m) c.put(w, Wh, m * w.NS, cell_emf(q, m));
     } else {
       prims_from<T, MIX>(u[0], u[1], u[2], u[3], u[4], eh, bl, bu, gam, mix.beta, q);
 #pragma unroll
-      for (int m = 0; m < 8; ++m) c.put(w, Wh + m * w.NS, q[m]);
+      for (int m = 0; m < 8; ++m) c.put(w, Wh, m * w.NS, q[m]);
     }
 #pragma unroll
-    for (int m = 0; m < 3; ++m) c.put(w, Bh + m * w.NS, bl[m]);
+    for (int m = 0; m < 3; ++m) c.put(w, Bh, m * w.NS, bl[m]);
   }
 }
 
@@ -853,299 +824,24 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
       }
     }
 #pragma unroll
-    for (int m = 0; m < 5; ++m) c.template put_level<0, 0>(w, U + m * N, u[m]);
+    for (int m = 0; m < 5; ++m) c.put_level(w, U, m * N, u[m]);
     if (MIX) mix.E64[c.index(w)] = e64;
 #pragma unroll
-    for (int m = 0; m < 3; ++m) c.template put_level<0, 0>(w, B + m * N, bf[m]);
+    for (int m = 0; m < 3; ++m) c.put_level(w, B, m * N, bf[m]);
     if constexpr (L) {
-      if (ex) c.template put_level<0, 1>(w, B, ux);
-      if (ey) c.template put_level<1, 1>(w, B + N, uy);
-      if (ez) c.template put_level<2, 1>(w, B + 2 * N, uz);
+      if (ex) B[c.template level_index<0, 1>(w)] = ux;
+      if (ey) B[N + c.template level_index<1, 1>(w)] = uy;
+      if (ez) B[2 * N + c.template level_index<2, 1>(w)] = uz;
     }
   }
 }
 
 // ------------------------------------------------------------ CTU
-// Step 1 of CTU: time-centred states at both edges of every cell in each
-// direction.  Face-indexed outputs: QR[d][m][p] is the state above the lower
-// d-face of cell p (from cell p), QL[d][m][p] the state below it (from the
-// cell p - e_d; written by that cell as its upper-edge state).
-template <typename T, int D, int RECON, bool ALLW, bool L>
-__device__ __forceinline__ void cell_states(const Work& w, const T* __restrict__ W, const T* __restrict__ B,
-                                            T* __restrict__ QL, T* __restrict__ QR, const Cell<T, L>& c, T dtdx,
-                                            T gam) {
-  const long long N = w.N, NS = w.NS;
-  T q[5][7];
-  if (RECON == 1) {
-    load_frame<T, D, -2, L>(w, W, c, q[0]);
-    load_frame<T, D, 2, L>(w, W, c, q[4]);
-  }
-  load_frame<T, D, -1, L>(w, W, c, q[1]);
-  load_frame<T, D, 0, L>(w, W, c, q[2]);
-  load_frame<T, D, 1, L>(w, W, c, q[3]);
-  T sl[7], sr[7];
-  trace_cell<T, RECON, ALLW>(q, c.template level<D, 0>(w, B + D * N), c.template level<D, 1>(w, B + D * N), dtdx, gam,
-                             sl, sr);
-#pragma unroll
-  for (int m = 0; m < 7; ++m) {
-    c.put(w, QR + ((long long)D * 7 + m) * NS, sl[m]);
-    c.template put_along<D, 1>(w, QL + ((long long)D * 7 + m) * NS, sr[m]);
-  }
-}
-
-// ALLW: trace waves moving away from an edge too (HLL-family solvers)
-template <typename T, int RECON, bool ALLW, bool L>
-__global__ void __launch_bounds__(kMaxBlock) k_ctu_states(Work w, const T* __restrict__ W, const T* __restrict__ B,
-                                                       T* __restrict__ QL, T* __restrict__ QR, DtSrc dts,
-                                                       T inv_dx, T gam) {
-  const T dtdx = T(get_dt(dts)) * inv_dx;
-  FOR_CELLS(T, L, w, c) {
-    cell_states<T, 0, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
-    cell_states<T, 1, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
-    cell_states<T, 2, RECON, ALLW, L>(w, W, B, QL, QR, c, dtdx, gam);
-  }
-}
-
-// ---- step 1 with PPM, tiled in LDS
-//
-// A block owns a TX x TY x TZ tile of a unit (the whole grid, or the item
-// box of one listed group).  Per direction D it stages the tile's 1D
-// primitives with two more cells on each side along D in LDS, computes each
-// MC slope of the padded tile and each PPM interface value of the tile's
-// faces once (the per-cell form computes every slope three times and every
-// interface twice), and then each thread limits and traces its own cell from
-// the shared values.  Every value is computed with the per-cell form's
-// arithmetic, so the states are the same.
-
-// scratch slot of position (a, b, c) of unit gg (a group's item box in list
-// mode, the grid otherwise); positions up to two cells outside the unit
-template <bool L>
-__device__ __forceinline__ long long unit_slot(const Work& w, long long gg, int a, int b, int c) {
-  if constexpr (L) {
-    const long long sb = w.sb;
-    return (gg + 1) * sb * sb * sb + ((long long)(c + w.soff) * sb + (b + w.soff)) * sb + (a + w.soff);
-  } else {
-    return lin(w, wrapc(a, w.nx), wrapc(b, w.ny), wrapc(c, w.nz));
-  }
-}
-
-// the site of position (a, b, c) inside unit gg
-template <bool L>
-__device__ __forceinline__ Site unit_site(const Work& w, long long gg, int a, int b, int c) {
-  Site st;
-  st.a = a; st.b = b; st.c = c;
-  if constexpr (L) {
-    const int* o = w.groups + 3 * gg;
-    st.i = wrapc((o[0] >> w.oshift) - w.halo + a, w.nx);
-    st.j = wrapc((o[1] >> w.oshift) - w.halo + b, w.ny);
-    st.k = wrapc((o[2] >> w.oshift) - w.halo + c, w.nz);
-  } else {
-    st.i = a; st.j = b; st.k = c;
-  }
-  st.p = lin(w, st.i, st.j, st.k);
-  st.s = L ? unit_slot<L>(w, gg, a, b, c) : st.p;
-  return st;
-}
-
-// extents of the tile padded by P cells on each side along D
-template <int TX, int TY, int TZ, int D, int P>
-struct Padded {
-  static constexpr int x = TX + (D == 0 ? 2 * P : 0);
-  static constexpr int y = TY + (D == 1 ? 2 * P : 0);
-  static constexpr int z = TZ + (D == 2 ? 2 * P : 0);
-  static constexpr int n = x * y * z;
-  static constexpr int stride = D == 0 ? 1 : (D == 1 ? x : x * y);   // index step along D
-};
-
-template <int TX, int TY, int TZ, int P>
-constexpr int padded_max() {
-  return Padded<TX, TY, TZ, 0, P>::n > Padded<TX, TY, TZ, 1, P>::n
-             ? (Padded<TX, TY, TZ, 0, P>::n > Padded<TX, TY, TZ, 2, P>::n ? Padded<TX, TY, TZ, 0, P>::n
-                                                                          : Padded<TX, TY, TZ, 2, P>::n)
-             : (Padded<TX, TY, TZ, 1, P>::n > Padded<TX, TY, TZ, 2, P>::n ? Padded<TX, TY, TZ, 1, P>::n
-                                                                          : Padded<TX, TY, TZ, 2, P>::n);
-}
-
-// faces of the tile along its largest direction count
-template <int TX, int TY, int TZ>
-constexpr int faces_max() {
-  return (TX + 1) * TY * TZ > TX * (TY + 1) * TZ
-             ? ((TX + 1) * TY * TZ > TX * TY * (TZ + 1) ? (TX + 1) * TY * TZ : TX * TY * (TZ + 1))
-             : (TX * (TY + 1) * TZ > TX * TY * (TZ + 1) ? TX * (TY + 1) * TZ : TX * TY * (TZ + 1));
-}
-
-// A tile: its unit, its origin in the unit and the unit's extents.
-struct Tile {
-  long long gg;
-  int a0, b0, c0;
-  int ux, uy, uz;
-};
-
-// LDS arrays of one direction D (component-major, [7][n] each): sW the
-// primitives at positions -2 .. T+1 along D (padding 2), sS the MC slopes at
-// -1 .. T (padding 1), sE the interface values at faces 0 .. T (face f
-// between cells f - 1 and f).
-template <int TX, int TY, int TZ, int D>
-struct TileLayout {
-  using PW = Padded<TX, TY, TZ, D, 2>;
-  using PS = Padded<TX, TY, TZ, D, 1>;
-  static constexpr int FX = TX + (D == 0), FY = TY + (D == 1), FZ = TZ + (D == 2), NF = FX * FY * FZ;
-  static constexpr int SF = D == 0 ? 1 : (D == 1 ? FX : FX * FY);
-  static constexpr int NT = TX * TY * TZ;
-  static constexpr int dx = D == 0, dy = D == 1, dz = D == 2;
-};
-
-// padded cell e of direction D: inside the loaded range (within two cells of
-// the unit along D, inside it across)?  Also returns its unit position.
-template <int TX, int TY, int TZ, int D>
-__device__ __forceinline__ bool padded_cell(const Tile& t, int e, int& a, int& b, int& c) {
-  using Ly = TileLayout<TX, TY, TZ, D>;
-  using PW = typename Ly::PW;
-  const int x = e % PW::x, y = (e / PW::x) % PW::y, z = e / (PW::x * PW::y);
-  a = t.a0 + x - 2 * Ly::dx;
-  b = t.b0 + y - 2 * Ly::dy;
-  c = t.c0 + z - 2 * Ly::dz;
-  return a < t.ux + 2 * Ly::dx && b < t.uy + 2 * Ly::dy && c < t.uz + 2 * Ly::dz;
-}
-
-// the padded primitives of direction D into sW
-template <typename T, bool L, int TX, int TY, int TZ, int D>
-__device__ __forceinline__ void stage_prims(const Work& w, const T* __restrict__ W, const Tile& t, int tid, T* sW) {
-  using Ly = TileLayout<TX, TY, TZ, D>;
-  for (int e = tid; e < Ly::PW::n; e += Ly::NT) {
-    int a, b, c;
-    if (padded_cell<TX, TY, TZ, D>(t, e, a, b, c)) {
-      T q[7];
-      load_w1d<T, D>(W, w.NS, unit_slot<L>(w, t.gg, a, b, c), q);
-#pragma unroll
-      for (int m = 0; m < 7; ++m) sW[m * Ly::PW::n + e] = q[m];
-    }
-  }
-}
-
-// slopes and interface values of direction D from the staged primitives
-// (two block barriers)
-template <typename T, int TX, int TY, int TZ, int D>
-__device__ __forceinline__ void tile_interfaces(int tid, const T* sW, T* sS, T* sE) {
-  using Ly = TileLayout<TX, TY, TZ, D>;
-  using PW = typename Ly::PW;
-  using PS = typename Ly::PS;
-  constexpr int dx = Ly::dx, dy = Ly::dy, dz = Ly::dz;
-  // slopes: position -1 + s along D at padded index s; its cell sits one
-  // further in the primitives' padding
-  for (int e = tid; e < PS::n; e += Ly::NT) {
-    const int x = e % PS::x, y = (e / PS::x) % PS::y, z = e / (PS::x * PS::y);
-    const int iw = (x + dx) + PW::x * ((y + dy) + PW::y * (z + dz));
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      const T* q = sW + m * PW::n + iw;
-      sS[m * PS::n + e] = mc_slope(q[-PW::stride], q[0], q[PW::stride]);
-    }
-  }
-  __syncthreads();
-  // interface values: face f between cell f - 1 (primitive index f + 1,
-  // slope index f along D) and cell f
-  for (int e = tid; e < Ly::NF; e += Ly::NT) {
-    const int x = e % Ly::FX, y = (e / Ly::FX) % Ly::FY, z = e / (Ly::FX * Ly::FY);
-    const int iw = (x + dx) + PW::x * ((y + dy) + PW::y * (z + dz));
-    const int is = x + PS::x * (y + PS::y * z);
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      const T* q = sW + m * PW::n + iw;
-      const T* sl = sS + m * PS::n + is;
-      sE[m * Ly::NF + e] = ppm_interface(q[0], q[PW::stride], sl[0], sl[PS::stride]);
-    }
-  }
-  __syncthreads();
-}
-
-// each thread's own cell: limit its parabola, trace, store the two states
-template <typename T, bool ALLW, bool L, int TX, int TY, int TZ, int D>
-__device__ __forceinline__ void tile_trace(const Work& w, const T* __restrict__ B, T* __restrict__ QL,
-                                           T* __restrict__ QR, const Tile& t, int tid, T dtdx, T gam,
-                                           const T* sW, const T* sE) {
-  using Ly = TileLayout<TX, TY, TZ, D>;
-  using PW = typename Ly::PW;
-  constexpr int dx = Ly::dx, dy = Ly::dy, dz = Ly::dz;
-  const int lx = tid % TX, ly = (tid / TX) % TY, lz = tid / (TX * TY);
-  const int a = t.a0 + lx, b = t.b0 + ly, c = t.c0 + lz;
-  if (a < t.ux && b < t.uy && c < t.uz) {
-    const int iw = (lx + 2 * dx) + PW::x * ((ly + 2 * dy) + PW::y * (lz + 2 * dz));
-    const int ie = lx + Ly::FX * (ly + Ly::FY * lz);
-    T q[7], sl[7], sr[7];
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      q[m] = sW[m * PW::n + iw];
-      sl[m] = sE[m * Ly::NF + ie];
-      sr[m] = sE[m * Ly::NF + ie + Ly::SF];
-      ppm_limit(q[m], sl[m], sr[m]);
-    }
-    const Site st = unit_site<L>(w, t.gg, a, b, c);
-    const long long N = w.N, NS = w.NS;
-    const long long pu = nbr(w, st.i, st.j, st.k, dx, dy, dz);
-    const long long su = snb<L>(w, st, dx, dy, dz);
-    trace_edges<T, ALLW>(q, B[D * N + st.p], B[D * N + pu], dtdx, gam, sl, sr);
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      QR[((long long)D * 7 + m) * NS + st.s] = sl[m];
-      QL[((long long)D * 7 + m) * NS + su] = sr[m];
-    }
-  }
-}
-
-// tiles of one unit
-template <int TX, int TY, int TZ>
-__host__ __device__ __forceinline__ long long unit_tiles(int ux, int uy, int uz) {
-  return (long long)((ux + TX - 1) / TX) * ((uy + TY - 1) / TY) * ((uz + TZ - 1) / TZ);
-}
-
-// one direction of a tile: stage, slopes and interfaces, trace (four block
-// barriers; the last one frees the arrays for the next direction)
-template <typename T, bool ALLW, bool L, int TX, int TY, int TZ, int D>
-__device__ __forceinline__ void tile_direction(const Work& w, const T* __restrict__ W, const T* __restrict__ B,
-                                               T* __restrict__ QL, T* __restrict__ QR, const Tile& t, int tid, T dtdx,
-                                               T gam, T* sW, T* sS, T* sE) {
-  stage_prims<T, L, TX, TY, TZ, D>(w, W, t, tid, sW);
-  __syncthreads();
-  tile_interfaces<T, TX, TY, TZ, D>(tid, sW, sS, sE);
-  tile_trace<T, ALLW, L, TX, TY, TZ, D>(w, B, QL, QR, t, tid, dtdx, gam, sW, sE);
-  __syncthreads();
-}
-
-// One block per tile of TX * TY * TZ cells (one thread per cell), walking
-// the tiles with a grid-wide stride.
-template <typename T, bool ALLW, bool L, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(TX * TY * TZ) k_ctu_states_tiled(Work w, const T* __restrict__ W,
-                                                                     const T* __restrict__ B, T* __restrict__ QL,
-                                                                     T* __restrict__ QR, DtSrc dts, T inv_dx,
-                                                                     T gam) {
-  constexpr int kW = padded_max<TX, TY, TZ, 2>(), kS = padded_max<TX, TY, TZ, 1>();
-  constexpr int kE = faces_max<TX, TY, TZ>();
-  __shared__ T smem[7 * (kW + kS + kE)];
-  T* sW = smem;
-  T* sS = smem + 7 * kW;
-  T* sE = smem + 7 * (kW + kS);
-  const int tid = (int)threadIdx.x;
-  const T dtdx = T(get_dt(dts)) * inv_dx;
-  const int ux = L ? w.box : w.nx, uy = L ? w.box : w.ny, uz = L ? w.box : w.nz;
-  const int tx = (ux + TX - 1) / TX, ty = (uy + TY - 1) / TY;
-  const long long per = unit_tiles<TX, TY, TZ>(ux, uy, uz);
-  const long long units = L ? work_items(w) / ((long long)w.box * w.box * w.box) : 1;
-  const long long ntiles = units * per;
-  for (long long id = block_rank(); id < ntiles; id += gridDim.x) {   // uniform over the block
-    Tile t;
-    const long long g = id / per;
-    const int r = (int)(id - g * per);
-    t.a0 = (r % tx) * TX;
-    t.b0 = ((r / tx) % ty) * TY;
-    t.c0 = (r / (tx * ty)) * TZ;
-    t.gg = L ? w.gbase + g : 0;
-    t.ux = ux; t.uy = uy; t.uz = uz;
-    tile_direction<T, ALLW, L, TX, TY, TZ, 0>(w, W, B, QL, QR, t, tid, dtdx, gam, sW, sS, sE);
-    tile_direction<T, ALLW, L, TX, TY, TZ, 1>(w, W, B, QL, QR, t, tid, dtdx, gam, sW, sS, sE);
-    tile_direction<T, ALLW, L, TX, TY, TZ, 2>(w, W, B, QL, QR, t, tid, dtdx, gam, sW, sS, sE);
-  }
-}
+// Steps 1, 2, 5 and 6 are the face kernels of mhd_faces.hpp; here are the
+// pieces they share with the learned flux, whose kernels take a face per lane
+// and read the traced states from memory: QR[d][m][p] is the state above the
+// lower d-face of cell p (from cell p), QL[d][m][p] the state below it (from the
+// cell p - e_d).
 
 // the two states of the cell's lower D-face
 template <typename T, int D, bool L>
@@ -1153,154 +849,87 @@ __device__ __forceinline__ void load_states(const Work& w, const T* __restrict__
                                             const Cell<T, L>& c, T wl[7], T wr[7]) {
 #pragma unroll
   for (int m = 0; m < 7; ++m) {
-    wl[m] = c.here(w, QL + ((long long)D * 7 + m) * w.NS);
-    wr[m] = c.here(w, QR + ((long long)D * 7 + m) * w.NS);
+    wl[m] = c.here(w, QL, ((long long)D * 7 + m) * w.NS);
+    wr[m] = c.here(w, QR, ((long long)D * 7 + m) * w.NS);
   }
 }
 
-template <typename T, int D, int SOLVER, bool L>
-__device__ __forceinline__ int traced_face_flux(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                                const T* __restrict__ B, T* __restrict__ F, const Cell<T, L>& c, T gam,
-                                                const Capture& cp) {
-  T wl[7], wr[7], f[7];
-  load_states<T, D, L>(w, QL, QR, c, wl, wr);
-  const T bn = c.template level<D, 0>(w, B + D * w.N);
-  const int fb = riemann<SOLVER>(wl, wr, bn, gam, f);
-  if constexpr (sizeof(T) == 4) {
-    if (cp.buf) capture_face(cp, 3 * c.index(w) + D, wl, wr, bn, f);
+// Step 5's share of one cell, the same for the states at both its D-edges: dt/2
+// times the transverse flux differences of step 2 (frame order: mass, normal
+// and transverse momenta, energy) and the transverse part of -curl E from the
+// step-3 EMFs E_D at the cell's four D-edges, averaged along the field's own
+// axis to the two faces it is differenced between.
+template <typename T>
+struct Transverse {
+  T g[5], c1, c2;
+};
+
+// Step 5: transverse correction of a state s of a cell on a face with normal
+// field bn at time n and bnh after the half step.  The state enters conserved
+// form with bn and leaves it with bnh (the transverse energy fluxes carry the
+// normal field's change of magnetic energy).  The conserved transverse flux
+// differences hold the div B terms of their directions, dBn/dn (0, B, v.B, v):
+// momentum and energy get (dt/2)(B, v.B) dBn/dn, hd = (dt/2) times the cell's
+// normal-field difference (the field's share is in the traced state).
+// Non-physical results keep the input.
+template <typename T>
+__device__ __forceinline__ void correct_state(const Transverse<T>& tr, T bn, T bnh, T hd, T gam, T s[7]) {
+  const T gm1 = gam - T(1), gm1inv = T(1) / gm1;
+  const T vb = s[1] * bn + s[2] * s[5] + s[3] * s[6];
+  const T d = s[0] - tr.g[0];
+  const T mn = s[0] * s[1] + hd * bn - tr.g[1];
+  const T m1 = s[0] * s[2] + hd * s[5] - tr.g[2];
+  const T m2 = s[0] * s[3] + hd * s[6] - tr.g[3];
+  const T e = s[4] * gm1inv + T(0.5) * s[0] * (s[1] * s[1] + s[2] * s[2] + s[3] * s[3]) +
+              T(0.5) * (bn * bn + s[5] * s[5] + s[6] * s[6]) + hd * vb - tr.g[4];
+  const T b1 = s[5] - tr.c1, b2 = s[6] + tr.c2;
+  const T id = T(1) / d;
+  const T vn = mn * id, v1 = m1 * id, v2 = m2 * id;
+  const T p = gm1 * (e - T(0.5) * d * (vn * vn + v1 * v1 + v2 * v2) - T(0.5) * (bnh * bnh + b1 * b1 + b2 * b2));
+  if (d > T(0) && p > T(0)) {
+    s[0] = d; s[1] = vn; s[2] = v1; s[3] = v2; s[4] = p; s[5] = b1; s[6] = b2;
   }
-  store_flux<T, D, L>(w, F, c, f);
-  return fb;
 }
 
-// Step 2: Riemann fluxes from the stored states with the time-n normal field
-template <typename T, int SOLVER, bool L>
-__global__ void __launch_bounds__(kMaxBlock) k_flux_q(Work w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                                   const T* __restrict__ B, T* __restrict__ F, T gam,
-                                                   unsigned long long* nfb, Capture cp) {
-  int fb = 0;
-  FOR_CELLS(T, L, w, c) {
-    fb += traced_face_flux<T, 0, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
-    fb += traced_face_flux<T, 1, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
-    fb += traced_face_flux<T, 2, SOLVER, L>(w, QL, QR, B, F, c, gam, cp);
-  }
-  if (SOLVER == 0) block_count_atomic(fb, nfb);
-}
-
-// Step 5: transverse correction of a state of direction D that comes from
-// the cell n along D (-1 or 0) and sits on a face with normal field bn at time n and bnh
-// after the half step.  Hydro variables: minus dt/2 times the transverse flux
-// differences of step 2 in that cell.  Transverse field: dt/2 times the
-// transverse part of -curl E with the step-3 edge EMFs E_D averaged to the
-// cell's faces.  The state enters conserved form with bn and leaves it with
-// bnh (the transverse energy fluxes carry the normal field's change of
-// magnetic energy).  The conserved transverse flux differences hold the
-// div B terms of their directions, dBn/dn (0, B, v.B, v): momentum and
-// energy get (dt/2)(B, v.B) dBn/dn with dbn the source cell's normal-field
-// difference (the field's share is in the traced state).  Non-physical
-// results keep the input.
+// Step 5's share of the cell n along D
 template <typename T, int D, int n, bool L>
-__device__ __forceinline__ void correct_state(const Work& w, const T* __restrict__ F1, const T* __restrict__ E1,
-                                              const Cell<T, L>& c, T bn, T bnh, T dbn, T hr, T gam, const T s[7],
-                                              T out[7]) {
+__device__ __forceinline__ Transverse<T> transverse_of(const Work& w, const T* __restrict__ F1,
+                                                       const T* __restrict__ E1, const Cell<T, L>& c, T hr) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   constexpr int X = D == 0 ? n : 0, Y = D == 1 ? n : 0, Z = D == 2 ? n : 0;   // the source cell
+  constexpr int comp[5] = {0, 1 + D, 1 + t1, 1 + t2, 4};
   const long long N = w.NS;
-  T v[3], b[3];
-  v[D] = s[1]; v[t1] = s[2]; v[t2] = s[3];
-  b[D] = bn; b[t1] = s[5]; b[t2] = s[6];
-  T u[5];
-  u[0] = s[0];
-  u[1] = s[0] * v[0];
-  u[2] = s[0] * v[1];
-  u[3] = s[0] * v[2];
-  u[4] = s[4] / (gam - T(1)) + T(0.5) * s[0] * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) +
-         T(0.5) * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-  const T vb = v[0] * b[0] + v[1] * b[1] + v[2] * b[2];
+  Transverse<T> r;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) u[1 + a] += hr * dbn * b[a];
-  u[4] += hr * dbn * vb;
-  // transverse flux differences across the source cell
-  const auto fluxes = [&](auto dir) {
-    constexpr int t = decltype(dir)::value;
-    const T* Ft = F1 + (long long)t * 7 * N;
-#pragma unroll
-    for (int m = 0; m < 5; ++m)
-      u[m] -= hr * (c.template at<X + (t == 0), Y + (t == 1), Z + (t == 2)>(w, Ft + m * N) -
-                    c.template at<X, Y, Z>(w, Ft + m * N));
-  };
-  fluxes(std::integral_constant<int, t1>{});
-  fluxes(std::integral_constant<int, t2>{});
-  // the transverse field: E_D at the four D-edges of the source cell, averaged
-  // along the field's own axis to the two faces it is differenced between
-  const T* Ed = E1 + (long long)D * N;
-  const T e00 = c.template at<X, Y, Z>(w, Ed);
-  const T e10 = c.template at<X + (t1 == 0), Y + (t1 == 1), Z + (t1 == 2)>(w, Ed);
-  const T e01 = c.template at<X + (t2 == 0), Y + (t2 == 1), Z + (t2 == 2)>(w, Ed);
-  const T e11 = c.template at<X + (t1 == 0) + (t2 == 0), Y + (t1 == 1) + (t2 == 1), Z + (t1 == 2) + (t2 == 2)>(w, Ed);
-  b[t1] += hr * T(-1) * (T(0.5) * (e01 + e11) - T(0.5) * (e00 + e10));
-  b[t2] += hr * (T(0.5) * (e10 + e11) - T(0.5) * (e00 + e01));
-  b[D] = bnh;
-  const T id = T(1) / u[0];
-  const T vx = u[1] * id, vy = u[2] * id, vz = u[3] * id;
-  const T pr = (gam - T(1)) * (u[4] - T(0.5) * u[0] * (vx * vx + vy * vy + vz * vz) -
-                               T(0.5) * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]));
-  if (u[0] > T(0) && pr > T(0)) {
-    const T vv[3] = {vx, vy, vz};
-    out[0] = u[0]; out[1] = vv[D]; out[2] = vv[t1]; out[3] = vv[t2]; out[4] = pr; out[5] = b[t1]; out[6] = b[t2];
-  } else {
-#pragma unroll
-    for (int m = 0; m < 7; ++m) out[m] = s[m];
+  for (int m = 0; m < 5; ++m) {
+    const long long f1 = (7 * t1 + comp[m]) * N, f2 = (7 * t2 + comp[m]) * N;
+    r.g[m] = hr * (c.template at<X + (t1 == 0), Y + (t1 == 1), Z + (t1 == 2)>(w, F1, f1) -
+                   c.template at<X, Y, Z>(w, F1, f1)) +
+             hr * (c.template at<X + (t2 == 0), Y + (t2 == 1), Z + (t2 == 2)>(w, F1, f2) -
+                   c.template at<X, Y, Z>(w, F1, f2));
   }
+  const long long ed = D * N;
+  const T e00 = c.template at<X, Y, Z>(w, E1, ed);
+  const T e10 = c.template at<X + (t1 == 0), Y + (t1 == 1), Z + (t1 == 2)>(w, E1, ed);
+  const T e01 = c.template at<X + (t2 == 0), Y + (t2 == 1), Z + (t2 == 2)>(w, E1, ed);
+  const T e11 =
+      c.template at<X + (t1 == 0) + (t2 == 0), Y + (t1 == 1) + (t2 == 1), Z + (t1 == 2) + (t2 == 2)>(w, E1, ed);
+  r.c1 = hr * (T(0.5) * (e01 + e11) - T(0.5) * (e00 + e10));
+  r.c2 = hr * (T(0.5) * (e10 + e11) - T(0.5) * (e00 + e01));
+  return r;
 }
 
+// the two states (wl, wr) of the cell's lower D-face corrected to the half-step
+// normal field bnh
 template <typename T, int D, bool L>
-__device__ __forceinline__ void corrected_states(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                                 const T* __restrict__ F1, const T* __restrict__ E1,
-                                                 const T* __restrict__ B, T bnh, const Cell<T, L>& c, T hr, T gam,
-                                                 T wl[7], T wr[7]) {
-  T sl[7], sr[7];
-  load_states<T, D, L>(w, QL, QR, c, sl, sr);
-  const T* Bd = B + D * w.N;
-  const T bn = c.template level<D, 0>(w, Bd);
-  const T bn_lo = c.template level<D, -1>(w, Bd);
-  const T bn_hi = c.template level<D, 1>(w, Bd);
-  correct_state<T, D, -1, L>(w, F1, E1, c, bn, bnh, bn - bn_lo, hr, gam, sl, wl);
-  correct_state<T, D, 0, L>(w, F1, E1, c, bn, bnh, bn_hi - bn, hr, gam, sr, wr);
-}
-
-template <typename T, int D, int SOLVER, bool L>
-__device__ __forceinline__ int corrected_face_flux(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                                   const T* __restrict__ F1, const T* __restrict__ E1,
-                                                   const T* __restrict__ B, const T* __restrict__ Bh,
-                                                   T* __restrict__ F2, const Cell<T, L>& c, T hr, T gam,
-                                                   const Capture& cp) {
-  T wl[7], wr[7], f[7];
-  const T bn = c.here(w, Bh + D * w.NS);
-  corrected_states<T, D, L>(w, QL, QR, F1, E1, B, bn, c, hr, gam, wl, wr);
-  const int fb = riemann<SOLVER>(wl, wr, bn, gam, f);
-  if constexpr (sizeof(T) == 4) {
-    if (cp.buf) capture_face(cp, 3 * c.index(w) + D, wl, wr, bn, f);
-  }
-  store_flux<T, D, L>(w, F2, c, f);
-  return fb;
-}
-
-// Steps 5-6: corrected states and Riemann fluxes with the half-step normal field
-template <typename T, int SOLVER, bool L>
-__global__ void __launch_bounds__(kMaxBlock) k_ctu_correct(Work w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                                        const T* __restrict__ F1, const T* __restrict__ E1,
-                                                        const T* __restrict__ B, const T* __restrict__ Bh,
-                                                        T* __restrict__ F2, DtSrc dts, T inv_dx, T gam,
-                                                        unsigned long long* nfb, Capture cp) {
-  int fb = 0;
-  const T hr = T(0.5 * get_dt(dts)) * inv_dx;
-  FOR_CELLS(T, L, w, c) {
-    fb += corrected_face_flux<T, 0, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
-    fb += corrected_face_flux<T, 1, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
-    fb += corrected_face_flux<T, 2, SOLVER, L>(w, QL, QR, F1, E1, B, Bh, F2, c, hr, gam, cp);
-  }
-  if (SOLVER == 0) block_count_atomic(fb, nfb);
+__device__ __forceinline__ void correct_states(const Work& w, const T* __restrict__ F1, const T* __restrict__ E1,
+                                               const T* __restrict__ B, T bnh, const Cell<T, L>& c, T hr, T gam,
+                                               T wl[7], T wr[7]) {
+  const T bn = c.template level<D, 0>(w, B, D * w.N);
+  const T bn_lo = c.template level<D, -1>(w, B, D * w.N);
+  const T bn_hi = c.template level<D, 1>(w, B, D * w.N);
+  correct_state(transverse_of<T, D, -1, L>(w, F1, E1, c, hr), bn, bnh, hr * (bn - bn_lo), gam, wl);
+  correct_state(transverse_of<T, D, 0, L>(w, F1, E1, c, hr), bn, bnh, hr * (bn_hi - bn), gam, wr);
 }
 
 // Learned flux (HLLD at strong jumps) of the D-faces in step 2 from the
@@ -1329,7 +958,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_flux_dir_mlp(Work w, const float*
     }
     if (c.on) {
       load_states<float, D, L>(w, QL, QR, c, wl, wr);
-      bn = c.template level<D, 0>(w, B + D * w.N);
+      bn = c.template level<D, 0>(w, B, D * w.N);
     }
     fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
     if (c.on) store_flux<float, D, L>(w, F, c, f);
@@ -1338,7 +967,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_flux_dir_mlp(Work w, const float*
 }
 
 // Learned-flux form of steps 5-6 for the D-faces in one kernel: each lane
-// corrects its face's two states (as k_ctu_correct does), then the network
+// corrects its face's two states, then the network
 // (or HLLD at strong jumps) gives the flux with the half-step normal field.
 template <int D, bool L>
 __global__ void __launch_bounds__(kBlock) k_ctu_correct_mlp(Work w, const float* __restrict__ QL,
@@ -1361,8 +990,9 @@ __global__ void __launch_bounds__(kBlock) k_ctu_correct_mlp(Work w, const float*
       wr[m] = 1.0f;
     }
     if (c.on) {
-      bn = c.here(w, Bh + D * w.NS);
-      corrected_states<float, D, L>(w, QL, QR, F1, E1, B, bn, c, hr, gam, wl, wr);
+      bn = c.here(w, Bh, D * w.NS);
+      load_states<float, D, L>(w, QL, QR, c, wl, wr);
+      correct_states<float, D, L>(w, F1, E1, B, bn, c, hr, gam, wl, wr);
     }
     fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
     if (c.on) store_flux<float, D, L>(w, F2, c, f);

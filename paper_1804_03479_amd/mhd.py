@@ -316,9 +316,8 @@ class Solver:
     def set_launch(self, blocks_per_cu: int = 0, threads: int = 0, batch: int = 0, tiles: int = 0):
         """Launch shape of the stage kernels: blocks per CU of the persistent
         grid (0: one item per thread), threads per block (0: 256), the
-        group-list batch of the middle stages (0: the whole list) and, for
-        CTU with PPM, the reconstruction stage on LDS tiles (1) or per cell
-        (0)."""
+        group-list batch of the middle stages (0: the whole list); tiles (0 or
+        1) is accepted and changes nothing."""
         _check(self.lib.mhd_set_launch(self.h, int(blocks_per_cu), int(threads), int(batch), int(tiles)),
                "mhd_set_launch")
 
@@ -352,7 +351,7 @@ class Solver:
                "mhd_prolong_time")
 
     def workspace_bytes(self, lv: Level) -> int:
-        """Device bytes of stage scratch this context needs to update lv."""
+        """Device bytes of stage scratch an update of lv is budgeted at (an upper bound)."""
         self._check_level(lv)
         d = lv.desc()
         v = ctypes.c_size_t()
