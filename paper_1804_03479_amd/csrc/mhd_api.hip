@@ -311,11 +311,12 @@ FaceGeo face_geometry(const Work& w) {
     g.cz = g.cy = len;
     g.lx = w.box;
   } else {
-    // marches of 2 (small grids: as many waves as can be had) to 8 cells; 128^3:
-    // 472-476 us for the whole float step with 4 or 8, 491 with 16, 500 with 2;
-    // 97 x 61 x 83: 137 us with 2, 158 with 8
-    const long long n = w.N >> 18;
-    const int len = n < 2 ? 2 : (n > 8 ? 8 : (int)n);
+    // the longer a march the less of its trace is repeated, the shorter the more
+    // waves a small grid has.  Whole step (us), CTU + PPM + HLLD, marches of 1 / 2 / 4
+    // / 8 cells: float 32^3 41 / 43 / 49 / -, 97 x 61 x 83 146 / 137 / 136 / 158,
+    // 128^3 - / 500 / 476 / 474; double 48^3 102 / 103 / 109 / -, 96^3 620 / 515 /
+    // 490 / 514
+    const int len = w.N < 1 << 16 ? 1 : w.N < 3 << 17 ? 2 : w.N < 3 << 19 ? 4 : 8;
     g.bx = w.nx;
     g.by = w.ny;
     g.bz = g.cz = g.cy = len;

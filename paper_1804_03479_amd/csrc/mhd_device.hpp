@@ -47,15 +47,20 @@ __device__ __forceinline__ void state_and_flux(const T w[7], T bn, T gm1inv, T u
   f[6] = b2 * vn - bn * v2;
 }
 
-// fast magnetosonic speed along the normal, cancellation-free root
+// fast magnetosonic speed along the normal (and its square), cancellation-free
+// root
 template <typename T>
-__device__ __forceinline__ T fast_speed(T d, T p, T bn, T b1, T b2, T gam) {
+__device__ __forceinline__ T fast_speed_sq(T d, T p, T bn, T b1, T b2, T gam) {
   const T id = T(1) / d;
   const T asq = gam * p * id;
   const T btsq = (b1 * b1 + b2 * b2) * id;
   const T bsq = bn * bn * id + btsq;
   const T df = asq - bsq;
-  return dsqrt(T(0.5) * (asq + bsq + dsqrt(df * df + T(4) * asq * btsq)));
+  return T(0.5) * (asq + bsq + dsqrt(df * df + T(4) * asq * btsq));
+}
+template <typename T>
+__device__ __forceinline__ T fast_speed(T d, T p, T bn, T b1, T b2, T gam) {
+  return dsqrt(fast_speed_sq(d, p, bn, b1, b2, gam));
 }
 
 // ---------------------------------------------------------------- HLLE
@@ -190,9 +195,9 @@ __device__ __forceinline__ int riemann_roe(const T wl[7], const T wr[7], T bn, T
     if (k < 6) {
 #pragma unroll
       for (int m = 0; m < 7; ++m) us[m] += alpha * r[m];
-      const T pint = g1 * (us[4] - T(0.5) * (us[1] * us[1] + us[2] * us[2] + us[3] * us[3]) / us[0] -
-                           T(0.5) * (bn * bn + us[5] * us[5] + us[6] * us[6]));
-      if (!(us[0] > T(0)) || !(pint > T(0))) bad = 1;
+      // rho > 0 and p > 0 without the division by rho
+      const T ei = us[4] - T(0.5) * (bn * bn + us[5] * us[5] + us[6] * us[6]);
+      if (!(us[0] > T(0)) || !(us[0] * ei > T(0.5) * (us[1] * us[1] + us[2] * us[2] + us[3] * us[3]))) bad = 1;
     }
   };
   {  // u - cf
@@ -254,102 +259,94 @@ __device__ __forceinline__ int riemann_roe(const T wl[7], const T wr[7], T bn, T
 // Miyoshi & Kusano (2005).  Outer speeds S_L = min(uL, uR) - max(cfL, cfR),
 // S_R = max(uL, uR) + max(cfL, cfR); contact S_M; rotational speeds
 // S*_{L,R} = S_M -/+ |bn| / sqrt(rho*).
+//
+// The flux is F + S (U* - U) + S* (U** - U*) of the side the contact moves away
+// from, each term only while its wave has not passed the face.  Of the other side
+// the ** state needs no more than density, transverse velocity and field of its *
+// state, so the side is selected first and only its energy, conserved state and
+// flux are formed; nothing but the two terms sits behind a branch (a wave has
+// faces of both signs: it ran both sides' flux sums).
 template <typename T>
-__device__ __forceinline__ void hlld_star(const T w[7], const T u[7], T bn, T S, T SM, T pts, T us[7]) {
-  const T d = w[0], vn = w[1];
-  const T sv = S - vn, sm = S - SM;
-  const T ism = T(1) / sm;
-  const T ds = d * sv * ism;
-  const T q = d * sv * sm;
+struct HlldStar {
+  T d, v1, v2, b1, b2, ism;
+};
+
+template <typename T>
+__device__ __forceinline__ HlldStar<T> hlld_star(const T w[7], T bn, T S, T SM) {
+  HlldStar<T> s;
+  const T sv = S - w[1], sm = S - SM;
+  s.ism = T(1) / sm;
+  s.d = w[0] * sv * s.ism;
+  const T q = w[0] * sv * sm;
   const T den = q - bn * bn;
-  T v1, v2, b1, b2;
   // degenerate switch (S = S*, Miyoshi & Kusano 2005): set well above the
   // arithmetic's rounding level, which q - bn^2 inherits from S and SM -- in
   // float a relative 1e-12 is below the noise and the division amplifies it
   const T eps = sizeof(T) == 4 ? T(1e-5) : T(1e-12);
-  if (dabs(den) <= eps * (dabs(q) + bn * bn)) {
-    v1 = w[2]; v2 = w[3]; b1 = w[5]; b2 = w[6];
-  } else {
-    const T iden = T(1) / den;
-    const T mf = bn * (SM - vn) * iden;
-    const T bf = (d * sv * sv - bn * bn) * iden;
-    v1 = w[2] - w[5] * mf;
-    v2 = w[3] - w[6] * mf;
-    b1 = w[5] * bf;
-    b2 = w[6] * bf;
-  }
-  const T pt = w[4] + T(0.5) * (bn * bn + w[5] * w[5] + w[6] * w[6]);
-  const T vb = vn * bn + w[2] * w[5] + w[3] * w[6];
-  const T vbs = SM * bn + v1 * b1 + v2 * b2;
-  const T es = (sv * u[4] - pt * vn + pts * SM + bn * (vb - vbs)) * ism;
-  us[0] = ds; us[1] = ds * SM; us[2] = ds * v1; us[3] = ds * v2; us[4] = es; us[5] = b1; us[6] = b2;
+  const bool flat = dabs(den) <= eps * (dabs(q) + bn * bn);
+  const T iden = T(1) / den;
+  const T mf = bn * (SM - w[1]) * iden;
+  const T bf = (w[0] * sv * sv - bn * bn) * iden;
+  s.v1 = flat ? w[2] : w[2] - w[5] * mf;
+  s.v2 = flat ? w[3] : w[3] - w[6] * mf;
+  s.b1 = flat ? w[5] : w[5] * bf;
+  s.b2 = flat ? w[6] : w[6] * bf;
+  return s;
 }
 
 template <typename T>
 __device__ __forceinline__ void riemann_hlld(const T wl[7], const T wr[7], T bn, T gam, T f[7]) {
   const T gm1inv = T(1) / (gam - T(1));
-  T ul[7], ur[7], fl[7], fr[7];
-  state_and_flux(wl, bn, gm1inv, ul, fl);
-  state_and_flux(wr, bn, gm1inv, ur, fr);
-  const T cmax = dmax(fast_speed(wl[0], wl[4], bn, wl[5], wl[6], gam),
-                      fast_speed(wr[0], wr[4], bn, wr[5], wr[6], gam));
+  const T cmax = dsqrt(dmax(fast_speed_sq(wl[0], wl[4], bn, wl[5], wl[6], gam),
+                            fast_speed_sq(wr[0], wr[4], bn, wr[5], wr[6], gam)));
   const T SL = dmin(wl[1], wr[1]) - cmax;
   const T SR = dmax(wl[1], wr[1]) + cmax;
-  if (SL >= T(0)) {
-#pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fl[m];
-    return;
-  }
-  if (SR <= T(0)) {
-#pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fr[m];
-    return;
-  }
   const T ptl = wl[4] + T(0.5) * (bn * bn + wl[5] * wl[5] + wl[6] * wl[6]);
   const T ptr = wr[4] + T(0.5) * (bn * bn + wr[5] * wr[5] + wr[6] * wr[6]);
   const T ml = wl[0] * (SL - wl[1]);
   const T mr = wr[0] * (SR - wr[1]);
   const T SM = (mr * wr[1] - ml * wl[1] - ptr + ptl) / (mr - ml);
   const T pts = ptl + ml * (SM - wl[1]);
-  T usl[7], usr[7];
-  hlld_star(wl, ul, bn, SL, SM, pts, usl);
-  hlld_star(wr, ur, bn, SR, SM, pts, usr);
-  const T isdl = drsqrt(usl[0]), isdr = drsqrt(usr[0]);
-  const T sdl = usl[0] * isdl, sdr = usr[0] * isdr;
-  const T SLs = SM - dabs(bn) * isdl;
-  const T SRs = SM + dabs(bn) * isdr;
-  if (SLs >= T(0)) {
-#pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fl[m] + SL * (usl[m] - ul[m]);
-    return;
-  }
-  if (SRs <= T(0)) {
-#pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fr[m] + SR * (usr[m] - ur[m]);
-    return;
-  }
+  const HlldStar<T> sl = hlld_star(wl, bn, SL, SM), sr = hlld_star(wr, bn, SR, SM);
+  const T isdl = drsqrt(sl.d), isdr = drsqrt(sr.d);
+  const T sdl = sl.d * isdl, sdr = sr.d * isdr;
   const T sgn = bn >= T(0) ? T(1) : T(-1);
   const T iden = T(1) / (sdl + sdr);
-  const T idl = isdl * isdl, idr = isdr * isdr;
-  const T v1l = usl[2] * idl, v2l = usl[3] * idl;
-  const T v1r = usr[2] * idr, v2r = usr[3] * idr;
-  const T v1ss = (sdl * v1l + sdr * v1r + (usr[5] - usl[5]) * sgn) * iden;
-  const T v2ss = (sdl * v2l + sdr * v2r + (usr[6] - usl[6]) * sgn) * iden;
-  const T b1ss = (sdl * usr[5] + sdr * usl[5] + sdl * sdr * (v1r - v1l) * sgn) * iden;
-  const T b2ss = (sdl * usr[6] + sdr * usl[6] + sdl * sdr * (v2r - v2l) * sgn) * iden;
+  const T v1ss = (sdl * sl.v1 + sdr * sr.v1 + (sr.b1 - sl.b1) * sgn) * iden;
+  const T v2ss = (sdl * sl.v2 + sdr * sr.v2 + (sr.b2 - sl.b2) * sgn) * iden;
+  const T b1ss = (sdl * sr.b1 + sdr * sl.b1 + sdl * sdr * (sr.v1 - sl.v1) * sgn) * iden;
+  const T b2ss = (sdl * sr.b2 + sdr * sl.b2 + sdl * sdr * (sr.v2 - sl.v2) * sgn) * iden;
   const T vbss = SM * bn + v1ss * b1ss + v2ss * b2ss;
-  if (SM >= T(0)) {
-    const T vbl = SM * bn + v1l * usl[5] + v2l * usl[6];
-    const T uss[7] = {usl[0], usl[0] * SM, usl[0] * v1ss, usl[0] * v2ss,
-                      usl[4] - sdl * (vbl - vbss) * sgn, b1ss, b2ss};
+  // the side whose state the face sees
+  const bool right = SL < T(0) && (SM < T(0) || SR <= T(0));
+  T w[7];
 #pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fl[m] + SL * (usl[m] - ul[m]) + SLs * (uss[m] - usl[m]);
-  } else {
-    const T vbr = SM * bn + v1r * usr[5] + v2r * usr[6];
-    const T uss[7] = {usr[0], usr[0] * SM, usr[0] * v1ss, usr[0] * v2ss,
-                      usr[4] + sdr * (vbr - vbss) * sgn, b1ss, b2ss};
-#pragma unroll
-    for (int m = 0; m < 7; ++m) f[m] = fr[m] + SR * (usr[m] - ur[m]) + SRs * (uss[m] - usr[m]);
+  for (int m = 0; m < 7; ++m) w[m] = right ? wr[m] : wl[m];
+  const T S = right ? SR : SL, pt = right ? ptr : ptl;
+  const T ds = right ? sr.d : sl.d, v1 = right ? sr.v1 : sl.v1, v2 = right ? sr.v2 : sl.v2;
+  const T b1 = right ? sr.b1 : sl.b1, b2 = right ? sr.b2 : sl.b2, ism = right ? sr.ism : sl.ism;
+  const T sd = right ? sdr : -sdl;                            // signed: right side of the contact, left side
+  const T Ss = SM + dabs(bn) * (right ? isdr : -isdl);
+  T u[7];
+  state_and_flux(w, bn, gm1inv, u, f);
+  if (right ? S > T(0) : S < T(0)) {
+    const T vb = w[1] * bn + w[2] * w[5] + w[3] * w[6];
+    const T vbs = SM * bn + v1 * b1 + v2 * b2;
+    const T es = ((S - w[1]) * u[4] - pt * w[1] + pts * SM + bn * (vb - vbs)) * ism;
+    f[0] += S * (ds - u[0]);
+    f[1] += S * (ds * SM - u[1]);
+    f[2] += S * (ds * v1 - u[2]);
+    f[3] += S * (ds * v2 - u[3]);
+    f[4] += S * (es - u[4]);
+    f[5] += S * (b1 - u[5]);
+    f[6] += S * (b2 - u[6]);
+    if (right ? Ss > T(0) : Ss < T(0)) {
+      f[2] += Ss * (ds * (v1ss - v1));
+      f[3] += Ss * (ds * (v2ss - v2));
+      f[4] += Ss * (sd * (vbs - vbss) * sgn);
+      f[5] += Ss * (b1ss - b1);
+      f[6] += Ss * (b2ss - b2);
+    }
   }
 }
 
@@ -391,11 +388,17 @@ __device__ __forceinline__ T mc_slope(T qm, T q0, T qp) {
   return minmod(dc, T(2) * minmod(dl, dr));
 }
 
+// twice the same slope (one multiplication less)
+template <typename T>
+__device__ __forceinline__ T mc_slope2(T qm, T q0, T qp) {
+  return minmod(qp - qm, T(4) * minmod(q0 - qm, qp - q0));
+}
+
 // PPM (Colella & Woodward 1984) interface value between cells a and b (a
-// below) from their values and MC-limited slopes
+// below) from their values and twice their MC-limited slopes
 template <typename T>
 __device__ __forceinline__ T ppm_interface(T qa, T qb, T sa, T sb) {
-  return T(0.5) * (qa + qb) - (sb - sa) * T(1.0 / 6.0);
+  return qa + T(0.5) * (qb - qa) - (sb - sa) * T(1.0 / 12.0);
 }
 
 // median of three values (one v_med3_f32 in float)
@@ -428,7 +431,7 @@ __device__ __forceinline__ void ppm_limit(T c, T& l, T& r) {
 // MC-limited slopes, then the monotonicity constraints
 template <typename T>
 __device__ __forceinline__ void ppm_edges(T q0, T q1, T q2, T q3, T q4, T& ql, T& qr) {
-  const T dm = mc_slope(q0, q1, q2), d0 = mc_slope(q1, q2, q3), dp = mc_slope(q2, q3, q4);
+  const T dm = mc_slope2(q0, q1, q2), d0 = mc_slope2(q1, q2, q3), dp = mc_slope2(q2, q3, q4);
   T l = ppm_interface(q1, q2, dm, d0);
   T r = ppm_interface(q2, q3, d0, dp);
   ppm_limit(q2, l, r);
@@ -562,23 +565,25 @@ __device__ __forceinline__ void trace_edges(const T c[7], T bn_lo, T bn_hi, T dt
 #pragma unroll
   for (int m = 0; m < 7; ++m) {
     dq[m] = sr[m] - sl[m];
-    q6[m] = T(6) * (c[m] - T(0.5) * (sl[m] + sr[m]));
+    q6[m] = c[m] - T(0.5) * (sl[m] + sr[m]);   // the profile's curvature / 6
   }
   const T bn = T(0.5) * (bn_lo + bn_hi);
   const T gp = gam * c[4];
   if (!ALLW || (sizeof(T) == 8 && c[5] * c[5] + c[6] * c[6] < T(1e-4) * (gp + bn * bn))) {
+#pragma unroll
+    for (int m = 0; m < 7; ++m) q6[m] *= T(6);
     trace_waves<T, ALLW>(c, dq, q6, bn, dtdx, gam, sl, sr);
   } else {
     const T id = T(1) / c[0];
-    const T h = T(0.5) * dtdx, t = dtdx * dtdx * T(1.0 / 3.0);
+    const T h = T(0.5) * dtdx, t = T(2) * dtdx * dtdx;   // 6 (dt/dx)^2 / 3
     T x[7], y[7], yy[7];
     jacobian(c, bn, id, gp, dq, x);
     jacobian(c, bn, id, gp, q6, y);
     jacobian(c, bn, id, gp, y, yy);
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
-      sr[m] -= h * (x[m] - y[m]) + t * yy[m];
-      sl[m] -= h * (x[m] + y[m]) + t * yy[m];
+      sr[m] = sr[m] - t * yy[m] - h * (x[m] - T(6) * y[m]);
+      sl[m] = sl[m] - t * yy[m] - h * (x[m] + T(6) * y[m]);
     }
   }
   // multidimensional source term of the transverse field

@@ -205,8 +205,8 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
       if (RECON == 1) {
-        s[c] = mc_slope(z1[c], q0[c], q1[c]);
-        lo[c] = ppm_interface(z1[c], q0[c], mc_slope(z0[c], z1[c], q0[c]), s[c]);
+        s[c] = mc_slope2(z1[c], q0[c], q1[c]);
+        lo[c] = ppm_interface(z1[c], q0[c], mc_slope2(z0[c], z1[c], q0[c]), s[c]);
       } else {
         s[c] = q0[c] - z1[c];
       }
@@ -238,7 +238,7 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
         lo[c] = park[64 * (7 + c)];
       }
       if (RECON == 1) {
-        const T s1 = mc_slope(q0[c], q1[c], q2[c]);
+        const T s1 = mc_slope2(q0[c], q1[c], q2[c]);
         hi[c] = ppm_interface(q0[c], q1[c], s[c], s1);
         s[c] = s1;
         sl[c] = lo[c];
@@ -340,12 +340,13 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
 }
 
 // ALLW: trace waves moving away from an edge too (HLL-family solvers).  The
-// double form is held to 168 registers (three waves per SIMD); it needs 173.
+// double form is held to 168 registers (three waves per SIMD; it needs 173), with
+// Roe, which would spill 90 words there, to 256.
 // Bound by vector issue: 128^3 PPM + HLLD takes 114 / 178 us in float for steps
 // 1-2 / 5-6 (a thread per cell and stored states: 257 / 185 us) and 270 / 490 us
 // in double (545 / 385 us).
 template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
-__global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? 3 : 1) k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx,
+__global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1) k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx,
                                                       unsigned long long* nfb) {
   A.dtdx = T(get_dt(dts)) * inv_dx;
   A.hr = T(0.5 * get_dt(dts)) * inv_dx;
