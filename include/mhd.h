@@ -107,9 +107,8 @@ int mhd_required_ghost(int scheme, int recon);
 /* Device bytes of stage scratch (in *bytes) that an update of lv is budgeted
  * at: 35 words per scratch cell (W, Bh, F, E), 98 with CTU, times the scratch
  * cells (the level's cells, or (groups + 2) boxes of (edge + 2 ghost)^3 cells
- * for a group list), plus the group occupancy map.  An upper bound: the
- * learned flux takes the 98 words, the other CTU forms 59.  mhd_step_noalloc
- * accepts a level by this figure.  The context allocates its scratch on the
+ * for a group list), plus the group occupancy map.  An upper bound: CTU takes
+ * 59 of the 98 words.  mhd_step_noalloc accepts a level by this figure.  The context allocates its scratch on the
  * first update of a level that needs more than it holds; the time-mean
  * registers of mhd_accumulate_registers (24 words per scratch cell) come on
  * top.  No HIP call. */

@@ -46,10 +46,8 @@ struct mhd_ctx_s {
   void* Bh;               // 3 * cap
   void* F;                // 21 * cap
   void* E;                // 3 * cap
-  void* QL;               // learned flux: 21 * cap, states below each face
-  void* QR;               // learned flux: 21 * cap, states above each face
   void* F2;               // CTU: 21 * cap, corrector fluxes
-  void* Rh;               // CTU: 3 * cap, the cells' EMFs at the half step (learned flux: in W, which it is done with)
+  void* Rh;               // CTU: 3 * cap, the cells' EMFs at the half step
   void* RF;               // time-averaged final fluxes of a sub-cycled level: 21 * cap_reg
   void* RE;               // time-averaged final EMFs: 3 * cap_reg
   long long cap_reg;
@@ -126,8 +124,7 @@ int check_level(const mhd_ctx_s* ctx, const mhd_level* lv) {
   } while (0)
 
 void free_scratch(mhd_ctx_s* c) {
-  if (c->Rh == c->W) c->Rh = nullptr;
-  void** bufs[] = {&c->W, &c->Bh, &c->F, &c->E, &c->QL, &c->QR, &c->F2, &c->Rh};
+  void** bufs[] = {&c->W, &c->Bh, &c->F, &c->E, &c->F2, &c->Rh};
   for (void** b : bufs) {
     hipFree(*b);
     *b = nullptr;
@@ -141,13 +138,8 @@ int ensure_capacity(mhd_ctx_s* c, long long cells) {
   const size_t e = c->elem;
   bool ok = hipMalloc(&c->W, 8 * cells * e) == hipSuccess && hipMalloc(&c->Bh, 3 * cells * e) == hipSuccess &&
             hipMalloc(&c->F, 21 * cells * e) == hipSuccess && hipMalloc(&c->E, 3 * cells * e) == hipSuccess;
-  if (ok && c->cfg.scheme == MHD_CTU) ok = hipMalloc(&c->F2, 21 * cells * e) == hipSuccess;
-  if (ok && c->cfg.riemann == MHD_MLP) {
-    ok = hipMalloc(&c->QL, 21 * cells * e) == hipSuccess && hipMalloc(&c->QR, 21 * cells * e) == hipSuccess;
-    c->Rh = c->W;
-  } else if (ok && c->cfg.scheme == MHD_CTU) {
-    ok = hipMalloc(&c->Rh, 3 * cells * e) == hipSuccess;
-  }
+  if (ok && c->cfg.scheme == MHD_CTU)
+    ok = hipMalloc(&c->F2, 21 * cells * e) == hipSuccess && hipMalloc(&c->Rh, 3 * cells * e) == hipSuccess;
   if (!ok) {
     free_scratch(c);
     return MHD_ERR_OUT_OF_MEMORY;
@@ -372,7 +364,7 @@ const char* stage_name(const mhd_ctx_s* c, int s) {
 // Stage scratch of one step: the context's (allocated on demand) or carved
 // from the static array of the allocation-free entry point.
 struct StepBufs {
-  void *W, *Bh, *F, *E, *QL, *QR, *F2, *Rh;
+  void *W, *Bh, *F, *E, *F2, *Rh;
   int* occ;
 };
 
@@ -383,7 +375,7 @@ struct CflOut {
 };
 
 StepBufs ctx_bufs(const mhd_ctx_s* c) {
-  return StepBufs{c->W, c->Bh, c->F, c->E, c->QL, c->QR, c->F2, c->Rh, c->occ};
+  return StepBufs{c->W, c->Bh, c->F, c->E, c->F2, c->Rh, c->occ};
 }
 
 // EMF stage: in double on a whole grid LDS tiles of 16 x 8 x 4 cells (15 %
@@ -469,8 +461,6 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
 //   k_ctu_faces    W^n, F1, E, B^{n+1/2} -> F2        steps 1, 5 and 6
 //   k_emf          F2, R^{n+1/2}        -> E          step 7
 //   k_final        U^n, B^n, F2, E      -> U^{n+1}, B^{n+1}   step 8
-// (learned flux: k_ctu_faces stores the traced states and its own kernels take
-// them from there).
 // Group halos (cells below, above each group): 4,4 / 2,2 / 1,2 / 1,1 / 1,1 /
 // 0,1 / 0,0, i.e. 4 ghost cells of U^n.
 template <typename T, int R, bool ALLW, int S, int STAGE, bool L>
@@ -478,7 +468,7 @@ void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_
   const FaceGeo g = face_geometry(w);
   unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
   k_ctu_faces<T, R, ALLW, S, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
-  if constexpr (std::is_same<T, float>::value && STAGE != FACE_STATES) {
+  if constexpr (std::is_same<T, float>::value && S != 3) {
     if (c->capture.buf) {
       nb = decompose(w, kBlock);
       k_capture<R, ALLW, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, A, dts, inv_dx, c->capture);
@@ -497,15 +487,13 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl,
   T* F1 = (T*)sb.F;
   T* F2 = (T*)sb.F2;
   T* E = (T*)sb.E;
-  T* QL = (T*)sb.QL;
-  T* QR = (T*)sb.QR;
   T* Rh = (T*)sb.Rh;
   const T gam = (T)c->cfg.gamma;
   const T inv_dx = (T)(1.0 / lv->dx);
   constexpr int G = 4;   // ghost cells of CTU + PPM
   const int nt = g_threads;
   Work wp = stage_work(lv, 4, 4, G);
-  const Work wq = stage_work(lv, 2, 2, G), wf1 = stage_work(lv, 2, 2, G);
+  const Work wq = stage_work(lv, 2, 2, G);
   const Work we1 = stage_work(lv, 1, 2, G), wh = stage_work(lv, 1, 1, G), wf2 = stage_work(lv, 1, 1, G);
   const Work we2 = stage_work(lv, 0, 1, G);
   Work wu = stage_work(lv, 0, 0, G);
@@ -522,46 +510,28 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl,
     k_prim<T, false, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
   }
   mark(1);
-  constexpr bool kMlp = S == 3 && std::is_same<T, float>::value;
-  const float dp = (float)c->cfg.mlp_dp, drho = (float)c->cfg.mlp_drho;
   const int batch = ev ? 0 : c->batch;   // profiling times whole stages
   for (int b = 0; b < num_batches(wq, batch); ++b) {
-    Work q = batch_of(wq, b, batch), f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch);
+    Work q = batch_of(wq, b, batch), e1 = batch_of(we1, b, batch);
     Work h = batch_of(wh, b, batch), f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
     q.rev = e1.rev = f2.rev = wu.rev = 1;
     // the HLL-family solvers (HLLE, HLLD, the learned flux standing in for
     // HLLD) take every wave in the tracing, Roe only those moving toward an edge
-    const FaceArgs<T> A{W, B, QL, QR, F1, nullptr, nullptr, nullptr, T(0), T(0), gam};
-    if constexpr (kMlp) {
-      launch_faces<T, R, true, S, FACE_STATES, L>(c, q, A, dts, inv_dx);
-      mark(2);
-      // the network kernels keep 256-thread blocks (one LDS stage per wave)
-      nb = decompose(f1, kBlock);
-      k_flux_dir_mlp<0, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
-      k_flux_dir_mlp<1, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
-      k_flux_dir_mlp<2, L><<<nb, kBlock, 0, st>>>(f1, QL, QR, B, F1, gam, c->mlpw, dp, drho, c->nfb, c->capture);
-    } else {
-      launch_faces<T, R, S != 0, S, FACE_PREDICT, L>(c, q, A, dts, inv_dx);
-      mark(2);
-    }
+    FaceArgs<T> A{W, B, F1, nullptr, nullptr, nullptr, gam, T(0), T(0), c->mlpw, (float)c->cfg.mlp_dp,
+                  (float)c->cfg.mlp_drho, c->capture};
+    launch_faces<T, R, S != 0, S, FACE_PREDICT, L>(c, q, A, dts, inv_dx);
+    mark(2);
     mark(3);
     launch_emf<T, L>(e1, F1, Bh, E, nt, st);
     mark(4);
     nb = decompose(h, nt);
     k_half<T, MIX, true, L><<<nb, nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, Rh, Bh);
     mark(5);
-    if constexpr (kMlp) {
-      nb = decompose(f2, kBlock);
-      k_ctu_correct_mlp<0, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
-                                                     drho, c->nfb, c->capture);
-      k_ctu_correct_mlp<1, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
-                                                     drho, c->nfb, c->capture);
-      k_ctu_correct_mlp<2, L><<<nb, kBlock, 0, st>>>(f2, QL, QR, F1, E, B, Bh, F2, dts, inv_dx, gam, c->mlpw, dp,
-                                                     drho, c->nfb, c->capture);
-    } else {
-      launch_faces<T, R, S != 0, S, FACE_CORRECT, L>(c, f2, FaceArgs<T>{W, B, nullptr, nullptr, F2, F1, E, Bh, T(0), T(0), gam}, dts,
-                                                     inv_dx);
-    }
+    A.F = F2;
+    A.F1 = F1;
+    A.E1 = E;
+    A.Bh = Bh;
+    launch_faces<T, R, S != 0, S, FACE_CORRECT, L>(c, f2, A, dts, inv_dx);
     mark(6);
     launch_emf<T, L>(e2, F2, Rh, E, nt, st);
     mark(7);
@@ -639,8 +609,8 @@ constexpr int kMaxDevices = 64;
 std::mutex g_static_mutex;
 unsigned char* g_static_ptr[kMaxDevices];   // per device: its copy's device address
 
-// scratch words per cell an update is budgeted at (W, Bh, F, E; CTU adds F2 and,
-// for the learned flux, QL and QR; the other CTU forms use 3 of those 42 words)
+// scratch words per cell an update is budgeted at (W, Bh, F, E; CTU adds 63, of
+// which it uses 24: F2 and Rh)
 long long step_words(const mhd_ctx_s* c) {
   long long words = 8 + 3 + 21 + 3;
   if (c->cfg.scheme == MHD_CTU) words += 63;
@@ -656,7 +626,8 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   const size_t e = c->elem;
   const bool ctu = c->cfg.scheme == MHD_CTU;
   const size_t n[7] = {8, 3, 21, 3, ctu ? 21u : 0u, ctu ? 21u : 0u, ctu ? 21u : 0u};
-  void** dst[7] = {&sb->W, &sb->Bh, &sb->F, &sb->E, &sb->QL, &sb->QR, &sb->F2};
+  void* spare;   // words of the budget that no stage uses
+  void** dst[7] = {&sb->W, &sb->Bh, &sb->F, &sb->E, &sb->Rh, &spare, &sb->F2};
   size_t off = 0;
   size_t at[8];
   for (int q = 0; q < 7; ++q) {
@@ -667,8 +638,6 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   if (list_mode(lv)) off = align_up(off + (size_t)occupancy_cells(lv) * sizeof(int));
   if (off > kStaticScratchBytes) return off;
   for (int q = 0; q < 7; ++q) *dst[q] = n[q] ? (void*)(base + at[q]) : nullptr;
-  // the learned flux alone keeps the traced states; its half-step EMFs go into W
-  sb->Rh = c->cfg.riemann == MHD_MLP ? sb->W : sb->QL;
   sb->occ = list_mode(lv) ? (int*)(base + at[7]) : nullptr;
   return off;
 }

@@ -14,8 +14,11 @@
 //
 // The traced states are not kept: steps 5-6 trace again from the primitives
 // (8 words a cell) instead of reading 42 words of stored states, which steps 1-2
-// would have to write.  Only the learned flux, whose network kernels take a face
-// per lane, has them stored.
+// would have to write.
+//
+// With the learned flux (SOLVER 3) all 64 lanes of a wave meet at each face, so
+// the network runs on the wave's 64 faces where a solver would run on each
+// lane's.
 //
 // The work is cut into units -- slabs of z-planes of a whole grid, or listed
 // groups' item boxes -- and a unit into wave tasks: first the z-marches, then
@@ -49,24 +52,27 @@ struct FaceGeo {
 // 1129 -> 770 us.  On group lists in float the cells read again miss the L2
 // (many groups' boxes are in flight), so the registers keep them there: 337
 // against 371 us for 191 groups (double 750 against 2200 us).
-template <typename T, bool L>
-constexpr bool kPark = sizeof(T) == 8 || !L;
+// The learned flux parks in both modes.
+template <typename T, int SOLVER, bool L>
+constexpr bool kPark = sizeof(T) == 8 || !L || SOLVER == 3;
 
-// What a launch does with the traced states: store them (step 1 alone), take
-// their fluxes (steps 1-2), or correct them first (steps 1, 5 and 6).
-enum FaceStage { FACE_STATES = 0, FACE_PREDICT = 1, FACE_CORRECT = 2 };
+// What a launch does with the traced states: take their fluxes (steps 1-2), or
+// correct them first (steps 1, 5 and 6).
+enum FaceStage { FACE_PREDICT = 1, FACE_CORRECT = 2 };
 
 template <typename T>
 struct FaceArgs {
   const T* W;      // primitives at time n
   const T* B;      // the level's face field at time n
-  T* QL;           // FACE_STATES: states below and above each face
-  T* QR;
   T* F;            // fluxes out
   const T* F1;     // FACE_CORRECT: predictor fluxes and EMFs, half-step face field
   const T* E1;
   const T* Bh;
-  T dtdx, hr, gam; // dt/dx, half of it
+  T gam;
+  T dtdx, hr;             // dt/dx, half of it (set in the kernel)
+  const MlpWeights* mw;   // learned flux: weights, fallback thresholds, capture
+  float dp, drho;
+  Capture cp;
 };
 
 // value of the lane below (lane 0 keeps its own)
@@ -102,6 +108,12 @@ struct Line {
     else if constexpr (D == 1) return (long long)wrapc(m, w.ny) * w.nx;
     else return (long long)wrapc(m, w.nz) * w.nx * w.ny;
   }
+  // the level index of position m
+  __device__ __forceinline__ long long index(const Work& w, int m) const {
+    if constexpr (L)
+      return p + (D == 1 ? (long long)wrapc(g0 + m, w.ny) * w.nx : (long long)wrapc(g0 + m, w.nz) * w.nx * w.ny);
+    else return o / sizeof(T) + step(w, m);
+  }
   // the level's B at position m
   __device__ __forceinline__ T face(const Work& w, const T* B, int m, unsigned off) const {
     if constexpr (L) {
@@ -113,33 +125,32 @@ struct Line {
   }
 };
 
-// a face is done: store its two states, or its flux
-template <typename T, int D, int SOLVER, int STAGE>
-__device__ __forceinline__ int emit_face(const Work& w, const FaceArgs<T>& A, long long at, unsigned o0, const T wl[7],
-                                         const T wr[7], T bn) {
+// A face is done: store its flux.  on: the lane has a face; every lane of a wave
+// calls (the learned flux runs on the whole wave).  index: the face's cell in the
+// level, for the learned flux's capture.
+template <typename T, int D, int SOLVER>
+__device__ __forceinline__ int emit_face(const Work& w, const FaceArgs<T>& A, MlpShared* sh, bool on, long long at,
+                                         unsigned o0, const T wl[7], const T wr[7], T bn, long long index) {
+  constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3, d = 7 * D;
   const long long NS = w.NS;
-  if constexpr (STAGE == FACE_STATES) {
-    const unsigned o = fresh_offset(o0);
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      store_at<T>(scalar(A.QL + ((7LL * D + m) * NS + at)), o, wl[m]);
-      store_at<T>(scalar(A.QR + ((7LL * D + m) * NS + at)), o, wr[m]);
-    }
-    return 0;
+  T f[7];
+  int fb = 0;
+  if constexpr (SOLVER == 3) {
+    fb = mlp_or_hlld(*sh, on, wl, wr, bn, A.gam, A.dp, A.drho, f, A.cp, 3 * index + D);
+    if (!on) return 0;
   } else {
-    constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3, d = 7 * D;
-    T f[7];
-    const int fb = riemann<SOLVER>(wl, wr, bn, A.gam, f);
-    const unsigned o = fresh_offset(o0);
-    store_at<T>(scalar(A.F + (d * NS + at)), o, f[0]);
-    store_at<T>(scalar(A.F + ((d + 1 + n) * NS + at)), o, f[1]);
-    store_at<T>(scalar(A.F + ((d + 1 + t1) * NS + at)), o, f[2]);
-    store_at<T>(scalar(A.F + ((d + 1 + t2) * NS + at)), o, f[3]);
-    store_at<T>(scalar(A.F + ((d + 4) * NS + at)), o, f[4]);
-    store_at<T>(scalar(A.F + ((d + 5) * NS + at)), o, f[6]);    // E_t1 = F_n[B_t2]
-    store_at<T>(scalar(A.F + ((d + 6) * NS + at)), o, -f[5]);   // E_t2 = -F_n[B_t1]
-    return fb;
+    if (!on) return 0;
+    fb = riemann<SOLVER>(wl, wr, bn, A.gam, f);
   }
+  const unsigned o = fresh_offset(o0);
+  store_at<T>(scalar(A.F + (d * NS + at)), o, f[0]);
+  store_at<T>(scalar(A.F + ((d + 1 + n) * NS + at)), o, f[1]);
+  store_at<T>(scalar(A.F + ((d + 1 + t1) * NS + at)), o, f[2]);
+  store_at<T>(scalar(A.F + ((d + 1 + t2) * NS + at)), o, f[3]);
+  store_at<T>(scalar(A.F + ((d + 4) * NS + at)), o, f[4]);
+  store_at<T>(scalar(A.F + ((d + 5) * NS + at)), o, f[6]);    // E_t1 = F_n[B_t2]
+  store_at<T>(scalar(A.F + ((d + 6) * NS + at)), o, -f[5]);   // E_t2 = -F_n[B_t1]
+  return fb;
 }
 
 // o, o1, o2, o12: byte offsets of the cell and of its upper neighbours along t1,
@@ -171,7 +182,8 @@ __device__ __forceinline__ Transverse<T> transverse(const Work& w, const FaceArg
 // LDS slots (kPark), 64 apart: 0..6 s, 7..13 lo, 14..20 below.
 template <typename T, int D, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
 __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, const Line<T, D, L>& ln, unsigned o1,
-                                          unsigned o2, unsigned o12, bool on, int start, int end, T* park) {
+                                          unsigned o2, unsigned o12, bool on, int start, int end, T* park,
+                                          MlpShared* sh) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
   const long long NS = w.NS;
@@ -189,7 +201,7 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
   // q0 the traced cell, q1 the next, q2 the one after it; s the slope and lo the
   // lower interface value of q0 (PPM), or s its difference from the cell before
   // (PLM); below the state below q0's lower face
-  constexpr bool parked = kPark<T, L>;
+  constexpr bool parked = kPark<T, SOLVER, L>;
   T q0[7], q1[7], q2[7], s[7], lo[7], below[7];
   T bl, hl;
   {
@@ -270,8 +282,9 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
         park[64 * (14 + c)] = sr[c];
       }
     }
-    if (on && m > start)
-      fb += emit_face<T, D, SOLVER, STAGE>(w, A, ln.step(w, m), ln.o, below, sl, STAGE == FACE_CORRECT ? hl : bl);
+    if (m > start)
+      fb += emit_face<T, D, SOLVER>(w, A, sh, on, ln.step(w, m), ln.o, below, sl, STAGE == FACE_CORRECT ? hl : bl,
+                                    SOLVER == 3 && A.cp.buf ? ln.index(w, m) : 0);
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
       if constexpr (!parked) {
@@ -296,7 +309,7 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
 // transverse().
 template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
 __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, const Line<T, 0, L>& ln, unsigned o1,
-                                         unsigned o2, unsigned o12, bool emit) {
+                                         unsigned o2, unsigned o12, bool emit, MlpShared* sh) {
   constexpr int comp[7] = {0, 1, 2, 3, 4, 6, 7};
   const long long NS = w.NS;
   const auto off = [&](int x, unsigned o) {   // offset of the cell x along the row
@@ -335,8 +348,8 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
   }
 #pragma unroll
   for (int c = 0; c < 7; ++c) sr[c] = lane_below(sr[c]);
-  if (!emit) return 0;
-  return emit_face<T, 0, SOLVER, STAGE>(w, A, ln.u, ln.o, sr, sl, STAGE == FACE_CORRECT ? hl : bl);
+  return emit_face<T, 0, SOLVER>(w, A, sh, emit, ln.u, ln.o, sr, sl, STAGE == FACE_CORRECT ? hl : bl,
+                                 L ? ln.p : (long long)(ln.o / sizeof(T)));
 }
 
 // ALLW: trace waves moving away from an edge too (HLL-family solvers).  The
@@ -344,10 +357,12 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
 // Roe, which would spill 90 words there, to 256.
 // Bound by vector issue: 128^3 PPM + HLLD takes 114 / 178 us in float for steps
 // 1-2 / 5-6 (a thread per cell and stored states: 257 / 185 us) and 270 / 490 us
-// in double (545 / 385 us).
+// in double (545 / 385 us).  SOLVER 3, the learned flux (float only): 300 / 422 us
+// against 417 / 536 us with states stored for kernels of their own, and 39 words a
+// cell of scratch less.
 template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
-__global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1) k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx,
-                                                      unsigned long long* nfb) {
+__global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1)
+    k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx, unsigned long long* nfb) {
   A.dtdx = T(get_dt(dts)) * inv_dx;
   A.hr = T(0.5 * get_dt(dts)) * inv_dx;
   const unsigned lane = threadIdx.x & 63;
@@ -365,7 +380,13 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
     return (i + 1 >= n ? (unsigned)(1 - n) : 1u) * stride * (unsigned)sizeof(T);
   };
   const unsigned plane = (unsigned)w.nx * (unsigned)w.ny;
-  __shared__ T parks[kPark<T, L> ? kBlock * 21 : 1];
+  __shared__ T parks[kPark<T, SOLVER, L> ? kBlock * 21 : 1];
+  MlpShared* sh = nullptr;
+  if constexpr (SOLVER == 3) {
+    __shared__ MlpShared shared;
+    sh = &shared;
+    mlp_load_weights(shared, A.mw);
+  }
   T* park = parks + (threadIdx.x >> 6) * (64 * 21) + lane;
   int fb = 0;
   for (unsigned r = block_rank(); r < blocks; r += gridDim.x) {
@@ -408,7 +429,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
       ln.g0 = oz;
       const unsigned o1 = L ? ln.o : ln.o + up(ln.i, w.nx, 1), dy = L ? 0u : up(ln.j, w.ny, (unsigned)w.nx);
       fb += march_line<T, 2, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dy, o1 + dy, on,
-                                                            z0 + za - (L && za == 0 ? 0 : 1), z0 + zb, park);
+                                                            z0 + za - (L && za == 0 ? 0 : 1), z0 + zb, park, sh);
       continue;
     }
     t -= g.w2;
@@ -422,7 +443,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
       ln.g0 = oy;
       const unsigned o1 = L ? ln.o : ln.o + up(ln.k, w.nz, plane), dx = L ? 0u : up(ln.i, w.nx, 1);
       fb += march_line<T, 1, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dx, o1 + dx, on,
-                                                            y0 - (L && y0 == 0 ? 0 : 1), y1, park);
+                                                            y0 - (L && y0 == 0 ? 0 : 1), y1, park, sh);
       continue;
     }
     t -= g.w1;
@@ -436,10 +457,10 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
       Line<T, 0, L> ln;
       place(ln, x, (int)y, z0 + (int)z, true, true, true);
       const unsigned o1 = L ? ln.o : ln.o + up(ln.j, w.ny, (unsigned)w.nx), dz = L ? 0u : up(ln.k, w.nz, plane);
-      fb += row_faces<T, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dz, o1 + dz, on && lane > 0 && q > 0);
+      fb += row_faces<T, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dz, o1 + dz, on && lane > 0 && q > 0, sh);
     }
   }
-  if (SOLVER == 0) block_count_atomic(fb, nfb);
+  if (SOLVER == 0 || SOLVER == 3) block_count_atomic(fb, nfb);
 }
 
 // Interface capture of the shock-capturing solvers, apart from the face kernels

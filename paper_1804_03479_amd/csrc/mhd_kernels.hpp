@@ -837,22 +837,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
 }
 
 // ------------------------------------------------------------ CTU
-// Steps 1, 2, 5 and 6 are the face kernels of mhd_faces.hpp; here are the
-// pieces they share with the learned flux, whose kernels take a face per lane
-// and read the traced states from memory: QR[d][m][p] is the state above the
-// lower d-face of cell p (from cell p), QL[d][m][p] the state below it (from the
-// cell p - e_d).
-
-// the two states of the cell's lower D-face
-template <typename T, int D, bool L>
-__device__ __forceinline__ void load_states(const Work& w, const T* __restrict__ QL, const T* __restrict__ QR,
-                                            const Cell<T, L>& c, T wl[7], T wr[7]) {
-#pragma unroll
-  for (int m = 0; m < 7; ++m) {
-    wl[m] = c.here(w, QL, ((long long)D * 7 + m) * w.NS);
-    wr[m] = c.here(w, QR, ((long long)D * 7 + m) * w.NS);
-  }
-}
+// Steps 1, 2, 5 and 6 are the face kernels of mhd_faces.hpp; here is step 5's
+// correction of a state.
 
 // Step 5's share of one cell, the same for the states at both its D-edges: dt/2
 // times the transverse flux differences of step 2 (frame order: mass, normal
@@ -930,74 +916,6 @@ __device__ __forceinline__ void correct_states(const Work& w, const T* __restric
   const T bn_hi = c.template level<D, 1>(w, B, D * w.N);
   correct_state(transverse_of<T, D, -1, L>(w, F1, E1, c, hr), bn, bnh, hr * (bn - bn_lo), gam, wl);
   correct_state(transverse_of<T, D, 0, L>(w, F1, E1, c, hr), bn, bnh, hr * (bn_hi - bn), gam, wr);
-}
-
-// Learned flux (HLLD at strong jumps) of the D-faces in step 2 from the
-// traced states and the level's time-n normal field B.  With capture on, the face's states and
-// the flux it used are recorded.  Held to 128 VGPRs (four waves per SIMD,
-// a few spilled words): the network's dependent MFMA and transcendental
-// chains need the extra waves to hide their latency (12 % faster than
-// three waves at 135 VGPRs without spills).
-template <int D, bool L>
-__global__ void __launch_bounds__(kBlock, 4) k_flux_dir_mlp(Work w, const float* __restrict__ QL,
-                                                         const float* __restrict__ QR, const float* __restrict__ B,
-                                                         float* __restrict__ F, float gam, const MlpWeights* mw,
-                                                         float dp, float drho, unsigned long long* nfb,
-                                                         Capture cp) {
-  __shared__ MlpShared sh;
-  mlp_load_weights(sh, mw);
-  int fb = 0;
-  // block-uniform trips: every lane of a wave takes part in the network
-  FOR_CHUNKS(float, L, w, c) {
-    float wl[7], wr[7], f[7];
-    float bn = 1.0f;
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      wl[m] = 1.0f;
-      wr[m] = 1.0f;
-    }
-    if (c.on) {
-      load_states<float, D, L>(w, QL, QR, c, wl, wr);
-      bn = c.template level<D, 0>(w, B, D * w.N);
-    }
-    fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
-    if (c.on) store_flux<float, D, L>(w, F, c, f);
-  }
-  block_count_atomic(fb, nfb);
-}
-
-// Learned-flux form of steps 5-6 for the D-faces in one kernel: each lane
-// corrects its face's two states, then the network
-// (or HLLD at strong jumps) gives the flux with the half-step normal field.
-template <int D, bool L>
-__global__ void __launch_bounds__(kBlock) k_ctu_correct_mlp(Work w, const float* __restrict__ QL,
-                                                            const float* __restrict__ QR, const float* __restrict__ F1,
-                                                            const float* __restrict__ E1, const float* __restrict__ B,
-                                                            const float* __restrict__ Bh, float* __restrict__ F2,
-                                                            DtSrc dts, float inv_dx, float gam, const MlpWeights* mw,
-                                                            float dp, float drho, unsigned long long* nfb, Capture cp) {
-  __shared__ MlpShared sh;
-  mlp_load_weights(sh, mw);
-  const float hr = float(0.5 * get_dt(dts)) * inv_dx;
-  int fb = 0;
-  // block-uniform trips: every lane of a wave takes part in the network
-  FOR_CHUNKS(float, L, w, c) {
-    float wl[7], wr[7], f[7];
-    float bn = 1.0f;
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      wl[m] = 1.0f;
-      wr[m] = 1.0f;
-    }
-    if (c.on) {
-      bn = c.here(w, Bh, D * w.NS);
-      load_states<float, D, L>(w, QL, QR, c, wl, wr);
-      correct_states<float, D, L>(w, F1, E1, B, bn, c, hr, gam, wl, wr);
-    }
-    fb += mlp_or_hlld(sh, c.on, wl, wr, bn, gam, dp, drho, f, cp, cp.buf ? 3 * c.index(w) + D : 0);
-    if (c.on) store_flux<float, D, L>(w, F2, c, f);
-  }
-  block_count_atomic(fb, nfb);
 }
 
 // group occupancy map of a list: clear, then mark

@@ -88,10 +88,14 @@ __device__ __forceinline__ f32x4 mfma32(bf16x4 a0, bf16x4 a1, bf16x4 b0, bf16x4 
 // Inference weights as the kernels read them: transposed, BF16, padded.
 //   W1t[64][16] (k = 15 zero), W2t[64][64], W3t[16][64] (rows >= 7 zero),
 //   biases in FP32: b1[64], b2[64], b3[16].
+// Rows lie kP1 and kP2 values apart: sixteen lanes read the same column of
+// sixteen rows, which at 16 and 64 values (32 and 128 bytes) share four banks and
+// one (each read took sixteen turns); at 40 and 144 bytes they do not.
+constexpr int kP1 = 20, kP2 = 72;
 struct MlpWeights {
-  unsigned short W1t[64 * 16];
-  unsigned short W2t[64 * 64];
-  unsigned short W3t[16 * 64];
+  unsigned short W1t[64 * kP1];
+  unsigned short W2t[64 * kP2];
+  unsigned short W3t[16 * kP2];
   float b1[64], b2[64], b3[16];
 };
 
@@ -100,15 +104,15 @@ __global__ void __launch_bounds__(256) k_mlp_pack(const float* __restrict__ P, M
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t < 64 * 16) {
     const int n = t / 16, k = t % 16;
-    out->W1t[t] = f2bf(k < kNin ? P[oW1 + k * kNh + n] : 0.0f);
+    out->W1t[n * kP1 + k] = f2bf(k < kNin ? P[oW1 + k * kNh + n] : 0.0f);
   }
   if (t < 64 * 64) {
     const int n = t / 64, k = t % 64;
-    out->W2t[t] = f2bf(P[oW2 + k * kNh + n]);
+    out->W2t[n * kP2 + k] = f2bf(P[oW2 + k * kNh + n]);
   }
   if (t < 16 * 64) {
     const int n = t / 64, k = t % 64;
-    out->W3t[t] = f2bf(n < kNout ? P[oW3 + k * kNout + n] : 0.0f);
+    out->W3t[n * kP2 + k] = f2bf(n < kNout ? P[oW3 + k * kNout + n] : 0.0f);
   }
   if (t < 64) {
     out->b1[t] = P[ob1 + t];
@@ -205,7 +209,7 @@ __device__ __forceinline__ void mlp_forward_wave(MlpShared& sh, const float x[16
     bf16x4 h1[4], h2[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const bf16x4 wa = *reinterpret_cast<const bf16x4*>(g.W1t + (16 * t + li) * 16 + 4 * lk);
+      const bf16x4 wa = *reinterpret_cast<const bf16x4*>(g.W1t + (16 * t + li) * kP1 + 4 * lk);
       const f32x4 z = mfma16(wa, xf, f32x4{0.f, 0.f, 0.f, 0.f});
       const float4 bb = *reinterpret_cast<const float4*>(g.b1 + 16 * t + 4 * lk);
       h1[t] = f2bf4(gelu(z[0] + bb.x), gelu(z[1] + bb.y), gelu(z[2] + bb.z), gelu(z[3] + bb.w));
@@ -215,7 +219,7 @@ __device__ __forceinline__ void mlp_forward_wave(MlpShared& sh, const float x[16
       f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kc = 0; kc < 2; ++kc) {
-        const unsigned short* wr = g.W2t + (16 * t + li) * 64 + 32 * kc + 4 * lk;
+        const unsigned short* wr = g.W2t + (16 * t + li) * kP2 + 32 * kc + 4 * lk;
         z = mfma32(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16), h1[2 * kc],
                    h1[2 * kc + 1], z);
       }
@@ -225,7 +229,7 @@ __device__ __forceinline__ void mlp_forward_wave(MlpShared& sh, const float x[16
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
-      const unsigned short* wr = g.W3t + li * 64 + 32 * kc + 4 * lk;
+      const unsigned short* wr = g.W3t + li * kP2 + 32 * kc + 4 * lk;
       o = mfma32(*reinterpret_cast<const bf16x4*>(wr), *reinterpret_cast<const bf16x4*>(wr + 16), h2[2 * kc],
                  h2[2 * kc + 1], o);
     }
