@@ -66,8 +66,7 @@ struct mhd_ctx_s {
   MlpWeights* mlpw;       // inference weights of the learned flux
   bool mlp_ready;
   Capture capture;        // interface capture (buf == nullptr: off)
-  float* mlp_ws;          // training workspace
-  long long cap_mlp;      // batch capacity of mlp_ws
+  float* mlp_ws;          // training workspace: kGradBlocks partial gradients
   int num_cu;             // compute units of the device
   long long max_blocks;   // cap on stage-kernel grids (0: none)
   int threads;            // threads per block of the stage kernels (64 .. 512)
@@ -1031,72 +1030,23 @@ int mhd_mlp_set_weights(mhd_ctx c, const float* params_dev) {
 }  // extern "C"
 
 namespace {
-// training workspace: Z1, H1, Z2, H2, dZ2, dZ1 (n x 64 each), Y, dY (n x 7),
-// loss partials
-constexpr int kSplitK = 256;            // batch rows per split-K chunk of a weight gradient
-constexpr int kGradParts = 64 * 64;     // largest weight-gradient tile set
+// training workspace: the gradient kernel's partial sums, one per block
+int grad_blocks(int n) {
+  const int tiles = (n - 1) / 64 + 1;
+  return tiles < kGradBlocks ? tiles : kGradBlocks;
+}
 
-int ensure_mlp_ws(mhd_ctx_s* c, long long n) {
-  if (n <= c->cap_mlp) return MHD_OK;
-  hipFree(c->mlp_ws);
-  c->mlp_ws = nullptr;
-  c->cap_mlp = 0;
-  const long long words = 6 * 64 * n + 2 * 7 * n + (7 * n + 255) / 256 + 16 + kGradParts * ((n + kSplitK - 1) / kSplitK);
-  if (hipMalloc(&c->mlp_ws, words * sizeof(float)) != hipSuccess) return MHD_ERR_OUT_OF_MEMORY;
-  c->cap_mlp = n;
+int ensure_mlp_ws(mhd_ctx_s* c) {
+  if (c->mlp_ws) return MHD_OK;
+  if (hipMalloc(&c->mlp_ws, (size_t)kGradBlocks * kGradPitch * sizeof(float)) != hipSuccess) {
+    c->mlp_ws = nullptr;
+    return MHD_ERR_OUT_OF_MEMORY;
+  }
   return MHD_OK;
 }
 
-struct MlpBufs {
-  float *Z1, *H1, *Z2, *H2, *dZ2, *dZ1, *Y, *dY, *part, *gpart;
-};
-
-MlpBufs mlp_bufs(mhd_ctx_s* c) {
-  const long long n = c->cap_mlp;
-  float* b = c->mlp_ws;
-  MlpBufs m;
-  m.Z1 = b; m.H1 = b + 64 * n; m.Z2 = b + 128 * n; m.H2 = b + 192 * n; m.dZ2 = b + 256 * n; m.dZ1 = b + 320 * n;
-  m.Y = b + 384 * n; m.dY = b + 391 * n; m.part = b + 398 * n;
-  m.gpart = m.part + (7 * n + 255) / 256 + 16;
-  return m;
-}
-
-// weight gradient C[M x N] = A^T B over the batch (K = n): split-K on MFMA
-// with an ordered sum of the chunks (deterministic), M, N <= 64
-void gemm_wgrad(hipStream_t st, int M, int N, int K, const float* A, long long sam, long long sak, const float* Bm,
-                long long sbk, long long sbn, float* C, int ldc, float* gpart) {
-  const int chunks = (K + kSplitK - 1) / kSplitK;
-  const long long waves = (long long)((M + 15) / 16) * ((N + 15) / 16) * chunks;
-  k_mlp_gemm_part<<<(unsigned)((waves + 3) / 4), 256, 0, st>>>(M, N, K, kSplitK, A, sam, sak, Bm, sbk, sbn, gpart);
-  k_mlp_sum_parts<<<(unsigned)((M * N + 255) / 256), 256, 0, st>>>(M, N, chunks, gpart, C, ldc);
-}
-
-template <int EPI>
-void gemm(hipStream_t st, int M, int N, int K, const float* A, long long sam, long long sak, const float* Bm,
-          long long sbk, long long sbn, const float* bias, const float* Zin, float* C, float* H, int ldc) {
-  const long long waves = (long long)((M + 15) / 16) * ((N + 15) / 16);
-  const unsigned blocks = (unsigned)((waves + 3) / 4);
-  k_mlp_gemm<EPI><<<blocks, 256, 0, st>>>(M, N, K, A, sam, sak, Bm, sbk, sbn, bias, Zin, C, H, ldc);
-}
-
-void mlp_forward(mhd_ctx_s* c, const float* P, const float* X, int n, const MlpBufs& b, float* Y) {
-  hipStream_t st = c->stream;
-  gemm<EPI_BIAS_GELU>(st, n, kNh, kNin, X, kNin, 1, P + oW1, kNh, 1, P + ob1, nullptr, b.Z1, b.H1, kNh);
-  gemm<EPI_BIAS_GELU>(st, n, kNh, kNh, b.H1, kNh, 1, P + oW2, kNh, 1, P + ob2, nullptr, b.Z2, b.H2, kNh);
-  gemm<EPI_BIAS>(st, n, kNout, kNh, b.H2, kNh, 1, P + oW3, kNout, 1, P + ob3, nullptr, Y, nullptr, kNout);
-}
-
-void mlp_backward(mhd_ctx_s* c, const float* P, const float* X, const float* dY, int n, const MlpBufs& b, float* G) {
-  hipStream_t st = c->stream;
-  gemm_wgrad(st, kNh, kNout, n, b.H2, 1, kNh, dY, kNout, 1, G + oW3, kNout, b.gpart);
-  k_mlp_colsum<<<kNout, 256, 0, st>>>(n, kNout, dY, G + ob3);
-  gemm<EPI_GELU_PRIME>(st, n, kNh, kNout, dY, kNout, 1, P + oW3, 1, kNout, nullptr, b.Z2, b.dZ2, nullptr, kNh);
-  k_mlp_colsum<<<kNh, 256, 0, st>>>(n, kNh, b.dZ2, G + ob2);
-  gemm_wgrad(st, kNh, kNh, n, b.H1, 1, kNh, b.dZ2, kNh, 1, G + oW2, kNh, b.gpart);
-  gemm<EPI_GELU_PRIME>(st, n, kNh, kNh, b.dZ2, kNh, 1, P + oW2, 1, kNh, nullptr, b.Z1, b.dZ1, nullptr, kNh);
-  k_mlp_colsum<<<kNh, 256, 0, st>>>(n, kNh, b.dZ1, G + ob1);
-  gemm_wgrad(st, kNin, kNh, n, X, 1, kNin, b.dZ1, kNh, 1, G + oW1, kNh, b.gpart);
-}
+// one parameter per lane of 32
+constexpr unsigned kReduceBlocks = (kGradPitch + 31) / 32;
 }  // namespace
 
 extern "C" {
@@ -1105,20 +1055,19 @@ int mhd_mlp_num_params(void) { return kParams; }
 
 int mhd_mlp_forward(mhd_ctx c, const float* params_dev, const float* X_dev, int n, float* Y_dev) {
   if (!c || !params_dev || !X_dev || !Y_dev || n <= 0) return MHD_ERR_INVALID_ARG;
-  int rc = ensure_mlp_ws(c, n);
-  if (rc) return rc;
-  mlp_forward(c, params_dev, X_dev, n, mlp_bufs(c), Y_dev);
+  const int blocks = (n - 1) / 64 + 1;
+  k_mlp_forward<<<blocks < 4 * c->num_cu ? blocks : 4 * c->num_cu, 256, 0, c->stream>>>(params_dev, X_dev, n, Y_dev);
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 
 int mhd_mlp_backward(mhd_ctx c, const float* params_dev, const float* X_dev, const float* dY_dev, int n,
                      float* grads_dev) {
   if (!c || !params_dev || !X_dev || !dY_dev || !grads_dev || n <= 0) return MHD_ERR_INVALID_ARG;
-  int rc = ensure_mlp_ws(c, n);
+  const int rc = ensure_mlp_ws(c);
   if (rc) return rc;
-  const MlpBufs b = mlp_bufs(c);
-  mlp_forward(c, params_dev, X_dev, n, b, b.Y);
-  mlp_backward(c, params_dev, X_dev, dY_dev, n, b, grads_dev);
+  const int nb = grad_blocks(n);
+  k_mlp_gradients<false><<<nb, 256, 0, c->stream>>>(params_dev, X_dev, dY_dev, n, c->mlp_ws);
+  k_mlp_reduce<false><<<kReduceBlocks, 256, 0, c->stream>>>(c->mlp_ws, nb, grads_dev, AdamArgs{});
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 
@@ -1127,20 +1076,14 @@ int mhd_mlp_train_step(mhd_ctx c, float* params_dev, float* adam_m, float* adam_
   if (!c || !params_dev || !adam_m || !adam_v || !grads_dev || !X_dev || !T_dev || n <= 0 || step < 1 ||
       !(lr > 0.f))
     return MHD_ERR_INVALID_ARG;
-  int rc = ensure_mlp_ws(c, n);
+  const int rc = ensure_mlp_ws(c);
   if (rc) return rc;
-  hipStream_t st = c->stream;
-  const MlpBufs b = mlp_bufs(c);
-  mlp_forward(c, params_dev, X_dev, n, b, b.Y);
-  const long long total = 7LL * n;
-  const unsigned nb = (unsigned)((total + 255) / 256);
-  k_mlp_mse<<<nb, 256, 0, st>>>(total, b.Y, T_dev, b.dY, b.part);
-  if (loss_dev) k_mlp_loss<<<1, 64, 0, st>>>(b.part, (int)nb, total, loss_dev);
-  mlp_backward(c, params_dev, X_dev, b.dY, n, b, grads_dev);
+  const int nb = grad_blocks(n);
   const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-  k_mlp_adam<<<(kParams + 255) / 256, 256, 0, st>>>(params_dev, adam_m, adam_v, grads_dev, kParams, lr, b1, b2, 1e-8f,
-                                                    c1, c2);
+  const AdamArgs a{params_dev, adam_m, adam_v, loss_dev, (float)(7LL * n), lr, b1, b2, 1e-8f,
+                   1.0f - powf(b1, (float)step), 1.0f - powf(b2, (float)step)};
+  k_mlp_gradients<true><<<nb, 256, 0, c->stream>>>(params_dev, X_dev, T_dev, n, c->mlp_ws);
+  k_mlp_reduce<true><<<kReduceBlocks, 256, 0, c->stream>>>(c->mlp_ws, nb, grads_dev, a);
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 

@@ -3,7 +3,7 @@
 // where the pressure or density jump exceeds a threshold), its training
 // kernels, and the capture of interface samples.  BF16 operands, FP32
 // accumulation on the MFMA units (v_mfma_f32_16x16x16_bf16, and for the
-// 64-deep layers of inference v_mfma_f32_16x16x32_bf16).
+// 64-deep layers inside a step v_mfma_f32_16x16x32_bf16).
 //
 // Features: the mean of the two face-frame primitive states (rho, vn, vt1,
 // vt2, p, Bt1, Bt2), the unit jump and the jump size s, and Bn, all in units
@@ -361,154 +361,297 @@ __global__ void __launch_bounds__(256) k_mlp_prepare(const float* __restrict__ S
   flag[i] = ((jp > dp) || (jr > drho) ? 1 : 0) | (x[4] < kTinyJump ? 2 : 0);
 }
 
-// Epilogues of the training GEMM
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_PRIME = 3 };
+// ---- the network on batches of rows
+//
+// Like the inference above the batch kernels run the network transposed, a wave
+// on 16 rows at a time, every layer's accumulator tile being the next layer's B
+// operand: activations never leave the registers.  The FP32 master weights are
+// rounded to BF16 into LDS by each block.  (One GEMM per layer with FP32
+// activations in memory moved 1 KB per row and, at the driver's batch of 4096,
+// spent its time on sixteen launches.)
+struct BatchWeights {
+  unsigned short W1t[64 * kP1], W2t[64 * kP2], W3t[16 * kP2];   // [out][in], as MlpWeights
+  float b1[64], b2[64], b3[16];
+};
 
-// C[M x N] = A[M x K] . B[K x N] with A(m,k) = A[m*sam + k*sak] and
-// B(k,n) = B[k*sbk + n*sbn] (FP32 in memory, rounded to BF16 on load,
-// FP32 accumulation).  One wave per 16 x 16 tile of C.
-//   EPI_STORE:      C
-//   EPI_BIAS:       C + bias[n]
-//   EPI_BIAS_GELU:  Z = C + bias[n] -> Z and H = gelu(Z)
-//   EPI_GELU_PRIME: C * gelu'(Zin[m][n])
-template <int EPI>
-__global__ void __launch_bounds__(256) k_mlp_gemm(int M, int N, int K, const float* __restrict__ A, long long sam,
-                                                  long long sak, const float* __restrict__ Bm, long long sbk,
-                                                  long long sbn, const float* __restrict__ bias,
-                                                  const float* __restrict__ Zin, float* __restrict__ C,
-                                                  float* __restrict__ H, int ldc) {
-  const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const int tiles_n = (N + 15) / 16;
-  const int tiles = ((M + 15) / 16) * tiles_n;
-  if (wave >= tiles) return;
-  const int m0 = (wave / tiles_n) * 16, n0 = (wave % tiles_n) * 16;
-  f32x4 c = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    bf16x4 a, b;
+__device__ __forceinline__ void load_batch_weights(BatchWeights& g, const float* __restrict__ P) {
+  for (int t = threadIdx.x; t < 64 * 16; t += blockDim.x) {
+    const int k = t >> 6, n = t & 63;
+    g.W1t[n * kP1 + k] = f2bf(k < kNin ? P[oW1 + k * kNh + n] : 0.0f);
+    // W3: k the output (rows past the seventh are zero), n the hidden unit
+    g.W3t[k * kP2 + n] = f2bf(k < kNout ? P[oW3 + n * kNout + k] : 0.0f);
+  }
+  for (int t = threadIdx.x; t < 64 * 64; t += blockDim.x) g.W2t[(t & 63) * kP2 + (t >> 6)] = f2bf(P[oW2 + t]);
+  for (int t = threadIdx.x; t < 64; t += blockDim.x) {
+    g.b1[t] = P[ob1 + t];
+    g.b2[t] = P[ob2 + t];
+    if (t < 16) g.b3[t] = t < kNout ? P[ob3 + t] : 0.0f;
+  }
+}
+
+// two 16-deep products, the first before the second: rounded as a 16-deep loop over
+// k, so that no activation falls on the other side of a BF16 rounding point
+__device__ __forceinline__ f32x4 mfma16x2(bf16x4 a0, bf16x4 a1, bf16x4 b0, bf16x4 b1, f32x4 c) {
+  return mfma16(a1, b1, mfma16(a0, b0, c));
+}
+
+__device__ __forceinline__ bf16x4 frag(const unsigned short* p) { return *reinterpret_cast<const bf16x4*>(p); }
+
+// features 4 lk .. 4 lk + 3 of one row of X (zero past the fifteenth and for rows past the batch)
+__device__ __forceinline__ bf16x4 row_features(const float* __restrict__ X, long long row, bool on, int lk) {
+  float x[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = k0 + 4 * lk + q;
-      const int m = m0 + li, n = n0 + li;
-      const float av = (m < M && k < K) ? A[m * sam + k * sak] : 0.0f;
-      const float bv = (n < N && k < K) ? Bm[k * sbk + n * sbn] : 0.0f;
-      a[q] = (short)f2bf(av);
-      b[q] = (short)f2bf(bv);
+  for (int i = 0; i < 4; ++i) x[i] = on && 4 * lk + i < kNin ? X[row * kNin + 4 * lk + i] : 0.0f;
+  return f2bf4(x[0], x[1], x[2], x[3]);
+}
+
+// pre-activations and BF16 activations of both hidden layers and the outputs of 16
+// rows: lane (li, lk) holds units 16 t + 4 lk + 0..3 (outputs 4 lk + 0..3) of row li
+struct BatchForward {
+  f32x4 z1[4], z2[4], o;
+  bf16x4 h1[4], h2[4];
+};
+
+__device__ __forceinline__ void batch_forward(const BatchWeights& g, bf16x4 xf, int li, int lk, BatchForward& r) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float4 b = *reinterpret_cast<const float4*>(g.b1 + 16 * t + 4 * lk);
+    r.z1[t] = mfma16(frag(g.W1t + (16 * t + li) * kP1 + 4 * lk), xf, f32x4{0.f, 0.f, 0.f, 0.f}) +
+              f32x4{b.x, b.y, b.z, b.w};
+    r.h1[t] = f2bf4(gelu(r.z1[t][0]), gelu(r.z1[t][1]), gelu(r.z1[t][2]), gelu(r.z1[t][3]));
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      const unsigned short* w = g.W2t + (16 * t + li) * kP2 + 32 * kc + 4 * lk;
+      z = mfma16x2(frag(w), frag(w + 16), r.h1[2 * kc], r.h1[2 * kc + 1], z);
     }
-    c = mfma16(a, b, c);
+    const float4 b = *reinterpret_cast<const float4*>(g.b2 + 16 * t + 4 * lk);
+    r.z2[t] = z + f32x4{b.x, b.y, b.z, b.w};
+    r.h2[t] = f2bf4(gelu(r.z2[t][0]), gelu(r.z2[t][1]), gelu(r.z2[t][2]), gelu(r.z2[t][3]));
   }
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int m = m0 + 4 * lk + q, n = n0 + li;
-    if (m >= M || n >= N) continue;
-    const long long o = (long long)m * ldc + n;
-    float v = c[q];
-    if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) v += bias[n];
-    if (EPI == EPI_GELU_PRIME) v *= gelu_prime(Zin[o]);
-    C[o] = v;
-    if (EPI == EPI_BIAS_GELU) H[o] = gelu(v);
+  for (int kc = 0; kc < 2; ++kc) {
+    const unsigned short* w = g.W3t + li * kP2 + 32 * kc + 4 * lk;
+    o = mfma16x2(frag(w), frag(w + 16), r.h2[2 * kc], r.h2[2 * kc + 1], o);
   }
+  const float4 b = *reinterpret_cast<const float4*>(g.b3 + 4 * lk);
+  r.o = o + f32x4{b.x, b.y, b.z, b.w};
 }
 
-// Split-K form of EPI_STORE for the weight gradients (small M x N, K = the
-// batch): wave w computes tile w % tiles over rows [kc (w / tiles), + kc) of
-// K into part[chunk][M][N]; k_mlp_sum_parts adds the chunks in order.
-__global__ void __launch_bounds__(256) k_mlp_gemm_part(int M, int N, int K, int kc, const float* __restrict__ A,
-                                                       long long sam, long long sak, const float* __restrict__ Bm,
-                                                       long long sbk, long long sbn, float* __restrict__ part) {
-  const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6;
+// Y = network(X).  Bound by the GELUs: 128 exponentials and reciprocals a row.
+// 250,000 rows: 218 us as three GEMMs, 22 us.  Four blocks per CU at most: a block
+// pays once for its copy of the weights.
+__global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X, int n,
+                                                     float* __restrict__ Y) {
+  __shared__ BatchWeights g;
+  load_batch_weights(g, P);
+  __syncthreads();
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const int tiles_n = (N + 15) / 16;
-  const int tiles = ((M + 15) / 16) * tiles_n;
-  const int chunks = (K + kc - 1) / kc;
-  if (wave >= tiles * chunks) return;
-  const int tile = wave % tiles, chunk = wave / tiles;
-  const int m0 = (tile / tiles_n) * 16, n0 = (tile % tiles_n) * 16;
-  const int kb = chunk * kc, ke = min(K, kb + kc);
-  f32x4 c = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kb; k0 < ke; k0 += 16) {
-    bf16x4 a, b;
+  const int tiles = (n - 1) / 16 + 1, step = gridDim.x * 4;
+  for (int tile = blockIdx.x * 4 + (threadIdx.x >> 6); tile < tiles; tile += step) {
+    const long long row = 16LL * tile + li;
+    const bool on = row < n;
+    BatchForward r;
+    batch_forward(g, row_features(X, row, on, lk), li, lk, r);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = k0 + 4 * lk + q;
-      const int m = m0 + li, n = n0 + li;
-      const float av = (m < M && k < ke) ? A[m * sam + k * sak] : 0.0f;
-      const float bv = (n < N && k < ke) ? Bm[k * sbk + n * sbn] : 0.0f;
-      a[q] = (short)f2bf(av);
-      b[q] = (short)f2bf(bv);
+    for (int i = 0; i < 4; ++i)
+      if (on && 4 * lk + i < kNout) Y[row * kNout + 4 * lk + i] = r.o[i];
+  }
+}
+
+// Gradients of a batch, one partial sum over rows per block.  A block takes 64
+// rows at a time: each wave runs 16 of them forward and backward in registers,
+// leaves the BF16 operands of the weight gradients transposed in LDS, and the
+// block then contracts over its 64 rows, each wave six of the 24 gradient tiles.
+// Bias gradients sum the FP32 values.  MSE: dY = 2 (Y - T) / (7 n) and the squared
+// error's sum; otherwise T holds dY.  part: kGradPitch floats per block.
+// Bound by latency (a block per CU and tile): a training step on 4096 rows takes
+// 19.5 us with the reduction (159 us as sixteen launches).
+constexpr int kGradPitch = kParams + 1;   // the gradients and the squared error
+constexpr int kGradBlocks = 256;          // blocks at most
+
+struct GradShared {
+  BatchWeights w;
+  unsigned short W2[64 * kP2], W3[64 * kP1];                                  // [in][out]
+  unsigned short Xt[16 * kP2], H1t[64 * kP2], H2t[64 * kP2];                  // [unit][row]
+  unsigned short D1t[64 * kP2], D2t[64 * kP2], D3t[16 * kP2];
+};
+
+template <bool MSE>
+__global__ void __launch_bounds__(256) k_mlp_gradients(const float* __restrict__ P, const float* __restrict__ X,
+                                                       const float* __restrict__ T, int n, float* __restrict__ part) {
+  __shared__ GradShared g;
+  load_batch_weights(g.w, P);
+  for (int t = threadIdx.x; t < 64 * 64; t += 256) g.W2[(t >> 6) * kP2 + (t & 63)] = f2bf(P[oW2 + t]);
+  for (int t = threadIdx.x; t < 64 * 16; t += 256) {
+    const int k = t & 15, m = t >> 4;
+    g.W3[m * kP1 + k] = f2bf(k < kNout ? P[oW3 + m * kNout + k] : 0.0f);
+  }
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4, wv = threadIdx.x >> 6;
+  const float total = (float)(7LL * n);
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 gw1 = zero, gw2[4], gw3 = zero, gb1[4], gb2[4], gb3 = zero;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) gw2[t] = gb1[t] = gb2[t] = zero;
+  float err = 0.0f;
+  const int tiles = (n - 1) / 64 + 1;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const long long row = 64LL * tile + 16 * wv + li;
+    const bool on = row < n;
+    __syncthreads();   // weights loaded; the operands of the tile before are read
+    const bf16x4 xf = row_features(X, row, on, lk);
+    BatchForward r;
+    batch_forward(g.w, xf, li, lk, r);
+    f32x4 dy = zero;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (!on || 4 * lk + i >= kNout) continue;
+      const float t = T[row * kNout + 4 * lk + i];
+      if (MSE) {
+        const float d = r.o[i] - t;
+        dy[i] = 2.0f * d / total;
+        err += d * d;
+      } else {
+        dy[i] = t;
+      }
     }
-    c = mfma16(a, b, c);
-  }
+    gb3 += dy;
+    const bf16x4 dyf = f2bf4(dy[0], dy[1], dy[2], dy[3]);
+    bf16x4 d2[4], d1[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int m = m0 + 4 * lk + q, n = n0 + li;
-    if (m < M && n < N) part[((long long)chunk * M + m) * N + n] = c[q];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_mlp_sum_parts(int M, int N, int chunks, const float* __restrict__ part,
-                                                       float* __restrict__ C, int ldc) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M * N) return;
-  float acc = 0.0f;
-  for (int ch = 0; ch < chunks; ++ch) acc += part[(long long)ch * M * N + i];
-  C[(long long)(i / N) * ldc + i % N] = acc;
-}
-
-// column sums of a [M x N] matrix (bias gradients), fixed order
-__global__ void __launch_bounds__(256) k_mlp_colsum(int M, int N, const float* __restrict__ S, float* __restrict__ out) {
-  __shared__ float red[256];
-  const int n = blockIdx.x;
-  float acc = 0.0f;
-  for (int m = threadIdx.x; m < M; m += 256) acc += S[(long long)m * N + n];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    for (int t = 0; t < 4; ++t) {
+      f32x4 d = mfma16(frag(g.W3 + (16 * t + li) * kP1 + 4 * lk), dyf, zero);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d[i] *= gelu_prime(r.z2[t][i]);
+      gb2[t] += d;
+      d2[t] = f2bf4(d[0], d[1], d[2], d[3]);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      f32x4 d = zero;
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) {
+        const unsigned short* w = g.W2 + (16 * t + li) * kP2 + 32 * kc + 4 * lk;
+        d = mfma16x2(frag(w), frag(w + 16), d2[2 * kc], d2[2 * kc + 1], d);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d[i] *= gelu_prime(r.z1[t][i]);
+      gb1[t] += d;
+      d1[t] = f2bf4(d[0], d[1], d[2], d[3]);
+    }
+    const int at = 4 * lk * kP2 + 16 * wv + li;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      g.Xt[at + i * kP2] = (unsigned short)xf[i];
+      g.D3t[at + i * kP2] = (unsigned short)dyf[i];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int q = at + (16 * t + i) * kP2;
+        g.H1t[q] = (unsigned short)r.h1[t][i];
+        g.H2t[q] = (unsigned short)r.h2[t][i];
+        g.D1t[q] = (unsigned short)d1[t][i];
+        g.D2t[q] = (unsigned short)d2[t][i];
+      }
+    }
     __syncthreads();
+    // contractions over the 64 rows: A [unit][row], B [row][unit], both read along
+    // the rows
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      const int c = li * kP2 + 32 * kc + 4 * lk, cw = c + 16 * wv * kP2;
+      const bf16x4 h0 = frag(g.H1t + cw), h1 = frag(g.H1t + cw + 16);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const unsigned short* d = g.D2t + c + 16 * t * kP2;
+        gw2[t] = mfma16x2(h0, h1, frag(d), frag(d + 16), gw2[t]);
+      }
+      gw1 = mfma16x2(frag(g.Xt + c), frag(g.Xt + c + 16), frag(g.D1t + cw), frag(g.D1t + cw + 16), gw1);
+      gw3 = mfma16x2(frag(g.H2t + cw), frag(g.H2t + cw + 16), frag(g.D3t + c), frag(g.D3t + c + 16), gw3);
+    }
   }
-  if (threadIdx.x == 0) out[n] = red[0];
-}
-
-// dY = 2 (Y - T) / (n * 7); per-block partial sums of (Y - T)^2
-__global__ void __launch_bounds__(256) k_mlp_mse(long long total, const float* __restrict__ Y, const float* __restrict__ T,
-                                                 float* __restrict__ dY, float* __restrict__ part) {
-  __shared__ float red[256];
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  float e = 0.0f;
-  if (i < total) {
-    const float d = Y[i] - T[i];
-    dY[i] = 2.0f * d / (float)total;
-    e = d * d;
+  float* out = part + (long long)blockIdx.x * kGradPitch;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = 4 * lk + i;
+    if (m < kNin) out[oW1 + m * kNh + 16 * wv + li] = gw1[i];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) out[oW2 + (16 * wv + m) * kNh + 16 * t + li] = gw2[t][i];
+    if (li < kNout) out[oW3 + (16 * wv + m) * kNout + li] = gw3[i];
   }
-  red[threadIdx.x] = e;
+  // bias gradients and the error: over the sixteen rows of a wave, then the waves
+  __shared__ float sums[4][64 + 64 + 16 + 4];
+  const auto rows = [&](float v) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
+    return v;
+  };
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float s1 = rows(gb1[t][i]), s2 = rows(gb2[t][i]);
+      if (li == 0) {
+        sums[wv][16 * t + 4 * lk + i] = s1;
+        sums[wv][64 + 16 * t + 4 * lk + i] = s2;
+      }
+    }
+    const float s3 = rows(gb3[i]);
+    if (li == 0) sums[wv][128 + 4 * lk + i] = s3;
+  }
+  const float se = rows(err);
+  if (li == 0) sums[wv][144 + lk] = se;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  const int t = threadIdx.x;
+  const auto waves = [&](int q) { return ((sums[0][q] + sums[1][q]) + sums[2][q]) + sums[3][q]; };
+  if (t < 64) {
+    out[ob1 + t] = waves(t);
+    out[ob2 + t] = waves(64 + t);
+    if (t < kNout) out[ob3 + t] = waves(128 + t);
+    if (t == 0) out[kParams] = ((waves(144) + waves(145)) + waves(146)) + waves(147);
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void k_mlp_loss(const float* __restrict__ part, int nb, long long total, float* __restrict__ loss) {
-  if (threadIdx.x != 0) return;
+// Sum the blocks' partials in a fixed order (32 parameters x 8 segments of the
+// blocks per block); ADAM: also the loss and one step of Adam (Kingma & Ba) on the
+// FP32 master parameters.
+struct AdamArgs {
+  float *P, *m, *v, *loss;
+  float total, lr, b1, b2, eps, c1, c2;
+};
+
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ part, int blocks, float* __restrict__ G,
+                                                    AdamArgs a) {
+  __shared__ float red[8][32];
+  const int q = threadIdx.x & 31, seg = threadIdx.x >> 5, i = blockIdx.x * 32 + q;
+  const int per = (blocks + 7) / 8, b0 = seg * per, b1 = min(blocks, b0 + per);
   float s = 0.0f;
-  for (int b = 0; b < nb; ++b) s += part[b];
-  *loss = s / (float)total;
-}
-
-// Adam (Kingma & Ba) on the FP32 master parameters
-__global__ void __launch_bounds__(256) k_mlp_adam(float* __restrict__ P, float* __restrict__ m, float* __restrict__ v,
-                                                  const float* __restrict__ g, int n, float lr, float b1, float b2,
-                                                  float eps, float c1, float c2) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  if (i < kGradPitch) {
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += part[(long long)b * kGradPitch + i];
+  }
+  red[seg][q] = s;
+  __syncthreads();
+  if (seg || i >= kGradPitch) return;
+  float g = red[0][q];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) g += red[k][q];
+  if (i == kParams) {
+    if (ADAM && a.loss) *a.loss = g / a.total;
+    return;
+  }
+  G[i] = g;
+  if (ADAM) {
+    const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * g;
+    const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * g * g;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.P[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  }
 }
 
 }  // namespace mhd
