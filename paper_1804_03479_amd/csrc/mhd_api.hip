@@ -56,7 +56,6 @@ struct mhd_ctx_s {
   int* occ_old;           // regridding: occupancy of the fine level's previous list
   long long cap_occ_old;
   double* parts;          // reduction partials
-  double* dres;           // 8 device doubles of reduction results
   Cfl* cfl;
   int* flag;
   unsigned long long* nfb;
@@ -641,6 +640,13 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   return off;
 }
 
+// kernels that only read the level address it by 64-bit indices in a group list, and
+// where a plane of a whole grid passes 4 GiB
+template <typename T>
+bool level_indexed(const Work& w) {
+  return w.groups || (long long)w.nx * w.ny * (long long)sizeof(T) > 0xffffffffLL;
+}
+
 // CFL maximum signal speed of a level into c->smax
 template <typename T, bool MIX>
 void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
@@ -649,16 +655,39 @@ void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
   const unsigned nb = decompose(w, kBlock);
   const Mix mix{lv->E64, c->cfg.beta_fp64};
   const T *U = (const T*)lv->U, *B = (const T*)lv->B;
-  if (w.groups) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
+  if (level_indexed<T>(w)) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
   else k_cfl<T, MIX, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
 }
 
 // ... closed into the context's dt and, if given, an output scalar
-void launch_cfl(mhd_ctx_s* c, const mhd_level* lv, double courant_dx, double* dt_out, int least) {
+void launch_cfl(mhd_ctx_s* c, const mhd_level* lv, double courant_dx, double* dt_out, int least,
+                double* host = nullptr) {
   if (c->cfg.prec == MHD_F64) launch_cfl_t<double, false>(c, lv);
   else if (c->cfg.prec == MHD_F32) launch_cfl_t<float, false>(c, lv);
   else launch_cfl_t<float, true>(c, lv);
-  k_close_cfl<<<1, kCflSlots, 0, c->stream>>>(c->cfl, courant_dx, dt_out, nullptr, least);
+  k_close_cfl<<<1, kCflSlots, 0, c->stream>>>(c->cfl, courant_dx, dt_out, nullptr, least, c->flag, host);
+}
+
+// grid of a deterministic reduction: blocks of one full residency at most, so that
+// the partials of a large level stay few
+unsigned reduce_blocks(mhd_ctx_s* c, Work& w) {
+  g_max_blocks = 8LL * c->num_cu;
+  const unsigned nb = decompose(w, kBlock);
+  g_max_blocks = 0;
+  return nb;
+}
+
+template <typename T>
+void launch_divb(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb) {
+  if (level_indexed<T>(w)) k_divb<T, true><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
+  else k_divb<T, false><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
+}
+
+template <typename T>
+void launch_sums(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb, const double* e64) {
+  const T *U = (const T*)lv->U, *B = (const T*)lv->B;
+  if (level_indexed<T>(w)) k_sums<T, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
+  else k_sums<T, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
 }
 
 int read_flag(mhd_ctx_s* c, int* flag) {
@@ -746,7 +775,7 @@ int mhd_init(const mhd_config* cfg, void* hip_stream, mhd_ctx* out) {
     if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) c->num_cu = prop.multiProcessorCount;
     if (c->num_cu <= 0) c->num_cu = 256;
   }
-  if (hipMalloc(&c->dres, 8 * sizeof(double)) != hipSuccess || hipMalloc(&c->cfl, sizeof(Cfl)) != hipSuccess ||
+  if (hipMalloc(&c->cfl, sizeof(Cfl)) != hipSuccess ||
       hipMalloc(&c->flag, sizeof(int)) != hipSuccess || hipMalloc(&c->nfb, sizeof(unsigned long long)) != hipSuccess ||
       hipHostMalloc(&c->host, 16 * sizeof(double)) != hipSuccess) {
     mhd_finalize(c);
@@ -775,7 +804,7 @@ int mhd_finalize(mhd_ctx c) {
   hipFree(c->RE);
   hipFree(c->rflags);
   hipFree(c->occ_old);
-  hipFree(c->parts); hipFree(c->dres); hipFree(c->cfl); hipFree(c->flag); hipFree(c->nfb); hipFree(c->occ);
+  hipFree(c->parts); hipFree(c->cfl); hipFree(c->flag); hipFree(c->nfb); hipFree(c->occ);
   if (c->host) hipHostFree(c->host);
   delete c;
   return MHD_OK;
@@ -806,14 +835,11 @@ int mhd_cfl_dt(mhd_ctx c, const mhd_level* lv, double* dt_host, double* dt_dev) 
   int rc = check_level(c, lv);
   if (rc) return rc;
   const double cdx = c->cfg.courant * lv->dx;
-  launch_cfl(c, lv, cdx, dt_dev, 0);
+  launch_cfl(c, lv, cdx, dt_dev, 0, dt_host ? c->host : nullptr);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
   if (dt_host) {
-    HIP_TRY(hipMemcpyAsync(c->host, &c->cfl->smax, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
-    int flag = 0;
-    rc = read_flag(c, &flag);
-    if (rc) return rc;
-    if (flag) return MHD_ERR_NONPHYSICAL;
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (c->host[1] != 0.0) return MHD_ERR_NONPHYSICAL;
     const double smax = c->host[0];
     if (!(smax > 0.0)) return MHD_ERR_NONPHYSICAL;
     *dt_host = cdx / smax;
@@ -967,17 +993,14 @@ int mhd_divB(mhd_ctx c, const mhd_level* lv, double* max_abs, double* l1) {
   if (!c) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  const Work w = make_work(lv, 0, 0);
-  const unsigned nb = nblocks(w);
+  Work w = make_work(lv, 0, 0);
+  const unsigned nb = reduce_blocks(c, w);
   rc = ensure_parts(c, 2LL * nb);
   if (rc) return rc;
-  if (c->cfg.prec == MHD_F64)
-    k_divb<double><<<nb, kBlock, 0, c->stream>>>(w, (const double*)lv->B, 1.0 / lv->dx, c->parts);
-  else
-    k_divb<float><<<nb, kBlock, 0, c->stream>>>(w, (const float*)lv->B, 1.0 / lv->dx, c->parts);
-  k_finish<<<1, kBlock, 0, c->stream>>>(c->parts, (int)nb, 2, 1, c->dres);
+  if (c->cfg.prec == MHD_F64) launch_divb<double>(c, lv, w, nb);
+  else launch_divb<float>(c, lv, w, nb);
+  k_finish<<<2, kBlock, 0, c->stream>>>(c->parts, (int)nb, 1, c->host);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
-  HIP_TRY(hipMemcpyAsync(c->host, c->dres, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (l1) *l1 = c->host[0] / (double)w.N;
   if (max_abs) *max_abs = c->host[1];
@@ -988,18 +1011,14 @@ int mhd_sums(mhd_ctx c, const mhd_level* lv, double out[7]) {
   if (!c || !out) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  const Work w = make_work(lv, 0, 0);
-  const unsigned nb = nblocks(w);
+  Work w = make_work(lv, 0, 0);
+  const unsigned nb = reduce_blocks(c, w);
   rc = ensure_parts(c, 7LL * nb);
   if (rc) return rc;
-  const double* e64 = c->cfg.prec == MHD_F32_MIXED ? lv->E64 : nullptr;
-  if (c->cfg.prec == MHD_F64)
-    k_sums<double><<<nb, kBlock, 0, c->stream>>>(w, (const double*)lv->U, (const double*)lv->B, nullptr, c->parts);
-  else
-    k_sums<float><<<nb, kBlock, 0, c->stream>>>(w, (const float*)lv->U, (const float*)lv->B, e64, c->parts);
-  k_finish<<<1, kBlock, 0, c->stream>>>(c->parts, (int)nb, 7, 7, c->dres);
+  if (c->cfg.prec == MHD_F64) launch_sums<double>(c, lv, w, nb, nullptr);
+  else launch_sums<float>(c, lv, w, nb, c->cfg.prec == MHD_F32_MIXED ? lv->E64 : nullptr);
+  k_finish<<<7, kBlock, 0, c->stream>>>(c->parts, (int)nb, 7, c->host);
   if (hipGetLastError() != hipSuccess) return MHD_ERR_HIP;
-  HIP_TRY(hipMemcpyAsync(c->host, c->dres, 7 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   const double dv = lv->dx * lv->dx * lv->dx;
   for (int q = 0; q < 7; ++q) out[q] = c->host[q] * dv;

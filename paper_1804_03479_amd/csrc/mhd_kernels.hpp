@@ -160,9 +160,10 @@ __device__ __forceinline__ void cell_of(const Work& w, long long t, int& i, int&
 // or one add of a wrapped distance (along x and y).  The cell's coordinates
 // come from two multiplications.  (One 64-bit linear index per thread, split
 // by 64-bit divisions, and a 64-bit product per neighbour took 35-80 % of the
-// stages' vector instructions.)  A plane or box is below 4 GB: a plane of
+// stages' vector instructions.)  In a step a plane or box is below 4 GiB: planes of
 // 2^29 cells would need more memory than the device has, since a level has at
-// least four of them and at least 35 words of scratch per cell.
+// least four of them and at least 35 words of scratch per cell.  The kernels that
+// need no scratch (CFL, diagnostics) take such a level by 64-bit level indices.
 // A uniform address the compiler takes as it stands: without this it regroups
 // (array + component + plane) + thread into (array + thread) + component and
 // spends a 64-bit vector add per access instead of a scalar one (a tenth of
@@ -195,7 +196,15 @@ struct Cell {
     const unsigned unit = fdiv(w.by_chunks, rank);
     const unsigned l = (rank - unit * w.chunks) * blockDim.x + threadIdx.x;
     on = l < w.per;
-    if constexpr (L) {
+    if (L && w.groups == nullptr) {   // a whole grid by level indices only (level_indexed)
+      j = (int)(l / (unsigned)w.nx);
+      i = (int)(l - (unsigned)j * (unsigned)w.nx);
+      k = (int)unit;
+      a = i; b = j; c = k;
+      u = 0;
+      o = 0;
+      p = lin(w, i, j, k);
+    } else if constexpr (L) {
       const unsigned box = w.box;
       c = (int)fdiv(w.by_plane, l);
       const unsigned r = l - (unsigned)c * box * box;
@@ -476,10 +485,10 @@ __global__ void __launch_bounds__(kBlock) k_cfl(Work w, const T* __restrict__ U,
 }
 
 // Close a CFL reduction (one wave): its maximum, dt = courant dx / smax, and
-// optionally dt into an output scalar (or, with `least`, the smaller of the two)
-// and t += dt.
+// optionally dt into an output scalar (or, with `least`, the smaller of the two),
+// t += dt, and the maximum and the non-physical flag to pinned host memory.
 __global__ void __launch_bounds__(kCflSlots) k_close_cfl(Cfl* cfl, double courant_dx, double* dt_out, double* t_out,
-                                                         int least) {
+                                                         int least, const int* flag = nullptr, double* host = nullptr) {
   unsigned long long* slot = cfl->slot + threadIdx.x * kCflPitch;
   const double m = wave_max(__longlong_as_double((long long)*slot));
   *slot = 0ull;
@@ -489,6 +498,10 @@ __global__ void __launch_bounds__(kCflSlots) k_close_cfl(Cfl* cfl, double couran
   cfl->dt = dt;
   if (dt_out && (!least || dt < *dt_out)) *dt_out = dt;
   if (t_out) *t_out += dt;
+  if (host) {
+    host[0] = m;
+    host[1] = *flag ? 1.0 : 0.0;
+  }
 }
 
 // ------------------------------------------------------------ fluxes
@@ -965,8 +978,12 @@ __global__ void __launch_bounds__(kBlock) k_prim_to_cons(Work w, const T* __rest
 }
 
 // ------------------------------------------------------------ diagnostics
-// Two-pass deterministic reductions: fixed per-block trees write partials,
-// one block combines them in index order.
+// Two-pass deterministic reductions: a fixed number of blocks sum their cells
+// through fixed trees, then one block per quantity combines the partials in index
+// order and writes the result where the host reads it (pinned memory: no copy to
+// wait for).  All three diagnostics on 128^3 in double, with their waits: 219 us with
+// a block per 256 cells, one block for all rows of partials, 64-bit divisions for the
+// cell and a copy of the result; 108 us so.
 template <int NQ>
 __device__ __forceinline__ void block_partials(double v[NQ], double* part, int stride) {
   __shared__ double red[NQ][kBlock / 64];
@@ -988,17 +1005,16 @@ __device__ __forceinline__ void block_partials(double v[NQ], double* part, int s
 }
 
 // discrete divergence (Eq. 16): partial sums of |div B| and partial maxima
-template <typename T>
+template <typename T, bool L>
 __global__ void __launch_bounds__(kBlock) k_divb(Work w, const T* __restrict__ B, double inv_dx, double* part) {
   double a = 0.0, amax = 0.0;
-  FOR_ITEMS(w, t) {
-    int i, j, k;
-    cell_of(w, t, i, j, k);
-    const long long N = w.N;
-    const long long p = lin(w, i, j, k);
-    const double dv = ((double)B[nbr(w, i, j, k, 1, 0, 0)] - (double)B[p]) * inv_dx +
-                      ((double)B[N + nbr(w, i, j, k, 0, 1, 0)] - (double)B[N + p]) * inv_dx +
-                      ((double)B[2 * N + nbr(w, i, j, k, 0, 0, 1)] - (double)B[2 * N + p]) * inv_dx;
+  const long long N = w.N;
+  FOR_CELLS(T, L, w, c) {
+    const double bx = c.template level<0, 0>(w, B, 0), by = c.template level<0, 0>(w, B, N),
+                 bz = c.template level<0, 0>(w, B, 2 * N);
+    const double dv = ((double)c.template level<0, 1>(w, B, 0) - bx) * inv_dx +
+                      ((double)c.template level<1, 1>(w, B, N) - by) * inv_dx +
+                      ((double)c.template level<2, 1>(w, B, 2 * N) - bz) * inv_dx;
     a += fabs(dv);
     amax = fmax(amax, fabs(dv));
   }
@@ -1015,50 +1031,45 @@ __global__ void __launch_bounds__(kBlock) k_divb(Work w, const T* __restrict__ B
 }
 
 // volume totals: mass, Mx, My, Mz, e, magnetic energy, kinetic energy
-template <typename T>
+template <typename T, bool L>
 __global__ void __launch_bounds__(kBlock) k_sums(Work w, const T* __restrict__ U, const T* __restrict__ B,
                                                  const double* __restrict__ E64, double* part) {
   double v[7] = {0, 0, 0, 0, 0, 0, 0};
-  FOR_ITEMS(w, t) {
-    int i, j, k;
-    cell_of(w, t, i, j, k);
-    const long long N = w.N;
-    const long long p = lin(w, i, j, k);
+  const long long N = w.N;
+  FOR_CELLS(T, L, w, c) {
     double u[5];
 #pragma unroll
-    for (int m = 0; m < 5; ++m) u[m] = (double)U[m * N + p];
-    if (E64) u[4] = E64[p];
+    for (int m = 0; m < 5; ++m) u[m] = (double)c.template level<0, 0>(w, U, m * N);
+    const double bx = 0.5 * ((double)c.template level<0, 0>(w, B, 0) + (double)c.template level<0, 1>(w, B, 0));
+    const double by = 0.5 * ((double)c.template level<0, 0>(w, B, N) + (double)c.template level<1, 1>(w, B, N));
+    const double bz = 0.5 * ((double)c.template level<0, 0>(w, B, 2 * N) + (double)c.template level<2, 1>(w, B, 2 * N));
+    if (E64) u[4] = E64[c.index(w)];
 #pragma unroll
     for (int m = 0; m < 5; ++m) v[m] += u[m];
-    const double bx = 0.5 * ((double)B[p] + (double)B[nbr(w, i, j, k, 1, 0, 0)]);
-    const double by = 0.5 * ((double)B[N + p] + (double)B[N + nbr(w, i, j, k, 0, 1, 0)]);
-    const double bz = 0.5 * ((double)B[2 * N + p] + (double)B[2 * N + nbr(w, i, j, k, 0, 0, 1)]);
     v[5] += 0.5 * (bx * bx + by * by + bz * bz);
     v[6] += 0.5 * (u[1] * u[1] + u[2] * u[2] + u[3] * u[3]) / u[0];
   }
   block_partials<7>(v, part, gridDim.x);
 }
 
-// combine nq rows of nb partials (sum for rows < nsum, max otherwise)
-__global__ void __launch_bounds__(kBlock) k_finish(const double* part, int nb, int nq, int nsum, double* out) {
+// combine row blockIdx.x of nb partials (sum for rows < nsum, max otherwise)
+__global__ void __launch_bounds__(kBlock) k_finish(const double* part, int nb, int nsum, double* out) {
   __shared__ double red[kBlock];
-  for (int q = 0; q < nq; ++q) {
-    const bool is_max = q >= nsum;
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kBlock) {
-      const double x = part[(long long)q * nb + b];
-      acc = is_max ? fmax(acc, x) : acc + x;
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-      if (threadIdx.x < s) red[threadIdx.x] = is_max ? fmax(red[threadIdx.x], red[threadIdx.x + s])
-                                                     : red[threadIdx.x] + red[threadIdx.x + s];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[q] = red[0];
+  const int q = blockIdx.x;
+  const bool is_max = q >= nsum;
+  double acc = 0.0;
+  for (int b = threadIdx.x; b < nb; b += kBlock) {
+    const double x = part[(long long)q * nb + b];
+    acc = is_max ? fmax(acc, x) : acc + x;
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int s = kBlock / 2; s > 0; s >>= 1) {
+    if (threadIdx.x < s) red[threadIdx.x] = is_max ? fmax(red[threadIdx.x], red[threadIdx.x + s])
+                                                   : red[threadIdx.x] + red[threadIdx.x + s];
     __syncthreads();
   }
+  if (threadIdx.x == 0) out[q] = red[0];
 }
 
 }  // namespace mhd
