@@ -13,10 +13,13 @@ namespace mhd {
 // offset d of a cell from its group's origin on a periodic level of n cells,
 // taken in the group box's own range [lo, lo + n) (lo = minus the box's
 // ghost width): unique for every box position since levels with group
-// lists are at least edge + 8 cells wide
-__device__ __forceinline__ int box_offset(int d, int lo, int n) {
-  const int r = (d - lo) % n;
-  return (r < 0 ? r + n : r) + lo;
+// lists are at least edge + 8 cells wide.  Cells reach one past the level at most
+// and origins lie in it, so -n <= d - lo <= n + 9 < 2 n.
+__device__ __forceinline__ int box_offset(int d, int lo, int n) { return wrapc(d - lo, n) + lo; }
+
+// entry of an occupancy map for the group of cell (x, y, z) of the (listed) level
+__device__ __forceinline__ int occ_at(const Work& w, const int* __restrict__ occ, int x, int y, int z) {
+  return occ[((long long)fdiv(w.by_edge, z) * w.gny + fdiv(w.by_edge, y)) * w.gnx + fdiv(w.by_edge, x)];
 }
 
 // Prolongation from a coarse level (nc) to a fine level (2 nc), paper
@@ -236,7 +239,6 @@ template <typename T>
 __global__ void __launch_bounds__(kBlock) k_prolong_ghosts(Work wc, Work wf, Coarse<T> Uc,
                                                            Coarse<T> Bc, T* __restrict__ Uf,
                                                            T* __restrict__ Bf, T gam) {
-  const long long per = (long long)wc.box * wc.box * wc.box;
   FOR_ITEMS(wc, t) {
     int i, j, k, a0, b0, c0;
     cell_of(wc, t, i, j, k, a0, b0, c0);
@@ -245,13 +247,13 @@ __global__ void __launch_bounds__(kBlock) k_prolong_ghosts(Work wc, Work wf, Coa
     if (a0 >= lo && a0 < hi && b0 >= lo && b0 < hi && c0 >= lo && c0 < hi) continue;
     auto listed = [&](int x, int y, int z) {
       x = wrapc(x, wf.nx); y = wrapc(y, wf.ny); z = wrapc(z, wf.nz);
-      return wf.occ[((long long)(z / wf.edge) * wf.gny + y / wf.edge) * wf.gnx + x / wf.edge] != 0;
+      return occ_at(wf, wf.occ, x, y, z) != 0;
     };
     const int I0 = 2 * i, J0 = 2 * j, K0 = 2 * k;
     if (listed(I0, J0, K0)) continue;
     const bool lx = listed(I0 - 1, J0, K0), ly = listed(I0, J0 - 1, K0), lz = listed(I0, J0, K0 - 1);
     // children inside the requested fine halo box [o - halo, o + edge + halo + 1) of this item's group
-    const int* o = wf.groups + 3 * (t / per);
+    const int* o = wf.groups + 3LL * (wc.items < 1LL << 31 ? (long long)fdiv(wc.by_box, (unsigned)t) : t / ((long long)wc.box * wc.box * wc.box));
     auto in_box = [&](int x, int y, int z) {
       const int blo = -wf.halo, bhi = wf.edge + wf.halo + 1;
       const int dx = box_offset(x - o[0], blo, wf.nx), dy = box_offset(y - o[1], blo, wf.ny),
@@ -279,7 +281,30 @@ __global__ void __launch_bounds__(kBlock) k_prolong_ghosts(Work wc, Work wf, Coa
 __device__ __forceinline__ bool refined(const Work& wf, int ci, int cj, int ck) {
   if (!wf.groups) return true;
   const int I = wrapc(2 * ci, wf.nx), J = wrapc(2 * cj, wf.ny), K = wrapc(2 * ck, wf.nz);
-  return wf.occ[((long long)(K / wf.edge) * wf.gny + J / wf.edge) * wf.gnx + I / wf.edge] != 0;
+  return occ_at(wf, wf.occ, I, J, K) != 0;
+}
+
+// The refined ones among the 27 coarse cells around (i, j, k): bit (dx + 1) + 3 (dy + 1)
+// + 9 (dz + 1).  All lookups are in flight at once: one test after the other, each
+// waiting for its entry, was what the corrections spent their time on.
+__device__ __forceinline__ constexpr int around(int dx, int dy, int dz) { return dx + 1 + 3 * (dy + 1) + 9 * (dz + 1); }
+__device__ __forceinline__ unsigned refined_around(const Work& wf, int i, int j, int k) {
+  if (!wf.groups) return (1u << 27) - 1;
+  int x[3], y[3];
+  long long z[3];
+#pragma unroll
+  for (int o = 0; o < 3; ++o) {
+    x[o] = (int)fdiv(wf.by_edge, wrapc(2 * (i + o - 1), wf.nx));
+    y[o] = (int)fdiv(wf.by_edge, wrapc(2 * (j + o - 1), wf.ny)) * wf.gnx;
+    z[o] = (long long)fdiv(wf.by_edge, wrapc(2 * (k + o - 1), wf.nz)) * wf.gny * wf.gnx;
+  }
+  int v[27];
+#pragma unroll
+  for (int q = 0; q < 27; ++q) v[q] = wf.occ[z[q / 9] + y[q / 3 % 3] + x[q % 3]];
+  unsigned m = 0;
+#pragma unroll
+  for (int q = 0; q < 27; ++q) m |= v[q] != 0 ? 1u << q : 0u;
+  return m;
 }
 
 // mean of the four fine faces of direction A on the lower A-face of coarse
@@ -344,13 +369,14 @@ struct LevelScratch {
   const int* occ;       // group index + 1 per group of the level (list mode)
   const int* groups;
   int edge, gnx, gny, gnz, nx, ny, nz;
+  FastDiv by_edge;
 };
 
 
 // listed group holding cell (i, j, k) of the level, or -1
 __device__ __forceinline__ int group_at(const LevelScratch& v, int i, int j, int k) {
   i = wrapc(i, v.nx); j = wrapc(j, v.ny); k = wrapc(k, v.nz);
-  return v.occ[((long long)(k / v.edge) * v.gny + j / v.edge) * v.gnx + i / v.edge] - 1;
+  return v.occ[((long long)fdiv(v.by_edge, k) * v.gny + fdiv(v.by_edge, j)) * v.gnx + fdiv(v.by_edge, i)] - 1;
 }
 
 // scratch slot of cell (i, j, k) inside the box of group g (list mode), or
@@ -376,8 +402,12 @@ __global__ void __launch_bounds__(kBlock) k_correct_u(Work wc, Work wf, LevelScr
   FOR_ITEMS(wc, t) {
     int i, j, k;
     cell_of(wc, t, i, j, k);
-    if (refined(wf, i, j, k)) continue;
+    const unsigned near = refined_around(wf, i, j, k);
+    constexpr unsigned sides = 1u << around(-1, 0, 0) | 1u << around(1, 0, 0) | 1u << around(0, -1, 0) |
+                               1u << around(0, 1, 0) | 1u << around(0, 0, -1) | 1u << around(0, 0, 1);
+    if ((near >> around(0, 0, 0) & 1) || !(near & sides)) continue;
     T du[5] = {T(0), T(0), T(0), T(0), T(0)};
+    bool any = false;
     const int C[3] = {i, j, k};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -386,11 +416,12 @@ __global__ void __launch_bounds__(kBlock) k_correct_u(Work wc, Work wf, LevelScr
       for (int sgn = -1; sgn <= 1; sgn += 2) {
         int D[3] = {i, j, k};
         D[a] += sgn;
-        if (!refined(wf, D[0], D[1], D[2])) continue;
+        if (!(near >> around(a == 0 ? sgn : 0, a == 1 ? sgn : 0, a == 2 ? sgn : 0) & 1)) continue;
         // the face is the lower a-face of its owner O (D above, C below)
         const int* O = sgn > 0 ? D : C;
         const int gc = sc.sb ? group_at(sc, O[0], O[1], O[2]) : 0;
         if (gc < 0) continue;
+        any = true;
         const long long qc = slot_at(sc, O[0], O[1], O[2], gc);
         T ff[5] = {T(0), T(0), T(0), T(0), T(0)};
 #pragma unroll
@@ -409,28 +440,30 @@ __global__ void __launch_bounds__(kBlock) k_correct_u(Work wc, Work wf, LevelScr
         for (int m = 0; m < 5; ++m) du[m] += T(sgn) * r * (Fc[((long long)a * 7 + m) * sc.NS + qc] - T(0.25) * ff[m]);
       }
     }
+    if (!any) continue;
     const long long pc = lin(wc, i, j, k);
 #pragma unroll
     for (int m = 0; m < 5; ++m) Uc[m * wc.N + pc] += du[m];
   }
 }
 
-// EMF difference on the coarse edge along Q owned by coarse cell X (its
-// lower corner edge): mean of the two fine EMFs along it minus the coarse
-// EMF, when the edge touches the refined region, else 0.
-template <typename T, int Q>
-__device__ __forceinline__ T edge_emf_jump(const Work& wf, const LevelScratch& sc, const LevelScratch& sf,
-                                           const T* __restrict__ Ec, const T* __restrict__ Ef, int x, int y, int z) {
+// EMF difference on the coarse edge along Q owned by the coarse cell X =
+// (i, j, k) + (ox, oy, oz) (its lower corner edge): mean of the two fine EMFs
+// along it minus the coarse EMF, when the edge touches the refined region, else 0.
+// near: refined_around (i, j, k).
+template <typename T, int Q, int ox, int oy, int oz>
+__device__ __forceinline__ T edge_emf_jump(unsigned near, const LevelScratch& sc, const LevelScratch& sf,
+                                           const T* __restrict__ Ec, const T* __restrict__ Ef, int i, int j, int k) {
   constexpr int q1 = (Q + 1) % 3, q2 = (Q + 2) % 3;
-  const int X[3] = {x, y, z};
+  const int X[3] = {i + ox, j + oy, k + oz};
   int Y[3] = {0, 0, 0};
   bool touch = false;
 #pragma unroll
-  for (int s = 0; s < 4 && !touch; ++s) {
-    int Z[3] = {X[0], X[1], X[2]};
-    Z[q1] -= s & 1;
-    Z[q2] -= s >> 1;
-    if (refined(wf, Z[0], Z[1], Z[2])) {
+  for (int s = 0; s < 4; ++s) {
+    const int d1 = s & 1, d2 = s >> 1;
+    const int Z[3] = {X[0] - (q1 == 0 ? d1 : 0) - (q2 == 0 ? d2 : 0), X[1] - (q1 == 1 ? d1 : 0) - (q2 == 1 ? d2 : 0),
+                      X[2] - (q1 == 2 ? d1 : 0) - (q2 == 2 ? d2 : 0)};
+    if (!touch && (near >> around(Z[0] - i, Z[1] - j, Z[2] - k) & 1)) {
       touch = true;
       Y[0] = Z[0]; Y[1] = Z[1]; Y[2] = Z[2];
     }
@@ -455,20 +488,18 @@ __device__ __forceinline__ T edge_emf_jump(const Work& wf, const LevelScratch& s
   return T(0.5) * ef - ec;
 }
 
-template <typename T, int A>
-__device__ __forceinline__ T face_emf_correction(const Work& wf, const LevelScratch& sc, const LevelScratch& sf,
-                                                 const T* __restrict__ Ec, const T* __restrict__ Ef, int x, int y,
-                                                 int z, T r) {
-  // CT update of the lower A-face of cell (x, y, z) by the edge EMF jumps
-  // (same stencil as the update of Eq. 13)
+// CT update of the lower A-face (UP: the upper one) of cell (i, j, k) by the edge
+// EMF jumps (same stencil as the update of Eq. 13)
+template <typename T, int A, int UP>
+__device__ __forceinline__ T face_emf_correction(unsigned near, const LevelScratch& sc, const LevelScratch& sf,
+                                                 const T* __restrict__ Ec, const T* __restrict__ Ef, int i, int j,
+                                                 int k, T r) {
   constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
-  int Pb[3] = {x, y, z}, Pc[3] = {x, y, z};
-  Pb[b] += 1;
-  Pc[c] += 1;
-  const T dc0 = edge_emf_jump<T, c>(wf, sc, sf, Ec, Ef, x, y, z);
-  const T dc1 = edge_emf_jump<T, c>(wf, sc, sf, Ec, Ef, Pb[0], Pb[1], Pb[2]);
-  const T db0 = edge_emf_jump<T, b>(wf, sc, sf, Ec, Ef, x, y, z);
-  const T db1 = edge_emf_jump<T, b>(wf, sc, sf, Ec, Ef, Pc[0], Pc[1], Pc[2]);
+  constexpr int x = A == 0 ? UP : 0, y = A == 1 ? UP : 0, z = A == 2 ? UP : 0;
+  const T dc0 = edge_emf_jump<T, c, x, y, z>(near, sc, sf, Ec, Ef, i, j, k);
+  const T dc1 = edge_emf_jump<T, c, x + (b == 0), y + (b == 1), z + (b == 2)>(near, sc, sf, Ec, Ef, i, j, k);
+  const T db0 = edge_emf_jump<T, b, x, y, z>(near, sc, sf, Ec, Ef, i, j, k);
+  const T db1 = edge_emf_jump<T, b, x + (c == 0), y + (c == 1), z + (c == 2)>(near, sc, sf, Ec, Ef, i, j, k);
   return -r * (dc1 - dc0) + r * (db1 - db0);
 }
 
@@ -477,84 +508,118 @@ __device__ __forceinline__ T face_emf_correction(const Work& wf, const LevelScra
 // so that a correction of the next coarser level across the same interface
 // uses the finest fluxes and EMFs (the hierarchy need not be properly
 // nested).  Items: the coarse footprints of the fine groups.  Faces and edges
-// shared by refined cells are written with the same value by each of them.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_correct_registers(Work wcf, Work wf, LevelScratch sc, LevelScratch sf) {
+// shared by refined cells have the same value from each; the first of them around
+// the face or edge writes it, to every listed coarse group whose box holds it.
+// Bound by the latency of its loads (111 fine words a cell): a step of a 64^3 root with
+// 31 and 67 groups of 16^3 took 104 us here with a lookup of the group, by integer
+// divisions, for every face and edge and each cell writing all that it touches, 35 us so.
+// One launch row (blockIdx.y) per direction a.
+template <typename T, int a>
+__device__ __forceinline__ void correct_registers(const Work& wcf, const Work& wf, const LevelScratch& sc,
+                                                  const LevelScratch& sf) {
   T* Fc = (T*)sc.F;
   T* Ec = (T*)sc.E;
   const T* Ff = (const T*)sf.F;
   const T* Ef = (const T*)sf.E;
   FOR_ITEMS(wcf, t) {
-    int i, j, k;
-    cell_of(wcf, t, i, j, k);
-    const int gc = sc.sb ? group_at(sc, i, j, k) : 0;
+    int C[3], P[3];
+    cell_of(wcf, t, C[0], C[1], C[2], P[0], P[1], P[2]);
+    const int gc = sc.sb ? group_at(sc, C[0], C[1], C[2]) : 0;
     if (gc < 0) continue;
+    // all eight children lie in one fine group, whose box also holds the fine faces
+    // and edges on the cell's upper sides
+    const int gf = sf.sb ? group_at(sf, 2 * C[0], 2 * C[1], 2 * C[2]) : 0;
+    const long long qf = slot_at(sf, 2 * C[0], 2 * C[1], 2 * C[2], gf < 0 ? 0 : gf);
+    const long long qc = slot_at(sc, C[0], C[1], C[2], gc);
+    const long long sfy = sf.sb ? sf.sb : sf.nx, scy = sc.sb ? sc.sb : sc.nx;
+    const long long fs[3] = {1, sfy, sfy * (sf.sb ? sf.sb : sf.ny)}, cs[3] = {1, scy, scy * (sc.sb ? sc.sb : sc.ny)};
+    const int fn[3] = {sf.nx, sf.ny, sf.nz}, cn[3] = {sc.nx, sc.ny, sc.nz};
+    long long f2[3], c1[3];   // two fine cells and one coarse cell up (a whole level wraps)
+    bool inner = true;        // the neighbours are in this cell's coarse group
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int b = (a + 1) % 3, c = (a + 2) % 3;
-      // the lower and the upper a-face of cell (i, j, k)
-#pragma unroll
-      for (int up = 0; up < 2; ++up) {
-        int O[3] = {i, j, k};
-        O[a] += up;
-        T ff[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int Of[3] = {2 * O[0], 2 * O[1], 2 * O[2]};
-          Of[b] += q & 1;
-          Of[c] += q >> 1;
-          int In[3] = {Of[0], Of[1], Of[2]};
-          if (up) In[a] -= 1;    // the refined fine cell below the face
-          const int gf = sf.sb ? group_at(sf, In[0], In[1], In[2]) : 0;
-          const long long qf = slot_at(sf, Of[0], Of[1], Of[2], gf < 0 ? 0 : gf);
-#pragma unroll
-          for (int m = 0; m < 7; ++m) ff[m] += Ff[((long long)a * 7 + m) * sf.NS + qf];
-        }
-        // every listed coarse group whose box holds the face keeps a copy
-        int L[3] = {O[0], O[1], O[2]};
-        L[a] -= 1;
-        const int gs[2] = {sc.sb ? group_at(sc, O[0], O[1], O[2]) : 0, sc.sb ? group_at(sc, L[0], L[1], L[2]) : 0};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          if (gs[u] < 0 || (u == 1 && gs[1] == gs[0])) continue;
-          const long long qc = slot_at(sc, O[0], O[1], O[2], gs[u]);
-#pragma unroll
-          for (int m = 0; m < 7; ++m) Fc[((long long)a * 7 + m) * sc.NS + qc] = T(0.25) * ff[m];
-        }
+    for (int d = 0; d < 3; ++d) {
+      f2[d] = (!sf.sb && 2 * C[d] + 2 >= fn[d] ? 2 - fn[d] : 2) * fs[d];
+      c1[d] = (!sc.sb && C[d] + 1 >= cn[d] ? 1 - cn[d] : 1) * cs[d];
+      if (sc.sb) {
+        const int at = C[d] - (int)fdiv(sc.by_edge, C[d]) * sc.edge;
+        inner = inner && at > 0 && at < sc.edge - 1;
       }
-      // the four a-edges of cell (i, j, k): owners (i, j, k) + {0, e_b} + {0, e_c}
+    }
+    const auto fine = [&](int d, int p) { return p == 2 ? f2[d] : p * fs[d]; };
+    // is the neighbour (dx, dy, dz) away an item of this kernel too, with a place
+    // for its results?
+    const auto covered = [&](int dx, int dy, int dz) {
+      if (!wcf.groups && !sc.sb) return true;
+      const auto in = [&](int p) { return p >= 0 && p < wcf.box; };
+      if (wcf.groups && inner && in(P[0] + dx) && in(P[1] + dy) && in(P[2] + dz)) return true;
+      return refined(wf, C[0] + dx, C[1] + dy, C[2] + dz) &&
+             (!sc.sb || group_at(sc, C[0] + dx, C[1] + dy, C[2] + dz) >= 0);
+    };
+    constexpr int b = (a + 1) % 3, c = (a + 2) % 3;
+    const auto unit = [&](int d, int x) { return x == d ? 1 : 0; };
+    // the lower and the upper a-face of the cell (the upper one is the lower one
+    // of a covered neighbour)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int X[3] = {i, j, k};
-        X[b] += e & 1;
-        X[c] += e >> 1;
-        T ef = T(0);
+    for (int up = 0; up < 2; ++up) {
+      if (up && covered(unit(a, 0), unit(a, 1), unit(a, 2))) continue;
+      T ff[7] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          int Xf[3] = {2 * X[0], 2 * X[1], 2 * X[2]};
-          Xf[a] += h;
-          int In[3] = {Xf[0], Xf[1], Xf[2]};   // a fine child of (i, j, k) next to the fine edge
-          if (e & 1) In[b] -= 1;
-          if (e >> 1) In[c] -= 1;
-          const int gf = sf.sb ? group_at(sf, In[0], In[1], In[2]) : 0;
-          ef += Ef[(long long)a * sf.NS + slot_at(sf, Xf[0], Xf[1], Xf[2], gf < 0 ? 0 : gf)];
-        }
-        // every listed coarse group whose box holds the edge keeps a copy
-        int gs[4];
+      for (int q = 0; q < 4; ++q) {
+        const long long at = qf + fine(a, 2 * up) + fine(b, q & 1) + fine(c, q >> 1);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          int Z[3] = {X[0], X[1], X[2]};
-          Z[b] -= u & 1;
-          Z[c] -= u >> 1;
-          gs[u] = sc.sb ? group_at(sc, Z[0], Z[1], Z[2]) : 0;
-          bool dup = gs[u] < 0;
+        for (int m = 0; m < 7; ++m) ff[m] += Ff[((long long)a * 7 + m) * sf.NS + at];
+      }
+      const long long to = qc + (up ? c1[a] : 0);
 #pragma unroll
-          for (int v = 0; v < u; ++v) dup = dup || gs[v] == gs[u];
-          if (!dup) Ec[(long long)a * sc.NS + slot_at(sc, X[0], X[1], X[2], gs[u])] = T(0.5) * ef;
-        }
+      for (int m = 0; m < 7; ++m) Fc[((long long)a * 7 + m) * sc.NS + to] = T(0.25) * ff[m];
+      if (inner) continue;
+      // the group on the face's other side keeps a copy
+      int O[3] = {C[0], C[1], C[2]}, Z[3] = {C[0], C[1], C[2]};
+      O[a] += up;
+      Z[a] += up ? 1 : -1;
+      const int g = group_at(sc, Z[0], Z[1], Z[2]);
+      if (g < 0 || g == gc) continue;
+      const long long other = slot_at(sc, O[0], O[1], O[2], g);
+#pragma unroll
+      for (int m = 0; m < 7; ++m) Fc[((long long)a * 7 + m) * sc.NS + other] = T(0.25) * ff[m];
+    }
+    // the four a-edges of the cell: owners X = cell + {0, e_b} + {0, e_c}; the cells
+    // around an edge are X - {0, e_b} - {0, e_c}, number e this one
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bool first = true;
+#pragma unroll
+      for (int u = 0; u < e; ++u) {
+        const int db = (e & 1) - (u & 1), dc = (e >> 1) - (u >> 1);
+        first = first && !covered(db * unit(b, 0) + dc * unit(c, 0), db * unit(b, 1) + dc * unit(c, 1),
+                                  db * unit(b, 2) + dc * unit(c, 2));
+      }
+      if (!first) continue;
+      const long long at = qf + fine(b, 2 * (e & 1)) + fine(c, 2 * (e >> 1));
+      const T ef = T(0.5) * (Ef[(long long)a * sf.NS + at] + Ef[(long long)a * sf.NS + at + fine(a, 1)]);
+      Ec[(long long)a * sc.NS + qc + (e & 1 ? c1[b] : 0) + (e >> 1 ? c1[c] : 0)] = ef;
+      if (inner) continue;
+      int X[3] = {C[0], C[1], C[2]};
+      X[b] += e & 1;
+      X[c] += e >> 1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (u == e) continue;
+        int Z[3] = {X[0], X[1], X[2]};
+        Z[b] -= u & 1;
+        Z[c] -= u >> 1;
+        const int g = group_at(sc, Z[0], Z[1], Z[2]);
+        if (g >= 0 && g != gc) Ec[(long long)a * sc.NS + slot_at(sc, X[0], X[1], X[2], g)] = ef;
       }
     }
   }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_correct_registers(Work wcf, Work wf, LevelScratch sc, LevelScratch sf) {
+  if (blockIdx.y == 0) correct_registers<T, 0>(wcf, wf, sc, sf);
+  else if (blockIdx.y == 1) correct_registers<T, 1>(wcf, wf, sc, sf);
+  else correct_registers<T, 2>(wcf, wf, sc, sf);
 }
 
 // Correction of the magnetic field (Sec. 3.3): coarse faces with both cells
@@ -562,42 +627,41 @@ __global__ void __launch_bounds__(kBlock) k_correct_registers(Work wcf, Work wf,
 // their edges that lie on the coarse-fine interface.  Each listed coarse
 // cell owns its lower faces, and its upper faces where the next group is not
 // listed (as in the update itself).
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_correct_b(Work wc, Work wf, LevelScratch sc, LevelScratch sf,
-                                                      T* __restrict__ Bc, const double* dt, T inv_dx) {
-  const T r = T(*dt) * inv_dx;
+// One launch row (blockIdx.y) per face direction: few cells have anything to do, and
+// what those cost is a chain of dependent loads (the hierarchy above: 68 us a step with
+// every lookup on its own, 43 us so).
+template <typename T, int A>
+__device__ __forceinline__ void correct_b(const Work& wc, const Work& wf, const LevelScratch& sc,
+                                          const LevelScratch& sf, T* __restrict__ Bc, T r) {
   const T* Ec = (const T*)sc.E;
   const T* Ef = (const T*)sf.E;
+  constexpr int ax = A == 0, ay = A == 1, az = A == 2;
   FOR_ITEMS(wc, t) {
     int i, j, k, a0, b0, c0;
     cell_of(wc, t, i, j, k, a0, b0, c0);
-    const int pos[3] = {a0, b0, c0};
-#pragma unroll
-    for (int A = 0; A < 3; ++A) {
-#pragma unroll
-      for (int up = 0; up < 2; ++up) {
-        int H[3] = {i, j, k};   // cell above the face (its owner)
-        if (up) {
-          if (!wc.groups || pos[A] != wc.edge - 1) continue;
-          int G[3] = {i / wc.edge, j / wc.edge, k / wc.edge};
-          G[A] += 1;
-          const bool listed = wc.occ[((long long)wrapc(G[2], wc.gnz) * wc.gny + wrapc(G[1], wc.gny)) * wc.gnx +
-                                     wrapc(G[0], wc.gnx)] != 0;
-          if (listed) continue;
-          H[A] += 1;
-        }
-        int L[3] = {H[0], H[1], H[2]};
-        L[A] -= 1;
-        if (refined(wf, L[0], L[1], L[2]) || refined(wf, H[0], H[1], H[2])) continue;
-        T db;
-        if (A == 0) db = face_emf_correction<T, 0>(wf, sc, sf, Ec, Ef, H[0], H[1], H[2], r);
-        else if (A == 1) db = face_emf_correction<T, 1>(wf, sc, sf, Ec, Ef, H[0], H[1], H[2], r);
-        else db = face_emf_correction<T, 2>(wf, sc, sf, Ec, Ef, H[0], H[1], H[2], r);
-        if (db != T(0))
-          Bc[A * wc.N + lin(wc, wrapc(H[0], wc.nx), wrapc(H[1], wc.ny), wrapc(H[2], wc.nz))] += db;
-      }
+    const unsigned near = refined_around(wf, i, j, k);
+    if (!near || (near >> around(0, 0, 0) & 1)) continue;   // both faces have a cell in the refined region
+    const int pos = A == 0 ? a0 : A == 1 ? b0 : c0;
+    if (!(near >> around(-ax, -ay, -az) & 1)) {
+      const T db = face_emf_correction<T, A, 0>(near, sc, sf, Ec, Ef, i, j, k, r);
+      if (db != T(0)) Bc[A * wc.N + lin(wc, i, j, k)] += db;
     }
+    if (!wc.groups || pos != wc.edge - 1 || (near >> around(ax, ay, az) & 1)) continue;
+    const int H[3] = {wrapc(i + ax, wc.nx), wrapc(j + ay, wc.ny), wrapc(k + az, wc.nz)};
+    if (occ_at(wc, wc.occ, H[0], H[1], H[2]) != 0) continue;
+    const T db = face_emf_correction<T, A, 1>(near, sc, sf, Ec, Ef, i, j, k, r);
+    if (db != T(0)) Bc[A * wc.N + lin(wc, H[0], H[1], H[2])] += db;
   }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_correct_b(Work wc, Work wf, LevelScratch sc, LevelScratch sf,
+                                                      T* __restrict__ Bc, const double* dt, T inv_dx) {
+  if (!wf.groups) return;   // every face lies in the refined region
+  const T r = T(*dt) * inv_dx;
+  if (blockIdx.y == 0) correct_b<T, 0>(wc, wf, sc, sf, Bc, r);
+  else if (blockIdx.y == 1) correct_b<T, 1>(wc, wf, sc, sf, Bc, r);
+  else correct_b<T, 2>(wc, wf, sc, sf, Bc, r);
 }
 
 // ---- regridding (refinement / derefinement operation, Sec. 3.3)
@@ -725,7 +789,7 @@ __device__ __forceinline__ void prolong_parent_kept(const Work& wc, const Work& 
   auto old_at = [&](int x, int y, int z) {
     if (!occ_old) return false;
     x = wrapc(x, wf.nx); y = wrapc(y, wf.ny); z = wrapc(z, wf.nz);
-    return occ_old[((long long)(z / wf.edge) * wf.gny + y / wf.edge) * wf.gnx + x / wf.edge] != 0;
+    return occ_at(wf, occ_old, x, y, z) != 0;
   };
   ParentFaces<T> P;
   load_face_pair<T, 0>(wc, Bc, i, j, k, P);
@@ -838,7 +902,7 @@ __global__ void __launch_bounds__(kBlock) k_prolong_created(Work wc, Work wf, Co
     cell_of(wc, t, i, j, k);
     if (occ_old) {
       const int I = wrapc(2 * i, wf.nx), J = wrapc(2 * j, wf.ny), K = wrapc(2 * k, wf.nz);
-      if (occ_old[((long long)(K / wf.edge) * wf.gny + J / wf.edge) * wf.gnx + I / wf.edge] != 0) continue;
+      if (occ_at(wf, occ_old, I, J, K) != 0) continue;
     }
     prolong_parent_kept(wc, wf, Uc, Bc, Uf, Bf, occ_old, i, j, k, gam);
   }

@@ -190,7 +190,8 @@ Work make_work(const mhd_level* lv, int lo, int hi) {
   w.units = 0;
   w.rev = 0;
   w.per = w.chunks = 0;
-  w.by_chunks = w.by_row = w.by_plane = FastDiv{0, 0, 0};
+  w.by_chunks = w.by_row = w.by_plane = w.by_box = FastDiv{0, 0, 0};
+  w.by_edge = make_div((unsigned)w.edge);
   return w;
 }
 
@@ -224,10 +225,15 @@ long long occupancy_cells(const mhd_level* lv) {
   return (long long)(lv->nx / lv->group_edge) * (lv->ny / lv->group_edge) * (lv->nz / lv->group_edge);
 }
 
-// fill an occupancy map of occupancy_cells(lv) ints (list mode only): clear
-// with a kernel, then mark the listed groups
+// fill an occupancy map of occupancy_cells(lv) ints (list mode only) with kernels
 void fill_occupancy(mhd_ctx_s* c, const mhd_level* lv, int* occ) {
   const long long ng = occupancy_cells(lv);
+  const int e = lv->group_edge;
+  if (ng <= kOccSmall && lv->n_groups <= kOccSmall) {
+    k_occ_small<<<1, 1024, 0, c->stream>>>(occ, (int)ng, lv->groups, lv->n_groups, lv->n_groups_dev, e, lv->nx / e,
+                                           lv->ny / e, lv->nz / e);
+    return;
+  }
   k_occ_clear<<<(unsigned)((ng + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(occ, ng);
   k_occ_set<<<(unsigned)((lv->n_groups + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
       occ, lv->groups, lv->n_groups, lv->n_groups_dev, lv->group_edge, lv->nx / lv->group_edge,
@@ -252,10 +258,6 @@ int build_occupancy_into(mhd_ctx_s* c, const mhd_level* lv, int** occ, long long
 // occupancy map of the level's group list in the context's map
 int build_occupancy(mhd_ctx_s* c, const mhd_level* lv) { return build_occupancy_into(c, lv, &c->occ, &c->cap_occ); }
 
-// grid of a reduction kernel: one thread per item (fixed, so results are
-// bitwise stable)
-unsigned nblocks(const Work& w) { return (unsigned)((w.items + kBlock - 1) / kBlock); }
-
 // grid of a stage kernel: capped by the context's launch shape
 thread_local long long g_max_blocks = 0;
 thread_local int g_threads = kBlock;
@@ -263,7 +265,15 @@ unsigned capped(long long b) {
   if (g_max_blocks > 0 && b > g_max_blocks) b = g_max_blocks;
   return (unsigned)(b < 1 ? 1 : b);
 }
-unsigned sblocks(const Work& w, int threads) { return capped((w.items + threads - 1) / threads); }
+
+// of a kernel that walks its items with FOR_ITEMS: fills the Work's item divisors
+unsigned item_blocks(Work& w) {
+  const unsigned row = w.groups ? w.box : w.nx, plane = row * (unsigned)(w.groups ? w.box : w.ny);
+  w.by_row = make_div(row);
+  w.by_plane = make_div(plane);
+  w.by_box = make_div(plane * (unsigned)w.box);
+  return capped((w.items + kBlock - 1) / kBlock);
+}
 
 // Block decomposition of a stage kernel (Cell) for blocks of `threads`: fills
 // the Work's unit fields and returns the grid
@@ -816,16 +826,18 @@ int mhd_prim_to_cons(mhd_ctx c, const mhd_level* lv, const void* W5) {
   if (!c || !W5) return MHD_ERR_INVALID_ARG;
   int rc = check_level(c, lv);
   if (rc) return rc;
-  const Work w = make_work(lv, 0, 0);
+  Work w = make_work(lv, 0, 0);
+  g_max_blocks = 0;
+  const unsigned nb = item_blocks(w);
   const Mix mix{lv->E64, c->cfg.beta_fp64};
   if (c->cfg.prec == MHD_F64)
-    k_prim_to_cons<double, false><<<nblocks(w), kBlock, 0, c->stream>>>(
+    k_prim_to_cons<double, false><<<nb, kBlock, 0, c->stream>>>(
         w, (const double*)W5, (const double*)lv->B, (double*)lv->U, mix, c->cfg.gamma);
   else if (c->cfg.prec == MHD_F32)
-    k_prim_to_cons<float, false><<<nblocks(w), kBlock, 0, c->stream>>>(
+    k_prim_to_cons<float, false><<<nb, kBlock, 0, c->stream>>>(
         w, (const float*)W5, (const float*)lv->B, (float*)lv->U, mix, (float)c->cfg.gamma);
   else
-    k_prim_to_cons<float, true><<<nblocks(w), kBlock, 0, c->stream>>>(
+    k_prim_to_cons<float, true><<<nb, kBlock, 0, c->stream>>>(
         w, (const float*)W5, (const float*)lv->B, (float*)lv->U, mix, (float)c->cfg.gamma);
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }

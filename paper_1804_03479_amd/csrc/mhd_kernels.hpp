@@ -80,6 +80,8 @@ struct Work {
   unsigned per, chunks;
   int rev;              // walk the blocks from the last to the first
   FastDiv by_chunks, by_row, by_plane;   // of the block rank; of a cell index by its row and by its plane
+  FastDiv by_box;       // of an item index by a group's item box (cell_of)
+  FastDiv by_edge;      // of a cell coordinate by the group edge
 };
 
 __device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -119,21 +121,34 @@ __device__ __forceinline__ long long work_items(const Work& w) {
 __device__ __forceinline__ long long item_stride() { return (long long)gridDim.x * blockDim.x; }
 
 // cell of work item t.  (a, b, c) is the position inside the unit's box (the
-// cell itself for a whole grid).
+// cell itself for a whole grid).  Item counts below 2^31 (all but whole levels of
+// more cells) are split by multiplications (by_box, by_plane, by_row: item_divs).
 __device__ __forceinline__ void cell_of(const Work& w, long long t, int& i, int& j, int& k, int& a, int& b, int& c) {
-  if (w.groups == nullptr) {
-    i = (int)(t % w.nx);
-    const long long r = t / w.nx;
-    j = (int)(r % w.ny);
-    k = (int)(r / w.ny);
-    a = i; b = j; c = k;
+  const bool list = w.groups != nullptr;
+  int g = 0;
+  if (w.items < 1LL << 31) {
+    unsigned l = (unsigned)t;
+    const unsigned row = list ? w.box : w.nx, plane = row * (unsigned)(list ? w.box : w.ny);
+    if (list) {
+      g = (int)fdiv(w.by_box, l);
+      l -= (unsigned)g * plane * (unsigned)w.box;
+    }
+    c = (int)fdiv(w.by_plane, l);
+    l -= (unsigned)c * plane;
+    b = (int)fdiv(w.by_row, l);
+    a = (int)(l - (unsigned)b * row);
   } else {
-    const long long per = (long long)w.box * w.box * w.box;
-    const int g = (int)(t / per);
-    const int l = (int)(t - (long long)g * per);
-    a = l % w.box;
-    b = (l / w.box) % w.box;
-    c = l / (w.box * w.box);
+    const long long row = list ? w.box : w.nx, plane = row * (list ? w.box : w.ny);
+    if (list) {
+      g = (int)(t / (plane * w.box));
+      t -= g * plane * w.box;
+    }
+    c = (int)(t / plane);
+    b = (int)((t - c * plane) / row);
+    a = (int)(t - c * plane - b * row);
+  }
+  i = a; j = b; k = c;
+  if (list) {
     const int* o = w.groups + 3LL * (w.gbase + g);
     i = wrapc((o[0] >> w.oshift) - w.halo + a, w.nx);
     j = wrapc((o[1] >> w.oshift) - w.halo + b, w.ny);
@@ -827,7 +842,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
       };
       const bool lx = c.a == w.edge - 1, ly = c.b == w.edge - 1, lz = c.c == w.edge - 1;
       if (lx || ly || lz) {
-        const int gi = c.i / w.edge, gj = c.j / w.edge, gk = c.k / w.edge;
+        const int gi = (int)fdiv(w.by_edge, c.i), gj = (int)fdiv(w.by_edge, c.j), gk = (int)fdiv(w.by_edge, c.k);
         ex = lx && !listed(gi + 1, gj, gk);
         ey = ly && !listed(gi, gj + 1, gk);
         ez = lz && !listed(gi, gj, gk + 1);
@@ -931,7 +946,26 @@ __device__ __forceinline__ void correct_states(const Work& w, const T* __restric
   correct_state(transverse_of<T, D, 0, L>(w, F1, E1, c, hr), bn, bnh, hr * (bn_hi - bn), gam, wr);
 }
 
-// group occupancy map of a list: clear, then mark
+// Occupancy map of a level's group list (list mode only) into occ[n]: cleared, then
+// the listed groups marked.  One block does both where its passes over the map are
+// few (two launches took 9.3 us, one 4.9 us on a map of 512, and a step of a
+// hierarchy builds several); a larger map takes a launch for each.
+__device__ __forceinline__ void occ_set(int* occ, const int* groups, int g, int edge, int gnx, int gny, int gnz) {
+  const int gi = groups[3 * g] / edge, gj = groups[3 * g + 1] / edge, gk = groups[3 * g + 2] / edge;
+  // origins outside the level are never written (the host binding rejects them)
+  if (groups[3 * g] < 0 || groups[3 * g + 1] < 0 || groups[3 * g + 2] < 0 || gi >= gnx || gj >= gny || gk >= gnz) return;
+  occ[((long long)gk * gny + gj) * gnx + gi] = g + 1;   // 0: not listed, else group index + 1
+}
+
+constexpr int kOccSmall = 16384;
+__global__ void __launch_bounds__(1024) k_occ_small(int* occ, int cells, const int* groups, int n_groups,
+                                                    const int* n_dev, int edge, int gnx, int gny, int gnz) {
+  for (int t = threadIdx.x; t < cells; t += 1024) occ[t] = 0;
+  const int n = n_dev ? min(*n_dev, n_groups) : n_groups;
+  __syncthreads();
+  for (int g = threadIdx.x; g < n; g += 1024) occ_set(occ, groups, g, edge, gnx, gny, gnz);
+}
+
 __global__ void __launch_bounds__(kBlock) k_occ_clear(int* occ, long long n) {
   const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
   if (t < n) occ[t] = 0;
@@ -941,11 +975,7 @@ __global__ void __launch_bounds__(kBlock) k_occ_set(int* occ, const int* groups,
                                                     int edge, int gnx, int gny, int gnz) {
   const int g = blockIdx.x * kBlock + threadIdx.x;
   const int n = n_dev ? min(*n_dev, n_groups) : n_groups;
-  if (g >= n) return;
-  const int gi = groups[3 * g] / edge, gj = groups[3 * g + 1] / edge, gk = groups[3 * g + 2] / edge;
-  // origins outside the level are never written (the host binding rejects them)
-  if (groups[3 * g] < 0 || groups[3 * g + 1] < 0 || groups[3 * g + 2] < 0 || gi >= gnx || gj >= gny || gk >= gnz) return;
-  occ[((long long)gk * gny + gj) * gnx + gi] = g + 1;   // 0: not listed, else group index + 1
+  if (g < n) occ_set(occ, groups, g, edge, gnx, gny, gnz);
 }
 
 // ------------------------------------------------------------ set-up

@@ -1,0 +1,70 @@
+"""The CTU face kernels where their decomposition changes: march lengths (whole
+grids of about 2^16, 3 2^17 and 3 2^19 cells; group lists of few and of many
+boxes), ragged rows, occupancy maps built by one block and by many.
+
+Bars: FP64 against the oracle within 1e-12 of each component's largest value;
+listed groups bit-identical to the same cells of a whole-grid step, which the
+arithmetic of both forms has in common.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+from paper_1804_03479_amd import inputs  # noqa: E402
+from paper_1804_03479_amd.mhd import Level, Solver  # noqa: E402
+
+RECON = {"plm": oracle.PLM, "ppm": oracle.PPM}
+SOLVERS = {"roe": oracle.ROE, "hlle": oracle.HLLE, "hlld": oracle.HLLD}
+
+
+def level(U, B, dx, dtype=torch.float64, **kw):
+    return Level(torch.from_numpy(U).to("cuda", dtype).contiguous(), torch.from_numpy(B).to("cuda", dtype).contiguous(),
+                 dx, **kw)
+
+
+@pytest.mark.parametrize("shape,recon,solver", [
+    ((5, 4, 7), "ppm", "hlld"), ((67, 5, 4), "ppm", "roe"), ((4, 4, 131), "plm", "hlld"),
+    ((41, 40, 39), "ppm", "hlld"), ((41, 40, 40), "ppm", "hlld"), ((41, 40, 40), "plm", "roe"),
+    ((73, 73, 73), "ppm", "hlld"), ((74, 73, 73), "ppm", "hlld"), ((74, 73, 73), "ppm", "hlle"),
+    ((117, 116, 116), "ppm", "hlld")])
+def test_whole_grid_step(shape, recon, solver):
+    p = inputs.smooth_problem(*shape, seed=sum(shape))
+    U, B = oracle.initial_state(p)
+    dt = oracle.cfl_dt(U, B, p["dx"])
+    Uo, Bo = oracle.step(U, B, dt, p["dx"], scheme=oracle.CTU, recon=RECON[recon], riemann=SOLVERS[solver])
+    s, lv = Solver("ctu", recon, solver), level(U, B, p["dx"])
+    s.step(lv, dt)
+    for got, want in ((lv.U, Uo), (lv.B, Bo)):
+        got = got.cpu().numpy()
+        for m in range(len(want)):
+            assert np.abs(got[m] - want[m]).max() <= 1e-12 * np.abs(want[m]).max()
+
+
+@pytest.mark.parametrize("edge,n,groups,prec", [(16, 128, 1, "f32"), (16, 128, 40, "f64"), (16, 128, 300, "f32"),
+                                                (4, 100, 9, "f64"), (4, 104, 9, "f32")])
+def test_listed_groups_equal_whole_grid(edge, n, groups, prec):
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    U, B = oracle.initial_state(p := inputs.smooth_problem(n, n, n, seed=4))
+    m = n // edge
+    pick = np.random.default_rng(groups).choice(m ** 3, groups, replace=False)
+    origins = np.stack([pick % m, pick // m % m, pick // m ** 2], 1) * edge
+    s = Solver("ctu", "ppm", "hlld", prec)
+    whole = level(U, B, p["dx"], dtype)
+    part = level(U, B, p["dx"], dtype, groups=torch.from_numpy(origins.astype(np.int32)).cuda(), group_edge=edge)
+    U0, B0 = part.U.clone(), part.B.clone()
+    dt = s.cfl_dt(whole)
+    s.step(whole, dt)
+    s.step(part, dt)
+    cell = torch.zeros((n, n, n), dtype=torch.bool, device="cuda")
+    for i, j, k in origins:
+        cell[k:k + edge, j:j + edge, i:i + edge] = True
+    assert torch.equal(part.U, torch.where(cell, whole.U, U0))
+    for a in range(3):                     # a listed cell's faces, its upper ones included
+        face = cell | torch.roll(cell, 1, 2 - a)
+        assert torch.equal(part.B[a], torch.where(face, whole.B[a], B0[a]))
