@@ -297,8 +297,10 @@ unsigned decompose(Work& w, int threads) {
 // grid, the item boxes of a group list.  A march repeats the trace of one cell
 // before its first face, so long marches save work and short ones give small
 // grids enough waves.
-FaceGeo face_geometry(const Work& w) {
+// Whole grids below tile_limit cells go without marches (kTileCells).
+FaceGeo face_geometry(const Work& w, long long tile_limit) {
   FaceGeo g;
+  g.fours = 0;
   const auto cut = [](int n, int len) { return (n + len - 1) / len; };
   if (w.groups) {
     // whole float step of 5 / 50 / 191 / 400 groups: 54 / 152 / 531 / 1098 us
@@ -322,12 +324,24 @@ FaceGeo face_geometry(const Work& w) {
     g.bz = g.cz = g.cy = len;
     g.units = cut(w.nz, g.bz);
     g.lx = w.nx + 1;
+    if (w.N < tile_limit) {
+      g.bz = w.nz;
+      g.units = 1;
+      g.fours = (unsigned)cut(w.nx, kTileCols);
+      g.by_fours = make_div(g.fours);
+      g.by_ly = make_div((unsigned)w.ny + 1);
+      g.by_lz = make_div((unsigned)w.nz + 1);
+    }
   }
   const auto waves = [](long long n, int k) { return (unsigned)((n + k - 1) / k); };
   g.w2c = waves((long long)g.bx * g.by, 64);
   g.w2 = g.w2c * (unsigned)cut(g.bz, g.cz);
   g.w1c = waves((long long)g.bx * g.bz, 64);
   g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
+  if (g.fours) {
+    g.w2 = waves((long long)g.fours * g.by * (g.bz + 1) - 1, kTileCells - 1);
+    g.w1 = waves((long long)g.fours * g.bz * (g.by + 1) - 1, kTileCells - 1);
+  }
   g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
   g.by_per = make_div(g.per);
   g.by_w2c = make_div(g.w2c);
@@ -473,9 +487,20 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
 // 0,1 / 0,0, i.e. 4 ghost cells of U^n.
 template <typename T, int R, bool ALLW, int S, int STAGE, bool L>
 void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_dx) {
-  const FaceGeo g = face_geometry(w);
+  // Tiles trace less per face, marches read along whole rows.  Whole step (us),
+  // marches / tiles, CTU + PPM + HLLD unless stated: double 24^3 53 / 44, 48^3 101 /
+  // 86, 64^3 172 / 153, 80^3 300 / 278, 96^3 491 / 539; float 24^3 35 / 34, 32^3 38.7
+  // / 39.5, 48^3 54 / 62; float Roe (PLM) 32^3 43 / 41, 64^3 108 / 106, 96^3 253 / 281;
+  // learned flux 32^3 57 / 52, 64^3 173 / 158
+  constexpr long long tile_limit = sizeof(T) == 8 ? 9 << 16 : S == 0 || S == 3 ? 5 << 16 : 1 << 15;
+  const FaceGeo g = face_geometry(w, tile_limit);
   unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
-  k_ctu_faces<T, R, ALLW, S, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+  if constexpr (!L) {
+    if (g.fours) k_ctu_faces<T, R, ALLW, S, STAGE, L, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    else k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+  } else {
+    k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+  }
   if constexpr (std::is_same<T, float>::value && S != 3) {
     if (c->capture.buf) {
       nb = decompose(w, kBlock);

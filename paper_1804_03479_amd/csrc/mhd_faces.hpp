@@ -40,6 +40,8 @@ struct FaceGeo {
   unsigned w1, w1c;        // ... y-marches
   unsigned per;            // waves of a unit
   FastDiv by_per, by_w2c, by_w1c, by_bx, by_by, by_lx;
+  unsigned fours;          // columns of a row in fours: z and y go in tiles (0: in marches)
+  FastDiv by_fours, by_ly, by_lz;
 };
 
 // Whether a march keeps what it carries from cell to cell -- slopes, interface
@@ -75,6 +77,12 @@ struct FaceArgs {
   Capture cp;
 };
 
+// Small whole grids take z and y without marches too: a wave holds 16 successive
+// cells of four neighbouring lines, lane 4 q + x, and hands each upper-edge state four
+// lanes on.  A march of one cell traces two cells for each face, and too few waves are
+// there to make it longer; a tile traces 16 cells for 15.
+constexpr int kTileCols = 4, kTileCells = 16;
+
 // value of the lane below (lane 0 keeps its own)
 __device__ __forceinline__ float lane_below(float v) {
   const int x = __float_as_int(v);
@@ -85,6 +93,10 @@ __device__ __forceinline__ double lane_below(double v) {
   return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, false),
                           __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false));
 }
+
+// ... of the lane four below: the cell before on the same line of a tile
+__device__ __forceinline__ float line_below(float v) { return __shfl_up(v, kTileCols, 64); }
+__device__ __forceinline__ double line_below(double v) { return __shfl_up(v, kTileCols, 64); }
 
 __device__ __forceinline__ unsigned fresh_offset(unsigned o) {
   asm volatile("" : "+v"(o));
@@ -305,17 +317,22 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
   return fb;
 }
 
-// 64 successive cells of the x-rows, one per lane.  (o1, o2, o12): see
+// Cells one per lane, their lower neighbours along D in the lane below (D = 0: 64
+// successive cells of the x-rows) or four below (tiles).  (o1, o2, o12): see
 // transverse().
-template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
-__device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, const Line<T, 0, L>& ln, unsigned o1,
+template <typename T, int D, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
+__device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, const Line<T, D, L>& ln, unsigned o1,
                                          unsigned o2, unsigned o12, bool emit, MlpShared* sh) {
-  constexpr int comp[7] = {0, 1, 2, 3, 4, 6, 7};
+  static_assert(D == 0 || !L, "tiles cover whole grids");
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
   const long long NS = w.NS;
-  const auto off = [&](int x, unsigned o) {   // offset of the cell x along the row
+  const int at = D == 0 ? ln.i : D == 1 ? ln.j : ln.k, size = D == 0 ? w.nx : D == 1 ? w.ny : w.nz;
+  const int stride = (D == 0 ? 1 : D == 1 ? w.nx : w.nx * w.ny) * (int)sizeof(T);
+  const auto off = [&](int x, unsigned o) {   // offset of the cell x along D
     if (L) return o;
-    const int i = ln.i + x;
-    return o + (unsigned)((i < 0 ? x + w.nx : (i >= w.nx ? x - w.nx : x)) * (int)sizeof(T));
+    const int i = at + x;
+    return o + (unsigned)((i < 0 ? x + size : (i >= size ? x - size : x)) * stride);
   };
   const auto value = [&](const T* arr, long long e, int x, unsigned o) {
     return load_at<T>(scalar(arr + (e + ln.u + (L ? x : 0))), off(x, o));
@@ -331,24 +348,24 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
     bl = A.B[ln.p];
     bu = A.B[ln.p + (ln.i + 1 >= w.nx ? 1 - w.nx : 1)];
   } else {
-    bl = value(A.B, 0, 0, o);
-    bu = value(A.B, 0, 1, o);
+    bl = value(A.B, D * w.N, 0, o);
+    bu = value(A.B, D * w.N, 1, o);
   }
   T hl = T(0), hu = T(0);
   if constexpr (STAGE == FACE_CORRECT) {
-    hl = value(A.Bh, 0, 0, o);
-    hu = value(A.Bh, 0, 1, o);
+    hl = value(A.Bh, D * NS, 0, o);
+    hu = value(A.Bh, D * NS, 1, o);
   }
   trace_cell<T, RECON, ALLW>(q, bl, bu, A.dtdx, A.gam, sl, sr);
   if constexpr (STAGE == FACE_CORRECT) {
-    const Transverse<T> tr = transverse<T, 0>(w, A, ln.u, o, o1, o2, o12, L ? w.sb : 0, L ? w.sb * w.sb : 0);
+    const Transverse<T> tr = transverse<T, D>(w, A, ln.u, o, o1, o2, o12, L ? w.sb : 0, L ? w.sb * w.sb : 0);
     const T hd = A.hr * (bu - bl);
     correct_state(tr, bl, hl, hd, A.gam, sl);
     correct_state(tr, bu, hu, hd, A.gam, sr);
   }
 #pragma unroll
-  for (int c = 0; c < 7; ++c) sr[c] = lane_below(sr[c]);
-  return emit_face<T, 0, SOLVER>(w, A, sh, emit, ln.u, ln.o, sr, sl, STAGE == FACE_CORRECT ? hl : bl,
+  for (int c = 0; c < 7; ++c) sr[c] = D == 0 ? lane_below(sr[c]) : line_below(sr[c]);
+  return emit_face<T, D, SOLVER>(w, A, sh, emit, ln.u, ln.o, sr, sl, STAGE == FACE_CORRECT ? hl : bl,
                                  L ? ln.p : (long long)(ln.o / sizeof(T)));
 }
 
@@ -360,7 +377,7 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
 // in double (545 / 385 us).  SOLVER 3, the learned flux (float only): 300 / 422 us
 // against 417 / 536 us with states stored for kernels of their own, and 39 words a
 // cell of scratch less.
-template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
+template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L, bool TILES>
 __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1)
     k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx, unsigned long long* nfb) {
   A.dtdx = T(get_dt(dts)) * inv_dx;
@@ -380,7 +397,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
     return (i + 1 >= n ? (unsigned)(1 - n) : 1u) * stride * (unsigned)sizeof(T);
   };
   const unsigned plane = (unsigned)w.nx * (unsigned)w.ny;
-  __shared__ T parks[kPark<T, SOLVER, L> ? kBlock * 21 : 1];
+  __shared__ T parks[kPark<T, SOLVER, L> && !TILES ? kBlock * 21 : 1];
   MlpShared* sh = nullptr;
   if constexpr (SOLVER == 3) {
     __shared__ MlpShared shared;
@@ -418,7 +435,34 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
         ln.o = (((unsigned)z * (unsigned)w.ny + (unsigned)y) * (unsigned)w.nx + (unsigned)x) * (unsigned)sizeof(T);
       }
     };
-    if (t < g.w2) {
+    if constexpr (TILES) {
+      if (t < g.w2 + g.w1) {
+        // position of the lines, one cell shared with the wave before: the lines of four
+        // neighbouring columns, each with its last cell before the first
+        const bool zdir = t < g.w2;
+        const unsigned c0 = lane & (kTileCols - 1), cell = lane / kTileCols;
+        const unsigned lines = g.fours * (unsigned)(zdir ? g.by : g.bz), len = (unsigned)(zdir ? g.bz : g.by) + 1;
+        const unsigned l = (zdir ? t : t - g.w2) * (kTileCells - 1) + cell;
+        const bool in = l < lines * len;
+        const unsigned c = in ? l : 0, line = zdir ? fdiv(g.by_lz, c) : fdiv(g.by_ly, c), q = c - line * len;
+        const unsigned other = fdiv(g.by_fours, line), x0 = (line - other * g.fours) * kTileCols + c0;
+        const bool on = in && x0 < (unsigned)g.bx;
+        const int x = on ? (int)x0 : 0, m = q == 0 ? (int)len - 2 : (int)q - 1;
+        const bool emit = on && cell > 0 && q > 0;
+        if (zdir) {
+          Line<T, 2, L> ln;
+          place(ln, x, (int)other, m, true, true, true);
+          const unsigned o1 = ln.o + up(ln.i, w.nx, 1), dy = up(ln.j, w.ny, (unsigned)w.nx);
+          fb += row_faces<T, 2, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dy, o1 + dy, emit, sh);
+        } else {
+          Line<T, 1, L> ln;
+          place(ln, x, m, (int)other, true, true, true);
+          const unsigned o1 = ln.o + up(ln.k, w.nz, plane), dx = up(ln.i, w.nx, 1);
+          fb += row_faces<T, 1, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dx, o1 + dx, emit, sh);
+        }
+        continue;
+      }
+    } else if (t < g.w2) {
       const unsigned chunk = fdiv(g.by_w2c, t), l = (t - chunk * g.w2c) * 64 + lane, n = (unsigned)(g.bx * g.by);
       const bool on = l < n;
       const unsigned c = on ? l : 0, y = fdiv(g.by_bx, c), x = c - y * (unsigned)g.bx;
@@ -433,7 +477,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
       continue;
     }
     t -= g.w2;
-    if (t < g.w1) {
+    if (!TILES && t < g.w1) {
       const unsigned chunk = fdiv(g.by_w1c, t), l = (t - chunk * g.w1c) * 64 + lane, n = (unsigned)(g.bx * bz);
       const bool on = l < n;
       const unsigned c = on ? l : 0, z = fdiv(g.by_bx, c), x = c - z * (unsigned)g.bx;
@@ -457,7 +501,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
       Line<T, 0, L> ln;
       place(ln, x, (int)y, z0 + (int)z, true, true, true);
       const unsigned o1 = L ? ln.o : ln.o + up(ln.j, w.ny, (unsigned)w.nx), dz = L ? 0u : up(ln.k, w.nz, plane);
-      fb += row_faces<T, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dz, o1 + dz, on && lane > 0 && q > 0, sh);
+      fb += row_faces<T, 0, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dz, o1 + dz, on && lane > 0 && q > 0, sh);
     }
   }
   if (SOLVER == 0 || SOLVER == 3) block_count_atomic(fb, nfb);
