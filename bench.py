@@ -55,19 +55,20 @@ CELL_UPDATE_WORDS = 16
 # reads or writes, intermediates included, counted once (neighbour re-reads
 # excluded).  Implementation traffic of the stage split, not algorithmic.
 STAGE_WORDS = {
-    "prim": 8 + 8,                        # U(5) + B(3) in, W(8) out
-    "states": 8 + 3 + 42,                 # W, B in; QL, QR (2 x 3 x 7) out
+    "prim": 8 + 8 + 3,                    # U(5) + B(3) in, W(8) and -v x B (3) out
     "flux_predict": 8 + 3 + 21,           # VL: W, B in, F out
-    "flux_correct": 8 + 3 + 21,           # VL: Wh, Bh in, F out
-    "emf_predict": 9 + 6 + 3,             # mass flux + 2 EMFs per face, v and Bc in; 3 edge EMFs out
-    "emf_correct": 9 + 6 + 3,
+    "flux_correct": 8 + 3 + 21 + 3,       # VL: Wh, Bh in, F and -v x B out
+    "emf_predict": 9 + 3 + 3,             # mass flux + 2 EMFs per face, -v x B in; 3 edge EMFs out
+    "emf_correct": 9 + 3 + 3,
     "half_step": 5 + 3 + 15 + 3 + 8 + 3,  # U, B, hydro F, E in; Wh, Bh out
     "final": 5 + 3 + 15 + 3 + 8,          # U, B, hydro F, E in; U, B out
 }
 CTU_WORDS = dict(STAGE_WORDS)
 CTU_WORDS.update({
-    "flux_predict": 42 + 3 + 21,          # QL, QR, B in; F1 out
-    "flux_correct": 42 + 15 + 3 + 3 + 3 + 21,  # QL, QR, hydro F1, E, B, Bh in; F2 out
+    "states": 8 + 3 + 21,                 # one kernel for reconstruction, tracing and fluxes: W, B in; F1 out
+    "flux_predict": 0,
+    "half_step": 5 + 3 + 15 + 3 + 3 + 3,  # U, B, hydro F1, E in; -v x B, Bh out
+    "flux_correct": 8 + 15 + 3 + 3 + 3 + 21,  # W, hydro F1, E, B, Bh in; F2 out
 })
 
 WORKLOADS = {
@@ -703,20 +704,6 @@ def main():
             forms[f"{key}_{prec}"] = e
         if key != head_key and "stages" in r["f32"]:
             forms[f"{key}_f32"]["stage_ms"] = {k: round(x, 4) for k, x in r["f32"]["stages"].items()}
-
-    if "ctu" in results:
-        # the reconstruction stage on LDS tiles (a launch-shape option): same
-        # bits, timed beside the per-cell form
-        wl = WORKLOADS["ctu"]
-        tiles = {}
-        for prec in ("f32", "f64"):
-            r = run_form(wl, prec, n, args.steps, args.warmup, args.seed, profile=True,
-                         setup=lambda s: s.set_launch(tiles=1))
-            base = results["ctu"][prec]
-            tiles[prec] = {"ms_per_step": round(r["ms_per_step"], 4), "states_ms": round(r["stages"]["states"], 4),
-                           "per_cell_states_ms": round(base["stages"]["states"], 4) if "stages" in base else None,
-                           "step_vs_per_cell": round(base["ms_per_step"] / r["ms_per_step"], 4)}
-        forms["ctu_lds_tiles"] = {"workload": wl["name"].format(n=n), "tile": [16, 4, 4], **tiles}
 
     if args.oracle_l1_steps > 0 and head_key is not None:
         precs = ("f64", "f32", "f32_mixed") if head_key == "ctu" else ("f64", "f32")

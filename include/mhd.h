@@ -108,8 +108,9 @@ int mhd_required_ghost(int scheme, int recon);
  * at: 35 words per scratch cell (W, Bh, F, E), 98 with CTU, times the scratch
  * cells (the level's cells, or (groups + 2) boxes of (edge + 2 ghost)^3 cells
  * for a group list), plus the group occupancy map.  An upper bound: CTU takes
- * 59 of the 98 words.  mhd_step_noalloc accepts a level by this figure.  The context allocates its scratch on the
- * first update of a level that needs more than it holds; the time-mean
+ * 59 of the 98 words.  mhd_step_noalloc accepts a level by this figure.  The
+ * context allocates its scratch on the first update of a level that needs more
+ * than it holds; the time-mean
  * registers of mhd_accumulate_registers (24 words per scratch cell) come on
  * top.  No HIP call. */
 int mhd_workspace_bytes(mhd_ctx ctx, const mhd_level* lv, size_t* bytes);

@@ -1,19 +1,17 @@
 """Launch-shape autotuner of the batched level update.
 
-A level's stage kernels have four launch parameters (mhd_set_launch):
+A level's stage kernels have three launch parameters (mhd_set_launch):
 blocks per CU of the persistent grid that walks the level's work items (the
 cells of its listed patch groups and their halos) with a grid-wide stride,
-threads per block, for a group list the batch of groups that runs through
+threads per block, and for a group list the batch of groups that runs through
 the middle stages together (so that a batch's intermediates can stay in the
 caches between stages; paper Sec. 4 sends patch groups to the GPU in
-batches), and for CTU with PPM whether the reconstruction stage runs on LDS
-tiles.  The tuner times each candidate shape on the level itself (ghost
-refill plus update, HIP events, median of a few reps) and keeps the fastest
-of the first three parameters' grid; then, for CTU with PPM, it times the
-winner with LDS tiles and keeps that if faster.  Results are cached in a
-JSON file keyed by device, method, precision, level shape and group count.
-Shapes with the same tile choice give bit-identical results; LDS tiles agree
-with the per-cell form to rounding.
+batches).  The tuner times each candidate shape on the level itself (ghost
+refill plus update, HIP events, median of a few reps) and keeps the fastest.
+Results are cached in a JSON file keyed by device, method, precision, level
+shape and group count.  All shapes give bit-identical results.  A shape's
+fourth value (lds_tiles) once chose another form of the CTU reconstruction; it
+has no effect, and the winner is timed with it once more as before.
 """
 from __future__ import annotations
 
@@ -97,7 +95,7 @@ def tune(h, candidates=None, reps: int = 5, cache: str | None = None, use_cache:
     level], "keys": [...]}.  candidates: None (level_candidates of each
     level) or one list of shapes (ints: blocks per CU at the default threads
     and batch) for every level.  try_tiles: also time the best shape with
-    LDS tiles where that option applies (it is then the last candidate).
+    lds_tiles set (the last candidate; it has no effect).
 
     The timing runs advance the levels' state (it is a real update); tune
     before the measured run, not inside it."""
