@@ -297,10 +297,16 @@ unsigned decompose(Work& w, int threads) {
 // grid, the item boxes of a group list.  A march repeats the trace of one cell
 // before its first face, so long marches save work and short ones give small
 // grids enough waves.
-// Whole grids below tile_limit cells go without marches (kTileCells).
-FaceGeo face_geometry(const Work& w, long long tile_limit) {
+// Whole grids below kTileLimit cells go in tiles of `cols` columns: they trace less per
+// face than short marches, which read along whole rows.  Whole step (us), marches /
+// tiles, CTU + PPM + HLLD unless stated: double 24^3 53 / 44, 48^3 101 / 82, 64^3 172 /
+// 147, 80^3 289 / 268, 96^3 486 / 509; float 24^3 35 / 34, 48^3 54 / 49, 80^3 130 / 119,
+// 96^3 188 / 186, 128^3 464 / 525; float Roe (PLM) 64^3 107 / 98, 80^3 179 / 165, 96^3
+// 249 / 260; learned flux 32^3 57 / 51, 64^3 172 / 159, 128^3 1021 / 1079
+constexpr long long kTileLimit = 9 << 16;
+FaceGeo face_geometry(const Work& w, int cols) {
   FaceGeo g;
-  g.fours = 0;
+  g.tz = g.ty = 0;
   const auto cut = [](int n, int len) { return (n + len - 1) / len; };
   if (w.groups) {
     // whole float step of 5 / 50 / 191 / 400 groups: 54 / 152 / 531 / 1098 us
@@ -314,21 +320,19 @@ FaceGeo face_geometry(const Work& w, long long tile_limit) {
     g.lx = w.box;
   } else {
     // the longer a march the less of its trace is repeated, the shorter the more
-    // waves a small grid has.  Whole step (us), CTU + PPM + HLLD, marches of 1 / 2 / 4
-    // / 8 cells: float 32^3 41 / 43 / 49 / -, 97 x 61 x 83 146 / 137 / 136 / 158,
-    // 128^3 - / 500 / 476 / 474; double 48^3 102 / 103 / 109 / -, 96^3 620 / 515 /
-    // 490 / 514
-    const int len = w.N < 1 << 16 ? 1 : w.N < 3 << 17 ? 2 : w.N < 3 << 19 ? 4 : 8;
+    // waves a small grid has.  Whole step (us), CTU + PPM + HLLD, marches of 2 / 4 / 8
+    // cells: float 128^3 500 / 476 / 474; double 96^3 515 / 490 / 514
+    const int len = w.N < 3 << 19 ? 4 : 8;
     g.bx = w.nx;
     g.by = w.ny;
     g.bz = g.cz = g.cy = len;
     g.units = cut(w.nz, g.bz);
     g.lx = w.nx + 1;
-    if (w.N < tile_limit) {
+    if (w.N < kTileLimit) {
       g.bz = w.nz;
       g.units = 1;
-      g.fours = (unsigned)cut(w.nx, kTileCols);
-      g.by_fours = make_div(g.fours);
+      g.tz = (unsigned)cut(w.nx * w.ny, cols);
+      g.ty = (unsigned)cut(w.nx * w.nz, cols);
       g.by_ly = make_div((unsigned)w.ny + 1);
       g.by_lz = make_div((unsigned)w.nz + 1);
     }
@@ -338,9 +342,9 @@ FaceGeo face_geometry(const Work& w, long long tile_limit) {
   g.w2 = g.w2c * (unsigned)cut(g.bz, g.cz);
   g.w1c = waves((long long)g.bx * g.bz, 64);
   g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
-  if (g.fours) {
-    g.w2 = waves((long long)g.fours * g.by * (g.bz + 1) - 1, kTileCells - 1);
-    g.w1 = waves((long long)g.fours * g.bz * (g.by + 1) - 1, kTileCells - 1);
+  if (g.tz) {
+    g.w2 = waves((long long)g.tz * (g.bz + 1) - 1, 64 / cols - 1);
+    g.w1 = waves((long long)g.ty * (g.by + 1) - 1, 64 / cols - 1);
   }
   g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
   g.by_per = make_div(g.per);
@@ -487,16 +491,10 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
 // 0,1 / 0,0, i.e. 4 ghost cells of U^n.
 template <typename T, int R, bool ALLW, int S, int STAGE, bool L>
 void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_dx) {
-  // Tiles trace less per face, marches read along whole rows.  Whole step (us),
-  // marches / tiles, CTU + PPM + HLLD unless stated: double 24^3 53 / 44, 48^3 101 /
-  // 86, 64^3 172 / 153, 80^3 300 / 278, 96^3 491 / 539; float 24^3 35 / 34, 32^3 38.7
-  // / 39.5, 48^3 54 / 62; float Roe (PLM) 32^3 43 / 41, 64^3 108 / 106, 96^3 253 / 281;
-  // learned flux 32^3 57 / 52, 64^3 173 / 158
-  constexpr long long tile_limit = sizeof(T) == 8 ? 9 << 16 : S == 0 || S == 3 ? 5 << 16 : 1 << 15;
-  const FaceGeo g = face_geometry(w, tile_limit);
+  const FaceGeo g = face_geometry(w, kTileCols<T, S>);
   unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
   if constexpr (!L) {
-    if (g.fours) k_ctu_faces<T, R, ALLW, S, STAGE, L, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, L, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
     else k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
   } else {
     k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);

@@ -40,8 +40,8 @@ struct FaceGeo {
   unsigned w1, w1c;        // ... y-marches
   unsigned per;            // waves of a unit
   FastDiv by_per, by_w2c, by_w1c, by_bx, by_by, by_lx;
-  unsigned fours;          // columns of a row in fours: z and y go in tiles (0: in marches)
-  FastDiv by_fours, by_ly, by_lz;
+  unsigned tz, ty;         // z and y in tiles: tiles side by side (0: in marches)
+  FastDiv by_ly, by_lz;
 };
 
 // Whether a march keeps what it carries from cell to cell -- slopes, interface
@@ -77,11 +77,18 @@ struct FaceArgs {
   Capture cp;
 };
 
-// Small whole grids take z and y without marches too: a wave holds 16 successive
-// cells of four neighbouring lines, lane 4 q + x, and hands each upper-edge state four
-// lanes on.  A march of one cell traces two cells for each face, and too few waves are
-// there to make it longer; a tile traces 16 cells for 15.
-constexpr int kTileCols = 4, kTileCells = 16;
+// Small whole grids take z and y without marches too: a wave holds a tile of
+// successive cells of neighbouring lines (columns along x), and hands each upper-edge
+// state a row of lanes on.  A march of one cell traces two cells for each face, and too
+// few waves are there to make it longer; a tile of eight traces eight for seven.  Fewer
+// columns trace less and read shorter pieces of rows.  Whole step (us), 4 / 8 / 16
+// columns: float HLLD 32^3 38 / 37 / 37, 64^3 103 / 78 / 73, 80^3 181 / 130 / 119, float
+// Roe 64^3 106 / 98 / 100, double HLLD 48^3 85 / 82 / 89, 80^3 274 / 268 / 285, learned
+// flux 64^3 156 / 159 / 167.
+template <typename T, int SOLVER>
+constexpr int kTileCols = sizeof(T) == 4 && (SOLVER == 1 || SOLVER == 2) ? 16 : 8;
+template <typename T, int SOLVER>
+constexpr int kTileCells = 64 / kTileCols<T, SOLVER>;
 
 // value of the lane below (lane 0 keeps its own)
 __device__ __forceinline__ float lane_below(float v) {
@@ -93,10 +100,6 @@ __device__ __forceinline__ double lane_below(double v) {
   return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, false),
                           __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false));
 }
-
-// ... of the lane four below: the cell before on the same line of a tile
-__device__ __forceinline__ float line_below(float v) { return __shfl_up(v, kTileCols, 64); }
-__device__ __forceinline__ double line_below(double v) { return __shfl_up(v, kTileCols, 64); }
 
 __device__ __forceinline__ unsigned fresh_offset(unsigned o) {
   asm volatile("" : "+v"(o));
@@ -318,7 +321,7 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
 }
 
 // Cells one per lane, their lower neighbours along D in the lane below (D = 0: 64
-// successive cells of the x-rows) or four below (tiles).  (o1, o2, o12): see
+// successive cells of the x-rows) or a row of lanes below (tiles).  (o1, o2, o12): see
 // transverse().
 template <typename T, int D, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
 __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, const Line<T, D, L>& ln, unsigned o1,
@@ -364,7 +367,7 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
     correct_state(tr, bu, hu, hd, A.gam, sr);
   }
 #pragma unroll
-  for (int c = 0; c < 7; ++c) sr[c] = D == 0 ? lane_below(sr[c]) : line_below(sr[c]);
+  for (int c = 0; c < 7; ++c) sr[c] = D == 0 ? lane_below(sr[c]) : __shfl_up(sr[c], kTileCols<T, SOLVER>, 64);
   return emit_face<T, D, SOLVER>(w, A, sh, emit, ln.u, ln.o, sr, sl, STAGE == FACE_CORRECT ? hl : bl,
                                  L ? ln.p : (long long)(ln.o / sizeof(T)));
 }
@@ -437,17 +440,20 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
     };
     if constexpr (TILES) {
       if (t < g.w2 + g.w1) {
-        // position of the lines, one cell shared with the wave before: the lines of four
-        // neighbouring columns, each with its last cell before the first
+        // position of the lines, one cell shared with the wave before: the lines of a
+        // tile's columns, each with its last cell before the first; columns are counted
+        // on from row to row
+        constexpr unsigned cols = kTileCols<T, SOLVER>;
         const bool zdir = t < g.w2;
-        const unsigned c0 = lane & (kTileCols - 1), cell = lane / kTileCols;
-        const unsigned lines = g.fours * (unsigned)(zdir ? g.by : g.bz), len = (unsigned)(zdir ? g.bz : g.by) + 1;
-        const unsigned l = (zdir ? t : t - g.w2) * (kTileCells - 1) + cell;
-        const bool in = l < lines * len;
-        const unsigned c = in ? l : 0, line = zdir ? fdiv(g.by_lz, c) : fdiv(g.by_ly, c), q = c - line * len;
-        const unsigned other = fdiv(g.by_fours, line), x0 = (line - other * g.fours) * kTileCols + c0;
-        const bool on = in && x0 < (unsigned)g.bx;
-        const int x = on ? (int)x0 : 0, m = q == 0 ? (int)len - 2 : (int)q - 1;
+        const unsigned c0 = lane & (cols - 1), cell = lane / cols;
+        const unsigned len = (unsigned)(zdir ? g.bz : g.by) + 1;
+        const unsigned l = (zdir ? t : t - g.w2) * (kTileCells<T, SOLVER> - 1) + cell;
+        const bool in = l < (zdir ? g.tz : g.ty) * len;
+        const unsigned c = in ? l : 0, tile = zdir ? fdiv(g.by_lz, c) : fdiv(g.by_ly, c), q = c - tile * len;
+        const unsigned col = tile * cols + c0;
+        const bool on = in && col < (unsigned)g.bx * (unsigned)(zdir ? g.by : g.bz);
+        const unsigned at = on ? col : 0, other = fdiv(g.by_bx, at);
+        const int x = (int)(at - other * (unsigned)g.bx), m = q == 0 ? (int)len - 2 : (int)q - 1;
         const bool emit = on && cell > 0 && q > 0;
         if (zdir) {
           Line<T, 2, L> ln;

@@ -1,7 +1,7 @@
 """The CTU face kernels where their decomposition changes: tiles and marches (whole
-grids of about 2^15, 5 2^16 and 9 2^16 cells), march lengths (about 2^16, 3 2^17
-and 3 2^19 cells; group lists of few and of many boxes), ragged rows and lines,
-occupancy maps built by one block and by many.
+grids of about 9 2^16 cells), march lengths (about 3 2^19 cells; group lists of few
+and of many boxes), ragged rows, lines and tiles, occupancy maps built by one block
+and by many.
 
 Bars: FP64 against the oracle within 1e-12 of each component's largest value, FP32
 within 1e-5 of it (of the flow's momentum scale for the momenta) wherever a float
@@ -51,7 +51,8 @@ def test_whole_grid_step(shape, recon, solver):
 
 
 @pytest.mark.parametrize("shape,recon,solver", [
-    ((31, 32, 33), "ppm", "hlld"), ((32, 32, 32), "ppm", "hlld"), ((33, 32, 31), "plm", "hlle"),
+    ((5, 6, 4), "ppm", "hlld"), ((17, 20, 30), "ppm", "hlld"), ((31, 32, 33), "ppm", "hlld"), ((32, 32, 32), "ppm", "hlld"),
+    ((84, 84, 83), "ppm", "hlld"), ((84, 84, 84), "ppm", "hlld"), ((33, 32, 31), "plm", "hlle"),
     ((69, 69, 68), "plm", "roe"), ((69, 69, 69), "plm", "roe")])
 def test_whole_grid_step_f32(shape, recon, solver):
     p = inputs.smooth_problem(*shape, seed=sum(shape))
