@@ -602,29 +602,36 @@ __device__ __forceinline__ void block_count_atomic(int v, unsigned long long* co
   }
 }
 
-// VL flux stage.  RECON 0 (predictor): the normal field is the level's B.
-// RECON 1 and 2 (corrector): it is the half-step scratch Bh, which each thread
-// reads at its own cell only and then overwrites with that cell's EMF of the
-// half-step state, for the edge EMFs of the next stage.
+// One direction of the VL flux stage.  RECON 0 (predictor): the normal field is the
+// level's B.  RECON 1 and 2 (corrector): it is the half-step scratch Bh, of which a
+// direction reads its component at the own cell only and then overwrites it with that
+// component of the cell's EMF of the half-step state, for the edge EMFs of the next
+// stage.
+template <typename T, int D, int RECON, int SOLVER, bool L>
+__device__ __forceinline__ int cell_flux(const Work& w, const T* __restrict__ W, const T* __restrict__ B, T* Bh,
+                                         T* __restrict__ F, const Cell<T, L>& c, T gam) {
+  const T bn = RECON == 0 ? c.template level<D, 0>(w, B, D * w.N) : c.here(w, (const T*)Bh, D * w.NS);
+  if constexpr (RECON != 0) {
+    constexpr int b = (D + 1) % 3, e = (D + 2) % 3;
+    T q[8];
+    q[1 + b] = c.here(w, W, (1 + b) * w.NS);
+    q[1 + e] = c.here(w, W, (1 + e) * w.NS);
+    q[5 + b] = c.here(w, W, (5 + b) * w.NS);
+    q[5 + e] = c.here(w, W, (5 + e) * w.NS);
+    c.put(w, Bh, D * w.NS, cell_emf(q, D));
+  }
+  return face_flux<T, D, RECON, SOLVER, L>(w, W, bn, F, c, gam);
+}
+
+// VL flux stage: all three directions of a cell, or one per launch row.
 template <typename T, int RECON, int SOLVER, bool L>
 __global__ void __launch_bounds__(kMaxBlock) k_flux(Work w, const T* __restrict__ W, const T* __restrict__ B, T* Bh,
                                                  T* __restrict__ F, T gam, unsigned long long* nfb) {
   int fb = 0;
   FOR_CELLS(T, L, w, c) {
-    T bn[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-      bn[d] = RECON == 0 ? c.template level<0, 0>(w, B, d * w.N) : c.here(w, (const T*)Bh, d * w.NS);
-    if constexpr (RECON != 0) {
-      T q[8];
-#pragma unroll
-      for (int m = 1; m < 8; ++m) q[m] = c.here(w, W, m * w.NS);
-#pragma unroll
-      for (int m = 0; m < 3; ++m) c.put(w, Bh, m * w.NS, cell_emf(q, m));
-    }
-    fb += face_flux<T, 0, RECON, SOLVER, L>(w, W, bn[0], F, c, gam);
-    fb += face_flux<T, 1, RECON, SOLVER, L>(w, W, bn[1], F, c, gam);
-    fb += face_flux<T, 2, RECON, SOLVER, L>(w, W, bn[2], F, c, gam);
+    if (gridDim.y == 1 || blockIdx.y == 0) fb += cell_flux<T, 0, RECON, SOLVER, L>(w, W, B, Bh, F, c, gam);
+    if (gridDim.y == 1 || blockIdx.y == 1) fb += cell_flux<T, 1, RECON, SOLVER, L>(w, W, B, Bh, F, c, gam);
+    if (gridDim.y == 1 || blockIdx.y == 2) fb += cell_flux<T, 2, RECON, SOLVER, L>(w, W, B, Bh, F, c, gam);
   }
   if (SOLVER == 0) block_count_atomic(fb, nfb);
 }

@@ -90,3 +90,19 @@ def test_listed_groups_equal_whole_grid(edge, n, groups, prec):
     for a in range(3):                     # a listed cell's faces, its upper ones included
         face = cell | torch.roll(cell, 1, 2 - a)
         assert torch.equal(part.B[a], torch.where(face, whole.B[a], B0[a]))
+
+
+@pytest.mark.parametrize("shape,recon,solver", [((5, 4, 7), "plm", "roe"), ((48, 48, 48), "plm", "roe"),
+                                                ((32, 40, 100), "ppm", "hlld"), ((32, 40, 103), "ppm", "hlld")])
+def test_vl_whole_grid_step(shape, recon, solver):
+    # the VL flux stage split by direction (fewer than 512 blocks of 256 cells) and whole
+    p = inputs.smooth_problem(*shape, seed=sum(shape))
+    U, B = oracle.initial_state(p)
+    dt = oracle.cfl_dt(U, B, p["dx"])
+    Uo, Bo = oracle.step(U, B, dt, p["dx"], scheme=oracle.VL, recon=RECON[recon], riemann=SOLVERS[solver])
+    s, lv = Solver("vl", recon, solver), level(U, B, p["dx"])
+    s.step(lv, dt)
+    for got, want in ((lv.U, Uo), (lv.B, Bo)):
+        got = got.cpu().numpy()
+        for m in range(len(want)):
+            assert np.abs(got[m] - want[m]).max() <= 1e-12 * np.abs(want[m]).max()
