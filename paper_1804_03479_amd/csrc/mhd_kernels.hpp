@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "mhd_device.hpp"
+#include "mhd_layout.hpp"
 #include "mhd_mlp.hpp"
 
 namespace mhd {
@@ -83,8 +84,6 @@ struct Work {
   FastDiv by_box;       // of an item index by a group's item box (cell_of)
   FastDiv by_edge;      // of a cell coordinate by the group edge
 };
-
-__device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 __device__ __forceinline__ long long lin(const Work& w, int i, int j, int k) {
   return ((long long)k * w.ny + j) * w.nx + i;
@@ -696,7 +695,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_emf(Work w, const T* __restrict__
 // each loaded once per tile instead of once per edge that uses it), then
 // computes the three lower-corner edges of each of its cells from LDS with
 // the arithmetic of k_emf.  Grids need not be multiples of the tile (cells
-// past the grid idle; the staged layer wraps periodically).
+// past the grid idle; the staged layer wraps periodically: staged_coord).
 template <typename T, int TX, int TY, int TZ>
 __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __restrict__ F, const T* __restrict__ R,
                                                          T* __restrict__ E) {
@@ -709,7 +708,7 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __r
   const long long N = w.NS;
   for (int h = threadIdx.x; h < NH; h += NT) {
     const int hx = h % HX, hy = (h / HX) % HY, hz = h / (HX * HY);
-    const long long q = lin(w, wrapc(tx0 - 1 + hx, w.nx), wrapc(ty0 - 1 + hy, w.ny), wrapc(tz0 - 1 + hz, w.nz));
+    const long long q = lin(w, staged_coord(tx0, hx, w.nx), staged_coord(ty0, hy, w.ny), staged_coord(tz0, hz, w.nz));
 #pragma unroll
     for (int a = 0; a < 3; ++a) sR[a][h] = R[(long long)a * N + q];
 #pragma unroll
