@@ -169,7 +169,10 @@ int mhd_advance(mhd_ctx ctx, const mhd_level* lv, double* dt_dev, double* t_dev)
  * (and the same dt_dev/t_dev) captures the step's kernels on the context's
  * stream and instantiates the graph; later calls replay it.  dt comes from
  * the on-device CFL reduction and a group count from n_groups_dev, so a
- * replay needs no host work.  A different description re-captures. */
+ * replay needs no host work.  A different description re-captures, and so
+ * does a call after the context's scratch or group map has grown for another
+ * level.  A graph that the caller captures holds those addresses as well:
+ * update the context's largest level once before capturing. */
 int mhd_advance_graph(mhd_ctx ctx, const mhd_level* lv, double* dt_dev, double* t_dev);
 
 /* Launch shape of the stage kernels (the batched level update):

@@ -121,6 +121,16 @@ int check_level(const mhd_ctx_s* ctx, const mhd_level* lv) {
     if ((x) != hipSuccess) return MHD_ERR_HIP;     \
   } while (0)
 
+void drop_graph(mhd_ctx_s* c) {
+  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
+  if (c->graph) (void)hipGraphDestroy(c->graph);
+  c->graph_exec = nullptr;
+  c->graph = nullptr;
+}
+
+// A captured step holds the addresses of the scratch and of the occupancy map:
+// whatever releases one of them drops the graph too, or its next replay would write
+// to memory that is no longer the context's.
 void free_scratch(mhd_ctx_s* c) {
   void** bufs[] = {&c->W, &c->Bh, &c->F, &c->E, &c->F2, &c->Rh};
   for (void** b : bufs) {
@@ -128,6 +138,7 @@ void free_scratch(mhd_ctx_s* c) {
     *b = nullptr;
   }
   c->cap_cells = 0;
+  drop_graph(c);
 }
 
 int ensure_capacity(mhd_ctx_s* c, long long cells) {
@@ -240,17 +251,25 @@ void fill_occupancy(mhd_ctx_s* c, const mhd_level* lv, int* occ) {
       lv->ny / lv->group_edge, lv->nz / lv->group_edge);
 }
 
+// room for the occupancy map of the level's group list (list mode only) in *occ
+int ensure_occupancy(mhd_ctx_s* c, const mhd_level* lv, int** occ, long long* cap) {
+  if (!list_mode(lv)) return MHD_OK;
+  const long long ng = occupancy_cells(lv);
+  if (ng <= *cap) return MHD_OK;
+  hipFree(*occ);
+  *occ = nullptr;
+  *cap = 0;
+  if (occ == &c->occ) drop_graph(c);
+  if (hipMalloc(occ, ng * sizeof(int)) != hipSuccess) return MHD_ERR_OUT_OF_MEMORY;
+  *cap = ng;
+  return MHD_OK;
+}
+
 // occupancy map of a level's group list (list mode only) into *occ
 int build_occupancy_into(mhd_ctx_s* c, const mhd_level* lv, int** occ, long long* cap) {
-  if (!lv->groups || lv->n_groups <= 0) return MHD_OK;
-  const long long ng = occupancy_cells(lv);
-  if (ng > *cap) {
-    hipFree(*occ);
-    *occ = nullptr;
-    *cap = 0;
-    if (hipMalloc(occ, ng * sizeof(int)) != hipSuccess) return MHD_ERR_OUT_OF_MEMORY;
-    *cap = ng;
-  }
+  if (!list_mode(lv)) return MHD_OK;
+  const int rc = ensure_occupancy(c, lv, occ, cap);
+  if (rc) return rc;
   fill_occupancy(c, lv, *occ);
   return MHD_OK;
 }
@@ -835,9 +854,7 @@ int mhd_finalize(mhd_ctx c) {
   if (!c) return MHD_ERR_INVALID_ARG;
   if (c->stream) hipStreamSynchronize(c->stream);
   else hipDeviceSynchronize();
-  if (c->graph_exec) hipGraphExecDestroy(c->graph_exec);
-  if (c->graph) hipGraphDestroy(c->graph);
-  free_scratch(c);
+  free_scratch(c);   // and the captured graph
   hipFree(c->mlpw);
   hipFree(c->mlp_ws);
   hipFree(c->RF);
@@ -953,13 +970,6 @@ int mhd_profile_step(mhd_ctx c, const mhd_level* lv, int nrep, double* stage_ms)
   return MHD_OK;
 }
 
-static void drop_graph(mhd_ctx_s* c) {
-  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-  if (c->graph) (void)hipGraphDestroy(c->graph);
-  c->graph_exec = nullptr;
-  c->graph = nullptr;
-}
-
 int mhd_set_launch(mhd_ctx c, int blocks_per_cu, int threads_per_block, int batch_groups, int lds_tiles) {
   if (!c || blocks_per_cu < 0 || batch_groups < 0 || (lds_tiles != 0 && lds_tiles != 1)) return MHD_ERR_INVALID_ARG;
   if (threads_per_block == 0) threads_per_block = kBlock;
@@ -984,17 +994,8 @@ int mhd_advance_graph(mhd_ctx c, const mhd_level* lv, double* dt_dev, double* t_
     // allocations happen before the capture
     rc = ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
     if (rc) return rc;
-    if (lv->groups && lv->n_groups > 0) {
-      const long long ng =
-          (long long)(lv->nx / lv->group_edge) * (lv->ny / lv->group_edge) * (lv->nz / lv->group_edge);
-      if (ng > c->cap_occ) {
-        hipFree(c->occ);
-        c->occ = nullptr;
-        c->cap_occ = 0;
-        if (hipMalloc(&c->occ, ng * sizeof(int)) != hipSuccess) return MHD_ERR_OUT_OF_MEMORY;
-        c->cap_occ = ng;
-      }
-    }
+    rc = ensure_occupancy(c, lv, &c->occ, &c->cap_occ);
+    if (rc) return rc;
     if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return MHD_ERR_HIP;
     const CflOut out{dt_dev, t_dev};
     rc = do_step(c, lv, DtSrc{0.0, &c->cfl->dt}, &out);
