@@ -20,8 +20,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-fno-hip-fp32-correctly-rounded-divide-sqrt",
          # float denormals flush to zero (double keeps them): the fast
          # reciprocal and square root then need no frexp / ldexp range
-         # scaling, 8-10 % fewer VALU instructions in the flux stages; no
-         # float value of the update comes near 1e-38
+         # scaling, 8-10 % fewer VALU instructions in the flux stages.
+         # States in small units (rho 1e-30, energies 1e-12 in cgs) stay clear
+         # of 1e-38 as long as no density is multiplied by another density or
+         # by an energy (tests/test_gpu_units.py)
          "-fgpu-flush-denormals-to-zero",
          # multiply-adds are fused inside an expression only: the same source
          # then rounds the same way in every kernel it is inlined into, so a

@@ -195,9 +195,15 @@ __device__ __forceinline__ int riemann_roe(const T wl[7], const T wr[7], T bn, T
     if (k < 6) {
 #pragma unroll
       for (int m = 0; m < 7; ++m) us[m] += alpha * r[m];
-      // rho > 0 and p > 0 without the division by rho
+      // rho > 0 and p > 0 without a division by rho: rho e_i > M^2 / 2.  In float, whose
+      // denormals are flushed, with rho and M over the mean state's density (rho of
+      // order one, M a velocity): rho e_i itself is zero in small units, below 1.2e-38
+      // (rho 1e-27, e_i 1e-12 in cgs), where every face would fall back to HLLE.
       const T ei = us[4] - T(0.5) * (bn * bn + us[5] * us[5] + us[6] * us[6]);
-      if (!(us[0] > T(0)) || !(us[0] * ei > T(0.5) * (us[1] * us[1] + us[2] * us[2] + us[3] * us[3]))) bad = 1;
+      const T sc = sizeof(T) == 4 ? id : T(1);
+      if (!(us[0] > T(0)) ||
+          !((us[0] * sc) * ei > T(0.5) * ((us[1] * sc) * us[1] + (us[2] * sc) * us[2] + (us[3] * sc) * us[3])))
+        bad = 1;
     }
   };
   {  // u - cf
