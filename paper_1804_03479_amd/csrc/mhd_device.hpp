@@ -401,10 +401,12 @@ __device__ __forceinline__ T mc_slope2(T qm, T q0, T qp) {
 }
 
 // PPM (Colella & Woodward 1984) interface value between cells a and b (a
-// below) from their values and twice their MC-limited slopes
+// below) from their values and twice their MC-limited slopes.  The mean of the
+// two, not a plus half the difference that the slopes need anyway: mirrored cells
+// have to give the same bits.
 template <typename T>
 __device__ __forceinline__ T ppm_interface(T qa, T qb, T sa, T sb) {
-  return qa + T(0.5) * (qb - qa) - (sb - sa) * T(1.0 / 12.0);
+  return T(0.5) * (qa + qb) - (sb - sa) * T(1.0 / 12.0);
 }
 
 // median of three values (one v_med3_f32 in float)
