@@ -294,23 +294,8 @@ unsigned item_blocks(Work& w) {
   return capped((w.items + kBlock - 1) / kBlock);
 }
 
-// Block decomposition of a stage kernel (Cell) for blocks of `threads`: fills
-// the Work's unit fields and returns the grid
-unsigned decompose(Work& w, int threads) {
-  if (w.groups) {
-    w.per = (unsigned)(w.box * w.box * w.box);
-    w.units = (int)(w.items / w.per);
-    w.by_row = make_div((unsigned)w.box);
-    w.by_plane = make_div((unsigned)(w.box * w.box));
-  } else {
-    w.per = (unsigned)((long long)w.nx * w.ny);
-    w.units = w.nz;
-    w.by_row = make_div((unsigned)w.nx);
-  }
-  w.chunks = (w.per + (unsigned)threads - 1) / (unsigned)threads;
-  w.by_chunks = make_div(w.chunks);
-  return capped((long long)w.units * w.chunks);
-}
+// grid of a stage kernel (Cell) addressed in `mode`, in blocks of `threads`
+unsigned stage_grid(Work& w, int mode, int threads) { return capped(decompose(w, mode, threads)); }
 
 // Decomposition of the CTU face kernels (k_ctu_faces): slabs of planes of a whole
 // grid, the item boxes of a group list.  A march repeats the trace of one cell
@@ -427,14 +412,14 @@ StepBufs ctx_bufs(const mhd_ctx_s* c) {
 // faster than one cell per item there); in float, and on group lists, one
 // cell per item (in float the tiles were 10-20 % slower for every shape
 // tried: 32 x 4 x 2, 32 x 8 x 2, 16 x 8 x 4, 64 x 2 x 2)
-template <typename T, bool L>
+template <typename T, int L>
 void launch_emf(Work& w, const T* F, const T* R, T* E, int nt, hipStream_t st) {
-  if constexpr (!L && sizeof(T) == 8) {
+  if constexpr (L == kWhole && sizeof(T) == 8) {
     constexpr int TX = 16, TY = 8, TZ = 4;
     const long long nb = (long long)((w.nx + TX - 1) / TX) * ((w.ny + TY - 1) / TY) * ((w.nz + TZ - 1) / TZ);
     k_emf_tiled<T, TX, TY, TZ><<<(unsigned)nb, TX * TY * TZ, 0, st>>>(w, F, R, E);
   } else {
-    const unsigned nb = decompose(w, nt);
+    const unsigned nb = stage_grid(w, L, nt);
     k_emf<T, L><<<nb, nt, 0, st>>>(w, F, R, E);
   }
 }
@@ -448,7 +433,7 @@ dim3 flux_grid(const mhd_ctx_s* c, unsigned nb) { return dim3(nb, nb < 2u * (uns
 
 // ev (optional): kNumStages + 1 events recorded around the stage kernels.
 // R: 1 = PLM (minmod), 2 = PPM at the half step.
-template <typename T, int S, int R, bool MIX, bool L>
+template <typename T, int S, int R, bool MIX, int L>
 void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   const Mix mix{MIX ? lv->E64 : nullptr, c->cfg.beta_fp64};
   hipStream_t st = c->stream;
@@ -473,7 +458,7 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
     if (ev) (void)hipEventRecord(ev[s], st);
   };
   mark(0);
-  unsigned nb = decompose(wp, nt);
+  unsigned nb = stage_grid(wp, L, nt);
   if (cfl) {
     k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
     k_close_cfl<<<1, kCflSlots, 0, st>>>(c->cfl, c->cfg.courant * lv->dx, cfl->dt, cfl->t, 0);
@@ -486,21 +471,21 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
     Work f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch), h = batch_of(wh, b, batch);
     Work f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
     f1.rev = h.rev = e2.rev = 1;
-    nb = decompose(f1, nt);
+    nb = stage_grid(f1, L, nt);
     k_flux<T, 0, S, L><<<flux_grid(c, nb), nt, 0, st>>>(f1, W, B, Bh, F, gam, c->nfb);
     mark(2);
     launch_emf<T, L>(e1, F, Bh, E, nt, st);
     mark(3);
-    nb = decompose(h, nt);
+    nb = stage_grid(h, L, nt);
     k_half<T, MIX, false, L><<<nb, nt, 0, st>>>(h, U, B, mix, F, E, dts, inv_dx, gam, W, Bh);
     mark(4);
-    nb = decompose(f2, nt);
+    nb = stage_grid(f2, L, nt);
     k_flux<T, R, S, L><<<flux_grid(c, nb), nt, 0, st>>>(f2, W, B, Bh, F, gam, c->nfb);
     mark(5);
     launch_emf<T, L>(e2, F, Bh, E, nt, st);
     mark(6);
   }
-  nb = decompose(wu, nt);
+  nb = stage_grid(wu, L, nt);
   k_final<T, MIX, L><<<nb, nt, 0, st>>>(wu, U, B, mix, F, E, dts, inv_dx);
   mark(7);
 }
@@ -515,25 +500,25 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
 //   k_final        U^n, B^n, F2, E      -> U^{n+1}, B^{n+1}   step 8
 // Group halos (cells below, above each group): 4,4 / 2,2 / 1,2 / 1,1 / 1,1 /
 // 0,1 / 0,0, i.e. 4 ghost cells of U^n.
-template <typename T, int R, bool ALLW, int S, int STAGE, bool L>
+template <typename T, int R, bool ALLW, int S, int STAGE, int L>
 void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_dx) {
   const FaceGeo g = face_geometry(w, kTileCols<T, S>);
   unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
-  if constexpr (!L) {
-    if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, L, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
-    else k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+  if constexpr (L != kList) {
+    if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, false, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    else k_ctu_faces<T, R, ALLW, S, STAGE, false, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
   } else {
-    k_ctu_faces<T, R, ALLW, S, STAGE, L, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    k_ctu_faces<T, R, ALLW, S, STAGE, true, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
   }
   if constexpr (std::is_same<T, float>::value && S != 3) {
     if (c->capture.buf) {
-      nb = decompose(w, kBlock);
+      nb = stage_grid(w, L, kBlock);
       k_capture<R, ALLW, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, A, dts, inv_dx, c->capture);
     }
   }
 }
 
-template <typename T, int S, int R, bool MIX, bool L>
+template <typename T, int S, int R, bool MIX, int L>
 void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   const Mix mix{MIX ? lv->E64 : nullptr, c->cfg.beta_fp64};
   hipStream_t st = c->stream;
@@ -559,7 +544,7 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl,
     if (ev) (void)hipEventRecord(ev[s], st);
   };
   mark(0);
-  unsigned nb = decompose(wp, nt);
+  unsigned nb = stage_grid(wp, L, nt);
   if (cfl) {
     k_prim<T, true, MIX, L><<<nb, nt, 0, st>>>(wp, U, B, mix, W, Bh, gam, c->cfl, c->flag);
     k_close_cfl<<<1, kCflSlots, 0, st>>>(c->cfl, c->cfg.courant * lv->dx, cfl->dt, cfl->t, 0);
@@ -581,7 +566,7 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl,
     mark(3);
     launch_emf<T, L>(e1, F1, Bh, E, nt, st);
     mark(4);
-    nb = decompose(h, nt);
+    nb = stage_grid(h, L, nt);
     k_half<T, MIX, true, L><<<nb, nt, 0, st>>>(h, U, B, mix, F1, E, dts, inv_dx, gam, Rh, Bh);
     mark(5);
     A.F = F2;
@@ -593,12 +578,12 @@ void launch_ctu(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl,
     launch_emf<T, L>(e2, F2, Rh, E, nt, st);
     mark(7);
   }
-  nb = decompose(wu, nt);
+  nb = stage_grid(wu, L, nt);
   k_final<T, MIX, L><<<nb, nt, 0, st>>>(wu, U, B, mix, F2, E, dts, inv_dx);
   mark(8);
 }
 
-template <typename T, int S, bool MIX, bool L>
+template <typename T, int S, bool MIX, int L>
 void launch_method(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
   if constexpr (S == 3) {
     // learned flux: CTU only (validated at mhd_init)
@@ -614,11 +599,13 @@ void launch_method(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* c
   else launch_ctu<T, S, 0, MIX, L>(c, lv, dts, cfl, ev, sb);
 }
 
-// group lists use per-group scratch boxes, whole grids the level's addressing
+// group lists use per-group scratch boxes, whole grids the level's addressing: plane by
+// plane, or cell by cell (flat_pays)
 template <typename T, int S, bool MIX>
 void launch_scheme(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev, const StepBufs& sb) {
-  if (list_mode(lv)) launch_method<T, S, MIX, true>(c, lv, dts, cfl, ev, sb);
-  else launch_method<T, S, MIX, false>(c, lv, dts, cfl, ev, sb);
+  if (list_mode(lv)) launch_method<T, S, MIX, kList>(c, lv, dts, cfl, ev, sb);
+  else if (flat_pays(lv->nx, lv->ny, lv->nz, sizeof(T), g_threads)) launch_method<T, S, MIX, kFlat>(c, lv, dts, cfl, ev, sb);
+  else launch_method<T, S, MIX, kWhole>(c, lv, dts, cfl, ev, sb);
 }
 
 template <typename T, bool MIX>
@@ -711,11 +698,15 @@ template <typename T, bool MIX>
 void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
   Work w = make_work(lv, 0, 0);
   g_max_blocks = 0;
-  const unsigned nb = decompose(w, kBlock);
   const Mix mix{lv->E64, c->cfg.beta_fp64};
   const T *U = (const T*)lv->U, *B = (const T*)lv->B;
-  if (level_indexed<T>(w)) k_cfl<T, MIX, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
-  else k_cfl<T, MIX, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
+  const auto launch = [&](auto mode) {
+    const unsigned nb = stage_grid(w, mode, kBlock);
+    k_cfl<T, MIX, mode><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
+  };
+  if (level_indexed<T>(w)) launch(std::integral_constant<int, kList>());
+  else if (flat_pays(w.nx, w.ny, w.nz, sizeof(T), kBlock)) launch(std::integral_constant<int, kFlat>());
+  else launch(std::integral_constant<int, kWhole>());
 }
 
 // ... closed into the context's dt and, if given, an output scalar
@@ -731,22 +722,22 @@ void launch_cfl(mhd_ctx_s* c, const mhd_level* lv, double courant_dx, double* dt
 // the partials of a large level stay few
 unsigned reduce_blocks(mhd_ctx_s* c, Work& w) {
   g_max_blocks = 8LL * c->num_cu;
-  const unsigned nb = decompose(w, kBlock);
+  const unsigned nb = stage_grid(w, kWhole, kBlock);
   g_max_blocks = 0;
   return nb;
 }
 
 template <typename T>
 void launch_divb(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb) {
-  if (level_indexed<T>(w)) k_divb<T, true><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
-  else k_divb<T, false><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
+  if (level_indexed<T>(w)) k_divb<T, kList><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
+  else k_divb<T, kWhole><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
 }
 
 template <typename T>
 void launch_sums(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb, const double* e64) {
   const T *U = (const T*)lv->U, *B = (const T*)lv->B;
-  if (level_indexed<T>(w)) k_sums<T, true><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
-  else k_sums<T, false><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
+  if (level_indexed<T>(w)) k_sums<T, kList><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
+  else k_sums<T, kWhole><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
 }
 
 int read_flag(mhd_ctx_s* c, int* flag) {

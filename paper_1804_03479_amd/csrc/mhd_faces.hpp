@@ -516,7 +516,7 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
 // Interface capture of the shock-capturing solvers, apart from the face kernels
 // (which it would cost registers): every sampled face's states, traced (and
 // corrected) again, and the flux the face kernel has stored.
-template <int D, int n, int RECON, bool ALLW, bool L>
+template <int D, int n, int RECON, bool ALLW, int L>
 __device__ __forceinline__ void traced_states(const Work& w, const float* __restrict__ W, const float* __restrict__ B,
                                               const Cell<float, L>& c, float dtdx, float gam, float sl[7],
                                               float sr[7]) {
@@ -530,12 +530,12 @@ __device__ __forceinline__ void traced_states(const Work& w, const float* __rest
                                  dtdx, gam, sl, sr);
 }
 
-template <int D, int RECON, bool ALLW, int STAGE, bool L>
+template <int D, int RECON, bool ALLW, int STAGE, int L>
 __device__ __forceinline__ void capture_sample(const Work& w, const FaceArgs<float>& A, const Cell<float, L>& c,
                                                const Capture& cp) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3, d = 7 * D;
   const long long face = 3 * c.index(w) + D;
-  if (face % cp.stride || (L && (D == 0 ? c.a : (D == 1 ? c.b : c.c)) == 0)) return;
+  if (face % cp.stride || (L == kList && (D == 0 ? c.a : (D == 1 ? c.b : c.c)) == 0)) return;
   float wl[7], wr[7], other[7];
   traced_states<D, -1, RECON, ALLW, L>(w, A.W, A.B, c, A.dtdx, A.gam, other, wl);
   traced_states<D, 0, RECON, ALLW, L>(w, A.W, A.B, c, A.dtdx, A.gam, wr, other);
@@ -553,7 +553,7 @@ __device__ __forceinline__ void capture_sample(const Work& w, const FaceArgs<flo
   capture_face(cp, face, wl, wr, bn, f);
 }
 
-template <int RECON, bool ALLW, int STAGE, bool L>
+template <int RECON, bool ALLW, int STAGE, int L>
 __global__ void __launch_bounds__(kBlock) k_capture(Work w, FaceArgs<float> A, DtSrc dts, float inv_dx, Capture cp) {
   A.dtdx = float(get_dt(dts)) * inv_dx;
   A.hr = float(0.5 * get_dt(dts)) * inv_dx;

@@ -13,12 +13,12 @@
 //   E [3][N]  edge EMFs: Ex on the x-edge at the lower (y, z) corner of the
 //             cell, Ey at the lower (z, x) corner, Ez at the lower (x, y) corner.
 //
-// Work mapping: a launch covers a list of units.  With no group list the
-// single unit is the whole grid; with a list each unit is the box of
-// (edge + 2*halo)^3 cells around one patch group, with periodic wrap.  Each
-// thread owns one cell of one unit.  Block ids are remapped so that each of
-// the eight XCDs (which take blocks round-robin) works on a contiguous range
-// of cells, which keeps stencil neighbours in that XCD's L2.
+// Work mapping: a launch covers units of cells -- the z-planes of a whole grid, its
+// cells as one row, or the (edge + 2 halo)^3 item box of each listed group, with
+// periodic wrap -- cut into blocks, a thread to a cell (mhd_layout.hpp).  Block ids
+// are remapped so that each of the eight XCDs (which take blocks round-robin)
+// works on a contiguous range of cells, which keeps stencil neighbours in that
+// XCD's L2.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -33,57 +33,6 @@ namespace mhd {
 
 constexpr int kBlock = 256;      // threads per block of the fixed-shape kernels
 constexpr int kMaxBlock = 512;   // largest block of the step's stage kernels (tuned per context)
-
-// n / d for 0 <= n < 2^31 by a divisor fixed on the host (make_div): one high
-// multiply, an add and a shift instead of a division's reciprocal sequence.
-struct FastDiv {
-  unsigned m, a, s;
-};
-__host__ __device__ __forceinline__ unsigned fdiv(const FastDiv& f, unsigned n) {
-  return ((unsigned)(((unsigned long long)n * f.m) >> 32) + (n & f.a)) >> f.s;
-}
-// d = 1: n itself.  d > 1: s = ceil(log2 d) - 1, m = floor(2^(32 + s) / d) + 1
-// < 2^32; m d exceeds 2^(32 + s) by at most d <= 2^(s + 1), so the quotient is
-// exact for n < 2^31.
-inline FastDiv make_div(unsigned d) {
-  if (d <= 1) return FastDiv{0u, ~0u, 0u};
-  unsigned s = 0;
-  while ((2ull << s) < d) ++s;
-  return FastDiv{(unsigned)((1ull << (32 + s)) / d + 1), 0u, s};
-}
-
-struct Work {
-  int nx, ny, nz;
-  long long N;          // cells of the grid
-  const int* groups;    // nullptr: whole grid
-  int edge;             // group edge in cells
-  int halo;             // extra cells around each group
-  int box;              // edge + 2 * halo
-  long long items;      // work items (cells), upper bound when n_dev is set
-  const int* occ;       // group occupancy map (list mode), gnx*gny*gnz
-  int gnx, gny, gnz;    // groups per dimension
-  const int* n_dev;     // list mode: number of groups read from device memory, or nullptr
-  int gbase;            // list mode: first group of this launch (a batch of the list)
-  int gcount;           // list mode: groups of this launch at most
-  int oshift;           // list mode: group origins are divided by 2^oshift (coarse footprint)
-  // Stage scratch (W, F, E, Q, Bh, ...) addressing.  Whole grid: like the
-  // level (slot = cell index, stride N).  Group list: each group owns a
-  // contiguous box of sb^3 slots (its cells plus sb/2 - edge/2 ghost layers),
-  // group g at slot (g + 1) sb^3, with one unused box before and after so
-  // stencil reads past a box edge stay inside the allocation.
-  long long NS;         // component stride of the scratch arrays
-  int sb;               // scratch box edge (0: scratch addressed like the level)
-  int soff;             // offset of this stage's item box inside the scratch box
-  // Block decomposition of the stage kernels (Cell): units (the grid's
-  // z-planes, or the listed groups' item boxes) of `per` cells, each covered
-  // by `chunks` blocks.
-  int units;
-  unsigned per, chunks;
-  int rev;              // walk the blocks from the last to the first
-  FastDiv by_chunks, by_row, by_plane;   // of the block rank; of a cell index by its row and by its plane
-  FastDiv by_box;       // of an item index by a group's item box (cell_of)
-  FastDiv by_edge;      // of a cell coordinate by the group edge
-};
 
 __device__ __forceinline__ long long lin(const Work& w, int i, int j, int k) {
   return ((long long)k * w.ny + j) * w.nx + i;
@@ -171,7 +120,7 @@ __device__ __forceinline__ void cell_of(const Work& w, long long t, int& i, int&
 // its base address is scalar; a thread keeps one 32-bit byte offset inside it,
 // and a neighbour costs nothing (a group box: every neighbour at a constant
 // distance from the scalar base), one scalar address (a whole grid, along z)
-// or one add of a wrapped distance (along x and y).  The cell's coordinates
+// or one add of a wrapped distance (along x and y; kFlat: along z too).  The cell's coordinates
 // come from two multiplications.  (One 64-bit linear index per thread, split
 // by 64-bit divisions, and a 64-bit product per neighbour took 35-80 % of the
 // stages' vector instructions.)  In a step a plane or box is below 4 GiB: planes of
@@ -197,20 +146,20 @@ __device__ __forceinline__ void store_at(gchar* base, unsigned off, T v) {
   *(__attribute__((address_space(1))) T*)(base + off) = v;
 }
 
-template <typename T, bool L>
+template <typename T, int L>
 struct Cell {
   bool on;              // the thread has a cell
   int i, j, k;          // cell of the level
-  int a, b, c;          // position in the group's item box (L)
-  unsigned o;           // byte offset in the plane or scratch box
+  int a, b, c;          // position in the group's item box (kList)
+  unsigned o;           // byte offset in the plane or scratch box (kFlat: in the component)
   long long u;          // element offset of the plane or scratch box (uniform)
-  long long p;          // level index (L)
+  long long p;          // level index (kList)
 
   __device__ __forceinline__ Cell(const Work& w, unsigned rank) {
     const unsigned unit = fdiv(w.by_chunks, rank);
     const unsigned l = (rank - unit * w.chunks) * blockDim.x + threadIdx.x;
     on = l < w.per;
-    if (L && w.groups == nullptr) {   // a whole grid by level indices only (level_indexed)
+    if (L == kList && w.groups == nullptr) {   // a whole grid by level indices only (level_indexed)
       j = (int)(l / (unsigned)w.nx);
       i = (int)(l - (unsigned)j * (unsigned)w.nx);
       k = (int)unit;
@@ -218,7 +167,7 @@ struct Cell {
       u = 0;
       o = 0;
       p = lin(w, i, j, k);
-    } else if constexpr (L) {
+    } else if constexpr (L == kList) {
       const unsigned box = w.box;
       c = (int)fdiv(w.by_plane, l);
       const unsigned r = l - (unsigned)c * box * box;
@@ -234,11 +183,17 @@ struct Cell {
       o = (unsigned)(((c + w.soff) * w.sb + (b + w.soff)) * w.sb + (a + w.soff)) * (unsigned)sizeof(T);
       p = lin(w, i, j, k);
     } else {
-      j = (int)fdiv(w.by_row, l);
-      i = (int)(l - (unsigned)j * (unsigned)w.nx);
-      k = (int)unit;
+      unsigned r = l;
+      if constexpr (L == kFlat) {
+        k = (int)fdiv(w.by_plane, l);
+        r -= (unsigned)k * (unsigned)w.nx * (unsigned)w.ny;
+      } else {
+        k = (int)unit;
+      }
+      j = (int)fdiv(w.by_row, r);
+      i = (int)(r - (unsigned)j * (unsigned)w.nx);
       a = i; b = j; c = k;
-      u = (long long)k * w.per;
+      u = L == kFlat ? 0 : (long long)k * w.per;
       o = l * (unsigned)sizeof(T);
       p = 0;
     }
@@ -262,26 +217,32 @@ struct Cell {
   __device__ __forceinline__ int dy(const Work& w) const {
     return Y == 0 ? 0 : (Y < 0 ? (j < -Y ? Y + w.ny : Y) : (j >= w.ny - Y ? Y - w.ny : Y));
   }
+  // (kFlat) ... and Z along z
+  template <int Z>
+  __device__ __forceinline__ int dz(const Work& w) const {
+    return Z == 0 ? 0 : (Z < 0 ? (k < -Z ? Z + w.nz : Z) : (k >= w.nz - Z ? Z - w.nz : Z));
+  }
   // the scalar part of an address: component offset e, plane or box, and the
   // neighbour's share of it
   template <int X, int Y, int Z>
   __device__ __forceinline__ gchar* base(const Work& w, const T* arr, long long e) const {
-    if constexpr (L) e += u + X + (long long)Y * w.sb + (long long)Z * w.sb * w.sb;
-    else if constexpr (Z == 0) e += u;
+    if constexpr (L == kList) e += u + X + (long long)Y * w.sb + (long long)Z * w.sb * w.sb;
+    else if constexpr (Z == 0 || L == kFlat) e += u;
     else e += (long long)wrapc(k + Z, w.nz) * w.per;
     return scalar(arr + e);
   }
-  template <int X, int Y>
+  template <int X, int Y, int Z>
   __device__ __forceinline__ unsigned off(const Work& w) const {
-    unsigned v = o;
-    if constexpr (!L && X != 0) v += (unsigned)(dx<X>(w) * (int)sizeof(T));
-    if constexpr (!L && Y != 0) v += (unsigned)(dy<Y>(w) * w.nx * (int)sizeof(T));
+    unsigned v = o;   // distances wrap modulo 2^32, as the offset itself does
+    if constexpr (L != kList && X != 0) v += (unsigned)dx<X>(w) * (unsigned)sizeof(T);
+    if constexpr (L != kList && Y != 0) v += (unsigned)dy<Y>(w) * ((unsigned)w.nx * (unsigned)sizeof(T));
+    if constexpr (L == kFlat && Z != 0) v += (unsigned)dz<Z>(w) * ((unsigned)w.nx * (unsigned)w.ny * (unsigned)sizeof(T));
     return v;
   }
   // one scratch component (arr + e) at the cell (X, Y, Z) away
   template <int X, int Y, int Z>
   __device__ __forceinline__ T at(const Work& w, const T* arr, long long e) const {
-    return load_at<T>(base<X, Y, Z>(w, arr, e), off<X, Y>(w));
+    return load_at<T>(base<X, Y, Z>(w, arr, e), off<X, Y, Z>(w));
   }
   // ... n cells along direction D
   template <int D, int n>
@@ -292,34 +253,34 @@ struct Cell {
   __device__ __forceinline__ void put(const Work& w, T* arr, long long e, T v) const {
     store_at<T>(base<0, 0, 0>(w, arr, e), o, v);
   }
-  // level index of the cell n along D (L)
+  // level index of the cell n along D (kList)
   template <int D, int n>
   __device__ __forceinline__ long long level_index(const Work& w) const {
     if constexpr (n == 0) return p;
     else if constexpr (D == 0) return p + dx<n>(w);
     else if constexpr (D == 1) return p + (long long)dy<n>(w) * w.nx;
-    else return p + (long long)(n < 0 ? (k < -n ? n + w.nz : n) : (k >= w.nz - n ? n - w.nz : n)) * w.nx * w.ny;
+    else return p + (long long)dz<n>(w) * w.nx * w.ny;
   }
   // one component of the level itself, n cells along D
   template <int D, int n>
   __device__ __forceinline__ T level(const Work& w, const T* arr, long long e) const {
-    if constexpr (L) return arr[e + level_index<D, n>(w)];
+    if constexpr (L == kList) return arr[e + level_index<D, n>(w)];
     else return along<D, n>(w, arr, e);
   }
   __device__ __forceinline__ void put_level(const Work& w, T* arr, long long e, T v) const {
-    if constexpr (L) arr[e + p] = v;
+    if constexpr (L == kList) arr[e + p] = v;
     else put(w, arr, e, v);
   }
   // the cell's level index (both modes)
-  __device__ __forceinline__ long long index(const Work& w) const { return L ? p : u + o / sizeof(T); }
+  __device__ __forceinline__ long long index(const Work& w) const { return L == kList ? p : u + o / sizeof(T); }
 };
 
 // blocks of a stage: all units' chunks, the unit count of a group list read
 // from device memory where the list lives there
-template <bool L>
+template <int L>
 __device__ __forceinline__ unsigned stage_blocks(const Work& w) {
   int n = w.units;
-  if constexpr (L) {
+  if constexpr (L == kList) {
     if (w.n_dev) {
       const int m = *w.n_dev - w.gbase;
       n = m < 0 ? 0 : (m < n ? m : n);
@@ -415,7 +376,7 @@ __device__ __forceinline__ void prims_from(T d, T mx, T my, T mz, T e, double e6
 }
 
 // primitives of a stage kernel's cell
-template <typename T, bool MIX, bool L>
+template <typename T, bool MIX, int L>
 __device__ __forceinline__ void cell_prims(const Work& w, const T* __restrict__ U, const T* __restrict__ B,
                                            const Mix& mix, const Cell<T, L>& c, T gam, T out[8]) {
   const long long N = w.N;
@@ -467,7 +428,7 @@ __device__ __forceinline__ void block_max_atomic(double v, Cfl* cfl) {
 // the edge EMFs read instead of v and B, six, which each of the twelve edges
 // around a cell would multiply out again); optionally the CFL maximum signal
 // speed and the sticky non-physical flag.
-template <typename T, bool CFL, bool MIX, bool L>
+template <typename T, bool CFL, bool MIX, int L>
 __global__ void __launch_bounds__(kMaxBlock) k_prim(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
                                                  T* __restrict__ W, T* __restrict__ R, T gam, Cfl* cfl, int* flag) {
   double s = 0.0;
@@ -485,7 +446,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_prim(Work w, const T* __restrict_
 }
 
 // CFL maximum signal speed only
-template <typename T, bool MIX, bool L>
+template <typename T, bool MIX, int L>
 __global__ void __launch_bounds__(kBlock) k_cfl(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
                                                 T gam, Cfl* cfl, int* flag) {
   double s = 0.0;
@@ -520,7 +481,7 @@ __global__ void __launch_bounds__(kCflSlots) k_close_cfl(Cfl* cfl, double couran
 
 // ------------------------------------------------------------ fluxes
 // 1D primitives of the cell n along D of a stage kernel's cell, in D's frame
-template <typename T, int D, int n, bool L>
+template <typename T, int D, int n, int L>
 __device__ __forceinline__ void load_frame(const Work& w, const T* __restrict__ W, const Cell<T, L>& c, T q[7]) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
@@ -528,7 +489,7 @@ __device__ __forceinline__ void load_frame(const Work& w, const T* __restrict__ 
   for (int m = 0; m < 7; ++m) q[m] = c.template along<D, n>(w, W, comp[m] * w.NS);
 }
 
-template <typename T, int D, bool L>
+template <typename T, int D, int L>
 __device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, const Cell<T, L>& c0, const T f[7]) {
   const Cell<T, L> c = c0.fresh();
   constexpr int n = D, t1 = (D + 1) % 3, t2 = (D + 2) % 3;
@@ -547,7 +508,7 @@ __device__ __forceinline__ void store_flux(const Work& w, T* __restrict__ F, con
 // 2 = PPM (the limited parabolas' upper edge of the left cell and lower edge
 // of the right cell, no tracing: the VL predictor centres the data in time).
 // bn: the face's normal field.
-template <typename T, int D, int RECON, int SOLVER, bool L>
+template <typename T, int D, int RECON, int SOLVER, int L>
 __device__ __forceinline__ int face_flux(const Work& w, const T* __restrict__ W, T bn, T* __restrict__ F,
                                          const Cell<T, L>& c0, T gam) {
   const Cell<T, L> c = c0.fresh();
@@ -606,7 +567,7 @@ __device__ __forceinline__ void block_count_atomic(int v, unsigned long long* co
 // direction reads its component at the own cell only and then overwrites it with that
 // component of the cell's EMF of the half-step state, for the edge EMFs of the next
 // stage.
-template <typename T, int D, int RECON, int SOLVER, bool L>
+template <typename T, int D, int RECON, int SOLVER, int L>
 __device__ __forceinline__ int cell_flux(const Work& w, const T* __restrict__ W, const T* __restrict__ B, T* Bh,
                                          T* __restrict__ F, const Cell<T, L>& c, T gam) {
   const T bn = RECON == 0 ? c.template level<D, 0>(w, B, D * w.N) : c.here(w, (const T*)Bh, D * w.NS);
@@ -623,7 +584,7 @@ __device__ __forceinline__ int cell_flux(const Work& w, const T* __restrict__ W,
 }
 
 // VL flux stage: all three directions of a cell, or one per launch row.
-template <typename T, int RECON, int SOLVER, bool L>
+template <typename T, int RECON, int SOLVER, int L>
 __global__ void __launch_bounds__(kMaxBlock) k_flux(Work w, const T* __restrict__ W, const T* __restrict__ B, T* Bh,
                                                  T* __restrict__ F, T gam, unsigned long long* nfb) {
   int fb = 0;
@@ -661,7 +622,7 @@ __device__ __forceinline__ T edge_emf_core(T eb0, T eb1, T ec0, T ec1, T mb0, T 
 // each face value is extrapolated to the edge with the derivative taken in the
 // upwind cell (sign of the face mass flux), and the four extrapolations are
 // averaged.  R: the cells' own EMFs (cell_emf).
-template <typename T, int A, bool L>
+template <typename T, int A, int L>
 __device__ __forceinline__ T edge_emf(const Work& w, const T* __restrict__ F, const T* __restrict__ R,
                                       const Cell<T, L>& p) {
   constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
@@ -678,7 +639,7 @@ __device__ __forceinline__ T edge_emf(const Work& w, const T* __restrict__ F, co
   return edge_emf_core(eb0, eb1, ec0, ec1, mb0, mb1, mc0, mc1, r00, r10, r01, r11);
 }
 
-template <typename T, bool L>
+template <typename T, int L>
 __global__ void __launch_bounds__(kMaxBlock) k_emf(Work w, const T* __restrict__ F, const T* __restrict__ R,
                                                 T* __restrict__ E) {
   FOR_CELLS(T, L, w, c) {
@@ -740,7 +701,7 @@ __global__ void __launch_bounds__(TX * TY * TZ) k_emf_tiled(Work w, const T* __r
 // U - r div F (Eq. 10), differences applied in the order x, y, z, for the first
 // NM components.  In the mixed form the energy is updated in double from E64
 // (returned in e64).
-template <typename T, bool MIX, bool L, int NM = 5>
+template <typename T, bool MIX, int L, int NM = 5>
 __device__ __forceinline__ void cell_update(const Work& w, const T* U, const T* __restrict__ F, const Mix& mix,
                                             const Cell<T, L>& c, T r, T out[5], double& e64) {
   const long long N = w.N, NS = w.NS;
@@ -770,7 +731,7 @@ __device__ __forceinline__ void cell_update(const Work& w, const T* U, const T* 
 
 // CT update (Eq. 13) of the lower A-face of the cell (n = 0) or of the next
 // cell along A (n = 1)
-template <typename T, int A, int n, bool L>
+template <typename T, int A, int n, int L>
 __device__ __forceinline__ T face_update(const Work& w, const T* B, const T* __restrict__ E, const Cell<T, L>& p, T r) {
   constexpr int b = (A + 1) % 3, c = (A + 2) % 3;
   constexpr int X = A == 0 ? n : 0, Y = A == 1 ? n : 0, Z = A == 2 ? n : 0;
@@ -786,7 +747,7 @@ __device__ __forceinline__ T face_update(const Work& w, const T* B, const T* __r
 // CTU's later stages need of the half-step cell state only its EMF (step 7),
 // so there the energy is left out and three words R = -v x B replace Wh's
 // eight.
-template <typename T, bool MIX, bool CTU, bool L>
+template <typename T, bool MIX, bool CTU, int L>
 __global__ void __launch_bounds__(kMaxBlock) k_half(Work w, const T* __restrict__ U, const T* __restrict__ B, Mix mix,
                                                  const T* __restrict__ F, const T* __restrict__ E, DtSrc dts,
                                                  T inv_dx, T gam, T* __restrict__ Wh, T* __restrict__ Bh) {
@@ -826,7 +787,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_half(Work w, const T* __restrict_
 // the face it shares with the next cell when the next cell's group is not
 // listed (occupancy map), so every face of a listed group advances exactly
 // once and no face is read after another thread has written it.
-template <typename T, bool MIX, bool L>
+template <typename T, bool MIX, int L>
 __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, T* __restrict__ B, Mix mix,
                                                   const T* __restrict__ F, const T* __restrict__ E, DtSrc dts,
                                                   T inv_dx) {
@@ -841,7 +802,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
     bf[2] = face_update<T, 2, 0, L>(w, B, E, c, r);
     T ux = T(0), uy = T(0), uz = T(0);
     bool ex = false, ey = false, ez = false;
-    if constexpr (L) {
+    if constexpr (L == kList) {
       // the group's place in the occupancy map: its boundary cells look at the next one
       const auto listed = [&](int x, int y, int z) {
         return w.occ[((long long)wrapc(z, w.gnz) * w.gny + wrapc(y, w.gny)) * w.gnx + wrapc(x, w.gnx)] != 0;
@@ -862,7 +823,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_final(Work w, T* __restrict__ U, 
     if (MIX) mix.E64[c.index(w)] = e64;
 #pragma unroll
     for (int m = 0; m < 3; ++m) c.put_level(w, B, m * N, bf[m]);
-    if constexpr (L) {
+    if constexpr (L == kList) {
       if (ex) B[c.template level_index<0, 1>(w)] = ux;
       if (ey) B[N + c.template level_index<1, 1>(w)] = uy;
       if (ez) B[2 * N + c.template level_index<2, 1>(w)] = uz;
@@ -912,7 +873,7 @@ __device__ __forceinline__ void correct_state(const Transverse<T>& tr, T bn, T b
 }
 
 // Step 5's share of the cell n along D
-template <typename T, int D, int n, bool L>
+template <typename T, int D, int n, int L>
 __device__ __forceinline__ Transverse<T> transverse_of(const Work& w, const T* __restrict__ F1,
                                                        const T* __restrict__ E1, const Cell<T, L>& c, T hr) {
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
@@ -941,7 +902,7 @@ __device__ __forceinline__ Transverse<T> transverse_of(const Work& w, const T* _
 
 // the two states (wl, wr) of the cell's lower D-face corrected to the half-step
 // normal field bnh
-template <typename T, int D, bool L>
+template <typename T, int D, int L>
 __device__ __forceinline__ void correct_states(const Work& w, const T* __restrict__ F1, const T* __restrict__ E1,
                                                const T* __restrict__ B, T bnh, const Cell<T, L>& c, T hr, T gam,
                                                T wl[7], T wr[7]) {
@@ -1041,7 +1002,7 @@ __device__ __forceinline__ void block_partials(double v[NQ], double* part, int s
 }
 
 // discrete divergence (Eq. 16): partial sums of |div B| and partial maxima
-template <typename T, bool L>
+template <typename T, int L>
 __global__ void __launch_bounds__(kBlock) k_divb(Work w, const T* __restrict__ B, double inv_dx, double* part) {
   double a = 0.0, amax = 0.0;
   const long long N = w.N;
@@ -1067,7 +1028,7 @@ __global__ void __launch_bounds__(kBlock) k_divb(Work w, const T* __restrict__ B
 }
 
 // volume totals: mass, Mx, My, Mz, e, magnetic energy, kinetic energy
-template <typename T, bool L>
+template <typename T, int L>
 __global__ void __launch_bounds__(kBlock) k_sums(Work w, const T* __restrict__ U, const T* __restrict__ B,
                                                  const double* __restrict__ E64, double* part) {
   double v[7] = {0, 0, 0, 0, 0, 0, 0};

@@ -41,3 +41,44 @@ int main() {
         if (t0 - 1 + h < n) CHECK(x == (t0 - 1 + h + n) %% n, "n %%d tile at %%d column %%d: %%d", n, t0, h, x);
       }
 }""" % (tile, tile))
+
+
+def test_stage_blocks_fill_their_lanes(tmp_path):
+    # whole grids, in the form the step picks: at least three quarters of the lanes
+    # launched have a cell wherever the grid itself fills a few blocks
+    run_host(tmp_path, r"""
+int main() {
+  const int sizes[] = {4, 5, 6, 7, 8, 9, 12, 16, 17, 24, 33, 61, 64, 97, 128, 200, 512, 4096, 65536};
+  for (int threads = 64; threads <= 512; threads += 64)
+    for (int nx : sizes) for (int ny : sizes) for (int nz : sizes) {
+      const long long n = (long long)nx * ny * nz;
+      if (n > 1LL << 28 || n < 8 * threads) continue;
+      Work w{};
+      w.nx = nx; w.ny = ny; w.nz = nz; w.N = w.items = n;
+      const int mode = flat_pays(nx, ny, nz, 4, threads) ? kFlat : kWhole;
+      const long long lanes = decompose(w, mode, threads) * threads;
+      CHECK(lanes >= n && 3 * lanes <= 4 * n, "%d x %d x %d, blocks of %d: %lld lanes for %lld cells", nx, ny, nz, threads, lanes, n);
+    }
+}""")
+
+
+def test_cells_of_the_flat_form(tmp_path):
+    # the splitting of a cell number by multiplications, for every cell of odd grids and
+    # for the last cells of the largest component 32-bit offsets reach
+    run_host(tmp_path, r"""
+static void check(int nx, int ny, int nz, unsigned from) {
+  Work w{};
+  w.nx = nx; w.ny = ny; w.nz = nz; w.N = w.items = (long long)nx * ny * nz;
+  decompose(w, kFlat, 256);
+  CHECK(w.per == (unsigned)w.N && w.units == 1 && w.chunks == (w.N + 255) / 256, "decomposition");
+  for (unsigned l = from; l < w.per; ++l) {
+    const unsigned k = fdiv(w.by_plane, l), r = l - k * (unsigned)nx * (unsigned)ny, j = fdiv(w.by_row, r);
+    CHECK(k == l / ((unsigned)nx * ny) && j == r / (unsigned)nx, "%d x %d x %d cell %u", nx, ny, nz, l);
+  }
+}
+int main() {
+  for (int nx = 4; nx < 40; nx += 3) for (int ny = 4; ny < 40; ny += 5) check(nx, ny, 41, 0);
+  check(4, 4, 1 << 26, (1u << 30) - 100000);
+  check(5, 7, ((1 << 30) - 1) / 35, 35u * (((1u << 30) - 1) / 35) - 100000);
+  check(1 << 13, 1 << 13, 16, (1u << 30) - 100000);
+}""")
