@@ -201,7 +201,7 @@ Work make_work(const mhd_level* lv, int lo, int hi) {
   w.units = 0;
   w.rev = 0;
   w.per = w.chunks = 0;
-  w.by_chunks = w.by_row = w.by_plane = w.by_box = FastDiv{0, 0, 0};
+  w.by_chunks = w.by_row = w.by_plane = w.by_box = FastDiv{0, 0};
   w.by_edge = make_div((unsigned)w.edge);
   return w;
 }
@@ -296,69 +296,6 @@ unsigned item_blocks(Work& w) {
 
 // grid of a stage kernel (Cell) addressed in `mode`, in blocks of `threads`
 unsigned stage_grid(Work& w, int mode, int threads) { return capped(decompose(w, mode, threads)); }
-
-// Decomposition of the CTU face kernels (k_ctu_faces): slabs of planes of a whole
-// grid, the item boxes of a group list.  A march repeats the trace of one cell
-// before its first face, so long marches save work and short ones give small
-// grids enough waves.
-// Whole grids below kTileLimit cells go in tiles of `cols` columns: they trace less per
-// face than short marches, which read along whole rows.  Whole step (us), marches /
-// tiles, CTU + PPM + HLLD unless stated: double 24^3 53 / 44, 48^3 101 / 82, 64^3 172 /
-// 147, 80^3 289 / 268, 96^3 486 / 509; float 24^3 35 / 34, 48^3 54 / 49, 80^3 130 / 119,
-// 96^3 188 / 186, 128^3 464 / 525; float Roe (PLM) 64^3 107 / 98, 80^3 179 / 165, 96^3
-// 249 / 260; learned flux 32^3 57 / 51, 64^3 172 / 159, 128^3 1021 / 1079
-constexpr long long kTileLimit = 9 << 16;
-FaceGeo face_geometry(const Work& w, int cols) {
-  FaceGeo g;
-  g.tz = g.ty = 0;
-  const auto cut = [](int n, int len) { return (n + len - 1) / len; };
-  if (w.groups) {
-    // whole float step of 5 / 50 / 191 / 400 groups: 54 / 152 / 531 / 1098 us
-    // with marches of 2 cells, 64 / 152 / 504 / 1029 with 5, 80 / 167 / 510 /
-    // 1017 with 10
-    const long long n = 2 + (w.items >> 18);
-    const int len = n > 10 ? 10 : (int)n;
-    g.bx = g.by = g.bz = w.box;
-    g.units = (int)(w.items / ((long long)w.box * w.box * w.box));
-    g.cz = g.cy = len;
-    g.lx = w.box;
-  } else {
-    // the longer a march the less of its trace is repeated, the shorter the more
-    // waves a small grid has.  Whole step (us), CTU + PPM + HLLD, marches of 2 / 4 / 8
-    // cells: float 128^3 500 / 476 / 474; double 96^3 515 / 490 / 514
-    const int len = w.N < 3 << 19 ? 4 : 8;
-    g.bx = w.nx;
-    g.by = w.ny;
-    g.bz = g.cz = g.cy = len;
-    g.units = cut(w.nz, g.bz);
-    g.lx = w.nx + 1;
-    if (w.N < kTileLimit) {
-      g.bz = w.nz;
-      g.units = 1;
-      g.tz = (unsigned)cut(w.nx * w.ny, cols);
-      g.ty = (unsigned)cut(w.nx * w.nz, cols);
-      g.by_ly = make_div((unsigned)w.ny + 1);
-      g.by_lz = make_div((unsigned)w.nz + 1);
-    }
-  }
-  const auto waves = [](long long n, int k) { return (unsigned)((n + k - 1) / k); };
-  g.w2c = waves((long long)g.bx * g.by, 64);
-  g.w2 = g.w2c * (unsigned)cut(g.bz, g.cz);
-  g.w1c = waves((long long)g.bx * g.bz, 64);
-  g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
-  if (g.tz) {
-    g.w2 = waves((long long)g.tz * (g.bz + 1) - 1, 64 / cols - 1);
-    g.w1 = waves((long long)g.ty * (g.by + 1) - 1, 64 / cols - 1);
-  }
-  g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
-  g.by_per = make_div(g.per);
-  g.by_w2c = make_div(g.w2c);
-  g.by_w1c = make_div(g.w1c);
-  g.by_bx = make_div((unsigned)g.bx);
-  g.by_by = make_div((unsigned)g.by);
-  g.by_lx = make_div((unsigned)g.lx);
-  return g;
-}
 
 // Batches of a group list: the middle stages (between the primitive pass,
 // which also reduces the CFL maximum over the whole list, and the final
@@ -503,7 +440,7 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
 template <typename T, int R, bool ALLW, int S, int STAGE, int L>
 void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_dx) {
   const FaceGeo g = face_geometry(w, kTileCols<T, S>);
-  unsigned nb = capped(((long long)g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
+  unsigned nb = capped((g.units * g.per + kBlock / 64 - 1) / (kBlock / 64));
   if constexpr (L != kList) {
     if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, false, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
     else k_ctu_faces<T, R, ALLW, S, STAGE, false, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);

@@ -20,29 +20,17 @@
 // the network runs on the wave's 64 faces where a solver would run on each
 // lane's.
 //
-// The work is cut into units -- slabs of z-planes of a whole grid, or listed
-// groups' item boxes -- and a unit into wave tasks: first the z-marches, then
-// the y-marches, then the (short) x-rows, so that the short ones fill the end.
+// The work is cut into slabs -- rows and planes of a whole grid or of a listed
+// group's item box -- and a slab into wave tasks: first the z-marches, then the
+// y-marches, then the (short) x-rows, so that the short ones fill the end
+// (face_geometry).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 
 #include "mhd_kernels.hpp"
 
 namespace mhd {
-
-// One launch's decomposition (face_geometry on the host).
-struct FaceGeo {
-  int bx, by, bz;          // cells of a unit: the grid's nx, ny and a slab's planes, or a group's item box
-  int units;
-  int cz, cy;              // cells of a z-march and of a y-march
-  int lx;                  // positions of a row in the x-rows: one more than its cells on a periodic grid
-  unsigned w2, w2c;        // waves of a unit's z-marches, and of one chunk of them
-  unsigned w1, w1c;        // ... y-marches
-  unsigned per;            // waves of a unit
-  FastDiv by_per, by_w2c, by_w1c, by_bx, by_by, by_lx;
-  unsigned tz, ty;         // z and y in tiles: tiles side by side (0: in marches)
-  FastDiv by_ly, by_lz;
-};
 
 // Whether a march keeps what it carries from cell to cell -- slopes, interface
 // values, the state below the next face: 21 words -- in LDS, each lane in slots of
@@ -331,11 +319,11 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
   constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
   const long long NS = w.NS;
   const int at = D == 0 ? ln.i : D == 1 ? ln.j : ln.k, size = D == 0 ? w.nx : D == 1 ? w.ny : w.nz;
-  const int stride = (D == 0 ? 1 : D == 1 ? w.nx : w.nx * w.ny) * (int)sizeof(T);
+  const unsigned stride = (D == 0 ? 1u : D == 1 ? (unsigned)w.nx : (unsigned)w.nx * (unsigned)w.ny) * (unsigned)sizeof(T);
   const auto off = [&](int x, unsigned o) {   // offset of the cell x along D
     if (L) return o;
     const int i = at + x;
-    return o + (unsigned)((i < 0 ? x + size : (i >= size ? x - size : x)) * stride);
+    return o + (unsigned)(i < 0 ? x + size : (i >= size ? x - size : x)) * stride;
   };
   const auto value = [&](const T* arr, long long e, int x, unsigned o) {
     return load_at<T>(scalar(arr + (e + ln.u + (L ? x : 0))), off(x, o));
@@ -372,6 +360,25 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
                                  L ? ln.p : (long long)(ln.o / sizeof(T)));
 }
 
+// The geometry read where it is used, from the kernel's argument segment (arguments lie
+// in it as in a struct), of which k_ctu_faces keeps two dozen words: as an ordinary
+// argument they are all loaded at its start and, over a hundred scalar registers, parked
+// in vector lanes and fetched from there in the marches (16 of the 519 vector
+// instructions a cell in float, steps 1-2; two so).
+struct FaceKernelArgs {
+  Work w;
+  FaceGeo g;
+};
+typedef __attribute__((address_space(4))) const FaceGeo ConstGeo;
+__device__ __forceinline__ const ConstGeo& face_geo() {
+  auto* p = (__attribute__((address_space(4))) const char*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const ConstGeo*)(p + offsetof(FaceKernelArgs, g));
+}
+__device__ __forceinline__ unsigned fdiv(__attribute__((address_space(4))) const FastDiv& f, unsigned n) {
+  return fdiv(FastDiv{f.m, f.s}, n);
+}
+
 // ALLW: trace waves moving away from an edge too (HLL-family solvers).  The
 // double form is held to 168 registers (three waves per SIMD; it needs 173), with
 // Roe, which would spill 90 words there, to 256.
@@ -382,18 +389,19 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
 // cell of scratch less.
 template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L, bool TILES>
 __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1)
-    k_ctu_faces(Work w, FaceGeo g, FaceArgs<T> A, DtSrc dts, T inv_dx, unsigned long long* nfb) {
+    k_ctu_faces(Work w, FaceGeo geo, FaceArgs<T> A, DtSrc dts, T inv_dx, unsigned long long* nfb) {
   A.dtdx = T(get_dt(dts)) * inv_dx;
   A.hr = T(0.5 * get_dt(dts)) * inv_dx;
   const unsigned lane = threadIdx.x & 63;
-  int units = g.units;
+  unsigned units = (unsigned)geo.units;
   if constexpr (L) {
     if (w.n_dev) {
       const int m = *w.n_dev - w.gbase;
-      units = m < 0 ? 0 : (m < units ? m : units);
+      const long long listed = (long long)m * geo.slabs;
+      units = m < 0 ? 0u : listed < (long long)units ? (unsigned)listed : units;
     }
   }
-  const unsigned waves = (unsigned)units * g.per, in_block = blockDim.x >> 6;
+  const unsigned waves = units * geo.per, in_block = blockDim.x >> 6;
   const unsigned blocks = (waves + in_block - 1) / in_block;
   // byte distance of the upper neighbour of coordinate i of n (stride in cells)
   const auto up = [](int i, int n, unsigned stride) {
@@ -410,19 +418,24 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
   T* park = parks + (threadIdx.x >> 6) * (64 * 21) + lane;
   int fb = 0;
   for (unsigned r = block_rank(); r < blocks; r += gridDim.x) {
+    const ConstGeo& g = face_geo();
     const unsigned rank = w.rev ? blocks - 1 - r : r;
     const unsigned wave = __builtin_amdgcn_readfirstlane(rank * in_block + (threadIdx.x >> 6));
     if (wave >= waves) continue;
     const unsigned unit = fdiv(g.by_per, wave);
     unsigned t = wave - unit * g.per;
-    const int z0 = L ? 0 : (int)unit * g.bz;                       // first plane of a slab
-    const int bz = L ? g.bz : (w.nz - z0 < g.bz ? w.nz - z0 : g.bz);
+    const unsigned group = L ? fdiv(g.by_slabs, unit) : 0u, slab = unit - group * g.slabs;
+    const unsigned row0 = L ? slab : fdiv(g.by_ux, slab), sz = fdiv(g.by_uy, row0);
+    // the slab's first cell
+    const int x0 = L ? 0 : (int)(slab - row0 * (unsigned)g.ux) * g.bx;
+    const int y0 = (int)(row0 - sz * (unsigned)g.uy) * g.by, z0 = (int)sz * g.bz;
+    const int bz = min((int)g.bz, (L ? w.box : w.nz) - z0), by = min((int)g.by, (L ? w.box : w.ny) - y0);
     int ox = 0, oy = 0, oz = 0;
     long long box = 0;
     if constexpr (L) {
-      const int* og = w.groups + 3LL * (w.gbase + unit);
+      const int* og = w.groups + 3LL * (w.gbase + group);
       ox = og[0] - w.halo; oy = og[1] - w.halo; oz = og[2] - w.halo;
-      box = (w.gbase + (int)unit + 1LL) * w.sb * w.sb * w.sb;
+      box = (w.gbase + (int)group + 1LL) * w.sb * w.sb * w.sb;
     }
     const auto place = [&](auto& ln, int x, int y, int z, bool fx, bool fy, bool fz) {
       // (x, y, z): position in the unit; f*: the coordinate counts toward the offsets
@@ -451,9 +464,11 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
         const bool in = l < (zdir ? g.tz : g.ty) * len;
         const unsigned c = in ? l : 0, tile = zdir ? fdiv(g.by_lz, c) : fdiv(g.by_ly, c), q = c - tile * len;
         const unsigned col = tile * cols + c0;
-        const bool on = in && col < (unsigned)g.bx * (unsigned)(zdir ? g.by : g.bz);
+        const bool on = in && col < (unsigned)g.bx * (unsigned)(zdir ? g.by : bz) && (!zdir || q <= (unsigned)bz);
         const unsigned at = on ? col : 0, other = fdiv(g.by_bx, at);
-        const int x = (int)(at - other * (unsigned)g.bx), m = q == 0 ? (int)len - 2 : (int)q - 1;
+        const int x = (int)(at - other * (unsigned)g.bx);
+        // the line's cell, wrapped where a line starts before the grid (lanes without one: the first)
+        const int m = !on ? 0 : zdir ? wrapc(z0 + (int)q - 1, w.nz) : wrapc((int)q - 1, w.ny);
         const bool emit = on && cell > 0 && q > 0;
         if (zdir) {
           Line<T, 2, L> ln;
@@ -462,50 +477,55 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
           fb += row_faces<T, 2, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dy, o1 + dy, emit, sh);
         } else {
           Line<T, 1, L> ln;
-          place(ln, x, m, (int)other, true, true, true);
+          place(ln, x, m, z0 + (int)other, true, true, true);
           const unsigned o1 = ln.o + up(ln.k, w.nz, plane), dx = up(ln.i, w.nx, 1);
           fb += row_faces<T, 1, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dx, o1 + dx, emit, sh);
         }
         continue;
       }
     } else if (t < g.w2) {
-      const unsigned chunk = fdiv(g.by_w2c, t), l = (t - chunk * g.w2c) * 64 + lane, n = (unsigned)(g.bx * g.by);
-      const bool on = l < n;
-      const unsigned c = on ? l : 0, y = fdiv(g.by_bx, c), x = c - y * (unsigned)g.bx;
-      // marches of a group's box start at its first cell, the others one cell early
+      const unsigned chunk = fdiv(g.by_w2c, t), l = (t - chunk * g.w2c) * 64 + lane, n = (unsigned)(g.bx * by);
+      const unsigned y = fdiv(g.by_bx, l), xs = l - y * (unsigned)g.bx;
+      const bool on = l < n && (L || x0 + (int)xs < w.nx);
+      const int x = x0 + (on ? (int)xs : 0), line = y0 + (on ? (int)y : 0);
+      // marches start one cell early, at a group box's first cell there
       const int za = (int)chunk * g.cz, zb = za + g.cz < bz ? za + g.cz : bz;
+      if (za >= bz || (t - chunk * g.w2c) * 64 >= n) continue;   // a remainder's
       Line<T, 2, L> ln;
-      place(ln, (int)x, (int)y, 0, true, true, false);
+      place(ln, x, line, 0, true, true, false);
       ln.g0 = oz;
       const unsigned o1 = L ? ln.o : ln.o + up(ln.i, w.nx, 1), dy = L ? 0u : up(ln.j, w.ny, (unsigned)w.nx);
       fb += march_line<T, 2, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dy, o1 + dy, on,
-                                                            z0 + za - (L && za == 0 ? 0 : 1), z0 + zb, park, sh);
+                                                            z0 + za - (L && z0 + za == 0 ? 0 : 1), z0 + zb, park, sh);
       continue;
     }
     t -= g.w2;
     if (!TILES && t < g.w1) {
       const unsigned chunk = fdiv(g.by_w1c, t), l = (t - chunk * g.w1c) * 64 + lane, n = (unsigned)(g.bx * bz);
-      const bool on = l < n;
-      const unsigned c = on ? l : 0, z = fdiv(g.by_bx, c), x = c - z * (unsigned)g.bx;
-      const int y0 = (int)chunk * g.cy, y1 = y0 + g.cy < g.by ? y0 + g.cy : g.by;
+      const unsigned z = fdiv(g.by_bx, l), xs = l - z * (unsigned)g.bx;
+      const bool on = l < n && (L || x0 + (int)xs < w.nx);
+      const int x = x0 + (on ? (int)xs : 0), line = z0 + (on ? (int)z : 0);
+      const int ya = (int)chunk * g.cy, yb = ya + g.cy < by ? ya + g.cy : by;
+      if (ya >= by || (t - chunk * g.w1c) * 64 >= n) continue;
       Line<T, 1, L> ln;
-      place(ln, (int)x, 0, z0 + (int)z, true, false, true);
+      place(ln, x, 0, line, true, false, true);
       ln.g0 = oy;
       const unsigned o1 = L ? ln.o : ln.o + up(ln.k, w.nz, plane), dx = L ? 0u : up(ln.i, w.nx, 1);
       fb += march_line<T, 1, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dx, o1 + dx, on,
-                                                            y0 - (L && y0 == 0 ? 0 : 1), y1, park, sh);
+                                                            y0 + ya - (L && y0 + ya == 0 ? 0 : 1), y0 + yb, park, sh);
       continue;
     }
     t -= g.w1;
     {
       // position of the rows, one lane shared with the wave before
       const unsigned l = t * 63 + lane, n = (unsigned)g.lx * (unsigned)g.by * (unsigned)bz;
-      const bool on = l < n;
-      const unsigned c = on ? l : 0, row = fdiv(g.by_lx, c), q = c - row * (unsigned)g.lx;
-      const unsigned z = fdiv(g.by_by, row), y = row - z * (unsigned)g.by;
-      const int x = L ? (int)q : (q == 0 ? w.nx - 1 : (int)q - 1);
+      const unsigned c = l < n ? l : 0, row = fdiv(g.by_lx, c), q = c - row * (unsigned)g.lx;
+      const unsigned z = fdiv(g.by_by, row), r = row - z * (unsigned)g.by;
+      const bool on = l < n && r < (unsigned)by && (L || x0 + (int)q <= w.nx);
+      const int y = y0 + (r < (unsigned)by ? (int)r : 0);
+      const int x = L ? (int)q : wrapc(x0 + (int)q - 1, w.nx);
       Line<T, 0, L> ln;
-      place(ln, x, (int)y, z0 + (int)z, true, true, true);
+      place(ln, x, y, z0 + (int)z, true, true, true);
       const unsigned o1 = L ? ln.o : ln.o + up(ln.j, w.ny, (unsigned)w.nx), dz = L ? 0u : up(ln.k, w.nz, plane);
       fb += row_faces<T, 0, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dz, o1 + dz, on && lane > 0 && q > 0, sh);
     }

@@ -6,22 +6,20 @@
 
 namespace mhd {
 
-// n / d for 0 <= n < 2^31 by a divisor fixed on the host (make_div): one high
-// multiply, an add and a shift instead of a division's reciprocal sequence.
+// n / d for 0 <= n < 2^31 by a divisor fixed on the host (make_div): a shift, one high
+// multiply and a shift instead of a division's reciprocal sequence.
 struct FastDiv {
-  unsigned m, a, s;
+  unsigned m, s;
 };
 __host__ __device__ __forceinline__ unsigned fdiv(const FastDiv& f, unsigned n) {
-  return ((unsigned)(((unsigned long long)n * f.m) >> 32) + (n & f.a)) >> f.s;
+  return (unsigned)(((unsigned long long)(2u * n) * f.m) >> 32) >> f.s;
 }
-// d = 1: n itself.  d > 1: s = ceil(log2 d) - 1, m = floor(2^(32 + s) / d) + 1
-// < 2^32; m d exceeds 2^(32 + s) by at most d <= 2^(s + 1), so the quotient is
-// exact for n < 2^31.
+// s = ceil(log2 d), m = floor(2^(31 + s) / d) + 1 < 2^32; m d exceeds 2^(31 + s) by at
+// most d <= 2^s, so the quotient is exact for n < 2^31.
 inline FastDiv make_div(unsigned d) {
-  if (d <= 1) return FastDiv{0u, ~0u, 0u};
-  unsigned s = 0;
-  while ((2ull << s) < d) ++s;
-  return FastDiv{(unsigned)((1ull << (32 + s)) / d + 1), 0u, s};
+  if (d <= 1) return FastDiv{(1u << 31) + 1u, 0u};
+  const unsigned s = 32u - (unsigned)__builtin_clz(d - 1);
+  return FastDiv{(unsigned)((1ull << (31 + s)) / d + 1), s};
 }
 
 struct Work {
@@ -96,6 +94,120 @@ inline long long decompose(Work& w, int mode, int threads) {
   w.chunks = (w.per + (unsigned)threads - 1) / (unsigned)threads;
   w.by_chunks = make_div(w.chunks);
   return (long long)w.units * w.chunks;
+}
+
+// Decomposition of the CTU face kernels (k_ctu_faces): slabs of rows and planes of a
+// whole grid or of a group's item box, each cut into wave tasks.
+struct FaceGeo {
+  int bx, by, bz;          // cells of a slab
+  int ux, uy;              // slabs side by side along x and y
+  unsigned slabs;          // of a box (of the grid)
+  long long units;         // slabs of the launch
+  int cz, cy;              // cells of a z-march and of a y-march
+  int lx;                  // positions of a row in the x-rows: one more than its cells on a periodic grid
+  unsigned w2, w2c;        // waves of a slab's z-marches, and of one chunk of them
+  unsigned w1, w1c;        // ... y-marches
+  unsigned per;            // waves of a slab
+  FastDiv by_per, by_slabs, by_ux, by_uy, by_w2c, by_w1c, by_bx, by_by, by_lx;
+  unsigned tz, ty;         // z and y in tiles: tiles side by side (0: in marches)
+  FastDiv by_ly, by_lz;
+};
+
+// A march repeats the trace of one cell before its first face, so long marches save
+// work and short ones give small grids enough waves.
+//
+// Whole grids below kTileLimit cells go in tiles of `cols` columns: they trace less per
+// face than short marches, which read along whole rows.  Whole step (us), marches /
+// tiles, CTU + PPM + HLLD unless stated: double 24^3 53 / 44, 48^3 101 / 82, 64^3 172 /
+// 147, 80^3 289 / 268, 96^3 486 / 509; float 24^3 35 / 34, 48^3 54 / 49, 80^3 130 / 119,
+// 96^3 188 / 186, 128^3 464 / 525; float Roe (PLM) 64^3 107 / 98, 80^3 179 / 165, 96^3
+// 249 / 260; learned flux 32^3 57 / 51, 64^3 172 / 159, 128^3 1021 / 1079.
+// So do grids whose planes are less than two waves of z-marches, or where not even all
+// planes fill the lanes of a y-march (65536 x 4 x 4, z first,
+// double 998 / 646; 65536 x 8 x 8 2776 / 2603; 4096 x 16 x 17 667 / 681).
+//
+// A slab's three directions read the same cells one after the other: a slab as large as
+// the grid leaves the caches in between.  CTU + PPM + HLLD (Roe), double, with slabs of
+// a march's planes only / as below: 4 x 512 x 512 881 / 590 (1353 / 831), 8 x 512 x 512
+// 2314 / 1164 (3743 / 1635), 4 x 1024 x 1024 5458 / 2344 (8794 / 3285), 8 x 8 x 65536
+// 4778 / 2319 (7683 / 3300); tiles of 65536 x 4 x 4 680 / 646, of 20000 x 10 x 10 1339 /
+// 1232; lists of one box of 64^3 270 / 218 (391 / 295), of 128^3 3056 / 1477.
+constexpr long long kTileLimit = 9 << 16;
+constexpr long long kTilePlane = 128;
+constexpr long long kTileSlab = 1 << 16;   // cells
+constexpr long long kListSlab = 1 << 15;
+
+inline FaceGeo face_geometry(const Work& w, int cols) {
+  FaceGeo g;
+  g.tz = g.ty = 0;
+  g.ux = g.uy = 1;
+  const auto cut = [](long long n, long long len) { return (int)((n + len - 1) / len); };
+  const bool list = w.groups != nullptr;
+  const int nx = list ? w.box : w.nx, ny = list ? w.box : w.ny, nz = list ? w.box : w.nz;
+  const long long plane = (long long)nx * ny, boxes = list ? w.items / (plane * nz) : 1;
+  // lists: whole float step of 5 / 50 / 191 / 400 groups: 54 / 152 / 531 / 1098 us
+  // with marches of 2 cells, 64 / 152 / 504 / 1029 with 5, 80 / 167 / 510 / 1017 with 10;
+  // 1 / 4 / 8 groups in double 54 / 65 / 80 with 1, 63 / 70 / 81 with 2.
+  // Whole grids, CTU + PPM + HLLD, marches of 2 / 4 / 8 cells: float 128^3 500 / 476 /
+  // 474; double 96^3 515 / 490 / 514
+  const long long n = w.items < 1 << 16 ? 1 : 2 + (w.items >> 18);
+  const int len = list ? (n > 10 ? 10 : (int)n) : w.N < 3 << 19 ? 4 : 8;
+  g.bx = nx;
+  g.by = ny;
+  g.bz = nz;
+  g.cz = g.cy = len;
+  if (list) {
+    const int parts = cut(plane * nz, kListSlab);
+    if (parts > 1) g.bz = len * cut(nz, (long long)len * parts);
+    if (g.bz > nz) g.bz = nz;
+  } else if (w.N < kTileLimit || plane < kTilePlane || (long long)nx * nz < 64) {
+    if (plane < kTilePlane && w.N >= 2 * kTileSlab) g.bz = (int)(kTileSlab / plane);
+    g.tz = (unsigned)cut(plane, cols);
+    g.ty = (unsigned)cut((long long)nx * g.bz, cols);
+    g.by_ly = make_div((unsigned)ny + 1);
+    g.by_lz = make_div((unsigned)g.bz + 1);
+  } else {
+    // planes of a march's length, of grids of few planes in equal parts; of several
+    // marches where rows are short, so that the lanes of the y-marches (a row times the
+    // planes) are four fifths in use
+    if (nz < 4 * len) g.cz = cut(nz, nz < len ? 1 : (nz + len / 2) / len);
+    g.bz = g.cz;
+    while (g.bz < 8 * g.cz && 5LL * nx * g.bz < 4 * 64LL * cut((long long)nx * g.bz, 64)) g.bz *= 2;
+    const int parts = nz < g.bz ? 1 : (nz + g.bz / 2) / g.bz;   // alike
+    g.bz = g.cz * cut(nz, (long long)g.cz * parts);
+    if (g.bz > nz) g.bz = nz;
+    // where that leaves fewer than 16 slabs, parts of the planes and, last, of the rows
+    const int sz = cut(nz, g.bz);
+    if (sz < 16) g.by = len * cut(ny, (long long)len * cut(16, sz));
+    if (g.by > ny) g.by = ny;
+    g.uy = cut(ny, g.by);
+    if (sz * g.uy < 16) g.bx = 64 * cut(nx, 64LL * cut(16, (long long)sz * g.uy));
+    if (g.bx > nx) g.bx = nx;
+    g.ux = cut(nx, g.bx);
+  }
+  g.lx = list ? nx : g.bx + 1;
+  g.slabs = (unsigned)(g.ux * g.uy * cut(nz, g.bz));
+  g.units = boxes * g.slabs;
+  const auto waves = [](long long n, int k) { return (unsigned)((n + k - 1) / k); };
+  g.w2c = waves((long long)g.bx * g.by, 64);
+  g.w2 = g.w2c * (unsigned)cut(g.bz, g.cz);
+  g.w1c = waves((long long)g.bx * g.bz, 64);
+  g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
+  if (g.tz) {
+    g.w2 = waves((long long)g.tz * (g.bz + 1) - 1, 64 / cols - 1);
+    g.w1 = waves((long long)g.ty * (g.by + 1) - 1, 64 / cols - 1);
+  }
+  g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
+  g.by_per = make_div(g.per);
+  g.by_slabs = make_div(g.slabs);
+  g.by_ux = make_div((unsigned)g.ux);
+  g.by_uy = make_div((unsigned)g.uy);
+  g.by_w2c = make_div(g.w2c);
+  g.by_w1c = make_div(g.w1c);
+  g.by_bx = make_div((unsigned)g.bx);
+  g.by_by = make_div((unsigned)g.by);
+  g.by_lx = make_div((unsigned)g.lx);
+  return g;
 }
 
 // a coordinate at most one period outside 0..n-1, wrapped into it

@@ -1,4 +1,4 @@
-"""Whole grids narrower than the EMF tiles (16 cells along x in double): the cells past
+"""Thin grids.  Whole grids narrower than the EMF tiles (16 cells along x in double): the cells past
 the grid repeat its last column, and the arrays here end on a page boundary (4 x 4 x 32
 cells of three doubles), where a column past them would not be mapped.
 
@@ -33,3 +33,68 @@ def test_narrow_grid_step(shape, scheme, recon, solver):
         got = got.cpu().numpy()
         for m in range(len(want)):
             assert np.abs(got[m] - want[m]).max() <= 1e-12 * np.abs(want[m]).max()
+
+
+# the face kernels' slabs: parts of planes (few planes), of rows (few planes of few rows),
+# several marches of planes (short rows), tiles of small planes in slabs, the last slab of
+# each kind a remainder; and the stage kernels' flat form (planes that fill blocks badly)
+SLABS = [(4, 404, 373), (5, 347, 353), (9, 261, 257), (4, 9, 16500), (8, 8, 9301), (173, 683, 5), (113, 331, 17),
+         (9001, 8, 9), (16411, 6, 6), (2311, 16, 17), (1021, 11, 9), (33, 4099, 5), (4, 36901, 5)]
+
+
+@pytest.mark.parametrize("shape", SLABS)
+@pytest.mark.parametrize("scheme,recon,solver,prec", [("ctu", "ppm", "hlld", "f64"), ("ctu", "plm", "roe", "f64"),
+                                                      ("vl", "plm", "hlle", "f64"), ("ctu", "ppm", "hlld", "f32")])
+def test_thin_grid_in_any_launch_shape(shape, scheme, recon, solver, prec):
+    """The whole grid against the oracle (double), and bit for bit the same with other blocks,
+    which change what is flat."""
+    p = inputs.smooth_problem(*reversed(shape), seed=sum(shape))
+    U, B = oracle.initial_state(p)
+    dt = oracle.cfl_dt(U, B, p["dx"])
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    out = []
+    for launch in ((0, 0), (0, 64), (1, 512)):
+        lv = Level(torch.from_numpy(U).to("cuda", dtype), torch.from_numpy(B).to("cuda", dtype), p["dx"])
+        s = Solver(scheme, recon, solver, prec)
+        s.set_launch(*launch)
+        s.step(lv, dt)
+        torch.cuda.synchronize()
+        out.append(lv)
+    for lv in out[1:]:
+        assert torch.equal(lv.U, out[0].U) and torch.equal(lv.B, out[0].B)
+    if prec == "f32":
+        return
+    oracle.set_threads(8)
+    Uo, Bo = oracle.step(U, B, dt, p["dx"], scheme={"vl": oracle.VL, "ctu": oracle.CTU}[scheme],
+                         recon={"plm": oracle.PLM, "ppm": oracle.PPM}[recon],
+                         riemann={"roe": oracle.ROE, "hlle": oracle.HLLE, "hlld": oracle.HLLD}[solver])
+    for got, want in ((out[0].U, Uo), (out[0].B, Bo)):
+        got = got.cpu().numpy()
+        for m in range(len(want)):
+            assert np.abs(got[m] - want[m]).max() <= 1e-12 * np.abs(want[m]).max()
+
+
+@pytest.mark.parametrize("edge,n,prec", [(36, 72, "f64"), (64, 128, "f32"), (40, 80, "f32")])
+def test_large_group_boxes_equal_the_whole_grid(edge, n, prec):
+    # item boxes in several slabs: listed cells are the whole grid's bit for bit
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    p = inputs.smooth_problem(n, n, n, seed=6)
+    U, B = oracle.initial_state(p)
+    origins = np.array([(0, 0, 0), (edge, edge, 0), (0, edge, edge)], dtype=np.int32)
+    s = Solver("ctu", "ppm", "hlld", prec)
+    whole, part = (Level(torch.from_numpy(U).to("cuda", dtype), torch.from_numpy(B).to("cuda", dtype), p["dx"])
+                   for _ in range(2))
+    part.group_edge = edge
+    part.set_groups(torch.from_numpy(origins).cuda())
+    for counted in (False, True):          # the list's length on the host, and on the device
+        if counted:
+            part.n_groups_dev = torch.tensor([2], dtype=torch.int32, device="cuda")
+        U0, listed = part.U.clone(), torch.zeros((n, n, n), dtype=torch.bool, device="cuda")
+        whole.U.copy_(part.U)
+        whole.B.copy_(part.B)
+        for i, j, k in origins[:2 if counted else 3]:
+            listed[k:k + edge, j:j + edge, i:i + edge] = True
+        dt = s.cfl_dt(whole)
+        s.step(whole, dt)
+        s.step(part, dt)
+        assert torch.equal(part.U, torch.where(listed, whole.U, U0))

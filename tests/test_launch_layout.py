@@ -82,3 +82,60 @@ int main() {
   check(5, 7, ((1 << 30) - 1) / 35, 35u * (((1u << 30) - 1) / 35) - 100000);
   check(1 << 13, 1 << 13, 16, (1u << 30) - 100000);
 }""")
+
+
+@pytest.mark.parametrize("cols", [8, 16])
+def test_face_slabs_of_whole_grids(tmp_path, cols):
+    # the slabs cover the grid once; no wave task traces many lanes per face; and no slab
+    # of a large grid holds more cells than its three directions can share in a cache
+    run_host(tmp_path, r"""
+int main() {
+  const int sizes[] = {4, 5, 6, 7, 8, 9, 12, 16, 17, 24, 33, 61, 64, 97, 128, 200, 400, 512, 1024, 4096, 65536};
+  for (int nx : sizes) for (int ny : sizes) for (int nz : sizes) {
+    const long long n = (long long)nx * ny * nz;
+    if (n > 1LL << 28 || n < 1 << 14) continue;
+    Work w{};
+    w.nx = nx; w.ny = ny; w.nz = nz; w.N = w.items = n;
+    const FaceGeo g = face_geometry(w, %d);
+    const long long sz = g.slabs / (g.ux * g.uy);
+    CHECK(g.units == g.slabs && sz * g.ux * g.uy == g.slabs, "%%d x %%d x %%d: units", nx, ny, nz);
+    CHECK(sz * g.bz >= nz && (sz - 1) * g.bz < nz && (long long)g.uy * g.by >= ny && (g.uy - 1LL) * g.by < ny &&
+          (long long)g.ux * g.bx >= nx && (g.ux - 1LL) * g.bx < nx,
+          "%%d x %%d x %%d: %%d slabs of %%d x %%d x %%d", nx, ny, nz, (int)g.units, g.bx, g.by, g.bz);
+    CHECK(g.units * g.per < 1LL << 31, "waves");
+    long long traced = 0;                  // waves' traces; marches trace one cell more than they have
+    for (int k0 = 0; k0 < nz; k0 += g.bz) for (int j0 = 0; j0 < ny; j0 += g.by) {
+      const int bz = nz - k0 < g.bz ? nz - k0 : g.bz, by = ny - j0 < g.by ? ny - j0 : g.by;
+      long long per = (long long)g.per - g.w2 - g.w1;
+      if (g.tz) per += g.w2 + g.w1;
+      else per += ((long long)g.bx * by + 63) / 64 * (bz + (bz + g.cz - 1) / g.cz) +
+                  ((long long)g.bx * bz + 63) / 64 * (by + (by + g.cy - 1) / g.cy);
+      traced += per * g.ux;
+    }
+    traced *= 64;
+    // (planes of 20 cells leave 12 of 32 columns of a pair of tiles empty)
+    CHECK(traced <= 3 * n * (nx * ny < kTilePlane || nx * nz < 64 ? 10 : 7) / 4, "%%d x %%d x %%d: %%lld lanes trace %%lld faces", nx, ny, nz, traced, 3 * n);
+    CHECK(n < 1 << 20 || nx * nz < 64 || 4LL * g.bx * g.by * g.bz <= n, "%%d x %%d x %%d: slabs of %%d x %%d x %%d", nx, ny, nz, g.bx, g.by, g.bz);
+  }
+}""" % cols)
+
+
+def test_division_by_a_fixed_divisor(tmp_path):
+    # every divisor at the multiples around which a quotient could round, up to 2^31 - 1
+    run_host(tmp_path, r"""
+static void check(unsigned d) {
+  const FastDiv f = make_div(d);
+  for (int e = 0; e < 32; ++e)
+    for (long long q = -2; q <= 2; ++q)
+      for (long long o = -1; o <= 1; ++o) {
+        const long long n = ((1LL << e) / d + q) * d + o;
+        if (n >= 0 && n < 1LL << 31) CHECK(fdiv(f, (unsigned)n) == (unsigned)n / d, "%lld / %u", n, d);
+      }
+  const unsigned last = (1u << 31) - 1;
+  for (unsigned n : {last, last - last % d, last - last % d - 1}) CHECK(fdiv(f, n) == n / d, "%u / %u", n, d);
+}
+int main() {
+  for (unsigned d = 1; d < 200000; ++d) check(d);
+  for (unsigned d = 200000; d < 1u << 31; d += d / 1000 + 7) check(d);
+  for (int b = 1; b < 31; ++b) for (int o = -1; o <= 1; ++o) check((1u << b) + o);
+}""")
