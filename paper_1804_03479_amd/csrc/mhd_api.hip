@@ -361,12 +361,10 @@ void launch_emf(Work& w, const T* F, const T* R, T* E, int nt, hipStream_t st) {
   }
 }
 
-// Grid of the VL flux stage: fewer blocks than two per CU are split by direction, as
-// one wave's chain of loads and divisions is what they wait for.  Whole step (us), all
-// directions in a thread / one each, VL + PLM + Roe: float 16^3 39 / 33, 32^3 41 / 36,
-// 48^3 55 / 53, 64^3 66 / 70; double 32^3 57 / 48, 40^3 74 / 66, 48^3 74 / 75, 64^3 122 /
-// 125
-dim3 flux_grid(const mhd_ctx_s* c, unsigned nb) { return dim3(nb, nb < 2u * (unsigned)c->num_cu ? 3 : 1); }
+dim3 flux_grid(const mhd_ctx_s* c, Work& w, int mode, int threads) {
+  const FluxGrid g = flux_blocks(decompose(w, mode, threads), c->num_cu, g_max_blocks);
+  return dim3(g.x, g.y);
+}
 
 // ev (optional): kNumStages + 1 events recorded around the stage kernels.
 // R: 1 = PLM (minmod), 2 = PPM at the half step.
@@ -408,16 +406,14 @@ void launch_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl
     Work f1 = batch_of(wf1, b, batch), e1 = batch_of(we1, b, batch), h = batch_of(wh, b, batch);
     Work f2 = batch_of(wf2, b, batch), e2 = batch_of(we2, b, batch);
     f1.rev = h.rev = e2.rev = 1;
-    nb = stage_grid(f1, L, nt);
-    k_flux<T, 0, S, L><<<flux_grid(c, nb), nt, 0, st>>>(f1, W, B, Bh, F, gam, c->nfb);
+    k_flux<T, 0, S, L><<<flux_grid(c, f1, L, nt), nt, 0, st>>>(f1, W, B, Bh, F, gam, c->nfb);
     mark(2);
     launch_emf<T, L>(e1, F, Bh, E, nt, st);
     mark(3);
     nb = stage_grid(h, L, nt);
     k_half<T, MIX, false, L><<<nb, nt, 0, st>>>(h, U, B, mix, F, E, dts, inv_dx, gam, W, Bh);
     mark(4);
-    nb = stage_grid(f2, L, nt);
-    k_flux<T, R, S, L><<<flux_grid(c, nb), nt, 0, st>>>(f2, W, B, Bh, F, gam, c->nfb);
+    k_flux<T, R, S, L><<<flux_grid(c, f2, L, nt), nt, 0, st>>>(f2, W, B, Bh, F, gam, c->nfb);
     mark(5);
     launch_emf<T, L>(e2, F, Bh, E, nt, st);
     mark(6);

@@ -96,6 +96,22 @@ inline long long decompose(Work& w, int mode, int threads) {
   return (long long)w.units * w.chunks;
 }
 
+// Grid of the VL flux stage for `blocks` blocks of work, at most max_blocks of them (0: no
+// limit): where there are fewer than two blocks per CU, a launch row for each direction,
+// as one wave's chain of loads and divisions is what they wait for.  The limit counts
+// all rows and does not make a large level a small one.  Whole step (us), all directions
+// in a thread / one each, VL + PLM + Roe: float 16^3 39 / 33, 32^3 41 / 36, 48^3 55 / 53,
+// 64^3 66 / 70; double 32^3 57 / 48, 40^3 74 / 66, 48^3 74 / 75, 64^3 122 / 125
+struct FluxGrid {
+  unsigned x, y;
+};
+inline FluxGrid flux_blocks(long long blocks, int num_cu, long long max_blocks) {
+  const unsigned rows = blocks < 2LL * num_cu ? 3 : 1;
+  const long long limit = max_blocks / rows;
+  if (max_blocks > 0 && blocks > limit) blocks = limit;
+  return FluxGrid{(unsigned)(blocks < 1 ? 1 : blocks), rows};
+}
+
 // Decomposition of the CTU face kernels (k_ctu_faces): slabs of rows and planes of a
 // whole grid or of a group's item box, each cut into wave tasks.
 struct FaceGeo {

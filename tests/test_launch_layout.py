@@ -139,3 +139,19 @@ int main() {
   for (unsigned d = 200000; d < 1u << 31; d += d / 1000 + 7) check(d);
   for (int b = 1; b < 31; ++b) for (int o = -1; o <= 1; ++o) check((1u << b) + o);
 }""")
+
+
+def test_flux_grid_keeps_the_block_limit(tmp_path):
+    # a launch row per direction only for levels of little work, whatever the limit, and
+    # never more blocks than the limit (of at least three: one a row)
+    run_host(tmp_path, r"""
+int main() {
+  const int cu = 256;
+  for (long long blocks = 1; blocks < 100000; blocks += 1 + blocks / 7)
+    for (int per_cu = 0; per_cu <= 16; ++per_cu) {
+      const FluxGrid g = flux_blocks(blocks, cu, (long long)per_cu * cu);
+      CHECK(g.y == (blocks < 2 * cu ? 3u : 1u), "%lld blocks of work, %d per CU: %u rows", blocks, per_cu, g.y);
+      CHECK(per_cu == 0 ? g.x == blocks : (long long)g.x * g.y <= (long long)per_cu * cu && g.x <= blocks,
+            "%lld blocks of work, %d per CU: %u x %u", blocks, per_cu, g.x, g.y);
+    }
+}""")
