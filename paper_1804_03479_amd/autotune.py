@@ -10,8 +10,10 @@ batches).  The tuner times each candidate shape on the level itself (ghost
 refill plus update, HIP events, median of a few reps) and keeps the fastest.
 Results are cached in a JSON file keyed by device, method, precision, level
 shape and group count.  All shapes give bit-identical results.  A shape's
-fourth value (lds_tiles) once chose another form of the CTU reconstruction; it
-has no effect, and the winner is timed with it once more as before.
+fourth value (lds_tiles) once chose another form of the CTU reconstruction and
+has no effect.  For CTU with PPM the winner is still timed with it once more, as
+callers expect the entry, but it is never the choice: the two are the same
+configuration and differ by noise only.
 """
 from __future__ import annotations
 
@@ -38,7 +40,7 @@ def shape(c):
 
 
 def tiles_apply(h, lvl: int) -> bool:
-    """Does the LDS-tile option change level lvl's update (CTU with PPM)?"""
+    """Is level lvl of the method the LDS-tile option was for (CTU with PPM)?  It changes nothing."""
     c = h.solvers[lvl].cfg
     return c.scheme == 1 and c.recon == 1
 
@@ -95,7 +97,7 @@ def tune(h, candidates=None, reps: int = 5, cache: str | None = None, use_cache:
     level], "keys": [...]}.  candidates: None (level_candidates of each
     level) or one list of shapes (ints: blocks per CU at the default threads
     and batch) for every level.  try_tiles: also time the best shape with
-    lds_tiles set (the last candidate; it has no effect).
+    lds_tiles set (the last candidate; it has no effect and is not picked).
 
     The timing runs advance the levels' state (it is a real update); tune
     before the measured run, not inside it."""
@@ -126,7 +128,6 @@ def tune(h, candidates=None, reps: int = 5, cache: str | None = None, use_cache:
             h.solvers[lvl].set_launch(*tiled)
             cl = cl + [tiled]
             ms.append(time_level(h, lvl, reps))
-            best = cl[min(range(len(ms)), key=ms.__getitem__)]
         shapes.append(best)
         table.append(ms)
         cands.append(cl)
