@@ -179,8 +179,11 @@ int mhd_advance_graph(mhd_ctx ctx, const mhd_level* lv, double* dt_dev, double* 
  *   blocks_per_cu      at most this many blocks per compute unit walk the
  *                      work with a grid-wide stride (0 = one thread per work
  *                      item, no cap);
- *   threads_per_block  64 .. 512, a multiple of 64 (0 = 256); the learned
- *                      flux's network kernels keep 256;
+ *   threads_per_block  64 .. 512, a multiple of 64 (0 = 256), of the stage
+ *                      kernels that run a thread per cell; the CTU face
+ *                      kernels (reconstruction, transverse correction and
+ *                      Riemann fluxes, with every solver), which work on
+ *                      lines and tiles of cells a wave, keep 256;
  *   batch_groups       with a group list, the stages between the primitive
  *                      pass (which also reduces the CFL maximum over the whole
  *                      list) and the final update run batch by batch, each

@@ -315,9 +315,9 @@ class Solver:
 
     def set_launch(self, blocks_per_cu: int = 0, threads: int = 0, batch: int = 0, tiles: int = 0):
         """Launch shape of the stage kernels: blocks per CU of the persistent
-        grid (0: one item per thread), threads per block (0: 256), the
-        group-list batch of the middle stages (0: the whole list); tiles (0 or
-        1) is accepted and changes nothing."""
+        grid (0: one item per thread), threads per block (0: 256; the CTU face
+        kernels keep 256), the group-list batch of the middle stages (0: the
+        whole list); tiles (0 or 1) is accepted and changes nothing."""
         _check(self.lib.mhd_set_launch(self.h, int(blocks_per_cu), int(threads), int(batch), int(tiles)),
                "mhd_set_launch")
 
