@@ -137,7 +137,10 @@ int mhd_prim_to_cons(mhd_ctx ctx, const mhd_level* lv, const void* W5);
 int mhd_cfl_dt(mhd_ctx ctx, const mhd_level* lv, double* dt_host, double* dt_dev);
 
 /* One full step of length dt (paper Sec. 3.2: CTU steps 1-8 or VL steps 1-7),
- * updating lv->U and lv->B in place.  Asynchronous. */
+ * updating lv->U and lv->B in place.  Asynchronous.  CTU refuses a whole grid
+ * whose components take 4 GiB or more (1024^3 cells in float) with
+ * MHD_ERR_OUT_OF_MEMORY, whatever memory is free: its scratch is budgeted at
+ * 98 words per cell (mhd_workspace_bytes), 392 GiB there. */
 int mhd_step(mhd_ctx ctx, const mhd_level* lv, double dt);
 
 /* Same, with dt read from device memory at run time (graph-capturable). */

@@ -568,9 +568,7 @@ int do_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hip
   int rc = check_level(c, lv);
   if (rc) return rc;
   if (c->cfg.riemann == MHD_MLP && !c->mlp_ready) return MHD_ERR_INVALID_ARG;
-  // the face kernels address one component of a whole grid by 32-bit byte
-  // offsets; a level beyond that does not fit the device either
-  if (c->cfg.scheme == MHD_CTU && !list_mode(lv) && scratch_cells(lv, 0) * (long long)c->elem > 0xffffffffLL)
+  if (c->cfg.scheme == MHD_CTU && !list_mode(lv) && !face_addressable(scratch_cells(lv, 0), (int)c->elem))
     return MHD_ERR_OUT_OF_MEMORY;
   rc = ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
   if (rc) return rc;

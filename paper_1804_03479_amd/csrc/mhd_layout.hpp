@@ -129,6 +129,12 @@ struct FaceGeo {
   FastDiv by_ly, by_lz;
 };
 
+// The face kernels address a component of a whole grid by 32-bit byte offsets.  A grid of
+// components of 4 GiB and more is refused as out of memory, without a look at what the
+// device holds: its step is budgeted at 98 words a cell (mhd_workspace_bytes), 392 GiB
+// at that size, more than a gfx950 device has, and was always refused so.
+inline bool face_addressable(long long cells, int elem) { return cells * elem < 1LL << 32; }
+
 // A march repeats the trace of one cell before its first face, so long marches save
 // work and short ones give small grids enough waves.
 //

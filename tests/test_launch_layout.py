@@ -155,3 +155,16 @@ int main() {
             "%lld blocks of work, %d per CU: %u x %u", blocks, per_cu, g.x, g.y);
     }
 }""")
+
+
+def test_largest_grid_of_the_face_kernels(tmp_path):
+    # every byte offset of the largest component is below 2^32; the next grid is refused
+    run_host(tmp_path, r"""
+int main() {
+  for (int elem : {4, 8}) {
+    const long long most = (1LL << 32) / elem - 1;
+    CHECK(face_addressable(most, elem) && (most - 1) * elem <= 0xffffffffLL, "%d bytes", elem);
+    CHECK(!face_addressable(most + 1, elem), "%d bytes: a component of 4 GiB", elem);
+    CHECK(98 * (most + 1) * elem > 288LL << 30, "the budget of a refused grid");
+  }
+}""")
