@@ -280,10 +280,7 @@ int build_occupancy(mhd_ctx_s* c, const mhd_level* lv) { return build_occupancy_
 // grid of a stage kernel: capped by the context's launch shape
 thread_local long long g_max_blocks = 0;
 thread_local int g_threads = kBlock;
-unsigned capped(long long b) {
-  if (g_max_blocks > 0 && b > g_max_blocks) b = g_max_blocks;
-  return (unsigned)(b < 1 ? 1 : b);
-}
+unsigned capped(long long b) { return launch_blocks(b, g_max_blocks); }
 
 // of a kernel that walks its items with FOR_ITEMS: fills the Work's item divisors
 unsigned item_blocks(Work& w) {
@@ -564,13 +561,18 @@ int run_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hi
   return hipGetLastError() == hipSuccess ? MHD_OK : MHD_ERR_HIP;
 }
 
+// scratch of a step of the level
+int ensure_step(mhd_ctx_s* c, const mhd_level* lv) {
+  if (c->cfg.scheme == MHD_CTU && !list_mode(lv) && !face_addressable(scratch_cells(lv, 0), (int)c->elem))
+    return MHD_ERR_OUT_OF_MEMORY;
+  return ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
+}
+
 int do_step(mhd_ctx_s* c, const mhd_level* lv, DtSrc dts, const CflOut* cfl, hipEvent_t* ev = nullptr) {
   int rc = check_level(c, lv);
   if (rc) return rc;
   if (c->cfg.riemann == MHD_MLP && !c->mlp_ready) return MHD_ERR_INVALID_ARG;
-  if (c->cfg.scheme == MHD_CTU && !list_mode(lv) && !face_addressable(scratch_cells(lv, 0), (int)c->elem))
-    return MHD_ERR_OUT_OF_MEMORY;
-  rc = ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
+  rc = ensure_step(c, lv);
   if (rc) return rc;
   rc = build_occupancy(c, lv);
   if (rc) return rc;
@@ -617,14 +619,7 @@ size_t carve_static(const mhd_ctx_s* c, const mhd_level* lv, unsigned char* base
   return off;
 }
 
-// kernels that only read the level address it by 64-bit indices in a group list, and
-// where a plane of a whole grid passes 4 GiB
-template <typename T>
-bool level_indexed(const Work& w) {
-  return w.groups || (long long)w.nx * w.ny * (long long)sizeof(T) > 0xffffffffLL;
-}
-
-// CFL maximum signal speed of a level into c->smax
+// CFL maximum signal speed of a level into the context's slots
 template <typename T, bool MIX>
 void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
   Work w = make_work(lv, 0, 0);
@@ -635,7 +630,7 @@ void launch_cfl_t(mhd_ctx_s* c, const mhd_level* lv) {
     const unsigned nb = stage_grid(w, mode, kBlock);
     k_cfl<T, MIX, mode><<<nb, kBlock, 0, c->stream>>>(w, U, B, mix, (T)c->cfg.gamma, c->cfl, c->flag);
   };
-  if (level_indexed<T>(w)) launch(std::integral_constant<int, kList>());
+  if (read_mode(w, sizeof(T)) == kList) launch(std::integral_constant<int, kList>());
   else if (flat_pays(w.nx, w.ny, w.nz, sizeof(T), kBlock)) launch(std::integral_constant<int, kFlat>());
   else launch(std::integral_constant<int, kWhole>());
 }
@@ -653,21 +648,21 @@ void launch_cfl(mhd_ctx_s* c, const mhd_level* lv, double courant_dx, double* dt
 // the partials of a large level stay few
 unsigned reduce_blocks(mhd_ctx_s* c, Work& w) {
   g_max_blocks = 8LL * c->num_cu;
-  const unsigned nb = stage_grid(w, kWhole, kBlock);
+  const unsigned nb = stage_grid(w, read_mode(w, (int)c->elem), kBlock);
   g_max_blocks = 0;
   return nb;
 }
 
 template <typename T>
 void launch_divb(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb) {
-  if (level_indexed<T>(w)) k_divb<T, kList><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
+  if (read_mode(w, sizeof(T)) == kList) k_divb<T, kList><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
   else k_divb<T, kWhole><<<nb, kBlock, 0, c->stream>>>(w, (const T*)lv->B, 1.0 / lv->dx, c->parts);
 }
 
 template <typename T>
 void launch_sums(mhd_ctx_s* c, const mhd_level* lv, const Work& w, unsigned nb, const double* e64) {
   const T *U = (const T*)lv->U, *B = (const T*)lv->B;
-  if (level_indexed<T>(w)) k_sums<T, kList><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
+  if (read_mode(w, sizeof(T)) == kList) k_sums<T, kList><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
   else k_sums<T, kWhole><<<nb, kBlock, 0, c->stream>>>(w, U, B, e64, c->parts);
 }
 
@@ -914,7 +909,7 @@ int mhd_advance_graph(mhd_ctx c, const mhd_level* lv, double* dt_dev, double* t_
   if (!same) {
     drop_graph(c);
     // allocations happen before the capture
-    rc = ensure_capacity(c, scratch_cells(lv, step_ghost(c)));
+    rc = ensure_step(c, lv);
     if (rc) return rc;
     rc = ensure_occupancy(c, lv, &c->occ, &c->cap_occ);
     if (rc) return rc;

@@ -32,7 +32,6 @@
 namespace mhd {
 
 constexpr int kBlock = 256;      // threads per block of the fixed-shape kernels
-constexpr int kMaxBlock = 512;   // largest block of the step's stage kernels (tuned per context)
 
 __device__ __forceinline__ long long lin(const Work& w, int i, int j, int k) {
   return ((long long)k * w.ny + j) * w.nx + i;
@@ -159,14 +158,17 @@ struct Cell {
     const unsigned unit = fdiv(w.by_chunks, rank);
     const unsigned l = (rank - unit * w.chunks) * blockDim.x + threadIdx.x;
     on = l < w.per;
-    if (L == kList && w.groups == nullptr) {   // a whole grid by level indices only (level_indexed)
-      j = (int)(l / (unsigned)w.nx);
-      i = (int)(l - (unsigned)j * (unsigned)w.nx);
-      k = (int)unit;
+    if (L == kList && w.groups == nullptr) {   // a whole grid by 64-bit level indices (read_mode)
+      p = (long long)unit * w.per + l;
+      on = on && p < w.N;
+      const long long plane = (long long)w.nx * w.ny;
+      k = (int)(p / plane);
+      const long long r = p - k * plane;
+      j = (int)(r / w.nx);
+      i = (int)(r - (long long)j * w.nx);
       a = i; b = j; c = k;
       u = 0;
       o = 0;
-      p = lin(w, i, j, k);
     } else if constexpr (L == kList) {
       const unsigned box = w.box;
       c = (int)fdiv(w.by_plane, l);

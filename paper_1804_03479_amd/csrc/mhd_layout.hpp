@@ -59,6 +59,12 @@ struct Work {
 // the item boxes of a group list, or a whole grid's cells one after the other.
 constexpr int kWhole = 0, kList = 1, kFlat = 2;
 
+// The kernels that only read the level (CFL, diagnostics) address it by 64-bit indices in a
+// group list, and where a plane of a whole grid passes 4 GiB (kList without a list).
+inline int read_mode(const Work& w, int elem) {
+  return w.groups || (long long)w.nx * w.ny * elem > 0xffffffffLL ? kList : kWhole;
+}
+
 // The planes form has its plane's address in scalar registers, but a plane fills whole
 // blocks: 4 x 4 cells use 16 of 256 lanes.  The flat form wraps along z per thread and
 // fills every lane; it is taken where planes fill less than 9/10 of their blocks, if a
@@ -81,6 +87,9 @@ inline long long decompose(Work& w, int mode, int threads) {
     w.units = (int)(w.items / w.per);
     w.by_row = make_div((unsigned)w.box);
     w.by_plane = make_div((unsigned)(w.box * w.box));
+  } else if (mode == kList) {
+    w.per = 1u << 30;   // planes may have 2^32 cells
+    w.units = (int)((w.N + w.per - 1) / w.per);
   } else if (mode == kFlat) {
     w.per = (unsigned)w.N;
     w.units = 1;
@@ -96,6 +105,16 @@ inline long long decompose(Work& w, int mode, int threads) {
   return (long long)w.units * w.chunks;
 }
 
+// Blocks of a launch over `blocks` blocks of work, at most max_blocks (0: no limit of the
+// caller's).  A launch has fewer than 2^32 threads; a kernel's blocks walk the rest.
+constexpr int kMaxBlock = 512;   // largest block of the step's stage kernels (tuned per context)
+constexpr long long kMaxLaunch = 0xffffffffLL / kMaxBlock;
+inline unsigned launch_blocks(long long blocks, long long max_blocks) {
+  if (max_blocks > 0 && blocks > max_blocks) blocks = max_blocks;
+  if (blocks > kMaxLaunch) blocks = kMaxLaunch;
+  return (unsigned)(blocks < 1 ? 1 : blocks);
+}
+
 // Grid of the VL flux stage for `blocks` blocks of work, at most max_blocks of them (0: no
 // limit): where there are fewer than two blocks per CU, a launch row for each direction,
 // as one wave's chain of loads and divisions is what they wait for.  The limit counts
@@ -108,8 +127,7 @@ struct FluxGrid {
 inline FluxGrid flux_blocks(long long blocks, int num_cu, long long max_blocks) {
   const unsigned rows = blocks < 2LL * num_cu ? 3 : 1;
   const long long limit = max_blocks / rows;
-  if (max_blocks > 0 && blocks > limit) blocks = limit;
-  return FluxGrid{(unsigned)(blocks < 1 ? 1 : blocks), rows};
+  return FluxGrid{launch_blocks(blocks, max_blocks > 0 && limit < 1 ? 1 : limit), rows};
 }
 
 // Decomposition of the CTU face kernels (k_ctu_faces): slabs of rows and planes of a

@@ -168,3 +168,26 @@ int main() {
     CHECK(98 * (most + 1) * elem > 288LL << 30, "the budget of a refused grid");
   }
 }""")
+
+
+def test_blocks_of_the_largest_levels(tmp_path):
+    # the diagnostics' blocks cover every level that is accepted (up to 2^34 cells, planes
+    # of up to 2^32) with numbers of cells in a unit and of blocks that fit their words
+    run_host(tmp_path, r"""
+int main() {
+  for (int elem : {4, 8})
+    for (int ax = 2; ax <= 32; ++ax) for (int ay = 2; ax + ay <= 32; ++ay) for (int d = 0; d < 2; ++d) {
+      const long long nx = (1LL << ax) - (ax > 2 ? d : 0), ny = 1LL << ay;
+      if (nx > 1LL << 30 || ny > 1LL << 30) continue;
+      long long nz = (1LL << 34) / (nx * ny);
+      if (nz > 1 << 30) nz = 1 << 30;
+      Work w{};
+      w.nx = (int)nx; w.ny = (int)ny; w.nz = (int)nz; w.N = w.items = nx * ny * nz;
+      const long long blocks = decompose(w, read_mode(w, elem), 256);
+      CHECK(blocks < 1LL << 31 && (long long)w.units * w.per >= w.N && (w.units - 1LL) * w.per < w.N && w.chunks * 256LL >= w.per,
+            "%lld x %lld x %lld: %d units of %u cells, %lld blocks", nx, ny, nz, w.units, w.per, blocks);
+      for (long long limit : {0LL, 256LL, 1LL << 40})
+        CHECK(launch_blocks(blocks, limit) * (long long)kMaxBlock < 1LL << 32 && launch_blocks(blocks, limit) <= blocks,
+              "%lld x %lld x %lld: launch of %u blocks", nx, ny, nz, launch_blocks(blocks, limit));
+    }
+}""")
