@@ -442,8 +442,11 @@ void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_
   }
   if constexpr (std::is_same<T, float>::value && S != 3) {
     if (c->capture.buf) {
-      nb = stage_grid(w, L, kBlock);
-      k_capture<R, ALLW, STAGE, L><<<nb, kBlock, 0, c->stream>>>(w, A, dts, inv_dx, c->capture);
+      constexpr int M = L == kList ? kList : kFlat;
+      const int stride = c->capture.stride, step = stride % 3 ? stride : stride / 3;
+      const long long blocks = decompose(w, M, kBlock), samples = (w.N - 1) / step + 1;
+      nb = capped(M == kList ? blocks : (samples + kBlock - 1) / kBlock);
+      k_capture<R, ALLW, STAGE, M><<<dim3(nb, 3), kBlock, 0, c->stream>>>(w, A, dts, inv_dx, c->capture);
     }
   }
 }

@@ -184,22 +184,34 @@ struct Cell {
       u = (g + 1LL) * sb * sb * sb;
       o = (unsigned)(((c + w.soff) * w.sb + (b + w.soff)) * w.sb + (a + w.soff)) * (unsigned)sizeof(T);
       p = lin(w, i, j, k);
+    } else if constexpr (L == kFlat) {
+      flat(w, l);
     } else {
-      unsigned r = l;
-      if constexpr (L == kFlat) {
-        k = (int)fdiv(w.by_plane, l);
-        r -= (unsigned)k * (unsigned)w.nx * (unsigned)w.ny;
-      } else {
-        k = (int)unit;
-      }
-      j = (int)fdiv(w.by_row, r);
-      i = (int)(r - (unsigned)j * (unsigned)w.nx);
+      j = (int)fdiv(w.by_row, l);
+      i = (int)(l - (unsigned)j * (unsigned)w.nx);
+      k = (int)unit;
       a = i; b = j; c = k;
-      u = L == kFlat ? 0 : (long long)k * w.per;
+      u = (long long)k * w.per;
       o = l * (unsigned)sizeof(T);
       p = 0;
     }
   }
+
+  // (kFlat) the grid's cell l
+  __device__ __forceinline__ void flat(const Work& w, unsigned l) {
+    k = (int)fdiv(w.by_plane, l);
+    const unsigned r = l - (unsigned)k * (unsigned)w.nx * (unsigned)w.ny;
+    j = (int)fdiv(w.by_row, r);
+    i = (int)(r - (unsigned)j * (unsigned)w.nx);
+    a = i; b = j; c = k;
+    u = 0;
+    o = l * (unsigned)sizeof(T);
+    p = 0;
+  }
+  struct AtCell {
+    unsigned l;
+  };
+  __device__ __forceinline__ Cell(const Work& w, AtCell at) : on(true) { flat(w, at.l); }
 
   // The same cell with its offset taken anew: the compiler selects "scalar base
   // + 32-bit offset" addresses only where it sees the offset's extension in the
