@@ -38,8 +38,8 @@ namespace mhd {
 // it in registers.  The Riemann solver then has the registers to itself: 72 / 96
 // (steps 1-2 / 5-6, PPM + HLLD) instead of 142 / 160 in float, seven and five
 // waves per SIMD instead of three; 139 / 162 and three waves instead of 256, spills
-// and one wave in double.  128^3, steps 1-2 + 5-6: float 328 -> 295 us, double
-// 1129 -> 770 us.  On group lists in float the cells read again miss the L2
+// and one wave in double.  128^3, steps 1-2 + 5-6: float 328 -> 292 us, double
+// 1129 -> 788 us.  On group lists in float the cells read again miss the L2
 // (many groups' boxes are in flight), so the registers keep them there: 337
 // against 371 us for 191 groups (double 750 against 2200 us).
 // The learned flux parks in both modes.
@@ -382,11 +382,12 @@ __device__ __forceinline__ unsigned fdiv(__attribute__((address_space(4))) const
 // ALLW: trace waves moving away from an edge too (HLL-family solvers).  The
 // double form is held to 168 registers (three waves per SIMD; it needs 173), with
 // Roe, which would spill 90 words there, to 256.
-// Bound by vector issue: 128^3 PPM + HLLD takes 114 / 178 us in float for steps
-// 1-2 / 5-6 (a thread per cell and stored states: 257 / 185 us) and 270 / 490 us
-// in double (545 / 385 us).  SOLVER 3, the learned flux (float only): 300 / 422 us
-// against 417 / 536 us with states stored for kernels of their own, and 39 words a
-// cell of scratch less.
+// Bound by vector issue: 128^3 PPM + HLLD takes 112 / 180 us in float for steps
+// 1-2 / 5-6 (a thread per cell and stored states: 257 / 185 us) and 266 / 522 us
+// in double (545 / 385 us); PPM + Roe 183 / 239 and 441 / 823 us.  SOLVER 3, the
+// learned flux (float only): 398 / 443 us against 417 / 536 us with states stored
+// for kernels of their own, and 39 words a cell of scratch less.  (Stage events of
+// mhd_profile_step.)
 template <typename T, int RECON, bool ALLW, int SOLVER, int STAGE, bool L, bool TILES>
 __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3) : 1)
     k_ctu_faces(Work w, FaceGeo geo, FaceArgs<T> A, DtSrc dts, T inv_dx, unsigned long long* nfb) {

@@ -442,9 +442,10 @@ __device__ __forceinline__ void batch_forward(const BatchWeights& g, bf16x4 xf, 
   r.o = o + f32x4{b.x, b.y, b.z, b.w};
 }
 
-// Y = network(X).  Bound by the GELUs: 128 exponentials and reciprocals a row.
-// 250,000 rows: 218 us as three GEMMs, 22 us.  Four blocks per CU at most: a block
-// pays once for its copy of the weights.
+// Y = network(X).  250,000 rows: 218 us as three GEMMs, 22 us, of which the GELUs (128
+// exponentials and reciprocals a row) take about 12 at the vector units' rate; the rest
+// is the start of the launch: each block rounds the weights into its LDS and waits for
+// them.  Four blocks per CU at most, so that a block does that once for several tiles.
 __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X, int n,
                                                      float* __restrict__ Y) {
   __shared__ BatchWeights g;
