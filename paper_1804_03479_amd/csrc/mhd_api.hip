@@ -438,7 +438,8 @@ void launch_faces(mhd_ctx_s* c, Work& w, const FaceArgs<T>& A, DtSrc dts, T inv_
     if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, false, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
     else k_ctu_faces<T, R, ALLW, S, STAGE, false, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
   } else {
-    k_ctu_faces<T, R, ALLW, S, STAGE, true, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    if (g.tz) k_ctu_faces<T, R, ALLW, S, STAGE, true, true><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
+    else k_ctu_faces<T, R, ALLW, S, STAGE, true, false><<<nb, kBlock, 0, c->stream>>>(w, g, A, dts, inv_dx, c->nfb);
   }
   if constexpr (std::is_same<T, float>::value && S != 3) {
     if (c->capture.buf) {

@@ -65,8 +65,8 @@ struct FaceArgs {
   Capture cp;
 };
 
-// Small whole grids take z and y without marches too: a wave holds a tile of
-// successive cells of neighbouring lines (columns along x), and hands each upper-edge
+// Small whole grids and most group lists (face_geometry) take z and y without marches
+// too: a wave holds a tile of successive cells of neighbouring lines (columns along x), and hands each upper-edge
 // state a row of lanes on.  A march of one cell traces two cells for each face, and too
 // few waves are there to make it longer; a tile of eight traces eight for seven.  Fewer
 // columns trace less and read shorter pieces of rows.  Whole step (us), 4 / 8 / 16
@@ -314,7 +314,6 @@ __device__ __forceinline__ int march_line(const Work& w, const FaceArgs<T>& A, c
 template <typename T, int D, int RECON, bool ALLW, int SOLVER, int STAGE, bool L>
 __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, const Line<T, D, L>& ln, unsigned o1,
                                          unsigned o2, unsigned o12, bool emit, MlpShared* sh) {
-  static_assert(D == 0 || !L, "tiles cover whole grids");
   constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   constexpr int comp[7] = {0, 1 + D, 1 + t1, 1 + t2, 4, 5 + t1, 5 + t2};
   const long long NS = w.NS;
@@ -325,8 +324,9 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
     const int i = at + x;
     return o + (unsigned)(i < 0 ? x + size : (i >= size ? x - size : x)) * stride;
   };
+  const auto slot = [&](int d) { return d == 0 ? 1 : d == 1 ? w.sb : w.sb * w.sb; };   // L: slots to the next cell
   const auto value = [&](const T* arr, long long e, int x, unsigned o) {
-    return load_at<T>(scalar(arr + (e + ln.u + (L ? x : 0))), off(x, o));
+    return load_at<T>(scalar(arr + (e + ln.u + (L ? (long long)x * slot(D) : 0))), off(x, o));
   };
   T q[5][7], sl[7], sr[7];
   const unsigned o = fresh_offset(ln.o);
@@ -336,8 +336,9 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
     for (int c = 0; c < 7; ++c) q[x + 2][c] = value(A.W, comp[c] * NS, x, o);
   T bl, bu;
   if constexpr (L) {
-    bl = A.B[ln.p];
-    bu = A.B[ln.p + (ln.i + 1 >= w.nx ? 1 - w.nx : 1)];
+    const T* face = A.B + D * w.N + ln.p;
+    bl = face[0];
+    bu = face[(long long)(at + 1 >= size ? 1 - size : 1) * (D == 0 ? 1 : D == 1 ? w.nx : (long long)w.nx * w.ny)];
   } else {
     bl = value(A.B, D * w.N, 0, o);
     bu = value(A.B, D * w.N, 1, o);
@@ -349,7 +350,7 @@ __device__ __forceinline__ int row_faces(const Work& w, const FaceArgs<T>& A, co
   }
   trace_cell<T, RECON, ALLW>(q, bl, bu, A.dtdx, A.gam, sl, sr);
   if constexpr (STAGE == FACE_CORRECT) {
-    const Transverse<T> tr = transverse<T, D>(w, A, ln.u, o, o1, o2, o12, L ? w.sb : 0, L ? w.sb * w.sb : 0);
+    const Transverse<T> tr = transverse<T, D>(w, A, ln.u, o, o1, o2, o12, L ? slot(t1) : 0, L ? slot(t2) : 0);
     const T hd = A.hr * (bu - bl);
     correct_state(tr, bl, hl, hd, A.gam, sl);
     correct_state(tr, bu, hu, hd, A.gam, sr);
@@ -455,31 +456,31 @@ __global__ void __launch_bounds__(kBlock, sizeof(T) == 8 ? (SOLVER == 0 ? 2 : 3)
     if constexpr (TILES) {
       if (t < g.w2 + g.w1) {
         // position of the lines, one cell shared with the wave before: the lines of a
-        // tile's columns, each with its last cell before the first; columns are counted
-        // on from row to row
+        // tile's columns, each (of a whole grid) with its last cell before the first;
+        // columns are counted on from row to row
         constexpr unsigned cols = kTileCols<T, SOLVER>;
         const bool zdir = t < g.w2;
         const unsigned c0 = lane & (cols - 1), cell = lane / cols;
-        const unsigned len = (unsigned)(zdir ? g.bz : g.by) + 1;
+        const unsigned len = (unsigned)(zdir ? g.bz : g.by) + (L ? 0 : 1);   // a group box's lines start at their first cell
         const unsigned l = (zdir ? t : t - g.w2) * (kTileCells<T, SOLVER> - 1) + cell;
         const bool in = l < (zdir ? g.tz : g.ty) * len;
         const unsigned c = in ? l : 0, tile = zdir ? fdiv(g.by_lz, c) : fdiv(g.by_ly, c), q = c - tile * len;
         const unsigned col = tile * cols + c0;
-        const bool on = in && col < (unsigned)g.bx * (unsigned)(zdir ? g.by : bz) && (!zdir || q <= (unsigned)bz);
+        const bool on = in && col < (unsigned)g.bx * (unsigned)(zdir ? g.by : bz) && (L || !zdir || q <= (unsigned)bz);
         const unsigned at = on ? col : 0, other = fdiv(g.by_bx, at);
         const int x = (int)(at - other * (unsigned)g.bx);
         // the line's cell, wrapped where a line starts before the grid (lanes without one: the first)
-        const int m = !on ? 0 : zdir ? wrapc(z0 + (int)q - 1, w.nz) : wrapc((int)q - 1, w.ny);
+        const int m = !on ? 0 : L ? (int)q : zdir ? wrapc(z0 + (int)q - 1, w.nz) : wrapc((int)q - 1, w.ny);
         const bool emit = on && cell > 0 && q > 0;
         if (zdir) {
           Line<T, 2, L> ln;
           place(ln, x, (int)other, m, true, true, true);
-          const unsigned o1 = ln.o + up(ln.i, w.nx, 1), dy = up(ln.j, w.ny, (unsigned)w.nx);
+          const unsigned o1 = L ? ln.o : ln.o + up(ln.i, w.nx, 1), dy = L ? 0u : up(ln.j, w.ny, (unsigned)w.nx);
           fb += row_faces<T, 2, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dy, o1 + dy, emit, sh);
         } else {
           Line<T, 1, L> ln;
           place(ln, x, m, z0 + (int)other, true, true, true);
-          const unsigned o1 = ln.o + up(ln.k, w.nz, plane), dx = up(ln.i, w.nx, 1);
+          const unsigned o1 = L ? ln.o : ln.o + up(ln.k, w.nz, plane), dx = L ? 0u : up(ln.i, w.nx, 1);
           fb += row_faces<T, 1, RECON, ALLW, SOLVER, STAGE, L>(w, A, ln, o1, ln.o + dx, o1 + dx, emit, sh);
         }
         continue;

@@ -176,6 +176,15 @@ constexpr long long kTileLimit = 9 << 16;
 constexpr long long kTilePlane = 128;
 constexpr long long kTileSlab = 1 << 16;   // cells
 constexpr long long kListSlab = 1 << 15;
+// Lists go in tiles as well, up to these many cells in all item boxes: for 8 and for 16
+// columns, and for boxes of more than kListSlab cells (kTileLimit).  Whole step (us),
+// marches / tiles, 16^3 groups, CTU + PPM: HLLD float 1 / 8 / 30 / 150 / 300 groups 38 /
+// 35, 52 / 47, 98 / 89, 361 / 361, 709 / 729; double 4 / 30 / 300 / 511 / 1024 64 / 53, 177
+// / 149, 1545 / 1491, 2596 / 2607, 5167 / 5248; Roe double 8 / 100 / 511 103 / 81, 712 /
+// 632, 3422 / 3285; learned flux 100 / 511 469 / 417, 2203 / 2084; boxes: 4 of 48^3 HLLD
+// double 376 / 352, 10 of them 881 / 917, 2 of 32^3 Roe double 139 / 100.
+constexpr long long kTileList8 = 4 << 20;
+constexpr long long kTileList16 = 1 << 20;
 
 inline FaceGeo face_geometry(const Work& w, int cols) {
   FaceGeo g;
@@ -196,7 +205,10 @@ inline FaceGeo face_geometry(const Work& w, int cols) {
   g.by = ny;
   g.bz = nz;
   g.cz = g.cy = len;
-  if (list) {
+  if (list && w.items < (plane * nz > kListSlab ? kTileLimit : cols > 8 ? kTileList16 : kTileList8)) {
+    g.tz = g.ty = (unsigned)cut(plane, cols);
+    g.by_ly = g.by_lz = make_div((unsigned)nx);
+  } else if (list) {
     const int parts = cut(plane * nz, kListSlab);
     if (parts > 1) g.bz = len * cut(nz, (long long)len * parts);
     if (g.bz > nz) g.bz = nz;
@@ -234,8 +246,8 @@ inline FaceGeo face_geometry(const Work& w, int cols) {
   g.w1c = waves((long long)g.bx * g.bz, 64);
   g.w1 = g.w1c * (unsigned)cut(g.by, g.cy);
   if (g.tz) {
-    g.w2 = waves((long long)g.tz * (g.bz + 1) - 1, 64 / cols - 1);
-    g.w1 = waves((long long)g.ty * (g.by + 1) - 1, 64 / cols - 1);
+    g.w2 = waves((long long)g.tz * (g.bz + !list) - 1, 64 / cols - 1);
+    g.w1 = waves((long long)g.ty * (g.by + !list) - 1, 64 / cols - 1);
   }
   g.per = g.w2 + g.w1 + waves((long long)g.lx * g.by * g.bz - 1, 63);
   g.by_per = make_div(g.per);

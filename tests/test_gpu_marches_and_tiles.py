@@ -59,6 +59,41 @@ def test_marches_repeat_the_tiles(small, times, riemann, prec, recon):
     assert torch.equal(b.U, a.U.repeat(1, *times)) and torch.equal(b.B, a.B.repeat(1, *times))
 
 
+# group lists on both sides of the switches (item boxes of 20^3 and 18^3 cells for groups
+# of 16^3: 2^20 cells of them for 16 columns, 2^22 for 8; large boxes 9 2^16), in one launch
+# and in batches, the list's length on the host and on the device
+@pytest.mark.parametrize("edge,side,groups,riemann,prec", [
+    (16, 128, 131, "hlld", "f32"), (16, 128, 132, "hlld", "f32"), (16, 128, 179, "hlle", "f32"), (16, 128, 180, "hlle", "f32"),
+    (16, 144, 524, "hlld", "f64"), (16, 144, 525, "roe", "f32"), (16, 144, 719, "mlp", "f32"), (16, 144, 720, "mlp", "f32"),
+    (8, 64, 37, "roe", "f64"), (4, 52, 300, "mlp", "f32"), (32, 96, 12, "roe", "f64"), (32, 96, 13, "roe", "f64"),
+    (32, 96, 13, "hlld", "f32"), (48, 96, 4, "hlld", "f64"), (48, 96, 5, "hlld", "f64")])
+def test_lists_of_tiles_and_of_marches_equal_the_whole_grid(edge, side, groups, riemann, prec):
+    p = inputs.smooth_problem(side, side, side, seed=groups)
+    U, B = oracle.initial_state(p)
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    U, B = torch.from_numpy(U).to("cuda", dtype), torch.from_numpy(B).to("cuda", dtype)
+    m = side // edge
+    pick = np.random.default_rng(groups).choice(m ** 3, groups, replace=False)
+    origins = (np.stack([pick % m, pick // m % m, pick // m ** 2], 1) * edge).astype(np.int32)
+    s = solver_of(riemann, prec)
+    whole = Level(U.clone(), B.clone(), p["dx"])
+    dt = 0.7 * s.cfl_dt(whole)
+    s.step(whole, dt)
+    for batch, used in ((0, None), (groups // 3 + 1, None), (0, max(1, groups - 3))):
+        s.set_launch(0, 0, batch)
+        part = Level(U.clone(), B.clone(), p["dx"], groups=torch.from_numpy(origins).cuda(), group_edge=edge)
+        if used is not None:
+            part.n_groups_dev = torch.tensor([used], dtype=torch.int32, device="cuda")
+        s.step(part, dt)
+        cell = torch.zeros((side,) * 3, dtype=torch.bool, device="cuda")
+        for i, j, k in origins[:used]:
+            cell[k:k + edge, j:j + edge, i:i + edge] = True
+        assert torch.equal(part.U, torch.where(cell, whole.U, U))
+        for a in range(3):
+            face = cell | torch.roll(cell, 1, 2 - a)
+            assert torch.equal(part.B[a], torch.where(face, whole.B[a], B[a]))
+
+
 @pytest.mark.parametrize("shape,stride", [((85, 84, 83), 197), ((85, 84, 83), 4098), ((5, 347, 353), 1001)])
 def test_learned_flux_of_marched_faces(shape, stride):
     n = int(np.prod(shape))

@@ -191,3 +191,32 @@ int main() {
               "%lld x %lld x %lld: launch of %u blocks", nx, ny, nz, launch_blocks(blocks, limit));
     }
 }""")
+
+
+@pytest.mark.parametrize("cols", [8, 16])
+def test_face_slabs_of_group_lists(tmp_path, cols):
+    # every group's box whole, in tiles whose waves share one cell or in slabs of marches
+    run_host(tmp_path, r"""
+int main() {
+  const int cols = %d;
+  static int origin[3];
+  for (int box = 6; box <= 140; ++box)
+    for (long long groups = 1; groups < 3000; groups += 1 + groups / 3) {
+      Work w{};
+      w.groups = origin; w.box = box; w.nx = w.ny = w.nz = 4096; w.N = 1LL << 36;
+      w.items = groups * box * box * box;
+      const FaceGeo g = face_geometry(w, cols);
+      const long long sz = g.slabs;
+      CHECK(g.ux == 1 && g.uy == 1 && g.bx == box && g.by == box && g.lx == box && g.units == groups * sz, "%%d: slabs", box);
+      CHECK(sz * g.bz >= box && (sz - 1) * g.bz < box, "box %%d: %%lld slabs of %%d planes", box, sz, g.bz);
+      if (g.tz) {
+        const long long cells = 64 / cols, waves = ((long long)g.tz * box - 1 + cells - 2) / (cells - 1);
+        CHECK(sz == 1 && g.tz == g.ty && (long long)g.tz * cols >= box * box && g.w2 == waves && g.w1 == waves &&
+              (long long)waves * (cells - 1) + 1 >= (long long)g.tz * box, "box %%d: tiles", box);
+      } else {
+        // as many cells as a slab may have, in whole marches
+        CHECK(sz == 1 || (long long)box * box * (g.bz - g.cz) <= kListSlab, "box %%d: slab of %%d planes", box, g.bz);
+      }
+      CHECK(g.units * g.per < 1LL << 31, "waves");
+    }
+}""" % cols)
